@@ -3,7 +3,8 @@
 Every step of the Attention-Gate path runs in the HIP kernels of libag.so; PyTorch is used
 for device memory and streams.  There is no CPU fallback: importing the library on a machine
 where libag.so has not been built raises, and every call returns the library's status as an
-exception.
+exception.  The calls of the path go through a small native module (csrc/ag_binding.cpp), which reads the
+tensors' shapes and addresses itself; everything else goes through ctypes.
 """
 from __future__ import annotations
 
@@ -13,6 +14,7 @@ from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libag.so")
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 AG_OK, AG_EINVAL, AG_EUNSUPPORTED, AG_ECAPACITY, AG_EWORKSPACE, AG_EHIP = range(6)
 AG_F32, AG_BF16 = 0, 1
@@ -46,14 +48,15 @@ class ag_kv_cache(C.Structure):
 
 
 _lib = None
+_native = None
 
 
 def load() -> C.CDLL:
-    """Load libag.so (built by paper_2410_12876_amd/build.py); raises if it is missing."""
-    global _lib
+    """Load libag.so and its binding module (built by paper_2410_12876_amd/build.py); raises if one is missing."""
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(BINDING_PATH):
         raise ImportError("libag.so is not built: run `python -m paper_2410_12876_amd.build` "
                           "(or __graft_entry__.build()) first; there is no fallback path")
     lib = C.CDLL(LIB_PATH)
@@ -121,7 +124,9 @@ def load() -> C.CDLL:
     lib.ag_decode_attn_recent.restype = C.c_int
     lib.ag_decode_attn_recent.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, f32, C.POINTER(ag_kv_cache),
                                           C.POINTER(ag_recent_ring), vp]
-    _lib = lib
+    import torch  # noqa: F401  (the binding module uses its libraries)
+    from . import _binding
+    _lib, _native = lib, _binding
     return lib
 
 
@@ -169,17 +174,19 @@ class Context:
         if st != AG_OK:
             raise AgError(st, "ag_create(device=%d, workspace=%d) failed" % (device, workspace))
         self._h = h
+        self._addr = h.value
+        self._native = _native
         self.device = device
 
     def close(self) -> None:
         if getattr(self, "_h", None):
             self._lib.ag_destroy(self._h)
-            self._h = None
+            self._h = self._addr = None
 
     __del__ = close
 
     def _check(self, st: int) -> None:
-        if st != AG_OK:
+        if st:  # not AG_OK
             raise AgError(st, self._lib.ag_last_error(self._h).decode())
 
     def poll_error(self, stream=None) -> None:
@@ -238,36 +245,26 @@ class KVCache:
 def ag_gate(ctx: Context, feat, w_gate, bias, tau: float, n_sink: int, logits_out, flags_out, stream=None) -> None:
     """feat [B, L, d_in], w_gate [d_in, H_f], bias f32 [H_f] -> logits_out f32 [B, L, H_f] (or None),
     flags_out u8 [B, H_f, L]."""
-    B, L, d_in = feat.shape
-    H_f = w_gate.shape[1]
-    ctx._check(ctx._lib.ag_gate(ctx._h, _stream_ptr(stream), _ptr(feat), _dtype_code(feat), B, L, d_in,
-                                _ptr(w_gate), _ptr(bias), H_f, tau, n_sink, _ptr(logits_out), _ptr(flags_out)))
+    ctx._check(ctx._native.gate(ctx._addr, stream, feat, w_gate, bias, tau, n_sink, logits_out, flags_out))
 
 
 def ag_rmsnorm_gate(ctx: Context, h, norm_w, eps: float, w_gate, bias, tau: float, n_sink: int, x_out, logits_out,
                     flags_out, stream=None) -> None:
     """h [B, L, d_in], norm_w [d_in], w_gate [d_in, H_f], bias f32 [H_f] -> x_out [B, L, d_in] (may be h),
     logits_out f32 [B, L, H_f] (or None), flags_out u8 [B, H_f, L]."""
-    B, L, d_in = h.shape
-    H_f = w_gate.shape[1]
-    ctx._check(ctx._lib.ag_rmsnorm_gate(ctx._h, _stream_ptr(stream), _ptr(h), _dtype_code(h), B, L, d_in,
-                                        _ptr(norm_w), eps, _ptr(w_gate), _ptr(bias), H_f, tau, n_sink, _ptr(x_out),
-                                        _ptr(logits_out), _ptr(flags_out)))
+    ctx._check(ctx._native.rmsnorm_gate(ctx._addr, stream, h, norm_w, eps, w_gate, bias, tau, n_sink, x_out,
+                                        logits_out, flags_out))
 
 
 def ag_compact_kv(ctx: Context, k, v, flags, pos0: int, cache: KVCache, stream=None) -> None:
     """k, v [B, Hkv, L, D], flags u8 [B, Hkv, L] -> cache (k, v, idx, len written)."""
-    L = k.shape[2]
-    ctx._check(ctx._lib.ag_compact_kv(ctx._h, _stream_ptr(stream), _ptr(k), _ptr(v), _ptr(flags), L, pos0,
-                                      C.byref(cache.c)))
+    ctx._check(ctx._native.compact_kv(ctx._addr, stream, k, v, flags, pos0, cache.c))
 
 
 def ag_pack_row_off(ctx: Context, flags, room: int, total_rows: int, row_off, rows_needed=None, stream=None) -> None:
     """flags u8 [B, Hkv, L] -> row_off i64 [B*Hkv + 1] of the packed layout (retained rows + room per unit, cut off at
     total_rows); rows_needed i64 [1] (or None) receives the rows the layout needs."""
-    B, Hkv, L = flags.shape
-    ctx._check(ctx._lib.ag_pack_row_off(ctx._h, _stream_ptr(stream), _ptr(flags), B, Hkv, L, room, total_rows,
-                                        _ptr(row_off), _ptr(rows_needed)))
+    ctx._check(ctx._native.pack_row_off(ctx._addr, stream, flags, room, total_rows, row_off, rows_needed))
 
 
 def project_compact_workspace_bytes(B: int, L: int, Hkv: int) -> int:
@@ -277,54 +274,40 @@ def project_compact_workspace_bytes(B: int, L: int, Hkv: int) -> int:
 def ag_project_compact_kv(ctx: Context, x, w_kv, flags, pos0: int, kv_out, cache: KVCache, stream=None) -> None:
     """x [B, L, d] bf16, w_kv [d, 2*Hkv*128] bf16 (K columns, then V columns), flags u8 [B, Hkv, L] ->
     kv_out [2, B, Hkv, L, 128] (k, v of every token) and cache (kept rows, idx, len)."""
-    B, L, d = x.shape
-    ctx._check(ctx._lib.ag_project_compact_kv(ctx._h, _stream_ptr(stream), _ptr(x), _dtype_code(x), B, L, d, _ptr(w_kv),
-                                              _ptr(flags), pos0, _ptr(kv_out), C.byref(cache.c)))
+    ctx._check(ctx._native.project_compact_kv(ctx._addr, stream, x, w_kv, flags, pos0, kv_out, cache.c))
 
 
 def ag_prefill_attn(ctx: Context, q, k, v, flags, scale: float, cache: Optional[KVCache], out, stream=None) -> None:
     """q, out [B, Hq, L, D]; k, v [B, Hkv, L, D]; flags u8 [B, Hkv, L]; cache from ag_compact_kv or None."""
-    B, Hq, L, D = q.shape
-    Hkv = k.shape[1]
-    ctx._check(ctx._lib.ag_prefill_attn(ctx._h, _stream_ptr(stream), _ptr(q), _ptr(k), _ptr(v), _ptr(flags),
-                                        B, L, Hq, Hkv, D, _dtype_code(q), scale,
-                                        C.byref(cache.c) if cache is not None else None, _ptr(out)))
+    ctx._check(ctx._native.prefill_attn(ctx._addr, stream, q, k, v, flags, scale,
+                                        cache.c if cache is not None else None, 1, out))
 
 
 def ag_prefill_attn_recent(ctx: Context, q, k, v, flags, scale: float, cache: Optional[KVCache], n_recent: int, out,
                            stream=None) -> None:
     """ag_prefill_attn with the n_recent - 1 tokens before each query visible whatever their flag."""
-    B, Hq, L, D = q.shape
-    Hkv = k.shape[1]
-    ctx._check(ctx._lib.ag_prefill_attn_recent(ctx._h, _stream_ptr(stream), _ptr(q), _ptr(k), _ptr(v), _ptr(flags),
-                                               B, L, Hq, Hkv, D, _dtype_code(q), scale,
-                                               C.byref(cache.c) if cache is not None else None, n_recent, _ptr(out)))
+    ctx._check(ctx._native.prefill_attn(ctx._addr, stream, q, k, v, flags, scale,
+                                        cache.c if cache is not None else None, n_recent, out))
 
 
 def ag_compact_prefill_attn(ctx: Context, q, k, v, flags, scale: float, pos0: int, cache: KVCache, out,
                             n_recent: int = 1, stream=None) -> None:
     """ag_compact_kv + ag_prefill_attn in one call (one flag scan): fills `cache` and `out`."""
-    B, Hq, L, D = q.shape
-    Hkv = k.shape[1]
-    ctx._check(ctx._lib.ag_compact_prefill_attn(ctx._h, _stream_ptr(stream), _ptr(q), _ptr(k), _ptr(v), _ptr(flags),
-                                                B, L, Hq, Hkv, D, _dtype_code(q), scale, pos0, C.byref(cache.c),
-                                                n_recent, _ptr(out)))
+    ctx._check(ctx._native.compact_prefill_attn(ctx._addr, stream, q, k, v, flags, scale, pos0, cache.c, n_recent,
+                                                out))
 
 
 def ag_decode_attn(ctx: Context, q, k_new, v_new, new_flags, pos: int, scale: float, cache: KVCache, out,
                    stream=None) -> None:
     """q, out [B, Hq, D]; k_new, v_new [B, Hkv, D]; new_flags u8 [B, Hkv] or None; cache updated in place."""
-    Hq = q.shape[1]
-    ctx._check(ctx._lib.ag_decode_attn(ctx._h, _stream_ptr(stream), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                       _ptr(new_flags), pos, Hq, scale, C.byref(cache.c), _ptr(out)))
+    ctx._check(ctx._native.decode_attn(ctx._addr, stream, q, k_new, v_new, new_flags, pos, scale, cache.c, None, out))
 
 
 def ag_decode_attn_static(ctx: Context, q, k_new, v_new, new_flags, pos: int, scale: float, cache: KVCache, out,
                           stream=None) -> None:
     """ag_decode_attn out of the library's static per-GPU scratch array: allocates nothing, needs no workspace."""
-    Hq = q.shape[1]
-    ctx._check(ctx._lib.ag_decode_attn_static(ctx._h, _stream_ptr(stream), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                              _ptr(new_flags), pos, Hq, scale, C.byref(cache.c), _ptr(out)))
+    ctx._check(ctx._native.decode_attn_static(ctx._addr, stream, q, k_new, v_new, new_flags, pos, scale, cache.c,
+                                              out))
 
 
 def decode_static_scratch_bytes() -> int:
@@ -346,18 +329,14 @@ class RecentRing:
 
 def ag_recent_fill(ctx: Context, k, v, flags, pos0: int, ring: RecentRing, stream=None) -> None:
     """k, v [B, Hkv, L, D], flags u8 [B, Hkv, L]: the ring takes the last prompt tokens."""
-    B, Hkv, L, D = k.shape
-    ctx._check(ctx._lib.ag_recent_fill(ctx._h, _stream_ptr(stream), _ptr(k), _ptr(v), _ptr(flags), B, L, Hkv, D,
-                                       _dtype_code(k), pos0, C.byref(ring.c)))
+    ctx._check(ctx._native.recent_fill(ctx._addr, stream, k, v, flags, pos0, ring.c))
 
 
 def ag_decode_attn_recent(ctx: Context, q, k_new, v_new, new_flags, pos: int, scale: float, cache: KVCache,
                           ring: Optional[RecentRing], out, stream=None) -> None:
     """ag_decode_attn with the evicted tokens of the ring's window visible; the ring then takes the new token."""
-    Hq = q.shape[1]
-    ctx._check(ctx._lib.ag_decode_attn_recent(ctx._h, _stream_ptr(stream), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                              _ptr(new_flags), pos, Hq, scale, C.byref(cache.c),
-                                              C.byref(ring.c) if ring is not None else None, _ptr(out)))
+    ctx._check(ctx._native.decode_attn(ctx._addr, stream, q, k_new, v_new, new_flags, pos, scale, cache.c,
+                                       ring.c if ring is not None else None, out))
 
 
 def gate_mha_workspace_bytes(B: int, L: int, d_model: int, h_prime: int, d_prime: int, H_f: int) -> int:
@@ -368,8 +347,5 @@ def ag_gate_mha(ctx: Context, x, w_qkv, h_prime: int, d_prime: int, w_o, bias, t
                 flags_out, stream=None) -> None:
     """The paper's main gate: x [B, L, d]; w_qkv [d, 3*h'*d'] (Q'|K'|V', head-major inside); w_o [h'*d', H_f];
     bias f32 [H_f]; logits_out f32 [B, L, H_f] or None; flags_out u8 [B, H_f, L]."""
-    B, L, d = x.shape
-    H_f = w_o.shape[1]
-    ctx._check(ctx._lib.ag_gate_mha(ctx._h, _stream_ptr(stream), _ptr(x), _dtype_code(x), B, L, d, _ptr(w_qkv),
-                                    h_prime, d_prime, _ptr(w_o), _ptr(bias), H_f, tau, n_sink, _ptr(logits_out),
-                                    _ptr(flags_out)))
+    ctx._check(ctx._native.gate_mha(ctx._addr, stream, x, w_qkv, h_prime, d_prime, w_o, bias, tau, n_sink,
+                                    logits_out, flags_out))
