@@ -1,77 +1,90 @@
-// Decode attention over ragged per-(batch, KV head) caches (Sec. 3.1, decoding stage) -- split-K.
+// Decode attention over ragged per-(batch, KV head) caches (Sec. 3.1, decoding stage), one launch per step.
 //
-// The step is bandwidth-bound: every cached K and V row is read once.  Work is cut into items of kChunk rows
-// of one unit; the item list is built on the device from len[] (no host read-back), and a persistent grid
-// walks it round-robin.  Inside an item each group of LPR lanes owns one row per load (16 bytes per lane, a
-// wave reads 1 KiB of contiguous rows per instruction), keeps an online-softmax state per query head of the
-// group, and the states are merged through LDS into one (max, sum, weighted-V) record per item and head.
-// A second kernel merges the records of each (batch, query head) with the new token's own key/value -- the
-// diagonal of Eq. 5 -- normalises, and appends the new row to the cache when its flag says so.
+// A step reads every cached K and V row once: large batches are bound by HBM, small ones by the number of dependent
+// round trips.  The kernel therefore does everything in one launch -- it builds its own work list from len[] (no host
+// read-back), streams the rows, merges, takes in the new token and appends it -- and hands data between workgroups only
+// where a unit is too long for one.
+//   * Work is counted in tiles of 32 rows of one unit; a wave takes every NW-th tile of its workgroup's segment, so the
+//     waves run without a barrier until their segment ends.  The new token's own key and value (the diagonal of
+//     Eq. 5) and the slots of the recent-token ring are extra tiles in front of a unit's cache rows.
+//   * bf16 runs on MFMA: K and V rows go from memory to the wave's own LDS by direct loads (whole 256-byte rows; the next
+//     tile's K is requested as soon as this tile's fragments are read, its V after the second product, so 8 to 16 KiB per
+//     wave are always in flight and no register holds them), S^T = K q^T and O^T = V^T p^T for all G query heads of the
+//     group at once.  p enters the second product as a bf16 pair (high part + remainder, two MFMAs): the weights keep 16
+//     bits, as a 32-bit product would.  fp32 caches run on the vector ALU.
+//   * Segments (what a workgroup works on between two merges) are chosen on the device.  If the whole step gives every
+//     workgroup at most one segment -- a unit of up to 4 rounds of its waves stays whole, a longer one is cut into
+//     pieces of two rounds -- a unit's pieces meet once; otherwise the tiles of all units are laid end to end and cut
+//     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.
+//   * A unit inside one workgroup is finished there, through LDS.  The pieces of a longer one are stored as records
+//     (written through, complete before the arrival is counted); the piece that arrives last merges them in order.
+#include <algorithm>
+#include <atomic>
 #include <mutex>
 
 #include "ag_internal.h"
 
-// Scratch of ag_decode_attn_static, the entry point for callers that cannot allocate: the per-item records the
-// two decode kernels exchange live here instead of in a context's workspace.  One copy per GPU, held until the
+// Scratch of ag_decode_attn_static, the entry point for callers that cannot allocate: the records that the pieces of a
+// unit exchange live here instead of in a context's workspace.  One copy per GPU, held until the
 // process ends.  In host code this name is only a stand-in for the symbol; the device address comes from
 // hipGetSymbolAddress (ag_static_scratch below) and is what every launch receives.
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 
-constexpr int kChunk = 128;      // rows per work item
-constexpr int kWgsPerCu = 2;     // persistent workgroups per CU (measured on 1024 ragged caches: 2 -> 5.7 TB/s,
-                                 // 3 -> 5.3, 4 -> 5.4, 1 -> 4.6; fewer concurrent streams keep DRAM pages open)
-constexpr int kMaxUnits = 8192;  // units whose item offsets fit in LDS
+constexpr int kChunk = 128;      // cache rows per record of scratch space (ag_decode_scratch_bytes)
+constexpr int kTileRows = 32;    // rows a wave takes at a time
+constexpr int kFewUnits = 256;   // up to here 8 waves per workgroup and one workgroup per CU: a unit's rows are spread over
+                                 // as many waves as LDS can feed; beyond, 4 waves and two workgroups per CU, so that one
+                                 // streams while the other merges
+constexpr float kEmptyMax = -1.0e30f;  // reference maximum before any row (finite on purpose)
 constexpr float kLog2e = 1.4426950408889634f;
 
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t nt_u32x4;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float nt_f32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+#define AG_LDS __attribute__((address_space(3)))
 
-template <typename T> struct elems;  // element count, widening and dot product of one 16-byte vector
-template <> struct elems<float> {
-  static constexpr int n = 4;
-  static __device__ __forceinline__ void widen(const uint4 &r, float *f) {
-    f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y); f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);
-  }
-  static __device__ __forceinline__ float dot(const uint4 &a, const uint4 &b) {
-    float d = __uint_as_float(a.x) * __uint_as_float(b.x);
-    d = fmaf(__uint_as_float(a.y), __uint_as_float(b.y), d);
-    d = fmaf(__uint_as_float(a.z), __uint_as_float(b.z), d);
-    return fmaf(__uint_as_float(a.w), __uint_as_float(b.w), d);
-  }
-};
-template <> struct elems<uint16_t> {  // bf16 bit patterns
-  static constexpr int n = 8;
-  static __device__ __forceinline__ void widen(const uint4 &r, float *f) {
-    f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
-    f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
-    f[4] = __uint_as_float(r.z << 16); f[5] = __uint_as_float(r.z & 0xffff0000u);
-    f[6] = __uint_as_float(r.w << 16); f[7] = __uint_as_float(r.w & 0xffff0000u);
-  }
-  // 8 bf16 products summed in fp32 by v_dot2c_f32_bf16, two per instruction, without widening either operand
-  static __device__ __forceinline__ float dot(const uint4 &a, const uint4 &b) {
-    float d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.x), __builtin_bit_cast(bf16x2, b.x), 0.f, false);
-    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.y), __builtin_bit_cast(bf16x2, b.y), d, false);
-    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.z), __builtin_bit_cast(bf16x2, b.z), d, false);
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.w), __builtin_bit_cast(bf16x2, b.w), d, false);
-  }
-};
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  const f32x2 x = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+}
 
-__device__ __forceinline__ float widen1(float x) { return x; }
-__device__ __forceinline__ float widen1(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
-__device__ __forceinline__ void narrow1(float x, float *o) { *o = x; }
-__device__ __forceinline__ void narrow1(float x, uint16_t *o) {  // round to nearest even
+__device__ __forceinline__ void to_bf16(float x, uint16_t *o) {  // round to nearest even
   uint32_t u = __float_as_uint(x);
   u += 0x7fffu + ((u >> 16) & 1u);
   *o = (uint16_t)(u >> 16);
 }
 
-// valid rows of a unit, never more than its slab holds
-__device__ __forceinline__ int unit_len(const int32_t *__restrict__ len, const int64_t *__restrict__ row_off, int u) {
-  const int64_t cap = row_off[u + 1] - row_off[u];
-  const int n = len[u];
-  return n < 0 ? 0 : (n < cap ? n : (int)cap);
+// 16 bytes that may (loose) lie at any even address
+__device__ __forceinline__ uint4 chunk16(const uint8_t *p, bool loose) {
+  if (!loose) return *reinterpret_cast<const uint4 *>(p);
+  const uint16_t *h = reinterpret_cast<const uint16_t *>(p);
+  auto two = [&](int i) { return (uint32_t)h[i] | ((uint32_t)h[i + 1] << 16); };
+  return make_uint4(two(0), two(2), two(4), two(6));
+}
+__device__ __forceinline__ void put16(uint8_t *p, const uint4 &x, bool loose) {
+  if (!loose) {
+    *reinterpret_cast<uint4 *>(p) = x;
+    return;
+  }
+  uint16_t *h = reinterpret_cast<uint16_t *>(p);
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { h[2 * i] = (uint16_t)w[i]; h[2 * i + 1] = (uint16_t)(w[i] >> 16); }
+}
+// a pair of floats written through to memory / read past the caches (see ag_internal.h on data between workgroups)
+__device__ __forceinline__ void put_pair(float *p, float a, float b) {
+  __hip_atomic_store(reinterpret_cast<uint64_t *>(p), (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ float2 get_pair(const float *p) {
+  const uint64_t x = __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return make_float2(__uint_as_float((uint32_t)x), __uint_as_float((uint32_t)(x >> 32)));
 }
 
 template <int CTRL> __device__ __forceinline__ float dpp(float x) {
@@ -89,319 +102,540 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Kernel 1: per-item partial attention.
-//   item_off [U+1] (global copy for the merge kernel), pm/pl [items*G], pacc [items*G, D]
-template <typename T, int D, int G>
-__global__ __launch_bounds__(256) void ag_decode_partial_kernel(const T *__restrict__ q, const T *__restrict__ kc,
-                                                                const T *__restrict__ vc,
-                                                                const int64_t *__restrict__ row_off,
-                                                                const int32_t *__restrict__ len, int U, int Hkv,
-                                                                int meta_lds, int grid_stream, float qscale,
-                                                                int32_t *__restrict__ item_off_g,
-                                                                float *__restrict__ pm, float *__restrict__ pl,
-                                                                float *__restrict__ pacc) {
-  constexpr int EPL = elems<T>::n;        // elements per lane
-  constexpr int LPR = D / EPL;            // lanes per row
-  constexpr int GPW = 64 / LPR;           // rows per wave load
-  constexpr int NST = 4 * GPW;            // online-softmax states per block
-  constexpr int NIT = kChunk / 4 / GPW;   // loads that cover a wave's quarter of an item
-  constexpr int UN = (G <= 2 ? 8 : 4) < NIT ? (G <= 2 ? 8 : 4) : NIT;  // rows in flight per lane group
-  static_assert(NIT % UN == 0, "a wave's rows must be a whole number of batches");
-  extern __shared__ int32_t smem[];
-  int32_t *item_off = smem;               // [U+1]
-  int32_t *scan = smem + (U + 1);         // [256]
-  float *st = reinterpret_cast<float *>(scan + 256);  // [NST][G][D+2]
-  // with few enough units their lengths and slab offsets also live in LDS, so that starting an item costs no
-  // round trip to memory
-  int32_t *s_len = reinterpret_cast<int32_t *>(st + (size_t)NST * G * (D + 2));  // [U]     (meta_lds)
-  int64_t *s_ro = reinterpret_cast<int64_t *>((reinterpret_cast<uintptr_t>(s_len + U) + 7) & ~uintptr_t(7));  // [U]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// LDS address key of row r of a wave's tile: the row's 16-byte chunk c lies at position c ^ key(r).  Among 16
+// consecutive rows all keys differ (K fragments: 16 rows, one chunk), and among the 8 rows that a transposing V read
+// serves together all pairs of chunks differ.  (D = 64: a row covers half of the banks, odd rows the other half.)
+template <int D> __device__ __forceinline__ int tile_key(int r) {
+  return D == 128 ? (((r & 7) << 1) | ((r >> 3) & 1)) : ((((r >> 1) & 3) << 1) | ((r >> 3) & 1));
+}
 
-  // ---- item offsets: exclusive scan of ceil(len/kChunk) over units ----
-  const int per = (U + 255) / 256;
-  const int u0 = tid * per, u1 = min(U, u0 + per);
-  int32_t sum = 0;
-  for (int u = u0; u < u1; ++u) {
-    const int n_u = unit_len(len, row_off, u);
-    if (meta_lds) { s_len[u] = n_u; s_ro[u] = row_off[u]; }
-    sum += (n_u + kChunk - 1) / kChunk;
-  }
-  // exclusive scan over the 256 threads: inside a wave by shuffles, across the four waves through LDS (one barrier)
-  int32_t incl = sum;
+// What a tile reads: rows row0 .. row0 + 31 of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
+struct dec_tile {
+  const void *k, *v;  // first row of the array the tile belongs to
+  uint32_t bytes;     // cache rows: size of the array (rows past its end read as zeros)
+  int row0;
+  uint32_t vis;
+  bool extra;         // new token or ring: rows whose bit is clear are not even read (they may hold anything)
+};
+
+// ---- bf16: one wave's pass over its tiles on MFMA -----------------------------------------------------------
+// Lane = (query head q = lane % 16, key group kg = lane / 16); heads q >= G are zero columns.
+template <int D, int G> struct wave_bf16 {
+  static constexpr int kRowB = D * 2, CPR = kRowB / 16, RPI = 64 / CPR;  // RPI rows per load instruction
+  static constexpr int NL = kTileRows / RPI;                             // load instructions per tile and operand
+  static constexpr int kWaveB = 2 * kTileRows * kRowB;                   // the wave's LDS: K tile, V tile
+  static constexpr int kStates = 1, kStateF = D + 4;                     // merge states a wave leaves, floats per head
+  static constexpr int KS = D / 32, DT = D / 16;
+  bf16x8 qf[KS];
+  f32x4 o[DT];
+  float m, l;
+  int ld_off[NL], k_off[KS], v_off[DT];
+  uint32_t lds_addr;
+  AG_LDS uint8_t *lds;
+  int lane, kg, col;
+
+  __device__ __forceinline__ void init(AG_LDS uint8_t *mem, int lane_) {
+    lane = lane_; kg = lane >> 4; col = lane & 15;
+    lds = mem;
+    lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)mem);
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int32_t up = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += up;
-  }
-  if (lane == 63) scan[wave] = incl;
-  __syncthreads();
-  int32_t run = incl - sum;
-  for (int w = 0; w < wave; ++w) run += scan[w];
-  for (int u = u0; u < u1; ++u) {
-    item_off[u] = run;
-    run += (unit_len(len, row_off, u) + kChunk - 1) / kChunk;
-  }
-  if (tid == 255) item_off[U] = scan[0] + scan[1] + scan[2] + scan[3];
-  __syncthreads();
-  const int n_items = item_off[U];
-  if (blockIdx.x == 0)
-    for (int u = tid; u <= U; u += 256) item_off_g[u] = item_off[u];
-
-  const int grp = lane / LPR, seg = lane % LPR;
-  // The launch holds more workgroups than the streaming regime wants (grid_stream = kWgsPerCu per CU).  If every
-  // item can have a workgroup of its own, it gets one -- a small step is one round of loads instead of two; else
-  // only the first grid_stream workgroups walk the list.
-  const int n_wg = n_items <= (int)gridDim.x ? n_items : min((int)gridDim.x, grid_stream);
-  if ((int)blockIdx.x >= n_wg) return;
-  for (int item = blockIdx.x; item < n_items; item += n_wg) {
-    // unit of this item: last u with item_off[u] <= item
-    int lo = 0, hi = U;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (item_off[mid] <= item) lo = mid; else hi = mid;
+    for (int i = 0; i < NL; ++i) {
+      const int r = RPI * i + lane / CPR;
+      ld_off[i] = r * kRowB + (((lane % CPR) ^ tile_key<D>(r)) << 4);
     }
-    const int u = lo;
-    const int c = item - item_off[u];
-    const int b = u / Hkv, g = u - b * Hkv;
-    const int n = meta_lds ? s_len[u] : unit_len(len, row_off, u);
-    const int64_t ro = meta_lds ? s_ro[u] : row_off[u];
-    const int row_end = min(n, (c + 1) * kChunk);
-    const int wrow0 = c * kChunk + wave * (kChunk / 4);
-    const uint4 *K = reinterpret_cast<const uint4 *>(kc + (size_t)ro * D);
-    const uint4 *V = reinterpret_cast<const uint4 *>(vc + (size_t)ro * D);
-
-    uint4 qr[G];  // this lane's 16 bytes of each query row, as stored; the score is scaled after the sum
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) qr[gg] = reinterpret_cast<const uint4 *>(q + ((size_t)(b * Hkv + g) * G + gg) * D)[seg];
-    float m[G], l[G], acc[G][EPL];
+    for (int ks = 0; ks < KS; ++ks) k_off[ks] = col * kRowB + (((4 * ks + kg) ^ tile_key<D>(col)) << 4);
+    const int vr = 4 * kg + (col >> 2);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+      v_off[dt] = vr * kRowB + (((2 * dt + ((col & 3) >> 1)) ^ tile_key<D>(vr)) << 4) + (col & 1) * 8;
+  }
+  // q: the G query rows of the unit
+  __device__ __forceinline__ void begin(const uint16_t *q) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 x = make_uint4(0, 0, 0, 0);
+      if (col < G) x = *reinterpret_cast<const uint4 *>(q + (size_t)col * D + 32 * ks + 8 * kg);
+      qf[ks] = __builtin_bit_cast(bf16x8, x);
+    }
+    m = kEmptyMax; l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // Cache rows of one operand straight into LDS; rows past the array arrive as zeros.  Every cached row is read once per
+  // step: non-temporal, so that the stream does not push the small hot data (queries, lengths, records) out of the caches.
+  __device__ __forceinline__ void load(const dec_tile &t, const void *base, uint32_t dst) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, t.bytes, 0x00020000);
+    const int soff = t.row0 * kRowB;
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "memory");
+  }
+  // The new token's row or ring slots, through registers: only the visible rows are read, the others become zeros.
+  __device__ __forceinline__ void load_extra(const dec_tile &t, bool loose) {
+    uint4 x[2][NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const bool see = (t.vis >> (RPI * i + lane / CPR)) & 1u;
+#pragma unroll
+      for (int kv = 0; kv < 2; ++kv) {
+        x[kv][i] = make_uint4(0, 0, 0, 0);
+        if (see) x[kv][i] = chunk16(static_cast<const uint8_t *>(kv ? t.v : t.k) + (size_t)t.row0 * kRowB + ld_off[i], loose);
+      }
+    }
+#pragma unroll
+    for (int kv = 0; kv < 2; ++kv)
+#pragma unroll
+      for (int i = 0; i < NL; ++i)
+        *reinterpret_cast<AG_LDS u32x4 *>(lds + (kv * kTileRows + i * RPI) * kRowB + lane * 16) =
+            u32x4{x[kv][i].x, x[kv][i].y, x[kv][i].z, x[kv][i].w};
+  }
+  __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, lds_addr); }
+  __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, lds_addr + kTileRows * kRowB); }
+
+  // tiles first, first + step, ... < last of the segment; get(i) describes tile i
+  // (a tile that is not cache rows can only be a wave's first: there are fewer of them than waves)
+  template <typename GET> __device__ __forceinline__ void run(int first, int last, int step, float qscale, bool loose, GET &&get) {
+    if (first >= last) return;
+    dec_tile t = get(first);
+    if (t.extra) {
+      load_extra(t, loose);
+    } else {
+      load_k(t);
+      load_v(t);
+    }
+    // the query's loads are waited for here, once: the compiler would otherwise put a wait for everything into the loop
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
+    for (int i = first; i < last; i += step) {
+      const bool more = i + step < last;
+      const uint32_t vis = t.vis;
+      if (more) t = get(i + step);
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NL) : "memory");  // K has landed (V, requested after it, may not have)
+      bf16x8 kf[2][KS];
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          kf[sub][ks] = *reinterpret_cast<const AG_LDS bf16x8 *>(lds + sub * 16 * kRowB + k_off[ks]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (more) load_k(t);
+      f32x4 s[2];
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) {
+        s[sub] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s[sub] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[sub][ks], qf[ks], s[sub], 0, 0, 0);
+      }
+      // s[sub][r]: key 16 sub + 4 kg + r, head col
+      float p[8], mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        p[e] = s[e >> 2][e & 3] * qscale;
+        if (vis != 0xffffffffu && !((vis >> (16 * (e >> 2) + 4 * kg + (e & 3))) & 1u)) p[e] = -INFINITY;
+        mx = fmaxf(mx, p[e]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      if (__any(m_new != m)) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
+      }
+      m = m_new;
+      l *= alpha;
+      float lo[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        p[e] = __builtin_amdgcn_exp2f(p[e] - m);
+        l += p[e];
+      }
+      uint4 ph = make_uint4(pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7]));
+      const uint32_t hw[4] = {ph.x, ph.y, ph.z, ph.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[2 * e] = p[2 * e] - __uint_as_float(hw[e] << 16);
+        lo[2 * e + 1] = p[2 * e + 1] - __uint_as_float(hw[e] & 0xffff0000u);
+      }
+      const uint4 pl = make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(lo[4], lo[5]), pack2(lo[6], lo[7]));
+      if (more)
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NL) : "memory");  // V has landed (the next K may not have)
+      else
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      bf16x8 vf[DT];  // row d = 16 dt + col of V^T, keys 4 kg + 0..3 and 16 + 4 kg + 0..3
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const AG_LDS uint8_t *base = lds + kTileRows * kRowB + v_off[dt];
+        const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)base);
+        const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(base + 16 * kRowB));
+        vf[dt] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (more) load_v(t);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], __builtin_bit_cast(bf16x8, ph), o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], __builtin_bit_cast(bf16x8, pl), o[dt], 0, 0, 0);
+      }
+    }
+  }
+  // the wave's state into its LDS: per head [max, sum, -, -, o[0..D)]
+  __device__ __forceinline__ void leave(AG_LDS float *st) {
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (col < G) {
+      AG_LDS float *h = st + col * kStateF;
+      if (kg == 0) { h[0] = m; h[1] = l; }
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<AG_LDS f32x4 *>(h + 4 + 16 * dt + 4 * kg) = o[dt];
+    }
+  }
+};
+
+// ---- fp32: one wave's pass on the vector ALU; each group of LPR lanes owns one row per load -------------------
+template <int D, int G> struct wave_f32 {
+  static constexpr int EPL = 4, LPR = D / EPL, GPW = 64 / LPR;   // lanes per row, rows per load
+  static constexpr int NIT = kTileRows / GPW;                    // loads that cover a tile
+  static constexpr int UN = (G <= 2 ? 8 : 4) < NIT ? (G <= 2 ? 8 : 4) : NIT;  // rows in flight per lane group
+  static constexpr int kStates = GPW, kStateF = D + 4;
+  static constexpr int kWaveB = GPW * G * kStateF * 4;
+  float4 qr[G];
+  float m[G], l[G], acc[G][EPL];
+  int grp, seg;
+  __device__ __forceinline__ void init(AG_LDS uint8_t *, int lane) { grp = lane / LPR; seg = lane % LPR; }
+  __device__ __forceinline__ void begin(const float *q) {
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) {
-      m[gg] = -INFINITY; l[gg] = 0.f;
+      qr[gg] = reinterpret_cast<const float4 *>(q + (size_t)gg * D)[seg];
+      m[gg] = kEmptyMax; l[gg] = 0.f;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[gg][e] = 0.f;
     }
-
-    for (int it0 = 0; it0 < NIT; it0 += UN) {
-      if (wrow0 + it0 * GPW >= row_end) break;  // wave-uniform
-      uint4 kk[UN], vv[UN];
-      bool ok[UN];
+  }
+  template <typename GET> __device__ __forceinline__ void run(int first, int last, int step, float qscale, bool, GET &&get) {
+    for (int i = first; i < last; i += step) {
+      const dec_tile t = get(i);
+      const nt_f32x4 *K = reinterpret_cast<const nt_f32x4 *>(t.k) + (size_t)t.row0 * LPR + seg;
+      const nt_f32x4 *V = reinterpret_cast<const nt_f32x4 *>(t.v) + (size_t)t.row0 * LPR + seg;
+      for (int it0 = 0; it0 < NIT; it0 += UN) {
+        nt_f32x4 kk[UN], vv[UN];
+        bool ok[UN];
 #pragma unroll
-      for (int j = 0; j < UN; ++j) {
-        const int r = wrow0 + (it0 + j) * GPW + grp;
-        ok[j] = r < row_end;
-        kk[j] = make_uint4(0, 0, 0, 0);
-        vv[j] = make_uint4(0, 0, 0, 0);
-        if (ok[j]) {  // every cached row is read exactly once per step: non-temporal, so that the stream does not
-                      // push the small hot data (queries, lengths, item records) out of the caches (measured on 1024
-                      // ragged caches: 200.7 -> 190.4 us per step, and the merge kernel 8.5 -> 6.5 us)
-          const nt_u32x4 kx = __builtin_nontemporal_load(reinterpret_cast<const nt_u32x4 *>(&K[(size_t)r * LPR + seg]));
-          const nt_u32x4 vx = __builtin_nontemporal_load(reinterpret_cast<const nt_u32x4 *>(&V[(size_t)r * LPR + seg]));
-          kk[j] = make_uint4(kx[0], kx[1], kx[2], kx[3]);
-          vv[j] = make_uint4(vx[0], vx[1], vx[2], vx[3]);
+        for (int j = 0; j < UN; ++j) {
+          const int r = (it0 + j) * GPW + grp;
+          ok[j] = (t.vis >> r) & 1u;
+          kk[j] = vv[j] = nt_f32x4{0.f, 0.f, 0.f, 0.f};
+          if (ok[j]) {
+            kk[j] = __builtin_nontemporal_load(K + (size_t)r * LPR);
+            vv[j] = __builtin_nontemporal_load(V + (size_t)r * LPR);
+          }
         }
-      }
-      float s[G][UN];
-#pragma unroll
-      for (int j = 0; j < UN; ++j) {
 #pragma unroll
         for (int gg = 0; gg < G; ++gg) {
-          const float d = group_sum<LPR>(elems<T>::dot(qr[gg], kk[j])) * qscale;
-          s[gg][j] = ok[j] ? d : -INFINITY;
-        }
-      }
+          float s[UN], mn = m[gg];
 #pragma unroll
-      for (int gg = 0; gg < G; ++gg) {
-        float mn = m[gg];
+          for (int j = 0; j < UN; ++j) {
+            float d = qr[gg].x * kk[j][0];
+            d = fmaf(qr[gg].y, kk[j][1], d);
+            d = fmaf(qr[gg].z, kk[j][2], d);
+            d = fmaf(qr[gg].w, kk[j][3], d);
+            d = group_sum<LPR>(d) * qscale;
+            s[j] = ok[j] ? d : -INFINITY;
+            mn = fmaxf(mn, s[j]);
+          }
+          const float alpha = exp2f(m[gg] - mn);
+          m[gg] = mn;
+          l[gg] *= alpha;
 #pragma unroll
-        for (int j = 0; j < UN; ++j) mn = fmaxf(mn, s[gg][j]);
-        if (mn == -INFINITY) continue;  // this lane group has seen no valid row yet
-        const float alpha = exp2f(m[gg] - mn);  // m = -inf -> 0
-        m[gg] = mn;
-        l[gg] *= alpha;
+          for (int e = 0; e < EPL; ++e) acc[gg][e] *= alpha;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[gg][e] *= alpha;
+          for (int j = 0; j < UN; ++j) {
+            const float p = exp2f(s[j] - mn);
+            l[gg] += p;
 #pragma unroll
-        for (int j = 0; j < UN; ++j) s[gg][j] = exp2f(s[gg][j] - mn);  // -inf -> 0
-      }
-#pragma unroll
-      for (int j = 0; j < UN; ++j) {
-        float vf[EPL];
-        elems<T>::widen(vv[j], vf);
-#pragma unroll
-        for (int gg = 0; gg < G; ++gg) {
-          const float p = m[gg] == -INFINITY ? 0.f : s[gg][j];
-          l[gg] += p;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[gg][e] = fmaf(p, vf[e], acc[gg][e]);
+            for (int e = 0; e < EPL; ++e) acc[gg][e] = fmaf(p, vv[j][e], acc[gg][e]);
+          }
         }
       }
     }
-
-    // ---- merge the NST states of the block ----
-    const int sidx = wave * GPW + grp;
+  }
+  __device__ __forceinline__ void leave(AG_LDS float *st) {
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) {
-      float *rec = st + ((size_t)sidx * G + gg) * (D + 2);
-      if (seg == 0) { rec[0] = m[gg]; rec[1] = l[gg]; }
+      AG_LDS float *h = st + (grp * G + gg) * kStateF;
+      if (seg == 0) { h[0] = m[gg]; h[1] = l[gg]; }
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) rec[2 + seg * EPL + e] = acc[gg][e];
+      for (int e = 0; e < EPL; ++e) h[4 + seg * EPL + e] = acc[gg][e];
     }
-    __syncthreads();
-    for (int o = tid; o < G * D; o += 256) {
-      const int gg = o / D, d = o - gg * D;
-      float M = -INFINITY;
+  }
+};
+template <typename T, int D, int G> struct wave_of;
+template <int D, int G> struct wave_of<uint16_t, D, G> { typedef wave_bf16<D, G> type; };
+template <int D, int G> struct wave_of<float, D, G> { typedef wave_f32<D, G> type; };
+
+struct dec_args {
+  const void *q, *k_new, *v_new;
+  const uint8_t *new_flags;
+  void *kc, *vc;
+  int32_t *idx;
+  const int64_t *row_off;
+  int32_t *len;
+  void *out;
+  float *rec;           // records [id][G][D + 2]: o, max, sum
+  int32_t *tickets;     // [U] pieces of a unit that have stored their record; zero between launches
+  int32_t *arrived;     // [1] workgroups that have read len[]; zero between launches
+  int32_t *d_err;
+  int U, pos, max_wgs;  // max_wgs: workgroups the equal-range split may use (two records each)
+  float qscale;
+  bool loose;           // k_new, v_new, the ring or out are not 16-byte aligned: they are accessed by elements
+  ag_ring_dev ring;
+};
+
+template <typename T, int D, int G, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
+  typedef typename wave_of<T, D, G>::type wave_t;
+  constexpr int NT = 64 * NW, SF = wave_t::kStateF;
+  constexpr int kPieceTiles = 2 * NW, kWholeTiles = 4 * NW;
+  constexpr int CPT = (int)(D * sizeof(T) / 16);  // 16-byte chunks per row
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  int32_t *s_len = reinterpret_cast<int32_t *>(smem + NW * wave_t::kWaveB);  // [U] valid rows; top bit: the unit has room
+  __shared__ int32_t w_tiles[NW], w_items[NW], s_start[2], s_last;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int U = a.U;
+  const bool has_ring = a.ring.k != nullptr;
+  const int extra = 1 + (has_ring ? (a.ring.n + kTileRows - 1) / kTileRows : 0);
+
+  // ---- the work list: tiles per unit, and the pieces they would be cut into ----
+  const int per = (U + NT - 1) / NT;
+  const int u0 = min(U, tid * per), u1 = min(U, u0 + per);
+  auto tiles_of = [&](int n) { return extra + (n + kTileRows - 1) / kTileRows; };
+  auto pieces_of = [&](int t) { return t <= kWholeTiles ? 1 : (t + kPieceTiles - 1) / kPieceTiles; };
+  int my_tiles = 0, my_items = 0;
+  for (int u = u0; u < u1; ++u) {
+    const int64_t cap = a.row_off[u + 1] - a.row_off[u];
+    const int n_raw = a.len[u];
+    const int n = n_raw < 0 ? 0 : (n_raw < cap ? n_raw : (int)cap);
+    s_len[u] = n | (n < cap ? 0x80000000 : 0);
+    const int t = tiles_of(n);
+    my_tiles += t;
+    my_items += pieces_of(t);
+  }
+  int inc_t = my_tiles, inc_i = my_items;
 #pragma unroll
-      for (int sI = 0; sI < NST; ++sI) M = fmaxf(M, st[((size_t)sI * G + gg) * (D + 2)]);
-      float L = 0.f, A = 0.f;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc_t, o, 64), i = __shfl_up(inc_i, o, 64);
+    if (lane >= o) { inc_t += t; inc_i += i; }
+  }
+  if (lane == 63) { w_tiles[wave] = inc_t; w_items[wave] = inc_i; }
+  __syncthreads();  // (every thread's reads of len[] are complete here: the scan has consumed them)
+  // The lengths may only change once every workgroup has read them: the workgroup that arrives last does it, at its end.
+  int order = 0;
+  if (tid == 0) order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int base_t = inc_t - my_tiles, base_i = inc_i - my_items, total_t = 0, total_i = 0;
 #pragma unroll
-      for (int sI = 0; sI < NST; ++sI) {
-        const float *rec = st + ((size_t)sI * G + gg) * (D + 2);
-        const float w = rec[0] == -INFINITY ? 0.f : exp2f(rec[0] - M);
-        L = fmaf(w, rec[1], L);
-        A = fmaf(w, rec[2 + d], A);
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) { base_t += w_tiles[w]; base_i += w_items[w]; }
+    total_t += w_tiles[w];
+    total_i += w_items[w];
+  }
+  const bool by_piece = total_i <= (int)gridDim.x;
+  const int wg = blockIdx.x;
+  // equal ranges of tiles: at most max_wgs of them
+  const int quota = by_piece ? 0 : (total_t + min((int)gridDim.x, a.max_wgs) - 1) / min((int)gridDim.x, a.max_wgs);
+  const int x = by_piece ? wg : wg * quota;  // the piece or the tile this workgroup starts at
+  const bool idle = by_piece ? x >= total_i : x >= total_t;
+  if (!idle) {
+    const int base = by_piece ? base_i : base_t;
+    if (base <= x && x < base + (by_piece ? my_items : my_tiles)) {  // exactly one thread
+      int at = base, u = u0;
+      for (;; ++u) {
+        const int t = tiles_of(s_len[u] & 0x7fffffff), n = by_piece ? pieces_of(t) : t;
+        if (x < at + n) break;
+        at += n;
       }
-      const size_t pr = (size_t)item * G + gg;
-      pacc[pr * D + d] = A;
-      if (d == 0) { pm[pr] = M; pl[pr] = L; }
+      s_start[0] = u;
+      s_start[1] = x - at;  // piece or tile inside the unit
     }
-    __syncthreads();
   }
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// Kernel 2: one block per (batch, query head): merge item records + the new token itself, write out, append.
-template <typename T, int D>
-__global__ __launch_bounds__(D) void ag_decode_merge_kernel(const T *__restrict__ q, const T *__restrict__ k_new,
-                                                            const T *__restrict__ v_new,
-                                                            const uint8_t *__restrict__ new_flags, int pos, int Hq,
-                                                            int Hkv, float qscale,
-                                                            const int32_t *__restrict__ item_off,
-                                                            const float *__restrict__ pm, const float *__restrict__ pl,
-                                                            const float *__restrict__ pacc, T *__restrict__ kc,
-                                                            T *__restrict__ vc, int32_t *__restrict__ idx,
-                                                            const int64_t *__restrict__ row_off,
-                                                            int32_t *__restrict__ len, T *__restrict__ out,
-                                                            int32_t *__restrict__ d_err, ag_ring_dev ring) {
-  __shared__ float red[D / 64 > 0 ? D / 64 : 1];
-  __shared__ float wts[64];
-  const int G = Hq / Hkv;
-  const int bi = blockIdx.x;  // b * Hq + i
-  const int b = bi / Hq, i = bi - b * Hq;
-  const int g = i / G, gg = i - g * G;
-  const int u = b * Hkv + g;
-  const int d = threadIdx.x, lane = d & 63;
-  // Everything that does not depend on another load is requested here, in one round trip: the launch is short and
-  // latency-bound, so the number of dependent round trips is its cost.
-  const T kn_raw = k_new[(size_t)u * D + d], vn_raw = v_new[(size_t)u * D + d];
-  const float kn = widen1(kn_raw), vn = widen1(vn_raw);
-  const float qd = widen1(q[(size_t)bi * D + d]) * qscale;
-  const int i0 = item_off[u], i1 = item_off[u + 1];
-  const bool keep_new = new_flags == nullptr || new_flags[u] != 0;
-  const int n_len = len[u];
-  const int64_t r0 = row_off[u], cap = row_off[u + 1] - r0;
-
-  // A batch of up to 64 item records: lane j takes the maximum and sum of record base + j; every thread also
-  // requests its column of the batch's first 8 records, so that they travel together with the maxima.
-  auto request = [&](int base, float &mj, float &lj, float (&x)[8]) {
-    const int n = min(64, i1 - base);
-    const size_t pr = (size_t)(base + lane) * G + gg;
-    mj = lane < n ? pm[pr] : -INFINITY;
-    lj = lane < n ? pl[pr] : 0.f;
-    const float *col = pacc + ((size_t)base * G + gg) * D + d;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = e < n ? col[(size_t)e * G * D] : 0.f;
-  };
-  float mj = -INFINITY, lj = 0.f, x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (i0 < i1) request(i0, mj, lj, x);
-
-  // self score: scale * q . k_new (in log2 units)
-  float part = qd * kn;
-  for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-  if ((d & 63) == 0) red[d >> 6] = part;
   __syncthreads();
-  float s_self = 0.f;
-#pragma unroll
-  for (int w = 0; w < (D + 63) / 64; ++w) s_self += red[w];
 
-  float M = s_self, L = 1.f, A = vn;  // state so far: the new token alone, relative to M
-  // recent-token ring (Table 6 of the appendix): an evicted token among the n_recent - 1 positions before `pos` is still visible
-  // (the kept ones are cache rows already).  Slot contents are block-uniform, so the branches are too.
-  if (ring.k) {
-    const T *rk = static_cast<const T *>(ring.k), *rv = static_cast<const T *>(ring.v);
-    for (int w = 0; w < ring.n; ++w) {
-      const size_t slot = (size_t)u * ring.n + w;
-      const int p = ring.pos[slot];
-      if (!(p < pos && p > pos - ring.n) || ring.flags[slot] != 0) continue;
-      float part_r = qd * widen1(rk[slot * D + d]);
-      for (int o = 32; o > 0; o >>= 1) part_r += __shfl_xor(part_r, o, 64);
-      __syncthreads();  // red[] of the previous reduction is consumed
-      if ((d & 63) == 0) red[d >> 6] = part_r;
-      __syncthreads();
-      float sr = 0.f;
-#pragma unroll
-      for (int xw = 0; xw < (D + 63) / 64; ++xw) sr += red[xw];
-      const float M_new = fmaxf(M, sr);
-      const float keep = exp2f(M - M_new), pr = exp2f(sr - M_new);
-      M = M_new;
-      L = L * keep + pr;
-      A = fmaf(pr, widen1(rv[slot * D + d]), A * keep);
+  wave_t wv;
+  AG_LDS uint8_t *my_lds = (AG_LDS uint8_t *)smem + wave * wave_t::kWaveB;
+  wv.init(my_lds, lane);
+  int left = idle ? 0 : by_piece ? 1 : min(quota, total_t - x);  // tiles (or the one piece) still to do
+  int u = idle ? 0 : s_start[0], sub = idle ? 0 : s_start[1], at = x;
+  while (left > 0) {
+    u = __builtin_amdgcn_readfirstlane(u);
+    const int sl = __builtin_amdgcn_readfirstlane(s_len[u]);
+    const int n = sl & 0x7fffffff;
+    const int T_u = tiles_of(n);
+    int t0, t1, rec0 = 0, n_rec, my_rec;  // tiles [t0, t1) of the unit; the unit's records and this one's number
+    if (by_piece) {
+      n_rec = pieces_of(T_u);
+      my_rec = sub;
+      t0 = (int)((int64_t)T_u * sub / n_rec);
+      t1 = (int)((int64_t)T_u * (sub + 1) / n_rec);
+      rec0 = wg - sub;
+      left = 0;
+    } else {
+      t0 = sub;
+      t1 = min(T_u, t0 + left);
+      left -= t1 - t0;
+      const int first = at - t0;  // the unit's first tile, counted over all units
+      at += t1 - t0;
+      const int g0 = first / quota, g1 = (first + T_u - 1) / quota;
+      n_rec = g1 - g0 + 1;
+      my_rec = wg - g0;
+      rec0 = g0;
     }
-  }
-  // the wave reduces the batch's maximum and sum, the weights go through LDS, and every thread then adds its
-  // column with independent loads
-  for (int base = i0; base < i1; base += 64) {
-    const int n = min(64, i1 - base);
-    if (base != i0) request(base, mj, lj, x);
-    float mb = mj;
-    for (int o = 32; o > 0; o >>= 1) mb = fmaxf(mb, __shfl_xor(mb, o, 64));
-    const float M_new = fmaxf(M, mb);
-    const float keep = exp2f(M - M_new);
-    const float wj = lane < n ? exp2f(mj - M_new) : 0.f;
-    float lsum = wj * lj;
-    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
-    __syncthreads();  // wts of the previous batch are consumed
-    if (d < 64) wts[d] = wj;
+    const int64_t ro = a.row_off[u];
+    const T *kn = static_cast<const T *>(a.k_new) + (size_t)u * D, *vn = static_cast<const T *>(a.v_new) + (size_t)u * D;
+    const bool first_piece = t0 == 0;  // this workgroup takes the new token in
+    // requested now, used at the segment's end
+    uint4 new_row = make_uint4(0, 0, 0, 0);
+    bool keep_new = true;
+    if (first_piece) {
+      if (tid < 2 * CPT) new_row = chunk16(reinterpret_cast<const uint8_t *>(tid < CPT ? kn : vn) + 16 * (tid % CPT), a.loose);
+      keep_new = a.new_flags == nullptr || a.new_flags[u] != 0;
+    }
+    uint64_t ring_vis = 0;
+    if (has_ring && t0 < extra) {  // evicted tokens of the window: the kept ones are cache rows already
+      bool see = false;
+      if (lane < a.ring.n) {
+        const int p = a.ring.pos[(size_t)u * a.ring.n + lane];
+        see = p < a.pos && p > a.pos - a.ring.n && a.ring.flags[(size_t)u * a.ring.n + lane] == 0;
+      }
+      ring_vis = __ballot(see);
+    }
+    wv.begin(static_cast<const T *>(a.q) + (size_t)u * G * D);
+    const T *K = static_cast<const T *>(a.kc) + (size_t)ro * D, *V = static_cast<const T *>(a.vc) + (size_t)ro * D;
+    wv.run(t0 + wave, t1, NW, a.qscale, a.loose, [&](int i) {
+      if (i >= extra) {
+        const int r = (i - extra) * kTileRows;
+        return dec_tile{K, V, (uint32_t)n * (uint32_t)(D * sizeof(T)), r, n - r >= 32 ? 0xffffffffu : (1u << (n - r)) - 1u, false};
+      }
+      if (i == 0) return dec_tile{kn, vn, (uint32_t)(D * sizeof(T)), 0, 1u, true};
+      const size_t ring0 = (size_t)u * a.ring.n * D;
+      return dec_tile{static_cast<const T *>(a.ring.k) + ring0, static_cast<const T *>(a.ring.v) + ring0,
+                      (uint32_t)a.ring.n * (uint32_t)(D * sizeof(T)), (i - 1) * kTileRows,
+                      (uint32_t)(ring_vis >> (32 * (i - 1))), true};
+    });
+    wv.leave((AG_LDS float *)my_lds);
     __syncthreads();
-    M = M_new;
-    L = L * keep + lsum;
-    A *= keep;
-    const float *col = pacc + ((size_t)base * G + gg) * D + d;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) A = fmaf(e < n ? wts[e] : 0.f, x[e], A);
-    int j = 8;
-    for (; j + 8 <= n; j += 8) {
-      float y[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) y[e] = col[(size_t)(j + e) * G * D];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) A = fmaf(wts[j + e], y[e], A);
-    }
-    for (; j < n; ++j) A = fmaf(wts[j], col[(size_t)j * G * D], A);
-  }
-  narrow1(A / L, &out[(size_t)bi * D + d]);
 
-  if (gg == 0 && keep_new) {
-    __syncthreads();  // every thread has read len[u] before it changes
-    if (n_len < cap) {
-      kc[(size_t)(r0 + n_len) * D + d] = kn_raw;
-      vc[(size_t)(r0 + n_len) * D + d] = vn_raw;
-      if (d == 0) { idx[r0 + n_len] = pos; len[u] = n_len + 1; }
-    } else if (d == 0) {
-      atomicOr(d_err, 1);
+    // ---- merge the waves' states; thread -> (head, two neighbouring columns) ----
+    const int n_states = min(NW, t1 - t0) * wave_t::kStates;
+    auto state = [&](int sI) {
+      return (AG_LDS float *)((AG_LDS uint8_t *)smem + (sI / wave_t::kStates) * wave_t::kWaveB) + (sI % wave_t::kStates) * G * SF;
+    };
+    auto store_out = [&](int gg, int d, float o0, float o1) {
+      T *dst = static_cast<T *>(a.out) + ((size_t)u * G + gg) * D + d;
+      if constexpr (sizeof(T) == 2) {
+        uint16_t lo, hi;
+        to_bf16(o0, &lo);
+        to_bf16(o1, &hi);
+        if (a.loose) {
+          dst[0] = lo;
+          dst[1] = hi;
+        } else {
+          *reinterpret_cast<uint32_t *>(dst) = (uint32_t)lo | ((uint32_t)hi << 16);
+        }
+      } else {
+        *reinterpret_cast<float2 *>(dst) = make_float2(o0, o1);
+      }
+    };
+    auto rec_at = [&](int k) {  // record of piece k of this unit
+      const int id = by_piece ? rec0 + k : 2 * (rec0 + k) + (k == 0 ? 1 : 0);
+      return a.rec + (size_t)id * G * (D + 2);
+    };
+    for (int e = tid; e < G * D / 2; e += NT) {
+      const int gg = e / (D / 2), d = 2 * (e - gg * (D / 2));
+      float M = kEmptyMax;
+      for (int sI = 0; sI < n_states; ++sI) M = fmaxf(M, state(sI)[gg * SF]);
+      float L = 0.f, A0 = 0.f, A1 = 0.f;
+      for (int sI = 0; sI < n_states; ++sI) {
+        const AG_LDS float *h = state(sI) + gg * SF;
+        const float w = exp2f(h[0] - M);
+        L = fmaf(w, h[1], L);
+        A0 = fmaf(w, h[4 + d], A0);
+        A1 = fmaf(w, h[5 + d], A1);
+      }
+      if (n_rec == 1) {
+        store_out(gg, d, A0 / L, A1 / L);
+      } else {
+        float *r = rec_at(my_rec) + gg * (D + 2);
+        put_pair(r + d, A0, A1);
+        if (d == 0) put_pair(r + D, M, L);
+      }
     }
-  }
-  // The new token takes the ring slot pos % n_recent.  That slot held position pos - n_recent, which no query
-  // head of this step can see any more, and a reader that races with the write skips the slot whether it finds
-  // the old position (out of the window) or the new one (not before pos).
-  if (ring.k && gg == 0) {
-    const size_t slot = (size_t)u * ring.n + (size_t)(pos % ring.n);
-    static_cast<T *>(ring.k)[slot * D + d] = kn_raw;
-    static_cast<T *>(ring.v)[slot * D + d] = vn_raw;
-    if (d == 0) {
-      ring.flags[slot] = keep_new ? 1 : 0;
-      ring.pos[slot] = pos;
+    if (n_rec > 1) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the record is in memory
+      __syncthreads();
+      if (tid == 0)
+        s_last = __hip_atomic_fetch_add(&a.tickets[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_rec - 1;
+      __syncthreads();
+      if (s_last) {  // all pieces are there: add them in order
+        if (tid == 0) a.tickets[u] = 0;  // ready for the next launch
+        for (int e = tid; e < G * D / 2; e += NT) {
+          const int gg = e / (D / 2), d = 2 * (e - gg * (D / 2));
+          float M = kEmptyMax, L = 0.f, A0 = 0.f, A1 = 0.f;
+          for (int k0 = 0; k0 < n_rec; k0 += 8) {
+            float2 ml[8], o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const float *r = rec_at(min(k0 + j, n_rec - 1)) + gg * (D + 2);
+              ml[j] = get_pair(r + D);
+              o[j] = get_pair(r + d);
+            }
+            float M_new = M;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) M_new = fmaxf(M_new, ml[j].x);
+            const float keep = exp2f(M - M_new);
+            M = M_new;
+            L *= keep; A0 *= keep; A1 *= keep;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const float w = k0 + j < n_rec ? exp2f(ml[j].x - M) : 0.f;
+              L = fmaf(w, ml[j].y, L);
+              A0 = fmaf(w, o[j].x, A0);
+              A1 = fmaf(w, o[j].y, A1);
+            }
+          }
+          store_out(gg, d, A0 / L, A1 / L);
+        }
+      }
     }
+    if (first_piece) {  // the new token: its cache row (nobody reads past len in this launch) and its ring slot
+      if (keep_new && sl < 0) {
+        if (tid < 2 * CPT) reinterpret_cast<uint4 *>(static_cast<T *>(tid < CPT ? a.kc : a.vc) + (size_t)(ro + n) * D)[tid % CPT] = new_row;
+        if (tid == 0) a.idx[ro + n] = a.pos;
+      } else if (keep_new && tid == 0) {
+        atomicOr(a.d_err, 1);
+      }
+      if (has_ring) {  // slot pos % n_recent held position pos - n_recent, which no query sees any more
+        const size_t slot = (size_t)u * a.ring.n + (size_t)(a.pos % a.ring.n);
+        if (tid < 2 * CPT)
+          put16(reinterpret_cast<uint8_t *>(static_cast<T *>(tid < CPT ? a.ring.k : a.ring.v) + slot * D) + 16 * (tid % CPT), new_row, a.loose);
+        if (tid == 0) {
+          a.ring.flags[slot] = keep_new ? 1 : 0;
+          a.ring.pos[slot] = a.pos;
+        }
+      }
+    }
+    __syncthreads();  // the states have been read: the next segment may load over them
+    ++u;
+    sub = 0;
   }
+  // ---- the last workgroup to have read the lengths counts the appended rows ----
+  if (tid == 0) s_last = order == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!s_last) return;
+  for (int v = u0; v < u1; ++v)
+    if (s_len[v] < 0 && (a.new_flags == nullptr || a.new_flags[v] != 0)) a.len[v] = (s_len[v] & 0x7fffffff) + 1;
+  if (tid == 0) *a.arrived = 0;
 }
 
 // After prefilling: the ring takes the last min(L, n_recent) prompt tokens of every unit (kept or not); the other
@@ -431,61 +665,59 @@ __global__ __launch_bounds__(256) void ag_ring_fill_kernel(const T *__restrict__
   }
 }
 
-int64_t max_items(int units, int64_t cache_rows) { return cache_rows / kChunk + units; }
+int64_t max_records(int units, int64_t cache_rows) { return cache_rows / kChunk + units; }
 
-template <typename T, int D, int G>
-hipError_t launch_t(ag_ctx *ctx, hipStream_t s, const void *q, const void *k_new, const void *v_new,
-                    const uint8_t *new_flags, int pos, int B, int Hq, int Hkv, float scale, void *kc, void *vc,
-                    int32_t *idx, const int64_t *row_off, int32_t *len, int64_t total_rows, void *out, ws_cursor &ws,
-                    ag_ring_dev ring) {
-  const int num_cu = ctx->num_cu;
-  int32_t *d_err = ctx->d_err;
-  const int U = B * Hkv;
-  const int64_t items = max_items(U, total_rows);
-  int32_t *item_off = ws.take<int32_t>(U + 1);
-  float *pm = ws.take<float>(items * G);
-  float *pl = ws.take<float>(items * G);
-  float *pacc = ws.take<float>(items * G * D);
-  if (!ws.ok) return hipSuccess;
-  constexpr int EPL = elems<T>::n, LPR = D / EPL, GPW = 64 / LPR, NST = 4 * GPW;
-  const int meta_lds = U <= 2048;
-  const size_t shmem = (size_t)(U + 1 + 256) * 4 + (size_t)NST * G * (D + 2) * 4 +
-                       (meta_lds ? (size_t)U * 4 + 8 + (size_t)U * 8 : 0);
-  const float qscale = scale * kLog2e;
-  const int grid_stream = num_cu * kWgsPerCu;
-  int blocks = 2 * grid_stream;  // the kernel uses them all only when that gives every item its own workgroup
-  if (blocks > items) blocks = (int)items;
-  if (blocks < 1) blocks = 1;
+template <typename T, int D, int G, int NW>
+hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, int64_t records) {
+  typedef typename wave_of<T, D, G>::type wave_t;
+  const size_t shmem = (size_t)NW * wave_t::kWaveB + (size_t)a.U * 4;
+  // one workgroup per CU (8 waves) or two (4 waves); no more than the step can have pieces
+  const int64_t pieces = a.U + total_rows / (2 * NW * kTileRows) + 1;
+  const int blocks = (int)std::min<int64_t>(NW == 8 ? ctx->num_cu : 2 * ctx->num_cu, pieces);
+  a.max_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(records / 2, blocks));
   if (shmem > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_decode_partial_kernel<T, D, G>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return e;
+    static std::atomic<size_t> allowed[64];  // per device: the largest size asked for so far
+    std::atomic<size_t> &most = allowed[ctx->device & 63];
+    if (most.load(std::memory_order_relaxed) < shmem) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_decode_kernel<T, D, G, NW>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+      if (e != hipSuccess) return e;
+      most.store(shmem, std::memory_order_relaxed);
+    }
   }
-  AG_LAUNCH(ag_time_kernel(ctx, AG_K_DECODE_PARTIAL), (ag_decode_partial_kernel<T, D, G>), dim3(blocks), dim3(256), shmem, s, (const T *)q,
-                     (const T *)kc, (const T *)vc, row_off, len, U, Hkv, meta_lds, grid_stream, qscale, item_off, pm, pl, pacc);
-  AG_LAUNCH(ag_time_kernel(ctx, AG_K_DECODE_MERGE), (ag_decode_merge_kernel<T, D>), dim3(B * Hq), dim3(D), 0, s, (const T *)q, (const T *)k_new,
-                     (const T *)v_new, new_flags, pos, Hq, Hkv, qscale, item_off, pm, pl, pacc, (T *)kc, (T *)vc, idx,
-                     row_off, len, (T *)out, d_err, ring);
+  // (both timing ids report this launch: the merge is part of it)
+  ag_tick(ctx, AG_K_DECODE_MERGE, s);
+  AG_LAUNCH(ag_time_kernel(ctx, AG_K_DECODE_PARTIAL), (ag_decode_kernel<T, D, G, NW>), dim3(blocks), dim3(64 * NW), shmem, s, a);
+  ag_tock(ctx, AG_K_DECODE_MERGE, s);
   return hipGetLastError();
 }
 
-template <typename T, int D, typename... A>
-hipError_t launch_g(int G, A &&...a) {
+template <typename T, int D, int G>
+hipError_t launch_t(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, ws_cursor &ws) {
+  const int64_t records = max_records(a.U, total_rows);
+  a.rec = ws.take<float>((size_t)records * G * (D + 2));
+  if (!ws.ok) return hipSuccess;
+  return a.U <= kFewUnits ? launch_nw<T, D, G, 8>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4>(ctx, s, a, total_rows, records);
+}
+
+template <typename T, int D>
+hipError_t launch_g(int G, ag_ctx *ctx, hipStream_t s, const dec_args &a, int64_t total_rows, ws_cursor &ws) {
   switch (G) {
-    case 1: return launch_t<T, D, 1>(a...);
-    case 2: return launch_t<T, D, 2>(a...);
-    case 4: return launch_t<T, D, 4>(a...);
-    case 8: return launch_t<T, D, 8>(a...);
+    case 1: return launch_t<T, D, 1>(ctx, s, a, total_rows, ws);
+    case 2: return launch_t<T, D, 2>(ctx, s, a, total_rows, ws);
+    case 4: return launch_t<T, D, 4>(ctx, s, a, total_rows, ws);
+    case 8: return launch_t<T, D, 8>(ctx, s, a, total_rows, ws);
   }
   return hipErrorInvalidValue;
 }
 
 }  // namespace
 
+// Records: one per 128 cache rows and one per unit cover what the kernel can cut (see launch_nw).
 size_t ag_ws_decode_bytes(int units, int G, int D, int64_t cache_rows) {
-  const int64_t items = max_items(units, cache_rows);
-  return ag_align256((size_t)(units + 1) * 4) + 2 * ag_align256((size_t)items * G * 4) +
-         ag_align256((size_t)items * G * D * 4);
+  const int64_t records = max_records(units, cache_rows);
+  return ag_align256((size_t)(units + 1) * 4) + 2 * ag_align256((size_t)records * G * 4) +
+         ag_align256((size_t)records * G * D * 4);
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device (with that device current) and kept.
@@ -510,7 +742,7 @@ hipError_t ag_static_scratch(int device, char **ptr) {
 }
 
 bool ag_decode_supported(ag_dtype dt, int D, int G, int units) {
-  if (units > kMaxUnits) return false;
+  if (units > kDecodeMaxUnits) return false;
   if (!(G == 1 || G == 2 || G == 4 || G == 8)) return false;
   return dt == AG_BF16 ? (D == 64 || D == 128) : (D == 64 || D == 128);
 }
@@ -519,10 +751,15 @@ hipError_t ag_launch_decode(ag_ctx *ctx, hipStream_t s, const void *q, const voi
                             const uint8_t *new_flags, int pos, int B, int Hq, int Hkv, int D, ag_dtype dt,
                             float scale, void *kc, void *vc, int32_t *idx, const int64_t *row_off, int32_t *len,
                             int64_t total_rows, void *out, ws_cursor &ws, ag_ring_dev ring) {
-  const int G = Hq / Hkv;
-#define AG_DEC(T, DD)                                                                                              \
-  return launch_g<T, DD>(G, ctx, s, q, k_new, v_new, new_flags, pos, B, Hq, Hkv, scale, kc, vc, idx, row_off, len, \
-                         total_rows, out, ws, ring)
+  dec_args a;
+  a.q = q; a.k_new = k_new; a.v_new = v_new; a.new_flags = new_flags;
+  a.kc = kc; a.vc = vc; a.idx = idx; a.row_off = row_off; a.len = len; a.out = out;
+  a.rec = nullptr; a.tickets = ctx->decode_tickets; a.arrived = ctx->decode_tickets + kDecodeMaxUnits; a.d_err = ctx->d_err;
+  a.U = B * Hkv; a.pos = pos; a.max_wgs = 1;
+  a.qscale = scale * kLog2e;
+  a.loose = dt == AG_BF16 && (((uintptr_t)k_new | (uintptr_t)v_new | (uintptr_t)out | (uintptr_t)ring.k | (uintptr_t)ring.v) & 15) != 0;
+  a.ring = ring;
+#define AG_DEC(T, DD) return launch_g<T, DD>(Hq / Hkv, ctx, s, a, total_rows, ws)
   if (dt == AG_BF16) {
     if (D == 64) AG_DEC(uint16_t, 64);
     if (D == 128) AG_DEC(uint16_t, 128);

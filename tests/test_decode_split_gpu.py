@@ -1,0 +1,63 @@
+"""How the decode launch cuts its work: whole units, pieces of long ones, equal ranges over many; tile edges; arguments
+that are not 16-byte aligned.  All against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2410_12876_amd as ag
+import workloads as W
+from gpu_util import DEV, attn_error, attn_tolerance, cache_from_host, dev, ensure_built, host_f32, make_ctx
+from test_parity_gpu import check_decode
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    ensure_built()
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,lens", [
+    ("bf16", 1, 4, 4, 128, [31, 32, 33, 0]),                    # one tile, its edges
+    ("bf16", 1, 8, 8, 64, [1, 63, 64, 65, 991, 992, 993, 2]),   # a unit of 32 tiles stays whole, 33 are cut (8 waves)
+    ("bf16", 1, 8, 2, 128, [9000, 1025]),                       # few units, many pieces
+    ("bf16", 2, 32, 8, 128, [7000] * 15 + [3]),                 # more pieces than workgroups: equal ranges
+    ("bf16", 65, 4, 4, 128, [5, 170, 40, 480]),                 # 260 units: 4 waves, ranges that hold many units
+    ("bf16", 100, 16, 4, 64, [600, 30, 2000, 0]),
+    ("bf16", 1, 8, 1, 128, [12345]),                            # one unit, eight heads
+    ("f32", 1, 4, 4, 64, [33, 992, 2500, 0]),
+    ("f32", 70, 8, 4, 128, [7, 100, 31, 250]),
+])
+def test_decode_work_split(dtype, B, Hq, Hkv, D, lens):
+    U = B * Hkv
+    len0 = np.resize(np.asarray(lens, dtype=np.int32), U)
+    g = np.random.default_rng(U + D)
+    len0 = np.where(len0 > 100, len0 - g.integers(0, 3, size=U) * (U > 16), len0).astype(np.int32)
+    wl = W.decode_batch(60, "split", dtype, B, Hq, Hkv, D, len0, 2, pos0=int(len0.max()) + 1)
+    print("decode split", dtype, B, Hq, Hkv, D, int(len0.sum()), flush=True)
+    check_decode(wl, 2, 0.5, dtype)
+
+
+def test_decode_takes_new_rows_at_any_even_address():
+    B, Hq, Hkv, D = 2, 8, 2, 128
+    wl = W.decode_batch(61, "loose", "bf16", B, Hq, Hkv, D, np.array([40, 0, 700, 1300], dtype=np.int32), 1, pos0=1400)
+    ctx = make_ctx(B, 1, Hq, Hkv, D, ag.AG_BF16, cache_rows=int(wl.row_off[-1]))
+    cache = cache_from_host(B, Hkv, D, wl.k_cache, wl.v_cache, wl.idx, wl.row_off, wl.len0)
+    ref = oracle.Cache(wl.k_cache.f32.copy(), wl.v_cache.f32.copy(), wl.idx.copy(), wl.row_off.copy(), wl.len0.copy())
+    q, kn, vn, _ = wl.step_inputs(0, 0.5)
+
+    def shifted(t, by):
+        x = torch.zeros(t.numel() + 8, dtype=t.dtype, device=DEV)[by:by + t.numel()].view(t.shape)
+        return x.copy_(t)
+    out = shifted(dev(q), 3)
+    ag.ag_decode_attn(ctx, dev(q), shifted(dev(kn), 1), shifted(dev(vn), 5), None, wl.pos0, wl.scale, cache, out)
+    want, dropped = oracle.decode_step(q.f32, kn.f32, vn.f32, None, wl.pos0, ref, wl.scale)
+    assert dropped == 0
+    assert attn_error("bf16", host_f32(out), want) <= attn_tolerance("bf16", want)
+    gk = host_f32(cache.k)
+    for u in range(B * Hkv):
+        a, n = int(wl.row_off[u]), int(ref.len[u])
+        assert np.array_equal(gk[a:a + n], ref.k[a:a + n])
+    ctx.poll_error()
+    ctx.close()
