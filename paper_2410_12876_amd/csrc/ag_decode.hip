@@ -5,22 +5,27 @@
 // read-back), streams the rows, merges, takes in the new token and appends it -- and hands data between workgroups only
 // where a unit is too long for one.
 //   * Work is counted in tiles of 32 rows of one unit; a wave takes every NW-th tile of its workgroup's segment, so the
-//     waves run without a barrier until their segment ends.  The new token's own key and value (the diagonal of
-//     Eq. 5) and the slots of the recent-token ring are extra tiles in front of a unit's cache rows.
-//   * bf16 runs on MFMA: K and V rows go from memory to the wave's own LDS by direct loads (whole 256-byte rows; the next
-//     tile's K is requested as soon as this tile's fragments are read, its V after the second product, so 8 to 16 KiB per
+//     waves run without a barrier until their segment ends.  The slots of the recent-token ring are extra tiles in front
+//     of a unit's cache rows; the new token's own key and value (the diagonal of Eq. 5) are the state one wave starts from.
+//   * bf16 runs on MFMA: K and V rows go from memory to the wave's own LDS by direct loads (whole rows; the next tile's K
+//     is requested as soon as this tile's fragments are read, its V after the second product's, so 8 to 16 KiB per
 //     wave are always in flight and no register holds them), S^T = K q^T and O^T = V^T p^T for all G query heads of the
 //     group at once.  p enters the second product as a bf16 pair (high part + remainder, two MFMAs): the weights keep 16
 //     bits, as a 32-bit product would.  fp32 caches run on the vector ALU.
 //   * Segments (what a workgroup works on between two merges) are chosen on the device.  If the whole step gives every
 //     workgroup at most one segment -- a unit of up to 4 rounds of its waves stays whole, a longer one is cut into
 //     pieces of two rounds -- a unit's pieces meet once; otherwise the tiles of all units are laid end to end and cut
-//     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.
+//     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.  Many short units (more
+//     than a CU-filling launch has workgroups for) are given to single waves or pairs of them instead, all at once.
 //   * A unit inside one workgroup is finished there, through LDS.  The pieces of a longer one are stored as records
 //     (written through, complete before the arrival is counted); the piece that arrives last merges them in order.
+//   * A short step costs instructions as much as memory round trips (two waves share a SIMD, so each vector instruction of
+//     the straight-line path is 8 cycles): up to 256 units every wave builds the work list in its own registers, without
+//     LDS and barriers, and all addresses are one XOR away from a base.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "ag_internal.h"
 
@@ -54,11 +59,6 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
-__device__ __forceinline__ void to_bf16(float x, uint16_t *o) {  // round to nearest even
-  uint32_t u = __float_as_uint(x);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  *o = (uint16_t)(u >> 16);
-}
 
 // 16 bytes that may (loose) lie at any even address
 __device__ __forceinline__ uint4 chunk16(const uint8_t *p, bool loose) {
@@ -105,8 +105,22 @@ template <int LPR> __device__ __forceinline__ float group_sum(float x) {
 // LDS address key of row r of a wave's tile: the row's 16-byte chunk c lies at position c ^ key(r).  Among 16
 // consecutive rows all keys differ (K fragments: 16 rows, one chunk), and among the 8 rows that a transposing V read
 // serves together all pairs of chunks differ.  (D = 64: a row covers half of the banks, odd rows the other half.)
-template <int D> __device__ __forceinline__ int tile_key(int r) {
+template <int D> __device__ __forceinline__ constexpr int tile_key(int r) {
   return D == 128 ? (((r & 7) << 1) | ((r >> 3) & 1)) : ((((r >> 1) & 3) << 1) | ((r >> 3) & 1));
+}
+
+// Reductions over the four lanes that share lane % 16 (v_permlane*_swap: a register exchange, no LDS round trip)
+__device__ __forceinline__ float kg_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float kg_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // What a tile reads: rows row0 .. row0 + 31 of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
@@ -115,7 +129,7 @@ struct dec_tile {
   uint32_t bytes;     // cache rows: size of the array (rows past its end read as zeros)
   int row0;
   uint32_t vis;
-  bool extra;         // new token or ring: rows whose bit is clear are not even read (they may hold anything)
+  bool ring;          // ring slots: rows whose bit is clear are not even read (they may hold anything)
 };
 
 // ---- bf16: one wave's pass over its tiles on MFMA -----------------------------------------------------------
@@ -124,40 +138,32 @@ template <int D, int G> struct wave_bf16 {
   static constexpr int kRowB = D * 2, CPR = kRowB / 16, RPI = 64 / CPR;  // RPI rows per load instruction
   static constexpr int NL = kTileRows / RPI;                             // load instructions per tile and operand
   static constexpr int kWaveB = 2 * kTileRows * kRowB;                   // the wave's LDS: K tile, V tile
-  static constexpr int kStates = 1, kStateF = D + 4;                     // merge states a wave leaves, floats per head
+  static constexpr int kStateF = D + 4;                                  // floats per head of the state a wave leaves
   static constexpr int KS = D / 32, DT = D / 16;
   bf16x8 qf[KS];
   f32x4 o[DT];
   float m, l;
-  int ld_off[NL], k_off[KS], v_off[DT];
+  int ld_base, k_base, v_base;  // every offset below is one of these XOR a constant (rows only add constants)
   uint32_t lds_addr;
   AG_LDS uint8_t *lds;
   int lane, kg, col;
+
+  // load instruction i, lane (row lr = lane / CPR of its RPI rows, position lane % CPR) fetches chunk
+  // (lane % CPR) ^ key(RPI i + lr) of that row; key(RPI i + lr) = key(lr) ^ key(RPI i)
+  __device__ __forceinline__ int ld_off(int i) const { return ld_base ^ (tile_key<D>(RPI * i) << 4); }
+  // K fragment (A of S^T), k-step ks: row col (+ 16), chunk 4 ks + kg
+  __device__ __forceinline__ int k_off(int ks) const { return k_base ^ (ks << 6); }
+  // V fragment (A of O^T) by transposing read: rows 4 kg + 0..3 (+ 16), columns 16 dt + 0..15
+  __device__ __forceinline__ int v_off(int dt) const { return v_base ^ (dt << 5); }
 
   __device__ __forceinline__ void init(AG_LDS uint8_t *mem, int lane_) {
     lane = lane_; kg = lane >> 4; col = lane & 15;
     lds = mem;
     lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)mem);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int r = RPI * i + lane / CPR;
-      ld_off[i] = r * kRowB + (((lane % CPR) ^ tile_key<D>(r)) << 4);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_off[ks] = col * kRowB + (((4 * ks + kg) ^ tile_key<D>(col)) << 4);
-    const int vr = 4 * kg + (col >> 2);
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      v_off[dt] = vr * kRowB + (((2 * dt + ((col & 3) >> 1)) ^ tile_key<D>(vr)) << 4) + (col & 1) * 8;
-  }
-  // q: the G query rows of the unit
-  __device__ __forceinline__ void begin(const uint16_t *q) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      uint4 x = make_uint4(0, 0, 0, 0);
-      if (col < G) x = *reinterpret_cast<const uint4 *>(q + (size_t)col * D + 32 * ks + 8 * kg);
-      qf[ks] = __builtin_bit_cast(bf16x8, x);
-    }
+    const int lr = lane / CPR, vr = 4 * kg + (col >> 2);
+    ld_base = lr * kRowB + (((lane % CPR) ^ tile_key<D>(lr)) << 4);
+    k_base = col * kRowB + ((kg ^ tile_key<D>(col)) << 4);
+    v_base = vr * kRowB + ((((col & 3) >> 1) ^ tile_key<D>(vr)) << 4) + (col & 1) * 8;
     m = kEmptyMax; l = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -165,15 +171,21 @@ template <int D, int G> struct wave_bf16 {
   // Cache rows of one operand straight into LDS; rows past the array arrive as zeros.  Every cached row is read once per
   // step: non-temporal, so that the stream does not push the small hot data (queries, lengths, records) out of the caches.
   __device__ __forceinline__ void load(const dec_tile &t, const void *base, uint32_t dst) {
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, t.bytes, 0x00020000);
-    const int soff = t.row0 * kRowB;
+    const uint64_t at = (uint64_t)base;  // (wave-uniform, as the loads need it; said explicitly)
+    const uint64_t base_s = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)at) |
+                            ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(at >> 32)) << 32);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void *)base_s, 0, __builtin_amdgcn_readfirstlane(t.bytes), 0x00020000);
+    const int soff = __builtin_amdgcn_readfirstlane(t.row0 * kRowB);
 #pragma unroll
     for (int i = 0; i < NL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "memory");
+                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off(i)), "s"(rsrc), "s"(soff + i * RPI * kRowB) : "memory");
   }
-  // The new token's row or ring slots, through registers: only the visible rows are read, the others become zeros.
-  __device__ __forceinline__ void load_extra(const dec_tile &t, bool loose) {
+  __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, lds_addr); }
+  __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, lds_addr + kTileRows * kRowB); }
+  // Ring slots, through registers: only the visible rows are read, the others become zeros.
+  __device__ __forceinline__ void load_ring(const dec_tile &t, bool loose) {
     uint4 x[2][NL];
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -181,7 +193,8 @@ template <int D, int G> struct wave_bf16 {
 #pragma unroll
       for (int kv = 0; kv < 2; ++kv) {
         x[kv][i] = make_uint4(0, 0, 0, 0);
-        if (see) x[kv][i] = chunk16(static_cast<const uint8_t *>(kv ? t.v : t.k) + (size_t)t.row0 * kRowB + ld_off[i], loose);
+        if (see)
+          x[kv][i] = chunk16(static_cast<const uint8_t *>(kv ? t.v : t.k) + (size_t)(t.row0 + i * RPI) * kRowB + ld_off(i), loose);
       }
     }
 #pragma unroll
@@ -191,23 +204,60 @@ template <int D, int G> struct wave_bf16 {
         *reinterpret_cast<AG_LDS u32x4 *>(lds + (kv * kTileRows + i * RPI) * kRowB + lane * 16) =
             u32x4{x[kv][i].x, x[kv][i].y, x[kv][i].z, x[kv][i].w};
   }
-  __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, lds_addr); }
-  __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, lds_addr + kTileRows * kRowB); }
 
-  // tiles first, first + step, ... < last of the segment; get(i) describes tile i
-  // (a tile that is not cache rows can only be a wave's first: there are fewer of them than waves)
-  template <typename GET> __device__ __forceinline__ void run(int first, int last, int step, float qscale, bool loose, GET &&get) {
-    if (first >= last) return;
+  // Tiles first, first + step, ... < last of the segment; get(i) describes tile i.  q: the G query rows of the unit.
+  // own: start from the new token's key and value instead of from nothing.
+  // (a ring tile can only be a wave's first: there are no more of them than waves)
+  template <typename GET>
+  __device__ __forceinline__ void run(const uint16_t *q, int first, int last, int step, float qscale, bool own,
+                                      const uint16_t *k_new, const uint16_t *v_new, bool loose, GET &&get) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint4 x = make_uint4(0, 0, 0, 0);
+      if (col < G) x = *reinterpret_cast<const uint4 *>(q + (size_t)col * D + 32 * ks + 8 * kg);
+      qf[ks] = __builtin_bit_cast(bf16x8, x);
+    }
+    uint4 kn[KS];
+    uint2 vn[DT];
+    if (own) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kn[ks] = chunk16(reinterpret_cast<const uint8_t *>(k_new + 32 * ks + 8 * kg), loose);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const uint16_t *v = v_new + 16 * dt + 4 * kg;
+        if (!loose) vn[dt] = *reinterpret_cast<const uint2 *>(v);
+        else vn[dt] = make_uint2((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16));
+      }
+    }
     dec_tile t = get(first);
-    if (t.extra) {
-      load_extra(t, loose);
-    } else {
-      load_k(t);
-      load_v(t);
+    if (first < last) {
+      if (t.ring) {
+        load_ring(t, loose);
+      } else {
+        load_k(t);
+        load_v(t);
+      }
     }
     // the query's loads are waited for here, once: the compiler would otherwise put a wait for everything into the loop
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
+    if (own) {
+      float s = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const uint4 qa = __builtin_bit_cast(uint4, qf[ks]);
+        s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qa.x), __builtin_bit_cast(bf16x2, kn[ks].x), s, false);
+        s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qa.y), __builtin_bit_cast(bf16x2, kn[ks].y), s, false);
+        s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qa.z), __builtin_bit_cast(bf16x2, kn[ks].z), s, false);
+        s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qa.w), __builtin_bit_cast(bf16x2, kn[ks].w), s, false);
+      }
+      m = kg_sum(s) * qscale;
+      l = kg == 0 ? 1.f : 0.f;  // (summed over the key groups at the end)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        o[dt] = f32x4{__uint_as_float(vn[dt].x << 16), __uint_as_float(vn[dt].x & 0xffff0000u),
+                      __uint_as_float(vn[dt].y << 16), __uint_as_float(vn[dt].y & 0xffff0000u)};
+    }
     for (int i = first; i < last; i += step) {
       const bool more = i + step < last;
       const uint32_t vis = t.vis;
@@ -218,7 +268,7 @@ template <int D, int G> struct wave_bf16 {
       for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          kf[sub][ks] = *reinterpret_cast<const AG_LDS bf16x8 *>(lds + sub * 16 * kRowB + k_off[ks]);
+          kf[sub][ks] = *reinterpret_cast<const AG_LDS bf16x8 *>(lds + sub * 16 * kRowB + k_off(ks));
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (more) load_k(t);
       f32x4 s[2];
@@ -231,28 +281,30 @@ template <int D, int G> struct wave_bf16 {
       // s[sub][r]: key 16 sub + 4 kg + r, head col
       float p[8], mx = -INFINITY;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        p[e] = s[e >> 2][e & 3] * qscale;
-        if (vis != 0xffffffffu && !((vis >> (16 * (e >> 2) + 4 * kg + (e & 3))) & 1u)) p[e] = -INFINITY;
-        mx = fmaxf(mx, p[e]);
+      for (int e = 0; e < 8; ++e) p[e] = s[e >> 2][e & 3] * qscale;
+      if (vis != 0xffffffffu) {
+        const uint32_t mine = vis >> (4 * kg);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (!((mine >> (16 * (e >> 2) + (e & 3))) & 1u)) p[e] = -INFINITY;
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mx = fmaxf(mx, p[e]);
+      const float m_new = fmaxf(m, kg_max(mx));
       if (__any(m_new != m)) {
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        l *= alpha;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
+        m = m_new;
       }
-      m = m_new;
-      l *= alpha;
       float lo[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         p[e] = __builtin_amdgcn_exp2f(p[e] - m);
         l += p[e];
       }
-      uint4 ph = make_uint4(pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7]));
+      const uint4 ph = make_uint4(pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7]));
       const uint32_t hw[4] = {ph.x, ph.y, ph.z, ph.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -267,7 +319,7 @@ template <int D, int G> struct wave_bf16 {
       bf16x8 vf[DT];  // row d = 16 dt + col of V^T, keys 4 kg + 0..3 and 16 + 4 kg + 0..3
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        const AG_LDS uint8_t *base = lds + kTileRows * kRowB + v_off[dt];
+        const AG_LDS uint8_t *base = lds + kTileRows * kRowB + v_off(dt);
         const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)base);
         const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(base + 16 * kRowB));
         vf[dt] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -283,8 +335,7 @@ template <int D, int G> struct wave_bf16 {
   }
   // the wave's state into its LDS: per head [max, sum, -, -, o[0..D)]
   __device__ __forceinline__ void leave(AG_LDS float *st) {
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    l = kg_sum(l);
     if (col < G) {
       AG_LDS float *h = st + col * kStateF;
       if (kg == 0) { h[0] = m; h[1] = l; }
@@ -299,22 +350,43 @@ template <int D, int G> struct wave_f32 {
   static constexpr int EPL = 4, LPR = D / EPL, GPW = 64 / LPR;   // lanes per row, rows per load
   static constexpr int NIT = kTileRows / GPW;                    // loads that cover a tile
   static constexpr int UN = (G <= 2 ? 8 : 4) < NIT ? (G <= 2 ? 8 : 4) : NIT;  // rows in flight per lane group
-  static constexpr int kStates = GPW, kStateF = D + 4;
-  static constexpr int kWaveB = GPW * G * kStateF * 4;
+  static constexpr int kStateF = D + 4;
+  static constexpr int kWaveB = G * kStateF * 4;
   float4 qr[G];
   float m[G], l[G], acc[G][EPL];
   int grp, seg;
-  __device__ __forceinline__ void init(AG_LDS uint8_t *, int lane) { grp = lane / LPR; seg = lane % LPR; }
-  __device__ __forceinline__ void begin(const float *q) {
+  __device__ __forceinline__ void init(AG_LDS uint8_t *, int lane) {
+    grp = lane / LPR; seg = lane % LPR;
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) {
-      qr[gg] = reinterpret_cast<const float4 *>(q + (size_t)gg * D)[seg];
       m[gg] = kEmptyMax; l[gg] = 0.f;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[gg][e] = 0.f;
     }
   }
-  template <typename GET> __device__ __forceinline__ void run(int first, int last, int step, float qscale, bool, GET &&get) {
+  __device__ __forceinline__ float score(const float4 &q, const nt_f32x4 &k, float qscale) {
+    float d = q.x * k[0];
+    d = fmaf(q.y, k[1], d);
+    d = fmaf(q.z, k[2], d);
+    return group_sum<LPR>(fmaf(q.w, k[3], d)) * qscale;
+  }
+  template <typename GET>
+  __device__ __forceinline__ void run(const float *q, int first, int last, int step, float qscale, bool own,
+                                      const float *k_new, const float *v_new, bool, GET &&get) {
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) qr[gg] = reinterpret_cast<const float4 *>(q + (size_t)gg * D)[seg];
+    if (own) {
+      const nt_f32x4 kn = reinterpret_cast<const nt_f32x4 *>(k_new)[seg], vn = reinterpret_cast<const nt_f32x4 *>(v_new)[seg];
+#pragma unroll
+      for (int gg = 0; gg < G; ++gg) {
+        const float s = score(qr[gg], kn, qscale);
+        if (grp == 0) {
+          m[gg] = s; l[gg] = 1.f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[gg][e] = vn[e];
+        }
+      }
+    }
     for (int i = first; i < last; i += step) {
       const dec_tile t = get(i);
       const nt_f32x4 *K = reinterpret_cast<const nt_f32x4 *>(t.k) + (size_t)t.row0 * LPR + seg;
@@ -337,11 +409,7 @@ template <int D, int G> struct wave_f32 {
           float s[UN], mn = m[gg];
 #pragma unroll
           for (int j = 0; j < UN; ++j) {
-            float d = qr[gg].x * kk[j][0];
-            d = fmaf(qr[gg].y, kk[j][1], d);
-            d = fmaf(qr[gg].z, kk[j][2], d);
-            d = fmaf(qr[gg].w, kk[j][3], d);
-            d = group_sum<LPR>(d) * qscale;
+            const float d = score(qr[gg], kk[j], qscale);
             s[j] = ok[j] ? d : -INFINITY;
             mn = fmaxf(mn, s[j]);
           }
@@ -363,11 +431,25 @@ template <int D, int G> struct wave_f32 {
   }
   __device__ __forceinline__ void leave(AG_LDS float *st) {
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      AG_LDS float *h = st + (grp * G + gg) * kStateF;
-      if (seg == 0) { h[0] = m[gg]; h[1] = l[gg]; }
+    for (int gg = 0; gg < G; ++gg) {  // the lane groups' states first
+      float M = m[gg];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) h[4 + seg * EPL + e] = acc[gg][e];
+      for (int o = LPR; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+      const float w = exp2f(m[gg] - M);
+      l[gg] *= w;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[gg][e] *= w;
+#pragma unroll
+      for (int o = LPR; o < 64; o <<= 1) {
+        l[gg] += __shfl_xor(l[gg], o, 64);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[gg][e] += __shfl_xor(acc[gg][e], o, 64);
+      }
+      if (grp == 0) {
+        AG_LDS float *h = st + gg * kStateF;
+        if (seg == 0) { h[0] = M; h[1] = l[gg]; }
+        *reinterpret_cast<AG_LDS f32x4 *>(h + 4 + seg * EPL) = f32x4{acc[gg][0], acc[gg][1], acc[gg][2], acc[gg][3]};
+      }
     }
   }
 };
@@ -388,10 +470,24 @@ struct dec_args {
   int32_t *arrived;     // [1] workgroups that have read len[]; zero between launches
   int32_t *d_err;
   int U, pos, max_wgs;  // max_wgs: workgroups the equal-range split may use (two records each)
+  int team;             // waves per unit where every unit can have its own (4-wave workgroups; else unused)
   float qscale;
   bool loose;           // k_new, v_new, the ring or out are not 16-byte aligned: they are accessed by elements
   ag_ring_dev ring;
 };
+
+// exclusive prefix sum over the wave's lanes (x: the lane's own value); total = the wave's sum
+__device__ __forceinline__ int wave_prefix(int x, int &total) {
+  int y = x;
+  y += __builtin_amdgcn_update_dpp(0, y, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8: prefix inside each row of 16
+  y += __builtin_amdgcn_update_dpp(0, y, 0x112, 0xf, 0xf, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x114, 0xf, 0xf, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x118, 0xf, 0xf, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  y += __builtin_amdgcn_update_dpp(0, y, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  total = __builtin_amdgcn_readlane(y, 63);
+  return y - x;
+}
 
 template <typename T, int D, int G, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
@@ -399,179 +495,281 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   constexpr int NT = 64 * NW, SF = wave_t::kStateF;
   constexpr int kPieceTiles = 2 * NW, kWholeTiles = 4 * NW;
   constexpr int CPT = (int)(D * sizeof(T) / 16);  // 16-byte chunks per row
+  constexpr bool kRegs = NW == 8;                 // the work list lives in registers (at most 256 units)
+  constexpr int UPL = kFewUnits / 64;             // ... that many units per lane: unit 64 j + lane
+  // The arguments lie in three cache lines of memory that may be far away: all of them are requested here, in one trip,
+  // instead of one line after the other as the code below comes to need them.
+  asm volatile("" :: "s"(a.q), "s"(a.len), "s"(a.U), "s"(a.ring.n));
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-  int32_t *s_len = reinterpret_cast<int32_t *>(smem + NW * wave_t::kWaveB);  // [U] valid rows; top bit: the unit has room
-  __shared__ int32_t w_tiles[NW], w_items[NW], s_start[2], s_last;
+  int32_t *s_len = reinterpret_cast<int32_t *>(smem + NW * wave_t::kWaveB);  // (!kRegs) [U] valid rows; top bit: room
+  __shared__ int32_t w_sum[NW][2], s_start[2], s_last;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int U = a.U;
+  const int U = a.U, wg = blockIdx.x;
   const bool has_ring = a.ring.k != nullptr;
-  const int extra = 1 + (has_ring ? (a.ring.n + kTileRows - 1) / kTileRows : 0);
+  const int extra = has_ring ? (a.ring.n + kTileRows - 1) / kTileRows : 0;
 
-  // ---- the work list: tiles per unit, and the pieces they would be cut into ----
-  const int per = (U + NT - 1) / NT;
-  const int u0 = min(U, tid * per), u1 = min(U, u0 + per);
-  auto tiles_of = [&](int n) { return extra + (n + kTileRows - 1) / kTileRows; };
-  auto pieces_of = [&](int t) { return t <= kWholeTiles ? 1 : (t + kPieceTiles - 1) / kPieceTiles; };
-  int my_tiles = 0, my_items = 0;
-  for (int u = u0; u < u1; ++u) {
-    const int64_t cap = a.row_off[u + 1] - a.row_off[u];
+  // ---- the work list: tiles per unit (at least one), and the pieces it would be cut into ----
+  auto tiles_of = [&](int n) { return max(1, extra + (int)((unsigned)(n + kTileRows - 1) / kTileRows)); };
+  auto pieces_of = [&](int t) { return t <= kWholeTiles ? 1 : (int)((unsigned)(t + kPieceTiles - 1) / kPieceTiles); };
+  auto read_len = [&](int u, int64_t &r0) {  // valid rows of unit u, top bit set if another one fits
+    r0 = a.row_off[u];
+    const int64_t cap = a.row_off[u + 1] - r0;
     const int n_raw = a.len[u];
     const int n = n_raw < 0 ? 0 : (n_raw < cap ? n_raw : (int)cap);
-    s_len[u] = n | (n < cap ? 0x80000000 : 0);
-    const int t = tiles_of(n);
-    my_tiles += t;
-    my_items += pieces_of(t);
-  }
-  int inc_t = my_tiles, inc_i = my_items;
+    return n | (n < cap ? (int)0x80000000 : 0);
+  };
+  int sl_r[kRegs ? UPL : 1];       // kRegs: this lane's units
+  int64_t ro_r[kRegs ? UPL : 1];
+  const int per = (U + NT - 1) / NT, u0 = min(U, tid * per), u1 = min(U, u0 + per);  // !kRegs: this thread's units
+  int total_t = 0, total_i = 0, u = 0, sub = 0, team = NW, quota = 0, x = 0;
+  bool by_piece, idle;
+  // The lengths may only change once every workgroup has read them.  Each one counts its arrival when all its waves have
+  // (4 waves: after the barrier below; 8 waves, which need no barrier before their first merge: after that), and the one
+  // that arrives last counts the appended rows, at its end.
+  int order = -1;
+  if constexpr (kRegs) {
+    int base_t[UPL], base_i[UPL], cnt_t[UPL], cnt_i[UPL];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(inc_t, o, 64), i = __shfl_up(inc_i, o, 64);
-    if (lane >= o) { inc_t += t; inc_i += i; }
-  }
-  if (lane == 63) { w_tiles[wave] = inc_t; w_items[wave] = inc_i; }
-  __syncthreads();  // (every thread's reads of len[] are complete here: the scan has consumed them)
-  // The lengths may only change once every workgroup has read them: the workgroup that arrives last does it, at its end.
-  int order = 0;
-  if (tid == 0) order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  int base_t = inc_t - my_tiles, base_i = inc_i - my_items, total_t = 0, total_i = 0;
+    for (int j = 0; j < UPL; ++j) {
+      sl_r[j] = 0; ro_r[j] = 0;
+      if (64 * j < U && 64 * j + lane < U) sl_r[j] = read_len(64 * j + lane, ro_r[j]);
+    }
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (w < wave) { base_t += w_tiles[w]; base_i += w_items[w]; }
-    total_t += w_tiles[w];
-    total_i += w_items[w];
-  }
-  const bool by_piece = total_i <= (int)gridDim.x;
-  const int wg = blockIdx.x;
-  // equal ranges of tiles: at most max_wgs of them
-  const int quota = by_piece ? 0 : (total_t + min((int)gridDim.x, a.max_wgs) - 1) / min((int)gridDim.x, a.max_wgs);
-  const int x = by_piece ? wg : wg * quota;  // the piece or the tile this workgroup starts at
-  const bool idle = by_piece ? x >= total_i : x >= total_t;
-  if (!idle) {
-    const int base = by_piece ? base_i : base_t;
-    if (base <= x && x < base + (by_piece ? my_items : my_tiles)) {  // exactly one thread
-      int at = base, u = u0;
-      for (;; ++u) {
-        const int t = tiles_of(s_len[u] & 0x7fffffff), n = by_piece ? pieces_of(t) : t;
-        if (x < at + n) break;
-        at += n;
+    for (int j = 0; j < UPL; ++j) {
+      base_t[j] = base_i[j] = cnt_t[j] = cnt_i[j] = 0;
+      if (64 * j < U) {
+        int sum_t, sum_i;
+        cnt_t[j] = 64 * j + lane < U ? tiles_of(sl_r[j] & 0x7fffffff) : 0;
+        cnt_i[j] = 64 * j + lane < U ? pieces_of(cnt_t[j]) : 0;
+        base_t[j] = total_t + wave_prefix(cnt_t[j], sum_t);
+        base_i[j] = total_i + wave_prefix(cnt_i[j], sum_i);
+        total_t += sum_t;
+        total_i += sum_i;
       }
-      s_start[0] = u;
-      s_start[1] = x - at;  // piece or tile inside the unit
+    }
+    by_piece = total_i <= (int)gridDim.x;
+    if (!by_piece) {
+      const int wgs = min((int)gridDim.x, a.max_wgs);
+      quota = (int)((unsigned)(total_t + wgs - 1) / (unsigned)wgs);
+    }
+    x = by_piece ? wg : wg * quota;  // the piece or the tile this workgroup starts at
+    idle = by_piece ? x >= total_i : x >= total_t;
+#pragma unroll
+    for (int j = 0; j < UPL; ++j)
+      if (64 * j < U) {
+        const int bi = base_i[j], bt = base_t[j], ci = cnt_i[j], ct = cnt_t[j];
+        const int b = by_piece ? bi : bt, c = by_piece ? ci : ct;
+        const uint64_t hit = __ballot(b <= x && x < b + c);  // at most one unit
+        if (hit) {
+          const int at = __builtin_ctzll(hit);
+          u = 64 * j + at;
+          sub = x - __builtin_amdgcn_readlane(b, at);  // piece or tile inside the unit
+        }
+      }
+  } else {
+    int my_t = 0, max_t = 0;
+    for (int v = u0; v < u1; ++v) {
+      int64_t r0;
+      const int sl = read_len(v, r0), t = tiles_of(sl & 0x7fffffff);
+      s_len[v] = sl;
+      my_t += t;
+      max_t = max(max_t, t);
+    }
+    int sum_t;
+    const int pre = wave_prefix(my_t, sum_t);
+    for (int o = 32; o > 0; o >>= 1) max_t = max(max_t, __shfl_xor(max_t, o, 64));
+    if (lane == 0) { w_sum[wave][0] = sum_t; w_sum[wave][1] = max_t; }
+    __syncthreads();
+    if (tid == 0) order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int base = pre;
+    max_t = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) base += w_sum[w][0];
+      total_t += w_sum[w][0];
+      max_t = max(max_t, w_sum[w][1]);
+    }
+    // Every unit at once, on a.team waves each, if none of them takes longer than 8 rounds of those: then one pass
+    // (no merges, or one of two or four waves) is cheaper than several units one after the other on the whole workgroup.
+    by_piece = (int64_t)U * a.team <= (int64_t)gridDim.x * NW && max_t <= 8 * a.team && extra <= a.team;
+    if (by_piece) {
+      team = a.team;
+      u = wg * (NW / team) + wave / team;
+      idle = wg * (NW / team) >= U;
+    } else {
+      const int wgs = min((int)gridDim.x, a.max_wgs);
+      quota = (int)((unsigned)(total_t + wgs - 1) / (unsigned)wgs);
+      x = wg * quota;
+      idle = x >= total_t;
+      if (base <= x && x < base + my_t) {  // exactly one thread, if x < total_t
+        int at = base, v = u0;
+        for (;; ++v) {
+          const int t = tiles_of(s_len[v] & 0x7fffffff);
+          if (x < at + t) break;
+          at += t;
+        }
+        s_start[0] = v;
+        s_start[1] = x - at;
+      }
+      __syncthreads();
+      if (!idle) { u = s_start[0]; sub = s_start[1]; }
     }
   }
-  __syncthreads();
 
-  wave_t wv;
+  // (in a team of fewer waves than the workgroup: lanes and waves of the team)
+  const int wt = team == NW ? wave : wave & (team - 1), tt = wt * 64 + lane;
   AG_LDS uint8_t *my_lds = (AG_LDS uint8_t *)smem + wave * wave_t::kWaveB;
-  wv.init(my_lds, lane);
-  int left = idle ? 0 : by_piece ? 1 : min(quota, total_t - x);  // tiles (or the one piece) still to do
-  int u = idle ? 0 : s_start[0], sub = idle ? 0 : s_start[1], at = x;
-  while (left > 0) {
+  AG_LDS uint8_t *team_lds = (AG_LDS uint8_t *)smem + (wave - wt) * wave_t::kWaveB;
+  int left = idle || by_piece ? 0 : min(quota, total_t - x);  // tiles still to do
+  int at = x;
+  // One segment: a whole unit or a piece of it (PIECE, at most one per workgroup or team), or the next part of the
+  // workgroup's range.  Two copies of the code: the one for pieces is straight-line, without the loop whose invariants the
+  // compiler would compute, and spill, in front of it (a third of a short step).
+  auto segment = [&](auto piece_mode) {
+    constexpr bool PIECE = decltype(piece_mode)::value;
     u = __builtin_amdgcn_readfirstlane(u);
-    const int sl = __builtin_amdgcn_readfirstlane(s_len[u]);
+    const bool mine = kRegs || u < U;  // (a team past the last unit only takes part in the barriers)
+    int sl = 0;
+    int64_t ro = 0;
+    if constexpr (kRegs) {
+#pragma unroll
+      for (int j = 0; j < UPL; ++j)
+        if ((u >> 6) == j) {
+          sl = __builtin_amdgcn_readlane(sl_r[j], u & 63);
+          ro = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ro_r[j], u & 63) |
+                         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ro_r[j] >> 32), u & 63) << 32));
+        }
+    } else if (mine) {
+      sl = __builtin_amdgcn_readfirstlane(s_len[u]);
+      ro = a.row_off[u];
+    }
     const int n = sl & 0x7fffffff;
     const int T_u = tiles_of(n);
-    int t0, t1, rec0 = 0, n_rec, my_rec;  // tiles [t0, t1) of the unit; the unit's records and this one's number
-    if (by_piece) {
+    int t0 = 0, t1 = mine ? T_u : 0, rec0 = 0, n_rec = 1, my_rec = 0;  // tiles [t0, t1) of the unit; its records, this one's number
+    if constexpr (PIECE && kRegs) {
       n_rec = pieces_of(T_u);
       my_rec = sub;
-      t0 = (int)((int64_t)T_u * sub / n_rec);
-      t1 = (int)((int64_t)T_u * (sub + 1) / n_rec);
       rec0 = wg - sub;
-      left = 0;
-    } else {
+      if (n_rec > 1) {
+        t0 = sub * kPieceTiles;
+        t1 = min(T_u, t0 + kPieceTiles);
+      }
+    }
+    if constexpr (!PIECE) {
       t0 = sub;
       t1 = min(T_u, t0 + left);
       left -= t1 - t0;
       const int first = at - t0;  // the unit's first tile, counted over all units
       at += t1 - t0;
-      const int g0 = first / quota, g1 = (first + T_u - 1) / quota;
-      n_rec = g1 - g0 + 1;
-      my_rec = wg - g0;
-      rec0 = g0;
+      if (t0 > 0 || t1 < T_u) {   // a unit at one of the cuts
+        const int g0 = (int)((unsigned)first / (unsigned)quota), g1 = (int)((unsigned)(first + T_u - 1) / (unsigned)quota);
+        n_rec = g1 - g0 + 1;
+        my_rec = wg - g0;
+        rec0 = g0;
+      }
     }
-    const int64_t ro = a.row_off[u];
     const T *kn = static_cast<const T *>(a.k_new) + (size_t)u * D, *vn = static_cast<const T *>(a.v_new) + (size_t)u * D;
-    const bool first_piece = t0 == 0;  // this workgroup takes the new token in
+    const bool first_piece = mine && t0 == 0;  // this workgroup takes the new token in
     // requested now, used at the segment's end
     uint4 new_row = make_uint4(0, 0, 0, 0);
-    bool keep_new = true;
-    if (first_piece) {
-      if (tid < 2 * CPT) new_row = chunk16(reinterpret_cast<const uint8_t *>(tid < CPT ? kn : vn) + 16 * (tid % CPT), a.loose);
-      keep_new = a.new_flags == nullptr || a.new_flags[u] != 0;
+    int new_flag = 1;
+    if (first_piece && tt < 2 * CPT) {
+      new_row = chunk16(reinterpret_cast<const uint8_t *>(tt < CPT ? kn : vn) + 16 * (tt % CPT), a.loose);
+      if (a.new_flags) new_flag = a.new_flags[u];
     }
     uint64_t ring_vis = 0;
-    if (has_ring && t0 < extra) {  // evicted tokens of the window: the kept ones are cache rows already
+    if (has_ring && t0 < extra && mine) {  // evicted tokens of the window: the kept ones are cache rows already
       bool see = false;
       if (lane < a.ring.n) {
         const int p = a.ring.pos[(size_t)u * a.ring.n + lane];
-        see = p < a.pos && p > a.pos - a.ring.n && a.ring.flags[(size_t)u * a.ring.n + lane] == 0;
+        const uint8_t f = a.ring.flags[(size_t)u * a.ring.n + lane];
+        see = p < a.pos && p > a.pos - a.ring.n && f == 0;
       }
       ring_vis = __ballot(see);
     }
-    wv.begin(static_cast<const T *>(a.q) + (size_t)u * G * D);
     const T *K = static_cast<const T *>(a.kc) + (size_t)ro * D, *V = static_cast<const T *>(a.vc) + (size_t)ro * D;
-    wv.run(t0 + wave, t1, NW, a.qscale, a.loose, [&](int i) {
-      if (i >= extra) {
-        const int r = (i - extra) * kTileRows;
-        return dec_tile{K, V, (uint32_t)n * (uint32_t)(D * sizeof(T)), r, n - r >= 32 ? 0xffffffffu : (1u << (n - r)) - 1u, false};
-      }
-      if (i == 0) return dec_tile{kn, vn, (uint32_t)(D * sizeof(T)), 0, 1u, true};
-      const size_t ring0 = (size_t)u * a.ring.n * D;
-      return dec_tile{static_cast<const T *>(a.ring.k) + ring0, static_cast<const T *>(a.ring.v) + ring0,
-                      (uint32_t)a.ring.n * (uint32_t)(D * sizeof(T)), (i - 1) * kTileRows,
-                      (uint32_t)(ring_vis >> (32 * (i - 1))), true};
-    });
+    wave_t wv;
+    wv.init(my_lds, lane);
+    // the wave that never has more tiles than another one takes the new token
+    const bool own = first_piece && wt == team - 1;
+    if (t0 + wt < t1 || own)
+      wv.run(static_cast<const T *>(a.q) + (size_t)u * G * D, t0 + wt, t1, team, a.qscale, own, kn, vn, a.loose, [&](int i) {
+        if (i >= extra) {
+          const int r = (i - extra) * kTileRows;
+          return dec_tile{K, V, (uint32_t)n * (uint32_t)(D * sizeof(T)), r,
+                          n - r >= 32 ? 0xffffffffu : (1u << max(0, n - r)) - 1u, false};
+        }
+        const size_t ring0 = (size_t)u * a.ring.n * D;
+        return dec_tile{static_cast<const T *>(a.ring.k) + ring0, static_cast<const T *>(a.ring.v) + ring0, 0u,
+                        i * kTileRows, (uint32_t)(ring_vis >> (32 * i)), true};
+      });
     wv.leave((AG_LDS float *)my_lds);
     __syncthreads();
+    if (kRegs && tid == 0 && (PIECE || order < 0))
+      order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-    // ---- merge the waves' states; thread -> (head, two neighbouring columns) ----
-    const int n_states = min(NW, t1 - t0) * wave_t::kStates;
-    auto state = [&](int sI) {
-      return (AG_LDS float *)((AG_LDS uint8_t *)smem + (sI / wave_t::kStates) * wave_t::kWaveB) + (sI % wave_t::kStates) * G * SF;
-    };
-    auto store_out = [&](int gg, int d, float o0, float o1) {
+    // ---- merge the waves' states (every wave of the team left one); thread -> (head, two neighbouring columns) ----
+    auto store_out = [&](int gg, int d, float A0, float A1, float L) {
       T *dst = static_cast<T *>(a.out) + ((size_t)u * G + gg) * D + d;
       if constexpr (sizeof(T) == 2) {
-        uint16_t lo, hi;
-        to_bf16(o0, &lo);
-        to_bf16(o1, &hi);
+        const float inv = 1.f / L;
+        const uint32_t two = pack2(A0 * inv, A1 * inv);
         if (a.loose) {
-          dst[0] = lo;
-          dst[1] = hi;
+          dst[0] = (uint16_t)two;
+          dst[1] = (uint16_t)(two >> 16);
         } else {
-          *reinterpret_cast<uint32_t *>(dst) = (uint32_t)lo | ((uint32_t)hi << 16);
+          *reinterpret_cast<uint32_t *>(dst) = two;
         }
       } else {
-        *reinterpret_cast<float2 *>(dst) = make_float2(o0, o1);
+        *reinterpret_cast<float2 *>(dst) = make_float2(A0 / L, A1 / L);
       }
     };
     auto rec_at = [&](int k) {  // record of piece k of this unit
-      const int id = by_piece ? rec0 + k : 2 * (rec0 + k) + (k == 0 ? 1 : 0);
+      const int id = PIECE ? rec0 + k : 2 * (rec0 + k) + (k == 0 ? 1 : 0);
       return a.rec + (size_t)id * G * (D + 2);
     };
-    for (int e = tid; e < G * D / 2; e += NT) {
+    auto merge = [&](int e, auto waves) {
+      constexpr int NS = decltype(waves)::value;
       const int gg = e / (D / 2), d = 2 * (e - gg * (D / 2));
-      float M = kEmptyMax;
-      for (int sI = 0; sI < n_states; ++sI) M = fmaxf(M, state(sI)[gg * SF]);
-      float L = 0.f, A0 = 0.f, A1 = 0.f;
-      for (int sI = 0; sI < n_states; ++sI) {
-        const AG_LDS float *h = state(sI) + gg * SF;
-        const float w = exp2f(h[0] - M);
-        L = fmaf(w, h[1], L);
-        A0 = fmaf(w, h[4 + d], A0);
-        A1 = fmaf(w, h[5 + d], A1);
+      const AG_LDS float *h = (const AG_LDS float *)team_lds + gg * SF;
+      constexpr int WF = wave_t::kWaveB / 4;
+      float M = kEmptyMax, L = 0.f, A0 = 0.f, A1 = 0.f, ms[NS], ls[NS], o0[NS], o1[NS];
+#pragma unroll
+      for (int w = 0; w < NS; ++w) {
+        ms[w] = h[w * WF];
+        ls[w] = h[w * WF + 1];
+        o0[w] = h[w * WF + 4 + d];
+        o1[w] = h[w * WF + 5 + d];
+      }
+#pragma unroll
+      for (int w = 0; w < NS; ++w) M = fmaxf(M, ms[w]);
+#pragma unroll
+      for (int w = 0; w < NS; ++w) {
+        const float f = __builtin_amdgcn_exp2f(ms[w] - M);
+        L = fmaf(f, ls[w], L);
+        A0 = fmaf(f, o0[w], A0);
+        A1 = fmaf(f, o1[w], A1);
       }
       if (n_rec == 1) {
-        store_out(gg, d, A0 / L, A1 / L);
+        store_out(gg, d, A0, A1, L);
       } else {
         float *r = rec_at(my_rec) + gg * (D + 2);
         put_pair(r + d, A0, A1);
         if (d == 0) put_pair(r + D, M, L);
       }
+    };
+    if constexpr (kRegs || !PIECE) {
+      for (int e = tid; e < G * D / 2; e += NT) merge(e, std::integral_constant<int, NW>{});
+    } else if (mine) {
+      if (team == 4)
+        for (int e = tt; e < G * D / 2; e += 256) merge(e, std::integral_constant<int, 4>{});
+      else if (team == 2)
+        for (int e = tt; e < G * D / 2; e += 128) merge(e, std::integral_constant<int, 2>{});
+      else
+        for (int e = tt; e < G * D / 2; e += 64) merge(e, std::integral_constant<int, 1>{});
     }
-    if (n_rec > 1) {
+    if ((kRegs || !PIECE) && n_rec > 1) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the record is in memory
       __syncthreads();
       if (tid == 0)
@@ -593,48 +791,72 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
             float M_new = M;
 #pragma unroll
             for (int j = 0; j < 8; ++j) M_new = fmaxf(M_new, ml[j].x);
-            const float keep = exp2f(M - M_new);
+            const float keep = __builtin_amdgcn_exp2f(M - M_new);
             M = M_new;
             L *= keep; A0 *= keep; A1 *= keep;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              const float w = k0 + j < n_rec ? exp2f(ml[j].x - M) : 0.f;
+              const float w = k0 + j < n_rec ? __builtin_amdgcn_exp2f(ml[j].x - M) : 0.f;
               L = fmaf(w, ml[j].y, L);
               A0 = fmaf(w, o[j].x, A0);
               A1 = fmaf(w, o[j].y, A1);
             }
           }
-          store_out(gg, d, A0 / L, A1 / L);
+          store_out(gg, d, A0, A1, L);
         }
       }
     }
-    if (first_piece) {  // the new token: its cache row (nobody reads past len in this launch) and its ring slot
-      if (keep_new && sl < 0) {
-        if (tid < 2 * CPT) reinterpret_cast<uint4 *>(static_cast<T *>(tid < CPT ? a.kc : a.vc) + (size_t)(ro + n) * D)[tid % CPT] = new_row;
-        if (tid == 0) a.idx[ro + n] = a.pos;
-      } else if (keep_new && tid == 0) {
+    if (first_piece && tt < 2 * CPT) {  // the new token: its cache row (nobody reads past len in this launch) and its ring slot
+      if (new_flag != 0 && sl < 0) {
+        reinterpret_cast<uint4 *>(static_cast<T *>(tt < CPT ? a.kc : a.vc) + (size_t)(ro + n) * D)[tt % CPT] = new_row;
+        if (tt == 0) a.idx[ro + n] = a.pos;
+      } else if (new_flag != 0 && tt == 0) {
         atomicOr(a.d_err, 1);
       }
       if (has_ring) {  // slot pos % n_recent held position pos - n_recent, which no query sees any more
         const size_t slot = (size_t)u * a.ring.n + (size_t)(a.pos % a.ring.n);
-        if (tid < 2 * CPT)
-          put16(reinterpret_cast<uint8_t *>(static_cast<T *>(tid < CPT ? a.ring.k : a.ring.v) + slot * D) + 16 * (tid % CPT), new_row, a.loose);
-        if (tid == 0) {
-          a.ring.flags[slot] = keep_new ? 1 : 0;
+        put16(reinterpret_cast<uint8_t *>(static_cast<T *>(tt < CPT ? a.ring.k : a.ring.v) + slot * D) + 16 * (tt % CPT), new_row, a.loose);
+        if (tt == 0) {
+          a.ring.flags[slot] = new_flag != 0 ? 1 : 0;
           a.ring.pos[slot] = a.pos;
         }
       }
     }
-    __syncthreads();  // the states have been read: the next segment may load over them
     ++u;
     sub = 0;
+  };
+  if (by_piece) {
+    if (!idle) segment(std::true_type{});
+  } else {
+    while (left > 0) {
+      segment(std::false_type{});
+      if (left > 0) __syncthreads();  // the states have been read: the next segment may load over them
+    }
   }
-  // ---- the last workgroup to have read the lengths counts the appended rows ----
-  if (tid == 0) s_last = order == (int)gridDim.x - 1;
+  // ---- the last workgroup to arrive counts the appended rows ----
+  __syncthreads();
+  if (tid == 0) {
+    if (kRegs && order < 0) order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = order == (int)gridDim.x - 1;
+  }
   __syncthreads();
   if (!s_last) return;
-  for (int v = u0; v < u1; ++v)
-    if (s_len[v] < 0 && (a.new_flags == nullptr || a.new_flags[v] != 0)) a.len[v] = (s_len[v] & 0x7fffffff) + 1;
+  if constexpr (kRegs) {
+    if (wave == 0)
+#pragma unroll
+      for (int j = 0; j < UPL; ++j)
+        if (64 * j + lane < U && sl_r[j] < 0 && (a.new_flags == nullptr || a.new_flags[64 * j + lane] != 0))
+          a.len[64 * j + lane] = (sl_r[j] & 0x7fffffff) + 1;
+  } else {
+    for (int v0 = tid; v0 < U; v0 += 4 * NT) {  // (four flags requested together: this is the tail of the step)
+      uint8_t f[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = a.new_flags ? a.new_flags[min(v0 + j * NT, U - 1)] : (uint8_t)1;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (v0 + j * NT < U && f[j] != 0 && s_len[v0 + j * NT] < 0) a.len[v0 + j * NT] = (s_len[v0 + j * NT] & 0x7fffffff) + 1;
+    }
+  }
   if (tid == 0) *a.arrived = 0;
 }
 
@@ -670,11 +892,12 @@ int64_t max_records(int units, int64_t cache_rows) { return cache_rows / kChunk 
 template <typename T, int D, int G, int NW>
 hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, int64_t records) {
   typedef typename wave_of<T, D, G>::type wave_t;
-  const size_t shmem = (size_t)NW * wave_t::kWaveB + (size_t)a.U * 4;
+  const size_t shmem = (size_t)NW * wave_t::kWaveB + (NW == 8 ? 0 : (size_t)a.U * 4);
   // one workgroup per CU (8 waves) or two (4 waves); no more than the step can have pieces
   const int64_t pieces = a.U + total_rows / (2 * NW * kTileRows) + 1;
   const int blocks = (int)std::min<int64_t>(NW == 8 ? ctx->num_cu : 2 * ctx->num_cu, pieces);
   a.max_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(records / 2, blocks));
+  for (a.team = NW; a.team > 1 && (int64_t)a.U * a.team > (int64_t)blocks * NW;) a.team /= 2;
   if (shmem > 48 * 1024) {
     static std::atomic<size_t> allowed[64];  // per device: the largest size asked for so far
     std::atomic<size_t> &most = allowed[ctx->device & 63];
