@@ -13,8 +13,8 @@
 //     group at once.  p enters the second product as a bf16 pair (high part + remainder, two MFMAs): the weights keep 16
 //     bits, as a 32-bit product would.  fp32 caches run on the vector ALU.
 //   * Segments (what a workgroup works on between two merges) are chosen on the device.  If the whole step gives every
-//     workgroup at most one segment -- a unit of up to 4 rounds of its waves stays whole, a longer one is cut into
-//     pieces of two rounds -- a unit's pieces meet once; otherwise the tiles of all units are laid end to end and cut
+//     workgroup at most one segment -- a unit of up to 2 rounds of its waves stays whole, a longer one is cut into the
+//     smallest pieces that fit the launch -- a unit's pieces meet once; otherwise the tiles of all units are laid end to end and cut
 //     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.  Many short units (more
 //     than a CU-filling launch has workgroups for) are given to single waves or pairs of them instead, all at once.
 //   * A unit inside one workgroup is finished there, through LDS.  The pieces of a longer one are stored as records
@@ -493,7 +493,6 @@ template <typename T, int D, int G, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   typedef typename wave_of<T, D, G>::type wave_t;
   constexpr int NT = 64 * NW, SF = wave_t::kStateF;
-  constexpr int kPieceTiles = 2 * NW, kWholeTiles = 4 * NW;
   constexpr int CPT = (int)(D * sizeof(T) / 16);  // 16-byte chunks per row
   constexpr bool kRegs = NW == 8;                 // the work list lives in registers (at most 256 units)
   constexpr int UPL = kFewUnits / 64;             // ... that many units per lane: unit 64 j + lane
@@ -509,9 +508,12 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   const bool has_ring = a.ring.k != nullptr;
   const int extra = has_ring ? (a.ring.n + kTileRows - 1) / kTileRows : 0;
 
-  // ---- the work list: tiles per unit (at least one), and the pieces it would be cut into ----
+  // ---- the work list: tiles per unit (at least one), and the pieces it is cut into ----
+  constexpr int kWholeTiles = (D * sizeof(T) >= 256 ? 2 : 4) * NW;
+  int piece = NW;  // tiles per piece: `rounds` rounds of the workgroup's waves
+  uint32_t piece_inv = (uint32_t)((1ull << 32) / NW);  // ceil(2^32 / piece): x / piece for x piece < 2^32
   auto tiles_of = [&](int n) { return max(1, extra + (int)((unsigned)(n + kTileRows - 1) / kTileRows)); };
-  auto pieces_of = [&](int t) { return t <= kWholeTiles ? 1 : (int)((unsigned)(t + kPieceTiles - 1) / kPieceTiles); };
+  auto pieces_of = [&](int t) { return t <= max(kWholeTiles, piece) ? 1 : (int)__umulhi((uint32_t)(t + piece - 1), piece_inv); };
   auto read_len = [&](int u, int64_t &r0) {  // valid rows of unit u, top bit set if another one fits
     r0 = a.row_off[u];
     const int64_t cap = a.row_off[u + 1] - r0;
@@ -537,18 +539,44 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
     }
 #pragma unroll
     for (int j = 0; j < UPL; ++j) {
-      base_t[j] = base_i[j] = cnt_t[j] = cnt_i[j] = 0;
+      base_t[j] = cnt_t[j] = 0;
       if (64 * j < U) {
-        int sum_t, sum_i;
+        int sum_t;
         cnt_t[j] = 64 * j + lane < U ? tiles_of(sl_r[j] & 0x7fffffff) : 0;
-        cnt_i[j] = 64 * j + lane < U ? pieces_of(cnt_t[j]) : 0;
         base_t[j] = total_t + wave_prefix(cnt_t[j], sum_t);
-        base_i[j] = total_i + wave_prefix(cnt_i[j], sum_i);
         total_t += sum_t;
-        total_i += sum_i;
       }
     }
-    by_piece = total_i <= (int)gridDim.x;
+    // The smallest pieces that the launch has workgroups for: the rounds of an even spread if they fit, else what is sure
+    // to.  A round costs a workgroup about 1 us (what one CU's LDS keeps in flight), the meeting of a unit's pieces about
+    // as much, so units of up to two rounds of 16 KiB stay whole.  Measured on 8 units of up to 777 rows of 256 bytes:
+    // 7.9 us per step in pieces of one round, 8.4 us whole; rows of 128 bytes: 8.2 us and 7.4 us.
+    const int grid = gridDim.x;
+    bool last_try = false;
+    int rounds = 1;
+    if (total_t > NW * grid) rounds = (int)((unsigned)(total_t + NW * grid - 1) / (unsigned)(NW * grid));
+    for (;;) {
+      if (rounds > 1) {
+        piece = rounds * NW;
+        piece_inv = 0xffffffffu / (unsigned)piece + 1u;
+      }
+      total_i = 0;
+#pragma unroll
+      for (int j = 0; j < UPL; ++j) {
+        base_i[j] = cnt_i[j] = 0;
+        if (64 * j < U) {
+          int sum_i;
+          cnt_i[j] = 64 * j + lane < U ? pieces_of(cnt_t[j]) : 0;
+          base_i[j] = total_i + wave_prefix(cnt_i[j], sum_i);
+          total_i += sum_i;
+        }
+      }
+      if (total_i <= grid || last_try || U >= grid) break;
+      rounds = max(rounds, (int)((unsigned)(total_t + NW * (grid - U) - 1) / (unsigned)(NW * (grid - U))));
+      last_try = true;
+    }
+    // ... unless there are so many units that the remainders of their last pieces weigh more than equal ranges cost
+    by_piece = total_i <= grid && (rounds <= 2 || 4 * U <= grid);
     if (!by_piece) {
       const int wgs = min((int)gridDim.x, a.max_wgs);
       quota = (int)((unsigned)(total_t + wgs - 1) / (unsigned)wgs);
@@ -652,8 +680,8 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
       my_rec = sub;
       rec0 = wg - sub;
       if (n_rec > 1) {
-        t0 = sub * kPieceTiles;
-        t1 = min(T_u, t0 + kPieceTiles);
+        t0 = sub * piece;
+        t1 = min(T_u, t0 + piece);
       }
     }
     if constexpr (!PIECE) {
@@ -894,7 +922,7 @@ hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows,
   typedef typename wave_of<T, D, G>::type wave_t;
   const size_t shmem = (size_t)NW * wave_t::kWaveB + (NW == 8 ? 0 : (size_t)a.U * 4);
   // one workgroup per CU (8 waves) or two (4 waves); no more than the step can have pieces
-  const int64_t pieces = a.U + total_rows / (2 * NW * kTileRows) + 1;
+  const int64_t pieces = a.U + total_rows / (NW * kTileRows) + 1;
   const int blocks = (int)std::min<int64_t>(NW == 8 ? ctx->num_cu : 2 * ctx->num_cu, pieces);
   a.max_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(records / 2, blocks));
   for (a.team = NW; a.team > 1 && (int64_t)a.U * a.team > (int64_t)blocks * NW;) a.team /= 2;

@@ -20,7 +20,7 @@ def _lib():
 
 @pytest.mark.parametrize("dtype,B,Hq,Hkv,D,lens", [
     ("bf16", 1, 4, 4, 128, [31, 32, 33, 0]),                    # one tile, its edges
-    ("bf16", 1, 8, 8, 64, [1, 63, 64, 65, 991, 992, 993, 2]),   # a unit of 32 tiles stays whole, 33 are cut (8 waves)
+    ("bf16", 1, 8, 8, 64, [1, 63, 64, 65, 1023, 1024, 1025, 2]),   # a unit of 32 tiles stays whole, 33 are cut (8 waves)
     ("bf16", 1, 8, 2, 128, [9000, 1025]),                       # few units, many pieces
     ("bf16", 2, 32, 8, 128, [7000] * 15 + [3]),                 # more pieces than workgroups: equal ranges
     ("bf16", 65, 4, 4, 128, [5, 170, 40, 480]),                 # 260 units: 4 waves, ranges that hold many units
