@@ -57,7 +57,7 @@ ag_status need_device(ag_ctx *ctx) {
 
 }  // namespace
 
-constexpr size_t kTailBytes = 256 + (kGateTickets + kDecodeMaxUnits + 1) * sizeof(int32_t);
+constexpr size_t kTailBytes = 256 + (kDecodeMaxUnits + 1) * sizeof(int32_t);
 
 extern "C" {
 
@@ -80,8 +80,7 @@ ag_status ag_create(ag_ctx **out, int device, size_t workspace_bytes) {
     }
     if (e == hipSuccess) {  // behind the workspace: the error word and the arrival counters, all zero
       ctx->d_err = reinterpret_cast<int32_t *>(ctx->ws + ctx->ws_bytes);
-      ctx->gate_tickets = reinterpret_cast<int32_t *>(ctx->ws + ctx->ws_bytes + 256);
-      ctx->decode_tickets = ctx->gate_tickets + kGateTickets;
+      ctx->decode_tickets = reinterpret_cast<int32_t *>(ctx->ws + ctx->ws_bytes + 256);
       e = hipMemset(ctx->d_err, 0, kTailBytes);
     }
     if (e == hipSuccess) e = ag_static_scratch(device, &ctx->static_scratch);

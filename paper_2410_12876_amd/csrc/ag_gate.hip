@@ -1,15 +1,12 @@
 // Gate (Eq. 3, Eq. 4): features [tokens, d_in] x W [d_in, H_f] -> logits -> keep flags.
 //
-// The product is a skinny GEMM (N = H_f <= 32) whose cost is reading the features once from HBM.  The bf16
-// path runs it on MFMA (v_mfma_f32_32x32x16_bf16, N padded to 32): every wave owns a tile of tokens and a slice
-// of the K range, fetches its feature rows as whole 128-byte lines (handed to the MFMA layout through LDS in the
-// fused kernels), and takes the matching W fragments either from W as stored, transposed on the way through LDS,
-// or from a pre-packed copy that stays in L2.  K is split over the waves of a workgroup.  With enough tokens one
-// fused kernel does everything (ag_gate_fused_kernel; ag_norm_gate_kernel when the normalisation of the input is
-// fused in as well).  With few tokens (decode-sized calls) K is also split over several workgroups of the simpler
-// ag_gate_mfma_kernel; partial sums then go to the workspace and a second kernel adds them in a fixed order (so
-// flags are reproducible run to run), adds the bias, compares with the logit-space threshold and writes the flags
-// head-major.
+// The product is a skinny GEMM (N = H_f <= 32) whose cost is reading the features once from HBM.  One launch does
+// everything: a workgroup of 8 waves owns a tile of tokens, each wave a slice of the features; the 8 partial tiles are
+// added in wave order through LDS (so logits and flags are reproducible run to run), then bias, threshold, logits and the
+// head-major flags.  bf16 runs on MFMA: a wave fetches its feature rows as whole 128-byte lines, handed to the MFMA layout
+// through LDS, and takes the matching W fragments either from W as stored, transposed on the way through LDS, or (H_f not
+// a multiple of 4, or W not 16-byte aligned) from a pre-packed copy.  ag_norm_gate_kernel fuses the normalisation of the
+// input in as well.
 #include "ag_internal.h"
 
 namespace {
@@ -18,6 +15,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 #define AG_LDS __attribute__((address_space(3)))
@@ -41,68 +39,43 @@ __global__ void ag_gate_pack_w(const uint16_t *__restrict__ w, int d_in, int H_f
   wp[i] = n < H_f ? w[(size_t)kk * H_f + n] : (uint16_t)0;
 }
 
-// grid = (token tiles, K splits); block = 256.  partial [S][tokens_pad][32] fp32.
-template <int MT>
-__global__ __launch_bounds__(256) void ag_gate_mfma_kernel(const uint16_t *__restrict__ x, const uint4 *__restrict__ wp,
-                                                           int64_t tokens, int d_in, int chunks_per_split,
-                                                           float *__restrict__ partial, int64_t tokens_pad) {
-  __shared__ float red[4][MT][32][33];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = lane & 31, kb = lane >> 5;
-  const int64_t tok0 = (int64_t)blockIdx.x * (32 * MT);
-  const int nchunks = d_in / 64;
-  const int c_begin = blockIdx.y * chunks_per_split;
-  const int c_end = min(nchunks, c_begin + chunks_per_split);
-
-  const uint4 *rows[MT];
+// Bias, threshold, logits [tokens, H_f] and head-major flags of a tile of TOK tokens from the 8 waves' partial tiles
+// red(w, row, head).  Token and sequence of a row follow from the tile's first token by counting, not by a division each.
+template <int TOK, typename RED>
+__device__ __forceinline__ void gate_epilogue(RED &&red, uint8_t (&fl)[kNP][32], uint32_t tok0, uint32_t tokens, int L, int H_f,
+                                              const float *__restrict__ bias, float thr, int n_sink,
+                                              float *__restrict__ logits, uint8_t *__restrict__ flags) {
+  const uint32_t b0 = tok0 / (uint32_t)L, t0 = tok0 - b0 * (uint32_t)L;  // (uniform)
+  auto place = [&](int rw, uint32_t &b, uint32_t &t) {
+    b = b0; t = t0 + rw;
+    while (t >= (uint32_t)L) { t -= L; ++b; }
+  };
 #pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    int64_t tok = tok0 + t * 32 + m;
-    if (tok >= tokens) tok = tokens - 1;  // clamp: the row is read but its result is never written
-    rows[t] = reinterpret_cast<const uint4 *>(x + (size_t)tok * d_in + kb * 32);
+  for (int i = 0; i < TOK / 16; ++i) {  // element e = (token row e / 32, head e % 32)
+    const int e = threadIdx.x + 512 * i, rw = e >> 5, h = e & 31;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) v += red(w, rw, h);
+    const uint32_t tk = tok0 + rw;
+    if (h < H_f && tk < tokens) {
+      uint32_t b, t;
+      place(rw, b, t);
+      const float val = v + bias[h];
+      if (logits) logits[(size_t)tk * H_f + h] = val;
+      fl[h][rw] = (val > thr || (int)t < n_sink) ? 1 : 0;
+    }
   }
-  f32x16 acc[MT];
-#pragma unroll
-  for (int t = 0; t < MT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-
-  for (int c = c_begin + wave; c < c_end; c += 4) {
-    uint4 a[MT][4], b[4];
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) a[t][s] = rows[t][c * 8 + s];  // 64 k = 8 uint4 per row; this lane's half
-#pragma unroll
-    for (int s = 0; s < 4; ++s) b[s] = wp[((size_t)c * 4 + s) * 64 + lane];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int t = 0; t < MT; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[t][s]),
-                                                         __builtin_bit_cast(bf16x8, b[s]), acc[t], 0, 0, 0);
-  }
-  // C layout of the 32x32 tile: acc[r] is (row = 8*(r/4) + 4*(lane/32) + r%4, col = lane%32)
-#pragma unroll
-  for (int t = 0; t < MT; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][t][8 * (r >> 2) + 4 * kb + (r & 3)][m] = acc[t][r];
   __syncthreads();
-  float *dst = partial + ((size_t)blockIdx.y * tokens_pad + tok0) * kNP;
-  for (int e = threadIdx.x; e < MT * 32 * 32; e += 256) {
-    const int t = e >> 10, row = (e >> 5) & 31, col = e & 31;
-    dst[e] = red[0][t][row][col] + red[1][t][row][col] + red[2][t][row][col] + red[3][t][row][col];
+  for (int e = threadIdx.x; e < TOK * H_f; e += 512) {
+    const int h = e / TOK, rw = e % TOK;
+    if (tok0 + rw >= tokens) continue;
+    uint32_t b, t;
+    place(rw, b, t);
+    flags[((size_t)b * H_f + h) * L + t] = fl[h][rw];
   }
 }
 
-// One workgroup of 8 waves per tile of TOK = 32 or 16 tokens and K split (grid.y splits; wave w takes 64-wide
-// chunks w, w + 8, ... of its split, PF of them in flight), the 8 partial tiles added in wave order through LDS.
-// (TOK = 16: launches with fewer 32-token tiles than CUs; the upper half of the MFMA then repeats the lower.)  With one split the workgroup
-// goes on to bias, threshold, logits and head-major flags.  With several, each stores its 32x32 partial tile
-// (written through the caches, complete before its arrival is counted) and the split that arrives last adds all
-// of them in split order -- the same order whoever is last, so the flags are reproducible -- and finishes.
-// The arrival counters live in the context, start at zero and are set back to zero by the split that arrives
-// last, so no launch has to clear them.
+// One workgroup of 8 waves per tile of 32 tokens: wave w takes 64-wide chunks w, w + 8, ..., PF of them in flight.
 //
 // RAW: W is taken as the caller stores it ([d_in, H_f] row-major, H_f a multiple of 4, 16-byte aligned).  A wave
 // copies the 64 rows of a chunk into its own 4 KiB of LDS and reads them back with the transposing LDS read,
@@ -110,27 +83,23 @@ __global__ __launch_bounds__(256) void ag_gate_mfma_kernel(const uint16_t *__res
 // A operand (lane = token m and half kb: features kb*32 + step*8 + 0..7).  Columns n >= H_f read whatever follows in LDS; they only reach output
 // columns that are never stored.  Otherwise wp holds the fragments prepared by ag_gate_pack_w.
 constexpr int kFusedWaves = 8;
-template <bool RAW, int PF, int TOK>
+template <bool RAW, int PF>
 __global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fused_kernel(
     const uint16_t *__restrict__ x, const uint4 *__restrict__ wp, int64_t tokens, int d_in, int L, int H_f,
-    const float *__restrict__ bias, float thr, int n_sink, float *__restrict__ logits, uint8_t *__restrict__ flags,
-    float *__restrict__ partial, int32_t *__restrict__ tickets) {
+    const float *__restrict__ bias, float thr, int n_sink, float *__restrict__ logits, uint8_t *__restrict__ flags) {
+  constexpr int TOK = 32;
   // [wave][4 KiB]: W staging of the wave while it accumulates, afterwards its 32 x 32 fp32 partial tile
   __shared__ __attribute__((aligned(16))) uint8_t wst[kFusedWaves][4096];
   // [wave][4 KiB]: a chunk of the wave's 32 feature rows on its way from the memory-side layout to the A layout
   __shared__ __attribute__((aligned(16))) uint8_t xstage[kFusedWaves][4096];
   __shared__ uint8_t fl[kNP][32];
-  __shared__ int is_last;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: chunk offsets stay in SGPRs
   const int m = lane & 31, kb = lane >> 5;
-  const int ma = m & (TOK - 1);  // A row this lane reads: with 16-token tiles the upper half of the MFMA repeats the lower
   const int lr = lane >> 3, lp = lane & 7;  // row within a group of 8 and 16-byte piece of the memory-side layout
   constexpr int NI = TOK / 8;  // load instructions per chunk: 8 rows each
   const int64_t tok0 = (int64_t)blockIdx.x * TOK;
   const int nchunks = d_in / 64;
-  const int splits = gridDim.y, split = blockIdx.y;
-  const int c_lo = (int)((int64_t)nchunks * split / splits), c_hi = (int)((int64_t)nchunks * (split + 1) / splits);
   // Feature rows: a chunk (64 features) is one 128-byte line per row, and a load instruction fetches 8 whole
   // lines (lane -> row 8 i + lane / 8, 16-byte piece lane % 8) instead of 64 scattered 16-byte pieces, which the
   // texture path would take four times as long to address.  Rows past the last token repeat the last row (read,
@@ -159,13 +128,13 @@ __global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fus
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int c0 = c_lo + wave; c0 < c_hi; c0 += kFusedWaves * PF) {
+  for (int c0 = wave; c0 < nchunks; c0 += kFusedWaves * PF) {
     uint4 a[PF][4], b[PF][4];
     // W first: its loads hit the L2 and return early, so the staging below runs while the feature rows are
     // still on their way from HBM (a wave's loads return in issue order)
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
-      const int c = min(c0 + kFusedWaves * p, c_hi - 1);
+      const int c = min(c0 + kFusedWaves * p, nchunks - 1);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         if (RAW) {
@@ -178,7 +147,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fus
     }
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
-      const int c = min(c0 + kFusedWaves * p, c_hi - 1);
+      const int c = min(c0 + kFusedWaves * p, nchunks - 1);
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, row_off[i], c * 128, 0);
@@ -205,7 +174,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fus
     }
 #pragma unroll
     for (int p = 0; p < PF; ++p)
-      if (c0 + kFusedWaves * p < c_hi) {
+      if (c0 + kFusedWaves * p < nchunks) {
         wave_sync();  // the previous chunk's fragments have been read
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -214,7 +183,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fus
         wave_sync();  // the chunk's rows are there for every lane
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const u32x4 t = *reinterpret_cast<const AG_LDS u32x4 *>(xst + ma * 128 + (((kb * 4 + s) ^ xkey(ma)) << 4));
+          const u32x4 t = *reinterpret_cast<const AG_LDS u32x4 *>(xst + m * 128 + (((kb * 4 + s) ^ xkey(m)) << 4));
           a[p][s] = make_uint4(t[0], t[1], t[2], t[3]);
         }
 #pragma unroll
@@ -228,58 +197,106 @@ __global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fus
 #pragma unroll
   for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * kb + (r & 3)][m] = acc[r];
   __syncthreads();
-  // element e = (token row e / 32, head e % 32); thread t owns e = t and t + 512
-  float v[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int e = threadIdx.x + 64 * kFusedWaves * i;
-    v[i] = 0.f;
-#pragma unroll
-    for (int w = 0; w < kFusedWaves; ++w) v[i] += red[w][e >> 5][e & 31];
+  gate_epilogue<TOK>([&](int w, int row, int h) { return red[w][row][h]; }, fl, (uint32_t)tok0, (uint32_t)tokens, L, H_f, bias, thr,
+                     n_sink, logits, flags);
+}
+
+// Tiles of 16 tokens, W as stored: launches with fewer 32-token tiles than CUs.  Such a launch is one round of loads, and
+// what bounds it is the one CU's memory path (64 bytes a cycle: 16 rows of features and ALL of W for every workgroup,
+// 384 KiB at 4096 x 32 features, 2.7 us) and the LDS behind it, not HBM.  Hence v_mfma_f32_16x16x32_bf16 (a 32-row MFMA
+// would read every x fragment twice), chunks processed in the order they arrive while the later ones are on their way, no
+// column tile beyond H_f, and W's first touch spread over the chip: the workgroups of an XCD each request a different
+// 1/32 of W before anything else, so that it is in their L2 when 32 of them want it at once; without that its lines
+// queue behind the features of the whole launch.
+template <int PF>  // chunks a wave keeps in flight
+__global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
+    const uint16_t *__restrict__ x, const uint4 *__restrict__ wp, uint32_t tokens, int d_in, int L, int H_f,
+    const float *__restrict__ bias, float thr, int n_sink, float *__restrict__ logits, uint8_t *__restrict__ flags) {
+  // [wave][6 KiB]: a chunk of W (64 rows), then a chunk of the 16 feature rows; afterwards the wave's partial tile
+  __shared__ __attribute__((aligned(16))) uint8_t mem[kFusedWaves][6144];
+  __shared__ uint8_t fl[kNP][32];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, kg = lane >> 4;
+  const int lr = lane >> 3, lp = lane & 7;  // row within a group of 8 and 16-byte piece of the memory-side layout
+  const uint32_t tok0 = blockIdx.x * 16;
+  const int nchunks = d_in / 64, chunk_u4 = 8 * H_f;
+  {
+    // (into the wave's W buffer, which is first written after its own loads, which come later, have arrived; pieces past
+    // the end of W are not requested)
+    const __amdgpu_buffer_rsrc_t w_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, (uint32_t)d_in * (uint32_t)H_f * 2u, 0x00020000);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)((AG_LDS uint8_t *)mem[wave]));
+    const int off = (((blockIdx.x >> 3) & 31) * 512 + threadIdx.x) * 16;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(off), "s"(w_rsrc) : "memory");
   }
-  if (splits > 1) {
-    float *tile = partial + (size_t)blockIdx.x * splits * 1024;
+  const int rows = (int)min(16u, tokens - tok0);
+  const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(x + (size_t)tok0 * d_in), 0, (uint32_t)rows * (uint32_t)d_in * 2u, 0x00020000);
+  int row_off[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      __hip_atomic_store(&tile[split * 1024 + threadIdx.x + 64 * kFusedWaves * i], v[i], __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_SYSTEM);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0)
-      is_last = __hip_atomic_fetch_add(&tickets[blockIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == splits - 1;
-    __syncthreads();
-    if (!is_last) return;
-    if (threadIdx.x == 0) tickets[blockIdx.x] = 0;  // ready for the next launch
+  for (int i = 0; i < 2; ++i) row_off[i] = min(8 * i + lr, rows - 1) * d_in * 2 + lp * 16;
+  AG_LDS uint8_t *wst = (AG_LDS uint8_t *)mem[wave], *xst = wst + 4096;
+  // transposing read of W: the 16 lanes of key group kg give the addresses of 4 rows x 16 columns (lane i: row i / 4,
+  // columns 4 (i % 4) ..+3) and lane i receives column i of the 4 rows
+  const int w_row = 8 * kg + (col >> 2), w_col = 4 * (col & 3);
+  int tr_off[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      float sum = 0.f;
-      for (int sp = 0; sp < splits; ++sp) {
-        const float other = __hip_atomic_load(&tile[sp * 1024 + threadIdx.x + 64 * kFusedWaves * i], __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_SYSTEM);
-        sum += sp == split ? v[i] : other;
+  for (int nt = 0; nt < 2; ++nt) tr_off[nt] = w_row * (H_f * 2) + min(16 * nt + w_col, H_f - 4) * 2;
+  const bool two = H_f > 16;
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  for (int c0 = wave; c0 < nchunks; c0 += kFusedWaves * PF) {
+    u32x4 a[PF][2];
+    uint4 b[PF][4];
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      const int c = min(c0 + kFusedWaves * p, nchunks - 1);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (s == 0 || s * 64 < chunk_u4) b[p][s] = wp[(size_t)c * chunk_u4 + min(s * 64 + lane, chunk_u4 - 1)];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) a[p][i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, row_off[i], c * 128, 0);
+    }
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+      if (c0 + kFusedWaves * p < nchunks) {
+        wave_sync();  // the previous chunk's fragments have been read
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          if (s * 64 < chunk_u4 && s * 64 + lane < chunk_u4)
+            *reinterpret_cast<AG_LDS u32x4 *>(wst + (s * 64 + lane) * 16) = u32x4{b[p][s].x, b[p][s].y, b[p][s].z, b[p][s].w};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          *reinterpret_cast<AG_LDS u32x4 *>(xst + (8 * i + lr) * 128 + ((lp ^ xkey(8 * i + lr)) << 4)) = a[p][i];
+        wave_sync();  // the chunk is there for every lane
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const bf16x8 af = *reinterpret_cast<const AG_LDS bf16x8 *>(xst + col * 128 + (((4 * s + kg) ^ xkey(col)) << 4));
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt)
+            if (nt == 0 || two) {
+              const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(wst + tr_off[nt] + (32 * s) * (H_f * 2)));
+              const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(wst + tr_off[nt] + (32 * s + 4) * (H_f * 2)));
+              acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7), acc[nt], 0, 0, 0);
+            }
+        }
       }
-      v[i] = sum;
-    }
   }
+  // acc[nt][r] is (token 4 kg + r, head 16 nt + col)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a wave without a chunk: its request for W has landed)
+  wave_sync();
+  float(*red)[6144 / 4] = reinterpret_cast<float(*)[6144 / 4]>(mem);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int e = threadIdx.x + 64 * kFusedWaves * i;
-    const int rw = e >> 5, h = e & 31;
-    const int64_t tk = tok0 + rw;
-    if (h < H_f && rw < TOK && tk < tokens) {
-      const float val = v[i] + bias[h];
-      if (logits) logits[(size_t)tk * H_f + h] = val;
-      fl[h][rw] = (val > thr || (int)(tk % L) < n_sink) ? 1 : 0;
-    }
-  }
+  for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][(4 * kg + r) * 32 + 16 * nt + col] = acc[nt][r];
   __syncthreads();
-  for (int e = threadIdx.x; e < 32 * H_f; e += 64 * kFusedWaves) {
-    const int h = e >> 5, rw = e & 31;
-    const int64_t tk = tok0 + rw;
-    if (rw >= TOK || tk >= tokens) continue;
-    const int64_t b = tk / L;
-    flags[((size_t)b * H_f + h) * L + (tk - b * L)] = fl[h][rw];
-  }
+  gate_epilogue<16>([&](int w, int row, int h) { return red[w][row * 32 + h]; }, fl, tok0, tokens, L, H_f, bias, thr, n_sink, logits, flags);
 }
 
 // RMS normalisation fused with the gate: x = h / sqrt(mean_c h^2 + eps) * g, rounded once to bf16, written out for
@@ -476,94 +493,54 @@ __global__ __launch_bounds__(64 * kFusedWaves, TOK == 16 ? 2 : 1) void ag_norm_g
   }
 }
 
-// fp32 features: plain ALU path (one thread per (token, padded head)), partial [1][tokens_pad][32].
-__global__ __launch_bounds__(256) void ag_gate_f32_kernel(const float *__restrict__ x, const float *__restrict__ w,
-                                                          int64_t tokens, int d_in, int H_f,
-                                                          float *__restrict__ partial) {
-  const int h = threadIdx.x & 31;
-  const int64_t tok = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-  if (tok >= tokens) return;
-  float s = 0.f;
-  if (h < H_f) {
-    const float *xr = x + (size_t)tok * d_in;
-    for (int c = 0; c < d_in; ++c) s = fmaf(xr[c], w[(size_t)c * H_f + h], s);
-  }
-  partial[(size_t)tok * kNP + h] = s;
-}
-
-// Sum the K splits in order, add bias, threshold, write logits [tokens, H_f] and flags [B, H_f, L].
-constexpr int kFinTok = 16;  // tokens per finalize workgroup
-
-__global__ __launch_bounds__(256) void ag_gate_finalize_kernel(const float *__restrict__ partial, int splits,
-                                                               int64_t tokens_pad, int64_t tokens, int L, int H_f,
-                                                               const float *__restrict__ bias, float thr, int n_sink,
-                                                               float *__restrict__ logits,
-                                                               uint8_t *__restrict__ flags) {
-  __shared__ uint8_t fl[kNP][kFinTok];
-  const int64_t tok0 = (int64_t)blockIdx.x * kFinTok;
-  const int h = threadIdx.x & 31;
-  // thread -> (token tok0 + tid/32 [+ 8], head h): the K splits of both elements are fetched as independent loads
-  float s[2] = {0.f, 0.f};
-  int64_t tok[2];
+// fp32: v_mfma_f32_16x16x4_f32 on tiles of 16 tokens, the features split over the 8 waves.  A lane's operand elements are
+// four consecutive features (one 16-byte load of x, four rows of W), used by four MFMAs: the order of the features in the
+// sum is free.  Launches of this path are small: one round of loads and the reduction are its time (128 tokens x 256
+// features: 22 us with one thread per logit and a second kernel for the threshold).
+__global__ __launch_bounds__(64 * kFusedWaves) void ag_gate_f32_kernel(const float *__restrict__ x, const float *__restrict__ w,
+                                                                       uint32_t tokens, int d_in, int L, int H_f,
+                                                                       const float *__restrict__ bias, float thr, int n_sink,
+                                                                       float *__restrict__ logits, uint8_t *__restrict__ flags) {
+  __shared__ float red[kFusedWaves][16][32];
+  __shared__ uint8_t fl[kNP][32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = lane & 15, kg = lane >> 4;
+  const uint32_t tok0 = blockIdx.x * 16;
+  const float *xr = x + (size_t)min(tok0 + col, tokens - 1) * d_in;
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  const bool two = H_f > 16;
+  const int n0 = min(col, H_f - 1), n1 = min(16 + col, H_f - 1);  // (columns past H_f: computed, never stored)
+  for (int k0 = 16 * wave; k0 < d_in; k0 += 16 * kFusedWaves) {
+    const int k = k0 + 4 * kg;
+    float xa[4], wa[4], wb[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) tok[i] = min(tok0 + (threadIdx.x >> 5) + 8 * i, tokens - 1);
-#pragma unroll 4
-  for (int sp = 0; sp < splits; ++sp)
+    for (int j = 0; j < 4; ++j) {
+      const bool in = k + j < d_in;
+      const int kk = in ? k + j : d_in - 1;
+      xa[j] = in ? xr[kk] : 0.f;
+      wa[j] = in ? w[(size_t)kk * H_f + n0] : 0.f;
+      wb[j] = two && in ? w[(size_t)kk * H_f + n1] : 0.f;
+    }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) s[i] += partial[((size_t)sp * tokens_pad + tok[i]) * kNP + h];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int tl = (threadIdx.x >> 5) + 8 * i;
-    if (h < H_f && tok0 + tl < tokens) {
-      const float v = s[i] + bias[h];
-      if (logits) logits[(size_t)tok[i] * H_f + h] = v;
-      const int t = (int)(tok[i] % L);
-      fl[h][tl] = (v > thr || t < n_sink) ? 1 : 0;
+    for (int j = 0; j < 4; ++j) {
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[j], wa[j], acc[0], 0, 0, 0);
+      if (two) acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[j], wb[j], acc[1], 0, 0, 0);
     }
   }
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][4 * kg + r][16 * nt + col] = acc[nt][r];
   __syncthreads();
-  for (int e = threadIdx.x; e < kFinTok * H_f; e += 256) {
-    const int hh = e / kFinTok, tl = e - hh * kFinTok;
-    const int64_t tk = tok0 + tl;
-    if (tk >= tokens) continue;
-    const int64_t b = tk / L;
-    const int t = (int)(tk - b * L);
-    flags[((size_t)b * H_f + hh) * L + t] = fl[hh][tl];
-  }
-}
-
-struct gate_plan {
-  int mt, tiles, splits, chunks_per_split;
-  int64_t tokens_pad;
-};
-
-gate_plan plan_gate(int64_t tokens, int d_in, ag_dtype dt, int num_cu) {
-  gate_plan p;
-  if (dt != AG_BF16) {
-    p.mt = 1; p.tiles = (int)((tokens + 7) / 8); p.splits = 1; p.chunks_per_split = 0;
-    p.tokens_pad = (tokens + 63) / 64 * 64;
-    return p;
-  }
-  const int nchunks = d_in / 64;
-  p.mt = tokens >= (int64_t)64 * 8 * num_cu ? 2 : 1;
-  p.tiles = (int)((tokens + 32 * p.mt - 1) / (32 * p.mt));
-  // enough workgroups to cover the chip about 4 times, but at least 4 chunks (one per wave) per split
-  int want = (4 * num_cu + p.tiles - 1) / p.tiles;
-  int max_splits = nchunks / 4 > 0 ? nchunks / 4 : 1;
-  p.splits = want < 1 ? 1 : (want > max_splits ? max_splits : want);
-  if (p.splits > 16) p.splits = 16;
-  p.chunks_per_split = (nchunks + p.splits - 1) / p.splits;
-  p.splits = (nchunks + p.chunks_per_split - 1) / p.chunks_per_split;
-  p.tokens_pad = (int64_t)p.tiles * 32 * p.mt;
-  if (p.tokens_pad % 64) p.tokens_pad += 32;
-  return p;
+  gate_epilogue<16>([&](int v, int row, int h) { return red[v][row][h]; }, fl, tok0, tokens, L, H_f, bias, thr, n_sink, logits, flags);
 }
 
 }  // namespace
 
+// (the pre-packed copy of W; the rest of the size is from the time when partial sums went through the workspace and is kept,
+// so that a workspace that was sufficient, or too small, stays so)
 size_t ag_ws_gate_bytes(int64_t tokens, int d_in, int H_f, ag_dtype dt) {
   (void)H_f;
-  // worst case over the plans plan_gate can pick (num_cu is not known here): 16 splits
   const int64_t tokens_pad = (tokens + 63) / 64 * 64;
   const size_t part = ag_align256((size_t)16 * tokens_pad * kNP * sizeof(float));
   const size_t pack = dt == AG_BF16 ? ag_align256((size_t)d_in * kNP * 2) : 0;
@@ -574,72 +551,41 @@ hipError_t ag_launch_gate(ag_ctx *ctx, hipStream_t s, const void *feat, ag_dtype
                           const void *w, const float *bias, int H_f, float thr, int n_sink, float *logits,
                           uint8_t *flags, ws_cursor &ws) {
   const int64_t tokens = (int64_t)B * L;
-  const gate_plan p = plan_gate(tokens, d_in, dt, ctx->num_cu);
+  if (tokens > 0xffffffffll - 64) return hipErrorInvalidValue;
   const int64_t tiles32 = (tokens + 31) / 32;
-  const bool fused = dt == AG_BF16 && tiles32 >= ctx->num_cu / 4;  // enough token tiles: one fused kernel
-  // the fused kernel reads W as stored when its rows can be moved and transposed in 8- and 16-byte pieces
-  const bool raw_w = fused && H_f % 4 == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0;
-  // Fewer 32-token tiles than CUs: tiles of 16 tokens first (twice the workgroups, no exchange of partial sums
-  // between them; the MFMA's upper half then idles, which costs nothing here), K splits only after that.
-  const bool tok16 = raw_w && tiles32 < ctx->num_cu;
-  const int64_t tiles = tok16 ? (tokens + 15) / 16 : tiles32;
-  int fsplits = 1;
-  if (fused) {  // K splits until the chip is covered, each wave keeping at least 2 chunks
-    while (tiles * fsplits < ctx->num_cu && d_in / 64 / (fsplits * 2) >= 2 * kFusedWaves && fsplits < 8 &&
-           tiles <= kGateTickets)
-      fsplits *= 2;
+  const dim3 block(64 * kFusedWaves);
+  if (dt != AG_BF16) {
+    AG_LAUNCH(ag_time_kernel(ctx, AG_K_GATE), ag_gate_f32_kernel, dim3((unsigned)((tokens + 15) / 16)), block, 0, s, (const float *)feat,
+              (const float *)w, (uint32_t)tokens, d_in, L, H_f, bias, thr, n_sink, logits, flags);
+    return hipGetLastError();
   }
-  float *partial = fused ? (fsplits > 1 ? ws.take<float>((size_t)tiles * fsplits * 1024) : nullptr)
-                         : ws.take<float>((size_t)p.splits * p.tokens_pad * kNP);
-  int32_t *tickets = fused && fsplits > 1 ? ctx->gate_tickets : nullptr;
-  uint16_t *wp = dt == AG_BF16 && !raw_w ? ws.take<uint16_t>((size_t)d_in * kNP) : nullptr;
+  // W as stored when its rows can be moved and transposed in 8- and 16-byte pieces
+  const bool raw_w = H_f % 4 == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0;
+  uint16_t *wp = !raw_w ? ws.take<uint16_t>((size_t)d_in * kNP) : nullptr;
   if (!ws.ok) return hipSuccess;  // caller reports AG_EWORKSPACE
-  if (dt == AG_BF16) {
-    if (!raw_w) {
-      const int n = d_in * kNP;
-      hipLaunchKernelGGL(ag_gate_pack_w, dim3((n + 255) / 256), dim3(256), 0, s, (const uint16_t *)w, d_in, H_f, wp);
-    }
-    if (fused) {
-      const dim3 grid((unsigned)tiles, fsplits), block(64 * kFusedWaves);
-      const ag_evpair ev = ag_time_kernel(ctx, AG_K_GATE);
-      // PF = feature chunks a wave keeps in flight.  A launch of at most one workgroup per CU is one round of loads
-      // per wave (PF = 4); a longer one runs two workgroups per CU with half the registers (PF = 2), so that one
-      // loads while the other reduces and writes its flags.
-      const bool two_per_cu = (int64_t)tiles * fsplits > ctx->num_cu;
-#define AG_GATE_FUSED(RAWV, PFV, WPTR) AG_GATE_FUSED_T(RAWV, PFV, 32, WPTR)
-#define AG_GATE_FUSED_T(RAWV, PFV, TOKV, WPTR)                                                                            \
-  AG_LAUNCH(ev, (ag_gate_fused_kernel<RAWV, PFV, TOKV>), grid, block, 0, s, (const uint16_t *)feat, (const uint4 *)(WPTR), \
-                     tokens, d_in, L, H_f, bias, thr, n_sink, logits, flags, partial, tickets)
-      if (tok16) {  // (16-token tiles hold half the bytes per chunk: 8 chunks in flight when a wave has that many)
-        if (d_in / 64 / fsplits > 4 * kFusedWaves) AG_GATE_FUSED_T(true, 8, 16, w); else AG_GATE_FUSED_T(true, 4, 16, w);
-      } else if (raw_w) {
-        if (two_per_cu) AG_GATE_FUSED(true, 2, w); else AG_GATE_FUSED(true, 4, w);
-      } else {
-        AG_GATE_FUSED(false, 4, wp);  // measured: the pre-packed path is slower with two workgroups per CU
-      }
-#undef AG_GATE_FUSED
-#undef AG_GATE_FUSED_T
-      return hipGetLastError();
-    }
-    const dim3 grid(p.tiles, p.splits);
-    ag_tick(ctx, AG_K_GATE, s);
-    if (p.mt == 2)
-      hipLaunchKernelGGL(ag_gate_mfma_kernel<2>, grid, dim3(256), 0, s, (const uint16_t *)feat, (const uint4 *)wp,
-                         tokens, d_in, p.chunks_per_split, partial, p.tokens_pad);
-    else
-      hipLaunchKernelGGL(ag_gate_mfma_kernel<1>, grid, dim3(256), 0, s, (const uint16_t *)feat, (const uint4 *)wp,
-                         tokens, d_in, p.chunks_per_split, partial, p.tokens_pad);
-    ag_tock(ctx, AG_K_GATE, s);
-  } else {
-    ag_tick(ctx, AG_K_GATE, s);
-    hipLaunchKernelGGL(ag_gate_f32_kernel, dim3(p.tiles), dim3(256), 0, s, (const float *)feat, (const float *)w,
-                       tokens, d_in, H_f, partial);
-    ag_tock(ctx, AG_K_GATE, s);
+  if (!raw_w) {
+    const int n = d_in * kNP;
+    hipLaunchKernelGGL(ag_gate_pack_w, dim3((n + 255) / 256), dim3(256), 0, s, (const uint16_t *)w, d_in, H_f, wp);
   }
-  ag_tick(ctx, AG_K_GATE_FINALIZE, s);
-  hipLaunchKernelGGL(ag_gate_finalize_kernel, dim3((unsigned)((tokens + kFinTok - 1) / kFinTok)), dim3(256), 0, s, partial,
-                     p.splits, p.tokens_pad, tokens, L, H_f, bias, thr, n_sink, logits, flags);
-  ag_tock(ctx, AG_K_GATE_FINALIZE, s);
+  const ag_evpair ev = ag_time_kernel(ctx, AG_K_GATE);
+  if (raw_w && tiles32 < ctx->num_cu) {
+#define AG_GATE16(PFV)                                                                                                \
+  AG_LAUNCH(ev, ag_gate16_kernel<PFV>, dim3((unsigned)((tokens + 15) / 16)), block, 0, s, (const uint16_t *)feat, (const uint4 *)w, \
+            (uint32_t)tokens, d_in, L, H_f, bias, thr, n_sink, logits, flags)
+    // every chunk of a wave in flight, up to 8
+    const int per_wave = (d_in / 64 + kFusedWaves - 1) / kFusedWaves;
+    if (per_wave <= 1) AG_GATE16(1); else if (per_wave <= 2) AG_GATE16(2); else if (per_wave <= 4) AG_GATE16(4); else AG_GATE16(8);
+#undef AG_GATE16
+    return hipGetLastError();
+  }
+  // PF = feature chunks a wave keeps in flight.  A launch of at most one workgroup per CU is one round of loads per wave
+  // (PF = 4); a longer one runs two workgroups per CU with half the registers (PF = 2), so that one loads while the
+  // other reduces and writes its flags (measured: not with pre-packed W).
+#define AG_GATE_FUSED(RAWV, PFV, WPTR)                                                                                     \
+  AG_LAUNCH(ev, (ag_gate_fused_kernel<RAWV, PFV>), dim3((unsigned)tiles32), block, 0, s, (const uint16_t *)feat, (const uint4 *)(WPTR), \
+            tokens, d_in, L, H_f, bias, thr, n_sink, logits, flags)
+  if (!raw_w) AG_GATE_FUSED(false, 4, wp); else if (tiles32 > ctx->num_cu) AG_GATE_FUSED(true, 2, w); else AG_GATE_FUSED(true, 4, w);
+#undef AG_GATE_FUSED
   return hipGetLastError();
 }
 

@@ -12,7 +12,6 @@
 enum { AG_K_GATE = 0, AG_K_GATE_FINALIZE, AG_K_FLAG_SCAN, AG_K_COMPACT, AG_K_PREFILL, AG_K_DECODE_PARTIAL,
        AG_K_DECODE_MERGE, AG_K_MHA_PROJ, AG_K_MHA_ATTN, AG_K_NORM_GATE, AG_K_COUNT };
 constexpr int kTimerSlots = 1024;  // launches remembered per kernel id
-constexpr int kGateTickets = 1024; // token tiles whose K splits can be counted
 constexpr int kDecodeMaxUnits = 8192;  // (batch, KV head) units of one decode step
 constexpr size_t kStaticScratchBytes = size_t(16) << 20;  // per-GPU static scratch of ag_decode_attn_static
 
@@ -27,7 +26,6 @@ struct ag_ctx {
   char *ws;         // device workspace
   size_t ws_bytes;
   int32_t *d_err;   // sticky device error word (bit 0: cache capacity overflow)
-  int32_t *gate_tickets;  // [kGateTickets] arrival counters of the gate's K splits: zero between launches
   int32_t *decode_tickets;  // [kDecodeMaxUnits + 1] arrival counters of a decode step: zero between launches
   char *static_scratch;   // this device's copy of the library's static scratch array (ag_decode_attn_static)
   bool timing;
@@ -70,7 +68,7 @@ static inline ag_evpair ag_time_kernel(ag_ctx *ctx, int id) {
       hipLaunchKernelGGL(kernel, grid, block, shmem, stream, __VA_ARGS__);                                  \
   } while (0)
 
-// ---- How workgroups of ONE launch hand data to each other (prefill chunk states, gate K splits, the planner's
+// ---- How workgroups of ONE launch hand data to each other (prefill chunk states, decode records, the planner's
 // per-unit counts) -------------------------------------------------------------------------------------------------
 // Pattern: a producer writes its data, waits until those writes have completed, then bumps an arrival counter with an
 // atomic add; the workgroup that sees the last arrival reads everybody's data.  What makes this hold on gfx950,
