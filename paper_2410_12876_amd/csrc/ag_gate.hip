@@ -7,6 +7,8 @@
 // through LDS, and takes the matching W fragments either from W as stored, transposed on the way through LDS, or (H_f not
 // a multiple of 4, or W not 16-byte aligned) from a pre-packed copy.  ag_norm_gate_kernel fuses the normalisation of the
 // input in as well.
+#include <atomic>
+
 #include "ag_internal.h"
 
 namespace {
@@ -28,31 +30,78 @@ constexpr int kNP = 32;  // padded head count (MFMA N)
 // keys among rows of equal parity: bits 1..3 of the row.
 __device__ __forceinline__ int xkey(int r) { return (r >> 1) & 7; }
 
-// W [d_in, H_f] bf16 -> fragment order: [(chunk*4 + step)*64 + lane][8], lane = (n = lane%32, kb = lane/32),
-// element j = W[chunk*64 + kb*32 + step*8 + j][n]  (0 for n >= H_f).
+// W [d_in, H_f] bf16 -> the B fragments of v_mfma_f32_16x16x32_bf16: piece ((chunk * 2 + step) * 2 + column tile) * 64 + lane
+// of 8 elements, lane = (col = lane % 16, kg = lane / 16), element j = W[chunk * 64 + step * 32 + kg * 8 + j][16 tile + col]
+// (0 for columns >= H_f).
 __global__ void ag_gate_pack_w(const uint16_t *__restrict__ w, int d_in, int H_f, uint16_t *__restrict__ wp) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;  // one packed element
   if (i >= d_in * kNP) return;
-  const int j = i & 7, lane = (i >> 3) & 63, step = (i >> 9) & 3, chunk = i >> 11;
-  const int n = lane & 31, kb = lane >> 5;
-  const int kk = chunk * 64 + kb * 32 + step * 8 + j;
+  const int j = i & 7, lane = (i >> 3) & 63, nt = (i >> 9) & 1, step = (i >> 10) & 1, chunk = i >> 11;
+  const int n = 16 * nt + (lane & 15);
+  const int kk = chunk * 64 + step * 32 + (lane >> 4) * 8 + j;
   wp[i] = n < H_f ? w[(size_t)kk * H_f + n] : (uint16_t)0;
 }
 
-// Bias, threshold, logits [tokens, H_f] and head-major flags of a tile of TOK tokens from the 8 waves' partial tiles
-// red(w, row, head).  Token and sequence of a row follow from the tile's first token by counting, not by a division each.
-template <int TOK, typename RED>
-__device__ __forceinline__ void gate_epilogue(RED &&red, uint8_t (&fl)[kNP][32], uint32_t tok0, uint32_t tokens, int L, int H_f,
-                                              const float *__restrict__ bias, float thr, int n_sink,
+// ---- One 64-feature chunk of W, from the 4 x 16 bytes per lane it is loaded as to MFMA fragments ---------------------
+// RAW: W as the caller stores it ([d_in, H_f] row-major, H_f a multiple of 4, 16-byte aligned): lane l loads pieces l,
+// l + 64, ... of the chunk's 8 H_f; they go to the wave's 4 KiB of LDS and come back through the transposing read, which
+// hands lane (col, kg) the rows 32 step + 8 kg + 0..7 of column 16 tile + col.  (Columns >= H_f read whatever lies there;
+// they only reach output columns that are never stored.)  Otherwise the pieces are ag_gate_pack_w's fragments already.
+template <bool RAW> struct w_chunk {
+  int H_f, n_u4, tr_off[2];
+  AG_LDS uint8_t *st;
+  __device__ __forceinline__ void init(int H_f_, int lane, AG_LDS uint8_t *stage) {
+    H_f = H_f_; n_u4 = 8 * H_f; st = stage;
+    const int col = lane & 15, row = 8 * (lane >> 4) + (col >> 2);
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) tr_off[nt] = row * (H_f * 2) + min(16 * nt + 4 * (col & 3), H_f - 4) * 2;
+  }
+  __device__ __forceinline__ void load(uint4 (&b)[4], const uint4 *__restrict__ wp, int chunk, int lane) const {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (RAW) {
+        if (s == 0 || s * 64 < n_u4) b[s] = wp[(size_t)chunk * n_u4 + min(s * 64 + lane, n_u4 - 1)];
+      } else {
+        b[s] = wp[((size_t)chunk * 4 + s) * 64 + lane];
+      }
+    }
+  }
+  // the chunk's pieces -> LDS (RAW; between two wave_syncs)
+  __device__ __forceinline__ void stage(const uint4 (&b)[4], int lane) const {
+    if (RAW) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (s * 64 < n_u4 && s * 64 + lane < n_u4)
+          *reinterpret_cast<AG_LDS u32x4 *>(st + (s * 64 + lane) * 16) = u32x4{b[s].x, b[s].y, b[s].z, b[s].w};
+    }
+  }
+  __device__ __forceinline__ bf16x8 frag(const uint4 (&b)[4], int step, int nt) const {
+    if (!RAW) return __builtin_bit_cast(bf16x8, b[2 * step + nt]);
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(st + tr_off[nt] + (32 * step) * (H_f * 2)));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(st + tr_off[nt] + (32 * step + 4) * (H_f * 2)));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+};
+// lanes of one wave exchange data through LDS
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Bias, threshold, logits [tokens, H_f] and head-major flags of a tile of 16 tokens from the 8 waves' partial tiles
+// red(w, row, head), by 512 threads; bias_h: the bias of head threadIdx.x % 32 (see gate_bias).  Token and sequence of a row follow from the tile's first token by counting, not by a division each.
+template <typename RED>
+__device__ __forceinline__ void gate_epilogue(RED &&red, uint8_t (&fl)[kNP][16], uint32_t tok0, uint32_t tokens, int L, int H_f,
+                                              float bias_h, float thr, int n_sink,
                                               float *__restrict__ logits, uint8_t *__restrict__ flags) {
   const uint32_t b0 = tok0 / (uint32_t)L, t0 = tok0 - b0 * (uint32_t)L;  // (uniform)
   auto place = [&](int rw, uint32_t &b, uint32_t &t) {
     b = b0; t = t0 + rw;
     while (t >= (uint32_t)L) { t -= L; ++b; }
   };
-#pragma unroll
-  for (int i = 0; i < TOK / 16; ++i) {  // element e = (token row e / 32, head e % 32)
-    const int e = threadIdx.x + 512 * i, rw = e >> 5, h = e & 31;
+  {
+    const int rw = threadIdx.x >> 5, h = threadIdx.x & 31;  // thread -> (token row, head)
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < 8; ++w) v += red(w, rw, h);
@@ -60,173 +109,56 @@ __device__ __forceinline__ void gate_epilogue(RED &&red, uint8_t (&fl)[kNP][32],
     if (h < H_f && tk < tokens) {
       uint32_t b, t;
       place(rw, b, t);
-      const float val = v + bias[h];
+      const float val = v + bias_h;
       if (logits) logits[(size_t)tk * H_f + h] = val;
       fl[h][rw] = (val > thr || (int)t < n_sink) ? 1 : 0;
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < TOK * H_f; e += 512) {
-    const int h = e / TOK, rw = e % TOK;
-    if (tok0 + rw >= tokens) continue;
+  const int h = threadIdx.x >> 4, rw = threadIdx.x & 15;
+  if (h < H_f && tok0 + rw < tokens) {
     uint32_t b, t;
     place(rw, b, t);
     flags[((size_t)b * H_f + h) * L + t] = fl[h][rw];
   }
 }
 
-// One workgroup of 8 waves per tile of 32 tokens: wave w takes 64-wide chunks w, w + 8, ..., PF of them in flight.
-//
-// RAW: W is taken as the caller stores it ([d_in, H_f] row-major, H_f a multiple of 4, 16-byte aligned).  A wave
-// copies the 64 rows of a chunk into its own 4 KiB of LDS and reads them back with the transposing LDS read,
-// which hands lane (n, kb) the eight rows kb*32 + step*8 + 0..7 of column n: the B operand that matches the
-// A operand (lane = token m and half kb: features kb*32 + step*8 + 0..7).  Columns n >= H_f read whatever follows in LDS; they only reach output
-// columns that are never stored.  Otherwise wp holds the fragments prepared by ag_gate_pack_w.
-constexpr int kFusedWaves = 8;
-template <bool RAW, int PF>
-__global__ __launch_bounds__(64 * kFusedWaves, PF == 2 ? 2 : 1) void ag_gate_fused_kernel(
-    const uint16_t *__restrict__ x, const uint4 *__restrict__ wp, int64_t tokens, int d_in, int L, int H_f,
-    const float *__restrict__ bias, float thr, int n_sink, float *__restrict__ logits, uint8_t *__restrict__ flags) {
-  constexpr int TOK = 32;
-  // [wave][4 KiB]: W staging of the wave while it accumulates, afterwards its 32 x 32 fp32 partial tile
-  __shared__ __attribute__((aligned(16))) uint8_t wst[kFusedWaves][4096];
-  // [wave][4 KiB]: a chunk of the wave's 32 feature rows on its way from the memory-side layout to the A layout
-  __shared__ __attribute__((aligned(16))) uint8_t xstage[kFusedWaves][4096];
-  __shared__ uint8_t fl[kNP][32];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: chunk offsets stay in SGPRs
-  const int m = lane & 31, kb = lane >> 5;
-  const int lr = lane >> 3, lp = lane & 7;  // row within a group of 8 and 16-byte piece of the memory-side layout
-  constexpr int NI = TOK / 8;  // load instructions per chunk: 8 rows each
-  const int64_t tok0 = (int64_t)blockIdx.x * TOK;
-  const int nchunks = d_in / 64;
-  // Feature rows: a chunk (64 features) is one 128-byte line per row, and a load instruction fetches 8 whole
-  // lines (lane -> row 8 i + lane / 8, 16-byte piece lane % 8) instead of 64 scattered 16-byte pieces, which the
-  // texture path would take four times as long to address.  Rows past the last token repeat the last row (read,
-  // never written).  The chunk then goes through the wave's LDS buffer (pieces XOR-swizzled with the row, so that
-  // neither side has bank conflicts) to the A layout: lane (token m, half kb), step s: features kb*32 + s*8 .. +7.
-  const int rows = (int)min((int64_t)TOK, tokens - tok0);
-  const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(x + (size_t)tok0 * d_in), 0, (uint32_t)rows * (uint32_t)d_in * 2u, 0x00020000);
-  int row_off[NI];
-#pragma unroll
-  for (int i = 0; i < NI; ++i) row_off[i] = min(8 * i + lr, rows - 1) * d_in * 2 + lp * 16;
-  AG_LDS uint8_t *xst = (AG_LDS uint8_t *)xstage[wave];
-  // RAW: a chunk is 64 * H_f * 2 bytes = 8 * H_f uint4, lane l holds uint4 l, l + 64, ... of it
-  const int chunk_u4 = 8 * H_f;
-  AG_LDS uint8_t *stage = (AG_LDS uint8_t *)wst[wave];
-  // transposing read: the 16 lanes of a group give the addresses of 4 rows x 16 columns (lane i: row i / 4,
-  // columns 4 (i % 4) ..+3) and lane i receives column i of the 4 rows
-  const int gl = lane >> 4, li = lane & 15;
-  const int tr_col = min(16 * (gl & 1) + 4 * (li & 3), H_f - 4);
-  const int tr_off = ((gl >> 1) * 32 + (li >> 2)) * (H_f * 2) + tr_col * 2;
-  auto wave_sync = [] {  // lanes of one wave exchange data through LDS
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
-  f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int c0 = wave; c0 < nchunks; c0 += kFusedWaves * PF) {
-    uint4 a[PF][4], b[PF][4];
-    // W first: its loads hit the L2 and return early, so the staging below runs while the feature rows are
-    // still on their way from HBM (a wave's loads return in issue order)
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      const int c = min(c0 + kFusedWaves * p, nchunks - 1);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        if (RAW) {
-          const int i = min(s * 64 + lane, chunk_u4 - 1);
-          b[p][s] = wp[(size_t)c * chunk_u4 + i];
-        } else {
-          b[p][s] = wp[((size_t)c * 4 + s) * 64 + lane];
-        }
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-      const int c = min(c0 + kFusedWaves * p, nchunks - 1);
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, row_off[i], c * 128, 0);
-        a[p][i] = make_uint4(t[0], t[1], t[2], t[3]);
-      }
-    }
-    if (RAW) {
-#pragma unroll
-      for (int p = 0; p < PF; ++p) {
-        wave_sync();  // the fragments of the previous chunk have been read
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          if (s * 64 + lane < chunk_u4)
-            *reinterpret_cast<AG_LDS u32x4 *>(stage + (s * 64 + lane) * 16) =
-                u32x4{b[p][s].x, b[p][s].y, b[p][s].z, b[p][s].w};
-        wave_sync();  // the chunk's rows are there for every lane
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(stage + tr_off + (s * 8) * (H_f * 2)));
-          const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(stage + tr_off + (s * 8 + 4) * (H_f * 2)));
-          b[p][s] = __builtin_bit_cast(uint4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        }
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < PF; ++p)
-      if (c0 + kFusedWaves * p < nchunks) {
-        wave_sync();  // the previous chunk's fragments have been read
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-          *reinterpret_cast<AG_LDS u32x4 *>(xst + (8 * i + lr) * 128 + ((lp ^ xkey(8 * i + lr)) << 4)) =
-              u32x4{a[p][i].x, a[p][i].y, a[p][i].z, a[p][i].w};
-        wave_sync();  // the chunk's rows are there for every lane
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const u32x4 t = *reinterpret_cast<const AG_LDS u32x4 *>(xst + m * 128 + (((kb * 4 + s) ^ xkey(m)) << 4));
-          a[p][s] = make_uint4(t[0], t[1], t[2], t[3]);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[p][s]),
-                                                        __builtin_bit_cast(bf16x8, b[p][s]), acc, 0, 0, 0);
-      }
-  }
-  float(*red)[32][32] = reinterpret_cast<float(*)[32][32]>(wst);
-  if (RAW) wave_sync();  // the wave's staging area becomes its partial tile
-#pragma unroll
-  for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * kb + (r & 3)][m] = acc[r];
-  __syncthreads();
-  gate_epilogue<TOK>([&](int w, int row, int h) { return red[w][row][h]; }, fl, (uint32_t)tok0, (uint32_t)tokens, L, H_f, bias, thr,
-                     n_sink, logits, flags);
+__device__ __forceinline__ float gate_bias(const float *__restrict__ bias, int H_f) {
+  return bias[min((int)(threadIdx.x & 31), H_f - 1)];
 }
 
-// Tiles of 16 tokens, W as stored: launches with fewer 32-token tiles than CUs.  Such a launch is one round of loads, and
-// what bounds it is the one CU's memory path (64 bytes a cycle: 16 rows of features and ALL of W for every workgroup,
-// 384 KiB at 4096 x 32 features, 2.7 us) and the LDS behind it, not HBM.  Hence v_mfma_f32_16x16x32_bf16 (a 32-row MFMA
-// would read every x fragment twice), chunks processed in the order they arrive while the later ones are on their way, no
-// column tile beyond H_f, and W's first touch spread over the chip: the workgroups of an XCD each request a different
-// 1/32 of W before anything else, so that it is in their L2 when 32 of them want it at once; without that its lines
-// queue behind the features of the whole launch.
-template <int PF>  // chunks a wave keeps in flight
+constexpr int kFusedWaves = 8;
+
+// One tile of 16 tokens per workgroup: launches of a few tiles per CU at most (and any with more than 4096 features).  A
+// small launch is one round of loads, and what bounds it is the one CU's memory path (64 bytes a cycle: 16 rows of features
+// and ALL of W for every workgroup, 384 KiB at 4096 x 32 features, 2.7 us) and the LDS behind it, not HBM.  Hence
+// v_mfma_f32_16x16x32_bf16 (a 32-row MFMA would read every x fragment twice), chunks processed in the order they arrive
+// while the later ones are on their way, no column tile beyond H_f, and W's first touch spread over the chip: the
+// workgroups of an XCD each request a different 1/32 of W before anything else, so that it is in their L2 when 32 of
+// them want it at once; without that its lines queue behind the features of the whole launch.
+template <bool RAW, int PF>  // PF = chunks a wave keeps in flight
 __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
     const uint16_t *__restrict__ x, const uint4 *__restrict__ wp, uint32_t tokens, int d_in, int L, int H_f,
     const float *__restrict__ bias, float thr, int n_sink, float *__restrict__ logits, uint8_t *__restrict__ flags) {
   // [wave][6 KiB]: a chunk of W (64 rows), then a chunk of the 16 feature rows; afterwards the wave's partial tile
   __shared__ __attribute__((aligned(16))) uint8_t mem[kFusedWaves][6144];
-  __shared__ uint8_t fl[kNP][32];
+  __shared__ uint8_t fl[kNP][16];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, kg = lane >> 4;
   const int lr = lane >> 3, lp = lane & 7;  // row within a group of 8 and 16-byte piece of the memory-side layout
   const uint32_t tok0 = blockIdx.x * 16;
-  const int nchunks = d_in / 64, chunk_u4 = 8 * H_f;
+  const int nchunks = d_in / 64;
+  const float bias_h = gate_bias(bias, H_f);
+  AG_LDS uint8_t *wst = (AG_LDS uint8_t *)mem[wave], *xst = wst + 4096;
+  w_chunk<RAW> wc;
+  wc.init(H_f, lane, wst);
   {
     // (into the wave's W buffer, which is first written after its own loads, which come later, have arrived; pieces past
     // the end of W are not requested)
     const __amdgpu_buffer_rsrc_t w_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, (uint32_t)d_in * (uint32_t)H_f * 2u, 0x00020000);
-    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)((AG_LDS uint8_t *)mem[wave]));
+        __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, (uint32_t)d_in * (uint32_t)(RAW ? H_f : kNP) * 2u, 0x00020000);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)wst);
     const int off = (((blockIdx.x >> 3) & 31) * 512 + threadIdx.x) * 16;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(off), "s"(w_rsrc) : "memory");
   }
@@ -236,19 +168,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
   int row_off[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) row_off[i] = min(8 * i + lr, rows - 1) * d_in * 2 + lp * 16;
-  AG_LDS uint8_t *wst = (AG_LDS uint8_t *)mem[wave], *xst = wst + 4096;
-  // transposing read of W: the 16 lanes of key group kg give the addresses of 4 rows x 16 columns (lane i: row i / 4,
-  // columns 4 (i % 4) ..+3) and lane i receives column i of the 4 rows
-  const int w_row = 8 * kg + (col >> 2), w_col = 4 * (col & 3);
-  int tr_off[2];
-#pragma unroll
-  for (int nt = 0; nt < 2; ++nt) tr_off[nt] = w_row * (H_f * 2) + min(16 * nt + w_col, H_f - 4) * 2;
   const bool two = H_f > 16;
-  auto wave_sync = [] {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
   for (int c0 = wave; c0 < nchunks; c0 += kFusedWaves * PF) {
     u32x4 a[PF][2];
@@ -256,9 +176,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
       const int c = min(c0 + kFusedWaves * p, nchunks - 1);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s == 0 || s * 64 < chunk_u4) b[p][s] = wp[(size_t)c * chunk_u4 + min(s * 64 + lane, chunk_u4 - 1)];
+      wc.load(b[p], wp, c, lane);
 #pragma unroll
       for (int i = 0; i < 2; ++i) a[p][i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, row_off[i], c * 128, 0);
     }
@@ -266,10 +184,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
     for (int p = 0; p < PF; ++p)
       if (c0 + kFusedWaves * p < nchunks) {
         wave_sync();  // the previous chunk's fragments have been read
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          if (s * 64 < chunk_u4 && s * 64 + lane < chunk_u4)
-            *reinterpret_cast<AG_LDS u32x4 *>(wst + (s * 64 + lane) * 16) = u32x4{b[p][s].x, b[p][s].y, b[p][s].z, b[p][s].w};
+        wc.stage(b[p], lane);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
           *reinterpret_cast<AG_LDS u32x4 *>(xst + (8 * i + lr) * 128 + ((lp ^ xkey(8 * i + lr)) << 4)) = a[p][i];
@@ -279,11 +194,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
           const bf16x8 af = *reinterpret_cast<const AG_LDS bf16x8 *>(xst + col * 128 + (((4 * s + kg) ^ xkey(col)) << 4));
 #pragma unroll
           for (int nt = 0; nt < 2; ++nt)
-            if (nt == 0 || two) {
-              const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(wst + tr_off[nt] + (32 * s) * (H_f * 2)));
-              const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(wst + tr_off[nt] + (32 * s + 4) * (H_f * 2)));
-              acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7), acc[nt], 0, 0, 0);
-            }
+            if (nt == 0 || two) acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wc.frag(b[p], s, nt), acc[nt], 0, 0, 0);
         }
       }
   }
@@ -296,7 +207,110 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wave][(4 * kg + r) * 32 + 16 * nt + col] = acc[nt][r];
   __syncthreads();
-  gate_epilogue<16>([&](int w, int row, int h) { return red[w][row * 32 + h]; }, fl, tok0, tokens, L, H_f, bias, thr, n_sink, logits, flags);
+  gate_epilogue([&](int w, int row, int h) { return red[w][row * 32 + h]; }, fl, tok0, tokens, L, H_f, bias_h, thr, n_sink, logits, flags);
+}
+
+// Many tokens, d_in <= 8 waves x NCH x 64 features: one persistent workgroup per CU walks the 16-token tiles.  A wave keeps the
+// fragments of its NCH chunks of W in registers for the whole launch (16 each: no second read of W, no transposition per
+// tile), and the features stream through a ring of kRing 2-KiB chunks per wave, loaded straight into LDS: as soon as a
+// chunk's fragments are read, the chunk kRing further on -- of the same tile or of a later one -- is requested into its
+// place, so the memory system always sees 8 x kRing x 2 KiB per CU, also while a tile's partial sums are added and its
+// flags written.  32768 tokens x 4096 features x 32 heads: 62 us (4.3 TB/s) with tiles loaded, staged and finished one
+// after the other by two workgroups per CU.
+constexpr int kRing = 6;
+template <bool RAW, int NCH>
+__global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate_stream_kernel(
+    const uint16_t *__restrict__ x, const uint4 *__restrict__ wp, uint32_t tokens, int d_in, int L, int H_f,
+    const float *__restrict__ bias, float thr, int n_sink, float *__restrict__ logits, uint8_t *__restrict__ flags) {
+  // [wave][kRing x 2 KiB] ring of feature chunks, then [wave][4 KiB]: W staging before the loop, partial tiles in it
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  __shared__ uint8_t fl[kNP][16];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, kg = lane >> 4;
+  const int lr = lane >> 3, lp = lane & 7;
+  const int nchunks = d_in / 64, mine = (nchunks - wave + kFusedWaves - 1) / kFusedWaves;  // this wave's chunks (may be 0)
+  const int tiles = (int)((tokens + 15) / 16), stride = gridDim.x;
+  AG_LDS uint8_t *ring = (AG_LDS uint8_t *)smem + wave * (kRing * 2048);
+  AG_LDS uint8_t *wst = (AG_LDS uint8_t *)smem + kFusedWaves * kRing * 2048 + wave * 4096;
+  const uint32_t ring_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)ring);
+  int row_off[2];  // load instruction i, lane: row 8 i + lr, piece lp ^ key(row), to position lp
+#pragma unroll
+  for (int i = 0; i < 2; ++i) row_off[i] = (8 * i + lr) * d_in * 2 + ((lp ^ xkey(8 * i + lr)) << 4);
+  // the wave's stream: chunk p of tile blockIdx.x + j * stride; (it, ip) is the next one to request
+  uint32_t it = blockIdx.x;
+  int ip = 0, slot_in = 0;
+  auto request = [&]() {
+    if (it < (uint32_t)tiles && mine > 0) {
+      const uint32_t t0 = it * 16, rows = min(16u, tokens - t0);  // (rows past the last token arrive as zeros)
+      const __amdgpu_buffer_rsrc_t rsrc =
+          __builtin_amdgcn_make_buffer_rsrc((void *)(x + (size_t)t0 * d_in), 0, rows * (uint32_t)d_in * 2u, 0x00020000);
+      const uint32_t dst = ring_addr + slot_in * 2048;
+      const int soff = (wave + kFusedWaves * ip) * 128;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(row_off[0]), "s"(rsrc), "s"(soff) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst + 1024), "v"(row_off[1]), "s"(rsrc), "s"(soff) : "memory");
+      slot_in = slot_in + 1 == kRing ? 0 : slot_in + 1;
+      if (++ip == mine) { ip = 0; it += stride; }
+    }
+  };
+  // W first, as fragments in registers
+  bf16x8 wf[NCH][2][2];
+  {
+    w_chunk<RAW> wc;
+    wc.init(H_f, lane, wst);
+    uint4 b[NCH][4];
+#pragma unroll
+    for (int p = 0; p < NCH; ++p) wc.load(b[p], wp, min(wave + kFusedWaves * p, nchunks - 1), lane);
+#pragma unroll
+    for (int p = 0; p < NCH; ++p) {
+      wave_sync();
+      wc.stage(b[p], lane);
+      wave_sync();
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          wf[p][s][nt] = wc.frag(b[p], s, nt);
+          asm volatile("" : "+v"(wf[p][s][nt]));
+        }
+    }
+  }
+  float bias_h = gate_bias(bias, H_f);
+  asm volatile("" : "+v"(bias_h));  // loaded here: a wait for it inside the loop would be one for the whole ring
+  for (int i = 0; i < kRing; ++i) request();
+  int slot = 0, done = 0;
+  const int total = mine * (((int)tiles - (int)blockIdx.x + stride - 1) / stride);
+  float *red = reinterpret_cast<float *>(smem + kFusedWaves * kRing * 2048);
+  for (int tile = blockIdx.x; tile < tiles; tile += stride) {
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int p = 0; p < NCH; ++p)
+      if (p < mine) {
+        // two requests per chunk; the kRing - 1 later ones may still be on their way
+        if (done + kRing <= total) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (kRing - 1)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const AG_LDS uint8_t *xst = ring + slot * 2048;
+        bf16x8 af[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) af[s] = *reinterpret_cast<const AG_LDS bf16x8 *>(xst + col * 128 + (((4 * s + kg) ^ xkey(col)) << 4));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        slot = slot + 1 == kRing ? 0 : slot + 1;
+        ++done;
+        request();
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s], wf[p][s][nt], acc[nt], 0, 0, 0);
+      }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave * 1024 + (4 * kg + r) * 32 + 16 * nt + col] = acc[nt][r];
+    __syncthreads();
+    // (its barrier comes after the partial tiles have been read: the next tile's may be written)
+    gate_epilogue([&](int w, int row, int h) { return red[w * 1024 + row * 32 + h]; }, fl, (uint32_t)tile * 16, tokens, L, H_f, bias_h, thr,
+                  n_sink, logits, flags);
+  }
 }
 
 // RMS normalisation fused with the gate: x = h / sqrt(mean_c h^2 + eps) * g, rounded once to bf16, written out for
@@ -307,10 +321,9 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
 // -> row 8 i + lane / 8, 16-byte piece lane % 8).  The squares are summed per lane, over the 8 lanes of a row and
 // then over the waves through LDS in wave order.  After the scaling the chunk is stored from the same registers
 // and handed through a 4 KiB LDS buffer of the wave (pieces XOR-swizzled with the row: no bank conflicts on either
-// side) to the MFMA's A layout, lane (token m, half kb) holding features kb*32 + s*8 .. +7 for step s.  That
+// side) to the MFMA's A layout, lane (token col, group kg) holding features s*32 + kg*8 .. +7 for step s.  That
 // layout, the W fragments and the order of the MFMAs (chunks ascending per wave, then the waves in order) are
-// those of ag_gate_fused_kernel with one K split, so the logits are those ag_gate gives on the stored x bit for
-// bit whenever that kernel runs unsplit.
+// those of ag_gate, so the logits are those ag_gate gives on the stored x bit for bit.
 template <bool RAW, int TOK, int NCH>  // NCH = chunks a wave holds: d_in <= 8 waves x NCH x 64 features
 __global__ __launch_bounds__(64 * kFusedWaves, TOK == 16 ? 2 : 1) void ag_norm_gate_kernel(
     const uint16_t *h, const uint16_t *__restrict__ g, float eps, const uint4 *__restrict__ wp,
@@ -320,12 +333,12 @@ __global__ __launch_bounds__(64 * kFusedWaves, TOK == 16 ? 2 : 1) void ag_norm_g
   __shared__ __attribute__((aligned(16))) uint8_t wst[kFusedWaves][2][4096];
   __shared__ __attribute__((aligned(16))) uint16_t g_l[kFusedWaves * NCH * 64];
   __shared__ float ssq_l[kFusedWaves][32];
-  __shared__ uint8_t fl[kNP][32];
+  __shared__ uint8_t fl[kNP][16];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: chunk offsets stay in SGPRs
   constexpr int NI = TOK / 8;  // load / store instructions per chunk: 8 rows each
-  const int m = lane & 31, kb = lane >> 5;
-  const int ma = m & (TOK - 1);  // A row this lane reads: with 16-token tiles the upper half of the MFMA repeats the lower
+  const int col = lane & 15, kg = lane >> 4;
+  constexpr int MT = TOK / 16;  // 16-token tiles of the MFMA
   const int lr = lane >> 3, lp = lane & 7;  // row within a group of 8 and 16-byte piece of the memory-side layout
   const int64_t tok0 = (int64_t)blockIdx.x * TOK;
   const int nchunks = d_in / 64;
@@ -346,19 +359,10 @@ __global__ __launch_bounds__(64 * kFusedWaves, TOK == 16 ? 2 : 1) void ag_norm_g
 #pragma unroll
     for (int i = 0; i < NI; ++i) a[p][i] = to_u4(__builtin_amdgcn_raw_buffer_load_b128(h_rsrc, row_off[i], c * 128, 0));
   }
-  // W fragments (see ag_gate_fused_kernel for the two forms of wp), requested two chunks ahead of their use
-  const int chunk_u4 = 8 * H_f;
-  const __amdgpu_buffer_rsrc_t w_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, (uint32_t)d_in * (RAW ? H_f : kNP) * 2u, 0x00020000);
-  int w_off[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) w_off[s] = RAW ? min(s * 64 + lane, chunk_u4 - 1) * 16 : s * 1024 + lane * 16;
-  auto load_w = [&](uint4 (&bw)[4], int p) {
-    const int c = min(wave + kFusedWaves * p, nchunks - 1);
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      bw[s] = to_u4(__builtin_amdgcn_raw_buffer_load_b128(w_rsrc, w_off[s], c * (RAW ? chunk_u4 * 16 : 4096), 0));
-  };
+  // W, requested two chunks ahead of its use
+  w_chunk<RAW> wc;
+  wc.init(H_f, lane, (AG_LDS uint8_t *)wst[wave][1]);
+  auto load_w = [&](uint4 (&bw)[4], int p) { wc.load(bw, wp, min(wave + kFusedWaves * p, nchunks - 1), lane); };
   uint4 b[3][4];
   load_w(b[0], 0);
   load_w(b[1], 1);
@@ -398,18 +402,12 @@ __global__ __launch_bounds__(64 * kFusedWaves, TOK == 16 ? 2 : 1) void ag_norm_g
     r[i] = 1.f / sqrtf(tot / (float)d_in + eps);
   }
 
-  AG_LDS uint8_t *xst = (AG_LDS uint8_t *)wst[wave][0], *stage = (AG_LDS uint8_t *)wst[wave][1];
-  const int gl = lane >> 4, li = lane & 15;
-  const int tr_col = min(16 * (gl & 1) + 4 * (li & 3), H_f - 4);
-  const int tr_off = ((gl >> 1) * 32 + (li >> 2)) * (H_f * 2) + tr_col * 2;
-  auto wave_sync = [] {  // lanes of one wave exchange data through LDS
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
-  f32x16 acc;
+  AG_LDS uint8_t *xst = (AG_LDS uint8_t *)wst[wave][0];
+  const float bias_h = gate_bias(bias, H_f);
+  const bool two = H_f > 16;
+  f32x4 acc[MT][2];
 #pragma unroll
-  for (int r16 = 0; r16 < 16; ++r16) acc[r16] = 0.f;
+  for (int mt = 0; mt < MT; ++mt) acc[mt][0] = acc[mt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int p = 0; p < NCH; ++p) {
     __builtin_amdgcn_sched_barrier(0);  // one chunk at a time: interleaving them costs more registers than it hides
@@ -436,60 +434,40 @@ __global__ __launch_bounds__(64 * kFusedWaves, TOK == 16 ? 2 : 1) void ag_norm_g
       }
     }
     uint4(&bw)[4] = b[p % 3];
-    if (RAW) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s * 64 + lane < chunk_u4)
-          *reinterpret_cast<AG_LDS u32x4 *>(stage + (s * 64 + lane) * 16) = u32x4{bw[s].x, bw[s].y, bw[s].z, bw[s].w};
-    }
+    wc.stage(bw, lane);
     wave_sync();  // the chunk's x rows and W rows are there for every lane
-    if (RAW) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(stage + tr_off + (s * 8) * (H_f * 2)));
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(stage + tr_off + (s * 8 + 4) * (H_f * 2)));
-        bw[s] = __builtin_bit_cast(uint4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      }
-    }
     if (valid) {
-      u32x4 af[4];
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        af[s] = *reinterpret_cast<const AG_LDS u32x4 *>(xst + ma * 128 + (((kb * 4 + s) ^ xkey(ma)) << 4));
+      for (int s = 0; s < 2; ++s) {
+        bf16x8 af[MT];
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[s]),
-                                                      __builtin_bit_cast(bf16x8, bw[s]), acc, 0, 0, 0);
+        for (int mt = 0; mt < MT; ++mt)
+          af[mt] = *reinterpret_cast<const AG_LDS bf16x8 *>(xst + (16 * mt + col) * 128 + (((4 * s + kg) ^ xkey(16 * mt + col)) << 4));
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          if (nt == 0 || two) {
+            const bf16x8 wf = wc.frag(bw, s, nt);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mt], wf, acc[mt][nt], 0, 0, 0);
+          }
+      }
     }
     wave_sync();  // both buffers have been read
   }
   float(*red)[32][32] = reinterpret_cast<float(*)[32][32]>(wst);
   __syncthreads();  // (red[w] is not wave w's own buffer)
 #pragma unroll
-  for (int r16 = 0; r16 < 16; ++r16) red[wave][8 * (r16 >> 2) + 4 * kb + (r16 & 3)][m] = acc[r16];
-  __syncthreads();
-  // element e = (token row e / 32, head e % 32); thread t owns e = t and t + 512
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int e = threadIdx.x + 64 * kFusedWaves * i;
-    float v = 0.f;
+    for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-    for (int w = 0; w < kFusedWaves; ++w) v += red[w][e >> 5][e & 31];
-    const int rw = e >> 5, hh = e & 31;
-    const int64_t tk = tok0 + rw;
-    if (hh < H_f && rw < TOK && tk < tokens) {
-      const float val = v + bias[hh];
-      if (logits) logits[(size_t)tk * H_f + hh] = val;
-      fl[hh][rw] = (val > thr || (int)(tk % L) < n_sink) ? 1 : 0;
-    }
-  }
+      for (int r16 = 0; r16 < 4; ++r16) red[wave][16 * mt + 4 * kg + r16][16 * nt + col] = acc[mt][nt][r16];
   __syncthreads();
-  for (int e = threadIdx.x; e < 32 * H_f; e += 64 * kFusedWaves) {
-    const int hh = e >> 5, rw = e & 31;
-    const int64_t tk = tok0 + rw;
-    if (rw >= TOK || tk >= tokens) continue;
-    const int64_t bb = tk / L;
-    flags[((size_t)bb * H_f + hh) * L + (tk - bb * L)] = fl[hh][rw];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    if (mt > 0) __syncthreads();  // (the flags of the first 16 rows have left)
+    gate_epilogue([&](int w, int row, int hh) { return red[w][16 * mt + row][hh]; }, fl, (uint32_t)tok0 + 16 * mt, (uint32_t)tokens, L, H_f,
+                  bias_h, thr, n_sink, logits, flags);
   }
 }
 
@@ -502,11 +480,12 @@ __global__ __launch_bounds__(64 * kFusedWaves) void ag_gate_f32_kernel(const flo
                                                                        const float *__restrict__ bias, float thr, int n_sink,
                                                                        float *__restrict__ logits, uint8_t *__restrict__ flags) {
   __shared__ float red[kFusedWaves][16][32];
-  __shared__ uint8_t fl[kNP][32];
+  __shared__ uint8_t fl[kNP][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, kg = lane >> 4;
   const uint32_t tok0 = blockIdx.x * 16;
   const float *xr = x + (size_t)min(tok0 + col, tokens - 1) * d_in;
+  const float bias_h = gate_bias(bias, H_f);
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
   const bool two = H_f > 16;
   const int n0 = min(col, H_f - 1), n1 = min(16 + col, H_f - 1);  // (columns past H_f: computed, never stored)
@@ -532,7 +511,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void ag_gate_f32_kernel(const flo
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wave][4 * kg + r][16 * nt + col] = acc[nt][r];
   __syncthreads();
-  gate_epilogue<16>([&](int v, int row, int h) { return red[v][row][h]; }, fl, tok0, tokens, L, H_f, bias, thr, n_sink, logits, flags);
+  gate_epilogue([&](int v, int row, int h) { return red[v][row][h]; }, fl, tok0, tokens, L, H_f, bias_h, thr, n_sink, logits, flags);
 }
 
 }  // namespace
@@ -552,7 +531,6 @@ hipError_t ag_launch_gate(ag_ctx *ctx, hipStream_t s, const void *feat, ag_dtype
                           uint8_t *flags, ws_cursor &ws) {
   const int64_t tokens = (int64_t)B * L;
   if (tokens > 0xffffffffll - 64) return hipErrorInvalidValue;
-  const int64_t tiles32 = (tokens + 31) / 32;
   const dim3 block(64 * kFusedWaves);
   if (dt != AG_BF16) {
     AG_LAUNCH(ag_time_kernel(ctx, AG_K_GATE), ag_gate_f32_kernel, dim3((unsigned)((tokens + 15) / 16)), block, 0, s, (const float *)feat,
@@ -567,25 +545,46 @@ hipError_t ag_launch_gate(ag_ctx *ctx, hipStream_t s, const void *feat, ag_dtype
     const int n = d_in * kNP;
     hipLaunchKernelGGL(ag_gate_pack_w, dim3((n + 255) / 256), dim3(256), 0, s, (const uint16_t *)w, d_in, H_f, wp);
   }
+  const uint4 *wv = (const uint4 *)(raw_w ? w : wp);
+  const int64_t tiles = (tokens + 15) / 16;
+  const int per_wave = (d_in / 64 + kFusedWaves - 1) / kFusedWaves;  // 64-feature chunks per wave
   const ag_evpair ev = ag_time_kernel(ctx, AG_K_GATE);
-  if (raw_w && tiles32 < ctx->num_cu) {
-#define AG_GATE16(PFV)                                                                                                \
-  AG_LAUNCH(ev, ag_gate16_kernel<PFV>, dim3((unsigned)((tokens + 15) / 16)), block, 0, s, (const uint16_t *)feat, (const uint4 *)w, \
-            (uint32_t)tokens, d_in, L, H_f, bias, thr, n_sink, logits, flags)
-    // every chunk of a wave in flight, up to 8
-    const int per_wave = (d_in / 64 + kFusedWaves - 1) / kFusedWaves;
-    if (per_wave <= 1) AG_GATE16(1); else if (per_wave <= 2) AG_GATE16(2); else if (per_wave <= 4) AG_GATE16(4); else AG_GATE16(8);
-#undef AG_GATE16
+  // From two tiles per CU on, and as far as a wave's part of W fits its registers, tiles stream through one workgroup per CU.
+  if (tiles >= 2 * ctx->num_cu && per_wave <= 8) {
+    const size_t shmem = (size_t)kFusedWaves * (kRing * 2048 + 4096);
+#define AG_GATE_STREAM(RAWV, NCHV)                                                                                    \
+  do {                                                                                                                \
+    static std::atomic<bool> allowed[64];  /* more than 64 KiB of LDS: said once per device */                         \
+    if (!allowed[ctx->device & 63].load(std::memory_order_relaxed)) {                                                  \
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_gate_stream_kernel<RAWV, NCHV>),      \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);                \
+      if (e != hipSuccess) return e;                                                                                   \
+      allowed[ctx->device & 63].store(true, std::memory_order_relaxed);                                                \
+    }                                                                                                                  \
+    AG_LAUNCH(ev, (ag_gate_stream_kernel<RAWV, NCHV>), dim3(ctx->num_cu), block, shmem, s, (const uint16_t *)feat, wv, (uint32_t)tokens, \
+              d_in, L, H_f, bias, thr, n_sink, logits, flags);                                                          \
+  } while (0)
+#define AG_GATE_STREAM_N(RAWV)                                                                                        \
+  do {                                                                                                                \
+    if (per_wave <= 1) AG_GATE_STREAM(RAWV, 1); else if (per_wave <= 2) AG_GATE_STREAM(RAWV, 2);                        \
+    else if (per_wave <= 4) AG_GATE_STREAM(RAWV, 4); else AG_GATE_STREAM(RAWV, 8);                                      \
+  } while (0)
+    if (raw_w) AG_GATE_STREAM_N(true); else AG_GATE_STREAM_N(false);
+#undef AG_GATE_STREAM_N
+#undef AG_GATE_STREAM
     return hipGetLastError();
   }
-  // PF = feature chunks a wave keeps in flight.  A launch of at most one workgroup per CU is one round of loads per wave
-  // (PF = 4); a longer one runs two workgroups per CU with half the registers (PF = 2), so that one loads while the
-  // other reduces and writes its flags (measured: not with pre-packed W).
-#define AG_GATE_FUSED(RAWV, PFV, WPTR)                                                                                     \
-  AG_LAUNCH(ev, (ag_gate_fused_kernel<RAWV, PFV>), dim3((unsigned)tiles32), block, 0, s, (const uint16_t *)feat, (const uint4 *)(WPTR), \
-            tokens, d_in, L, H_f, bias, thr, n_sink, logits, flags)
-  if (!raw_w) AG_GATE_FUSED(false, 4, wp); else if (tiles32 > ctx->num_cu) AG_GATE_FUSED(true, 2, w); else AG_GATE_FUSED(true, 4, w);
-#undef AG_GATE_FUSED
+#define AG_GATE16(RAWV, PFV)                                                                                          \
+  AG_LAUNCH(ev, (ag_gate16_kernel<RAWV, PFV>), dim3((unsigned)tiles), block, 0, s, (const uint16_t *)feat, wv, (uint32_t)tokens, d_in, L, \
+            H_f, bias, thr, n_sink, logits, flags)
+#define AG_GATE16_N(RAWV)                                                                                             \
+  do {                                                                                                                \
+    if (per_wave <= 1) AG_GATE16(RAWV, 1); else if (per_wave <= 2) AG_GATE16(RAWV, 2);                                  \
+    else if (per_wave <= 4) AG_GATE16(RAWV, 4); else AG_GATE16(RAWV, 8);                                                \
+  } while (0)
+  if (raw_w) AG_GATE16_N(true); else AG_GATE16_N(false);  // (every chunk of a wave in flight, up to 8)
+#undef AG_GATE16_N
+#undef AG_GATE16
   return hipGetLastError();
 }
 

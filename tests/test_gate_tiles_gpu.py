@@ -1,5 +1,6 @@
 """The gate's launch shapes against the oracle: 16-token tiles (few tokens) with one to eight feature chunks per wave and
-more, ragged last tiles, sequences shorter than a tile, one and two column tiles; the fp32 gate at odd sizes."""
+more, ragged last tiles, sequences shorter than a tile, one and two column tiles; streams of tiles; the fp32 gate at odd
+sizes."""
 import math
 
 import numpy as np
@@ -20,6 +21,9 @@ def _lib():
     ("bf16", 1, 1, 64, 4, 0), ("bf16", 1, 5, 192, 32, 0), ("bf16", 1, 17, 512, 16, 1), ("bf16", 1, 15, 576, 20, 0), ("bf16", 9, 3, 1024, 32, 1),
     ("bf16", 2, 333, 2048, 8, 0), ("bf16", 1, 100, 4096, 12, 3), ("bf16", 1, 48, 8192, 32, 0), ("bf16", 1, 40, 4160, 28, 0),
     ("bf16", 1, 4095, 512, 32, 0), ("bf16", 2, 4096, 128, 4, 0), ("bf16", 1, 33, 256, 7, 0),
+    # two or more 16-token tiles per CU stream through persistent workgroups
+    ("bf16", 1, 8192, 64, 4, 0), ("bf16", 3, 3001, 1088, 12, 1), ("bf16", 1, 8321, 4096, 32, 0), ("bf16", 700, 13, 512, 7, 2),
+    ("bf16", 1, 8200, 4160, 8, 0),
     ("f32", 1, 1, 3, 1, 0), ("f32", 5, 7, 130, 17, 2), ("f32", 1, 257, 1021, 32, 0), ("f32", 2, 50, 64, 16, 0)])
 def test_gate_tiles(dtype, B, L, d_in, H, n_sink):
     x = rand_t(71, (B, L, d_in), dtype, 0.5)
