@@ -342,7 +342,7 @@ ag_status ag_pack_row_off(ag_ctx *ctx, void *hip_stream, const uint8_t *flags, i
   AG_REQUIRE(ws.ok, AG_EWORKSPACE, "ag_pack_row_off: workspace of %zu bytes is too small (need %zu)", ctx->ws_bytes, ws.off);
   ag_status st = need_device(ctx);
   if (st != AG_OK) return st;
-  AG_HIP(ag_launch_pack_row_off((hipStream_t)hip_stream, flags, units, L, room, total_rows, kept, row_off, rows_needed));
+  AG_HIP(ag_launch_pack_row_off(ctx, (hipStream_t)hip_stream, flags, units, L, room, total_rows, kept, row_off, rows_needed));
   return AG_OK;
 }
 

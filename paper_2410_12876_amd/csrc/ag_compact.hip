@@ -14,6 +14,23 @@ constexpr int kScanThreads = 256;
 
 constexpr int kSegWords = 16;  // mask words (1024 tokens) per scan workgroup
 
+// Non-zero bytes of f[0 .. n) that fall to thread tid of NT (at least 16): whole 16-byte blocks, and the bytes before the
+// first and after the last of them one by one (rows of flags start anywhere when L is odd).
+__device__ __forceinline__ int count_flags(const uint8_t *__restrict__ f, int n, int tid, int NT) {
+  const int head = min(n, (int)((16 - (reinterpret_cast<uintptr_t>(f) & 15)) & 15));
+  const int body = (n - head) >> 4, tail0 = head + 16 * body;
+  const uint4 *b = reinterpret_cast<const uint4 *>(f + head);
+  auto nz = [](uint32_t x) { return __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u); };
+  int c = 0;
+  if (tid < head) c += f[tid] != 0;
+  if (tid < n - tail0) c += f[tail0 + tid] != 0;
+  for (int i = tid; i < body; i += NT) {
+    const uint4 x = b[i];
+    c += nz(x.x) + nz(x.y) + nz(x.z) + nz(x.w);
+  }
+  return c;
+}
+
 // What the scan leaves for the D = 128 prefill kernel, run by every workgroup of a grid = (segments, units) launch
 // after it knows its unit's running total (unit_total is valid in thread 0 of a unit's last segment):
 // all workgroups clear the per-item arrival counters; the last segments publish their unit's kept-row count and the
@@ -90,7 +107,7 @@ __device__ __forceinline__ void plan_tail(const ag_pf_plan &plan, int num_units,
 
 
 // grid = (segments, units).  A workgroup builds the mask words of its 1024 tokens and needs the number of
-// kept tokens before them; it counts those itself (4 flags per load), so no workgroup waits for another.
+// kept tokens before them; it counts those itself (16 flags per load), so no workgroup waits for another.
 // flags == nullptr stands for "every token kept" (the attention inside the gate module evicts nothing): the words
 // and counts are then written without reading anything.
 __global__ __launch_bounds__(kScanThreads) void ag_flag_scan_kernel(const uint8_t *__restrict__ flags, int L, int nw,
@@ -119,14 +136,8 @@ __global__ __launch_bounds__(kScanThreads) void ag_flag_scan_kernel(const uint8_
   int before = 0;
   if (!flags) {
     before = tid == 0 ? t_end : 0;
-  } else if ((reinterpret_cast<uintptr_t>(f) & 3) == 0) {
-    const uint32_t *f4 = reinterpret_cast<const uint32_t *>(f);
-    for (int i = tid; i < t_end / 4; i += kScanThreads) {
-      const uint32_t x = f4[i];
-      before += __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u);  // non-zero bytes of x
-    }
   } else {
-    for (int i = tid; i < t_end; i += kScanThreads) before += f[i] != 0;
+    before = count_flags(f, t_end, tid, kScanThreads);
   }
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
   if (lane == 0) part[wave] = before;
@@ -158,7 +169,7 @@ __global__ __launch_bounds__(kScanThreads) void ag_flag_scan_kernel(const uint8_
 
 // The flag scan and the compaction in one launch.  LPR = lanes that share one row (16 bytes each); rows wider than
 // 1 KiB loop over segments.  grid = (ceil(nw / 4), units), 4 waves, wave w of workgroup x owns mask word 4 x + w.  A workgroup counts the kept
-// tokens before its 256 tokens itself (4 flags per load, at most L bytes, from the caches), so no workgroup waits
+// tokens before its 256 tokens itself (16 flags per load, at most L bytes, from the caches), so no workgroup waits
 // for another and the copy starts one round of loads after the launch instead of after a separate scan kernel.
 // It leaves words / blk_off / the prefill plan exactly as ag_flag_scan_kernel does; then a lane's rank inside the
 // word plus the word's prefix is the destination row, so the surviving rows are written back-to-back (fully
@@ -184,16 +195,7 @@ __global__ __launch_bounds__(256) void ag_scan_compact_kernel(const uint8_t *__r
   const uint8_t f_own = (w < nw && t_own < L) ? f[t_own] : (uint8_t)0;
   // kept tokens before the workgroup's first token
   const int t_end = blockIdx.x * 256;  // <= L
-  int before = 0;
-  if ((reinterpret_cast<uintptr_t>(f) & 3) == 0) {
-    const uint32_t *f4 = reinterpret_cast<const uint32_t *>(f);
-    for (int i = tid; i < t_end / 4; i += 256) {
-      const uint32_t x = f4[i];
-      before += __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u);  // non-zero bytes of x
-    }
-  } else {
-    for (int i = tid; i < t_end; i += 256) before += f[i] != 0;
-  }
+  int before = count_flags(f, t_end, tid, 256);
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
   const uint64_t word = __ballot(f_own != 0);
   const int n = __popcll(word);
@@ -274,39 +276,50 @@ __global__ void ag_slab_offsets_kernel(int64_t *row_off, int units, int L) {
   if (u <= units) row_off[u] = (int64_t)u * L;
 }
 
-// Packed layout, step 1: kept flags per unit.  grid = units.
-__global__ __launch_bounds__(256) void ag_count_kept_kernel(const uint8_t *__restrict__ flags, int L,
-                                                            int32_t *__restrict__ kept) {
-  __shared__ int32_t part[4];
-  const uint8_t *f = flags + (size_t)blockIdx.x * L;
-  const int tid = threadIdx.x;
-  int n = 0;
-  if ((reinterpret_cast<uintptr_t>(f) & 3) == 0) {
-    const uint32_t *f4 = reinterpret_cast<const uint32_t *>(f);
-    for (int i = tid; i < L / 4; i += 256) {
-      const uint32_t x = f4[i];
-      n += __popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u);  // non-zero bytes of x
-    }
-    for (int i = (L & ~3) + tid; i < L; i += 256) n += f[i] != 0;
-  } else {
-    for (int i = tid; i < L; i += 256) n += f[i] != 0;
-  }
-  for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-  if ((tid & 63) == 0) part[tid >> 6] = n;
-  __syncthreads();
-  if (tid == 0) kept[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
-}
-
-// Packed layout, step 2 (one workgroup): row_off[u + 1] = min(sum_{u' <= u} (kept[u'] + room), total_rows).
-__global__ __launch_bounds__(256) void ag_pack_offsets_kernel(const int32_t *__restrict__ kept, int units, int room,
-                                                              int64_t total_rows, int64_t *__restrict__ row_off,
-                                                              int64_t *__restrict__ rows_needed) {
-  __shared__ int64_t wave_sum[4];
+// Packed layout, one launch: a workgroup of 16 waves counts the kept flags of 16 / wpu units, wpu waves each, and the one that
+// arrives last turns the counts into row_off[u + 1] = min(sum_{u' <= u} (kept[u'] + room), total_rows).  wpu grows with L so
+// that a wave has about two loads; few workgroups matter because all of them count their arrival at one address (512 of
+// them: 5 us).  (Two launches, the first with a quarter of the
+// threads and 4 flags per load, took 14.5 us for 8 units of 32768 tokens and 9.6 us for 512 of 2048.)
+constexpr int kPackThreads = 1024;
+__global__ __launch_bounds__(kPackThreads) void ag_pack_row_off_kernel(const uint8_t *__restrict__ flags, int L, int units, int wpu, int room,
+                                                                       int64_t total_rows, int32_t *__restrict__ kept,
+                                                                       int64_t *__restrict__ row_off,
+                                                                       int64_t *__restrict__ rows_needed,
+                                                                       int32_t *__restrict__ arrivals) {
+  constexpr int NW = kPackThreads / 64;
+  __shared__ int32_t part[NW];
+  __shared__ int64_t wave_sum[NW];
+  __shared__ int is_last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per = (units + 255) / 256;
+  const int upw = NW / wpu, first = blockIdx.x * upw;  // units of this workgroup: first .. first + upw
+  const int u_w = first + wave / wpu;
+  int n = u_w < units ? count_flags(flags + (size_t)u_w * L, L, (wave % wpu) * 64 + lane, wpu * 64) : 0;
+  for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+  if (lane == 0) part[wave] = n;
+  __syncthreads();
+  if (wave == 0) {
+    // (written through, complete before the arrival is counted; see ag_internal.h on data between workgroups)
+    if (lane < upw && first + lane < units) {
+      int sum = 0;
+      for (int w = 0; w < wpu; ++w) sum += part[lane * wpu + w];
+      __hip_atomic_store(&kept[first + lane], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) {
+      is_last = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+      if (is_last) __hip_atomic_store(arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next call
+    }
+  }
+  __syncthreads();
+  if (!is_last) return;
+  const int per = (units + kPackThreads - 1) / kPackThreads;
   const int u0 = min(units, tid * per), u1 = min(units, u0 + per);
+  auto rows_of = [&](int u) {
+    return (int64_t)__hip_atomic_load(&kept[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + room;
+  };
   int64_t sum = 0;
-  for (int u = u0; u < u1; ++u) sum += (int64_t)kept[u] + room;
+  for (int u = u0; u < u1; ++u) sum += rows_of(u);
   int64_t incl = sum;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -315,23 +328,32 @@ __global__ __launch_bounds__(256) void ag_pack_offsets_kernel(const int32_t *__r
   }
   if (lane == 63) wave_sum[wave] = incl;
   __syncthreads();
-  int64_t run = incl - sum;
-  for (int w = 0; w < wave; ++w) run += wave_sum[w];
-  if (tid == 0) row_off[0] = 0;
+  int64_t run = incl - sum, all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) run += wave_sum[w];
+    all += wave_sum[w];
+  }
+  if (tid == 0) {
+    row_off[0] = 0;
+    if (rows_needed) *rows_needed = all;
+  }
   for (int u = u0; u < u1; ++u) {
-    run += (int64_t)kept[u] + room;
+    run += rows_of(u);
     row_off[u + 1] = run < total_rows ? run : total_rows;
   }
-  if (tid == 255 && rows_needed) *rows_needed = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
 }
 
 }  // namespace
 
-hipError_t ag_launch_pack_row_off(hipStream_t s, const uint8_t *flags, int units, int L, int room, int64_t total_rows,
-                                  int32_t *kept, int64_t *row_off, int64_t *rows_needed) {
-  hipLaunchKernelGGL(ag_count_kept_kernel, dim3(units), dim3(256), 0, s, flags, L, kept);
-  hipLaunchKernelGGL(ag_pack_offsets_kernel, dim3(1), dim3(256), 0, s, kept, units, room, total_rows, row_off,
-                     rows_needed);
+hipError_t ag_launch_pack_row_off(ag_ctx *ctx, hipStream_t s, const uint8_t *flags, int units, int L, int room,
+                                  int64_t total_rows, int32_t *kept, int64_t *row_off, int64_t *rows_needed) {
+  int32_t *arrivals = ctx->d_err + 32;  // zeroed at creation; the kernel leaves it at zero
+  int wpu = 1;
+  while (wpu < kPackThreads / 64 && L > 2048 * wpu) wpu *= 2;
+  const int upw = kPackThreads / 64 / wpu;
+  hipLaunchKernelGGL(ag_pack_row_off_kernel, dim3((units + upw - 1) / upw), dim3(kPackThreads), 0, s, flags, L, units, wpu, room,
+                     total_rows, kept, row_off, rows_needed, arrivals);
   return hipGetLastError();
 }
 
