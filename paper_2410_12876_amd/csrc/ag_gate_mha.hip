@@ -11,6 +11,8 @@
 //   3. the gate kernels of ag_gate.hip with d_in = h' 128 and W_g = W^{O'}.
 #include <string.h>
 
+#include <atomic>
+
 #include "ag_internal.h"
 
 namespace {
@@ -24,35 +26,18 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 #define AG_LDS __attribute__((address_space(3)))
 
-constexpr int kDh = 128;           // d'_k
-constexpr int kBM = 128;           // tokens per workgroup tile
-constexpr int kBNc = 128;          // output columns per workgroup tile
-constexpr int kBK = 64;            // k per pipeline step
-constexpr int kXRowB = kBK * 2;    // bytes per row of the X tile in LDS (128)
-constexpr int kWRowB = kBNc * 2;   // bytes per row of the W tile in LDS (256)
-constexpr int kXTileB = kBM * kXRowB;  // 16 KiB
-constexpr int kWTileB = kBK * kWRowB;  // 16 KiB
-
-__device__ __forceinline__ int swz_w(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }  // 16 chunks per W row
-__device__ __forceinline__ int swz_x(int r) { return (r >> 1) & 7; }                     // 8 chunks per X row
+constexpr int kDh = 128;  // head size
 
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   const f32x2 x = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
-// C^T[n, m] = sum_k W[k, n] X[m, k]: the A operand is W^T (transposing LDS reads of the row-major W tile), the B
-// operand is X^T (16-byte LDS reads of the row-major X tile), so a lane ends up with 4 consecutive output columns
-// of one token -- 8-byte stores into the head-major result.
-//   x [M, K] bf16 row-major, w [K, N] bf16 row-major, K % 64 == 0, N % 128 == 0, N = 3 * hp * 128.
-//   out: three tensors [B, hp, L, 128] back to back; token m = b * L + t.
-// grid = (N / 128, ceil(M / 128)); 4 waves, wave (wn, wm) owns the 64 x 64 quadrant of the tile.
-//
 // COMPACT (the layer's own K/V projection, N = 2 * hp * 128: K columns, then V columns): besides the two full tensors
-// -- every token needs its own k, v for the diagonal of Eq. 5 -- a tile, which is 128 tokens of one head, also
-// writes the rows of its kept tokens straight into the ragged cache, at the position the flag scan gives them
-// (words / blk_off: 64-bit keep masks and their exclusive prefix counts), so the compaction pass and its re-read of
-// K and V disappear.  The K tiles also write idx, the first token tile of a K head writes len.
+// -- every token needs its own k, v for the diagonal of Eq. 5 -- a tile also writes the rows of its kept tokens straight
+// into the ragged cache, at the position the flag scan gives them (words / blk_off: 64-bit keep masks and their exclusive
+// prefix counts), so the compaction pass and its re-read of K and V disappear.  The K tiles also write idx, the tile with
+// a sequence's first token and a K head's first column writes len.
 struct ag_proj_compact {
   const uint64_t *words;    // [units, nw]
   const int32_t *blk_off;   // [units, nw + 1]
@@ -62,172 +47,295 @@ struct ag_proj_compact {
   int nw, pos0;
 };
 
-template <bool COMPACT>
-__global__ __launch_bounds__(256, 2) void ag_proj_gemm_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
-                                                              int64_t M, int K, int N, int L, int hp,
-                                                              uint16_t *__restrict__ out, ag_proj_compact cp) {
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kXTileB + 2 * kWTileB];  // [X0][X1][W0][W1]
+// C^T[n, m] = sum_k W[k, n] X[m, k]: the A operand is W^T (transposing LDS reads of the row-major W tile), the B
+// operand is X^T (16-byte LDS reads of the row-major X tile), so a lane ends up with 4 consecutive output columns
+// of one token.
+//   x [M, K] bf16 row-major, w [K, N] bf16 row-major, K % 64 == 0, N % 128 == 0, N = (3 or 2) * hp * 128.
+//   out: tensors [B, hp, L, 128] back to back; token m = b * L + t.
+// A workgroup computes BM tokens x BN columns with WM x WN waves, each a block of 32-row MFMA tiles.  The operands stream
+// through a ring of ST stages of BK k-steps, loaded straight into LDS ST - 1 stages ahead; one barrier per stage.
+// What bounds it is LDS first: per 16 k-steps a wave reads (TM + TN) KiB for TM TN MFMAs of 32 cycles, so with 64 x 64 per
+// wave (TM = TN = 2) the reads alone fill all of LDS's 128 bytes a cycle at the full MFMA rate; 64 x 128 per wave needs 96
+// and the loads' own writes 31.  And under that load the chip's power: the vendor library's 8192^3 product reaches
+// 1.24 PFLOP/s here.
+template <int BM_, int BN_, int WM_, int WN_, int BK_, int ST_> struct proj_cfg {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, ST = ST_;
+  static constexpr int NT = 64 * WM * WN, TM = BM / WM / 32, TN = BN / WN / 32;
+  static constexpr int XRow = BK * 2, WRow = BN * 2;             // bytes per LDS row of the X and W tiles
+  static constexpr int XTile = BM * XRow, WTile = BK * WRow, Stage = XTile + WTile;
+  static constexpr int XL = XTile / 1024 / (NT / 64), WL = WTile / 1024 / (NT / 64);  // load instructions per wave and stage
+  static constexpr int Lds = ST * Stage > BM * WRow ? ST * Stage : BM * WRow;
+  static_assert(XTile % (1024 * (NT / 64)) == 0 && WTile % (1024 * (NT / 64)) == 0, "whole load instructions per wave");
+  // swizzle keys (chunks of 16 bytes): X rows of 64, 128 or 256 bytes, W rows of 128 bytes or more
+  static __device__ __forceinline__ int xkey(int r) { return BK == 32 ? (r >> 2) & 3 : BK == 64 ? (r >> 1) & 7 : r & 15; }
+  static __device__ __forceinline__ int wkey(int r) {
+    // rows of a multiple of 256 bytes start at the same bank; others alternate between the two halves of the banks
+    return WRow % 256 == 0 ? ((r & 3) << 2) | ((r >> 2) & 3) : ((r >> 1) & 1) << 2;
+  }
+};
+
+template <typename CFG, bool COMPACT>
+__global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
+                                                               int64_t M, int K, int N, int L, int hp,
+                                                               uint16_t *__restrict__ out, ag_proj_compact cp, int m_tiles,
+                                                               int n_tiles) {
+  constexpr int BM = CFG::BM, BN = CFG::BN, BK = CFG::BK, ST = CFG::ST, TM = CFG::TM, TN = CFG::TN, NT = CFG::NT;
+  constexpr int XRow = CFG::XRow, WRow = CFG::WRow, XL = CFG::XL, WL = CFG::WL;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave & 1, wm = wave >> 1;
-  const int n0 = blockIdx.x * kBNc;
-  const int64_t m0 = (int64_t)blockIdx.y * kBM;
+  const int wn = wave % CFG::WN, wm = wave / CFG::WN;
   const int col = lane & 31, kb = lane >> 5;
+  // Workgroup -> tile: workgroup i runs on XCD i % 8.  An XCD takes a contiguous part of the tile list, which walks groups
+  // of 8 token tiles column by column, so that the tiles in flight on it share W and X panels in its L2.
+  const int tiles = m_tiles * n_tiles, per_xcd = (tiles + 7) >> 3;
+  const int t_id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || t_id >= tiles) return;
+  const int grp = t_id / (8 * n_tiles), in_g = t_id - grp * 8 * n_tiles, gm = min(8, m_tiles - 8 * grp);
+  const int n0 = (in_g / gm) * BN;
+  const int64_t m0 = (int64_t)(8 * grp + in_g % gm) * BM;
 
   // ---- tile loaders (global -> LDS without registers); the swizzle is applied on the global side ----
-  const int64_t rows_left = M - m0;  // rows of x that exist from m0 on (>= 1)
+  const int64_t rows_left = M - m0;  // rows of x that exist from m0 on (>= 1); rows past the end arrive as zeros
   const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void *)(x + (size_t)m0 * K), 0, (int)min((int64_t)kBM, rows_left) * K * 2, 0x00020000);
+      (void *)(x + (size_t)m0 * K), 0, (int)min((int64_t)BM, rows_left) * K * 2, 0x00020000);
   const __amdgpu_buffer_rsrc_t w_rsrc =
       __builtin_amdgcn_make_buffer_rsrc((void *)(w + n0), 0, (int)(((size_t)K * N - n0) * 2), 0x00020000);
-  // X tile: wave fills rows [32 wave, +32), 8 rows (1 KiB) per instruction; lane -> (row, physical chunk lane % 8)
-  int xoff[4], woff[4];
+  constexpr int XC = XRow / 16, WC = WRow / 16;  // chunks per row
+  int xoff[XL], woff[WL];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 32 * wave + 8 * i + (lane >> 3);
-    xoff[i] = r * K * 2 + (((lane & 7) ^ swz_x(r)) << 4);
+  for (int i = 0; i < XL; ++i) {
+    const int r = (wave * XL + i) * (64 / XC) + lane / XC;
+    xoff[i] = r * K * 2 + (((lane % XC) ^ CFG::xkey(r)) << 4);
   }
-  // W tile: wave fills rows [16 wave, +16), 4 rows per instruction; lane -> (row, physical chunk lane % 16)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 16 * wave + 4 * i + (lane >> 4);
-    woff[i] = r * N * 2 + (((lane & 15) ^ swz_w(r)) << 4);
+  for (int i = 0; i < WL; ++i) {  // piece p of the tile, 64 pieces per instruction: row p / WC, position p % WC
+    const int p = (wave * WL + i) * 64 + lane, r = p / WC, c = p % WC;
+    woff[i] = r * N * 2 + ((c ^ CFG::wkey(r)) << 4);
   }
   const uint32_t lds0 = (uint32_t)(size_t)((AG_LDS uint8_t *)smem);
-  auto issue = [&](int t) {  // k-tile t -> buffers t & 1
-    const int xs = t * kBK * 2;        // byte offset of the k-tile inside a row of x
-    const int ws = t * kBK * N * 2;    // byte offset of the k-tile's first row of w
+  auto issue = [&](int t, int buf) {  // stage t -> ring position buf
+    const int xs = t * BK * 2, ws = t * BK * N * 2;
+    const uint32_t base = lds0 + buf * CFG::Stage;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t dx = lds0 + (t & 1) * kXTileB + (32 * wave + 8 * i) * kXRowB;
+    for (int i = 0; i < XL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(dx), "v"(xoff[i]), "s"(x_rsrc), "s"(xs) : "memory");
-    }
+                   :: "s"(base + (wave * XL + i) * 1024), "v"(xoff[i]), "s"(x_rsrc), "s"(xs) : "memory");
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t dw = lds0 + 2 * kXTileB + (t & 1) * kWTileB + (16 * wave + 4 * i) * kWRowB;
+    for (int i = 0; i < WL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(dw), "v"(woff[i]), "s"(w_rsrc), "s"(ws) : "memory");
-    }
+                   :: "s"(base + CFG::XTile + (wave * WL + i) * 1024), "v"(woff[i]), "s"(w_rsrc), "s"(ws) : "memory");
   };
 
   // ---- loop-invariant LDS offsets of this lane's fragments ----
-  // B operand (X^T): lane (token col, k half kb), slab sl: 16 bytes at row 64 wm + 32 mt + col, chunk 2 sl + kb
-  int x_off[2][4];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int sl = 0; sl < 4; ++sl) {
-      const int r = 64 * wm + 32 * mt + col;
-      x_off[mt][sl] = r * kXRowB + (((2 * sl + kb) ^ swz_x(r)) << 4);
-    }
+  // B operand (X^T): lane (token col, k half kb), slab sl: 16 bytes at row (wm TM + mt) 32 + col, chunk 2 sl + kb
+  // (the key only depends on the row mod 32, so the slab and the row tile are an XOR and an addition)
+  const int x_row = wm * TM * 32 + col;
+  const int x_base = x_row * XRow + ((kb ^ CFG::xkey(x_row)) << 4);
   // A operand (W^T) by transposing reads: 16-lane group gl covers columns 16 (gl % 2) + 0..15 of a 32-column
   // sub-tile and k half gl / 2; lane i supplies the address of row 8 (gl / 2) + i / 4 (+ 4), columns 4 (i % 4) .. +3
   const int gl = lane >> 4, li = lane & 15;
-  int w_off[2][2];
+  int w_off[TN][2];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+  for (int nt = 0; nt < TN; ++nt)
 #pragma unroll
     for (int h2 = 0; h2 < 2; ++h2) {
-      const int r = 8 * (gl >> 1) + (li >> 2) + 4 * h2;                       // row inside a 16-k slab
-      const int c = 4 * (2 * wn + nt) + 2 * (gl & 1) + ((li & 3) >> 1);       // 16-byte chunk of the 256-byte row
-      w_off[nt][h2] = r * kWRowB + ((c ^ swz_w(r)) << 4) + (li & 1) * 8;
+      const int r = 8 * (gl >> 1) + (li >> 2) + 4 * h2;                        // row inside a 16-k slab
+      const int c = 4 * (wn * TN + nt) + 2 * (gl & 1) + ((li & 3) >> 1);        // 16-byte chunk of the row
+      w_off[nt][h2] = CFG::XTile + r * WRow + ((c ^ CFG::wkey(r)) << 4) + (li & 1) * 8;
     }
 
-  f32x16 acc[2][2];  // [nt][mt]
+  f32x16 acc[TN][TM];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < TN; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < TM; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-  const int T = K / kBK;
-  issue(0);
-  for (int t = 0; t < T; ++t) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's share of tile t has landed
-    __syncthreads();                                  // ... and everyone's; tile t - 1 is fully consumed
-    if (t + 1 < T) issue(t + 1);
-    const AG_LDS uint8_t *Xt = (const AG_LDS uint8_t *)smem + (t & 1) * kXTileB;
-    const AG_LDS uint8_t *Wt = (const AG_LDS uint8_t *)smem + 2 * kXTileB + (t & 1) * kWTileB;
+  // The fragments of one 16-k slab are read from LDS while the MFMAs of the slab before it run, also across a stage's end:
+  // after a barrier the first MFMAs find their operands in registers.  For that the NEXT stage must have landed at every
+  // barrier, and a stage's place in the ring is free after the barrier that follows its last slab.
+  constexpr int NS = BK / 16, NM = TN * TM, RPM = (2 * TN + TM + NM - 1) / NM;  // slabs per stage, MFMAs per slab, reads per MFMA
+  const int T = K / BK;
+  bf16x8 fa[2][TN], fb[2][TM];
+  auto read = [&](const AG_LDS uint8_t *S, int sl, bf16x8 (&a)[TN], bf16x8 (&b)[TM]) {
 #pragma unroll
-    for (int sl = 0; sl < 4; ++sl) {
-      bf16x8 a[2], b[2];
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        // swz_w only depends on the row inside the slab (r & 15), so the slab base can be added afterwards
-        const AG_LDS uint8_t *base = Wt + 16 * sl * kWRowB;
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(base + w_off[nt][0]));
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(base + w_off[nt][1]));
-        a[nt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) b[mt] = *reinterpret_cast<const AG_LDS bf16x8 *>(Xt + x_off[mt][sl]);
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-          acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[nt], b[mt], acc[nt][mt], 0, 0, 0);
+    for (int nt = 0; nt < TN; ++nt) {
+      // wkey only depends on the row inside the slab (r & 15), so the slab base can be added afterwards
+      const AG_LDS uint8_t *base = S + 16 * sl * WRow;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(base + w_off[nt][0]));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((AG_LDS bf16x4 *)(base + w_off[nt][1]));
+      a[nt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     }
+#pragma unroll
+    for (int mt = 0; mt < TM; ++mt) b[mt] = *reinterpret_cast<const AG_LDS bf16x8 *>(S + (x_base ^ (sl << 5)) + mt * 32 * XRow);
+  };
+#pragma unroll
+  for (int t = 0; t < ST; ++t)
+    if (t < T) issue(t, t);
+  if (T > ST - 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 2) * (XL + WL)) : "memory");  // stages 0 and 1 have landed
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  read((const AG_LDS uint8_t *)smem, 0, fa[0], fb[0]);
+  int buf = 0;
+  for (int t = 0; t < T; ++t) {
+    const AG_LDS uint8_t *S = (const AG_LDS uint8_t *)smem + buf * CFG::Stage;
+    const int nxt = buf + 1 == ST ? 0 : buf + 1;
+    const AG_LDS uint8_t *Sn = (const AG_LDS uint8_t *)smem + nxt * CFG::Stage;
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) {
+      const int cur = sl & 1;
+      if (sl + 1 < NS) read(S, sl + 1, fa[cur ^ 1], fb[cur ^ 1]);
+      else read(Sn, 0, fa[cur ^ 1], fb[cur ^ 1]);  // (after the last stage: stale bytes that nothing uses)
+#pragma unroll
+      for (int nt = 0; nt < TN; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < TM; ++mt)
+          acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][nt], fb[cur][mt], acc[nt][mt], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      }
+    }
+    // this wave's share of stage t + 2 has landed (t + 3 .. may be on their way) ...
+    if (t + ST - 1 < T) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 3) * (XL + WL)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();  // ... and everyone's; stage t is fully read
+    if (t + ST < T) issue(t + ST, buf);
+    buf = nxt;
   }
 
-  // ---- epilogue: acc[nt][mt][r] = C[token m0 + 64 wm + 32 mt + col][n0 + 64 wn + 32 nt + 8 (r/4) + 4 kb + r%4] ----
-  // The tile is one head of one projection: 128 tokens x 128 features = 128 whole output rows of 256 bytes.  A lane
-  // owns 4-feature pieces of two tokens, so it would store scattered 8-byte pieces; the tile is laid out in the
-  // (now unused) operand buffers instead, 16-byte chunks XOR-swizzled with the row, and leaves as whole rows, 4 per
-  // instruction (lane -> row 4 i + lane / 16, chunk lane % 16), to the output and, for a kept token, to its cache row.
-  const int hd = hp * kDh;
-  const int which_t = n0 / hd, head_t = (n0 - which_t * hd) / kDh;
-  __syncthreads();  // every wave is done with the last k-tile
+  // ---- epilogue: acc[nt][mt][r] = C[token m0 + 32 (wm TM + mt) + col][n0 + 32 (wn TN + nt) + 8 (r/4) + 4 kb + r%4] ----
+  // A lane owns 4-column pieces of its tokens, so it would store scattered 8-byte pieces; the tile is laid out in the (now
+  // unused) ring instead, 16-byte chunks XOR-swizzled with the row, and leaves in whole rows, to the output and, for a
+  // kept token, to its cache row.
+  __syncthreads();  // every wave is done with the last stage
   AG_LDS uint8_t *ost = (AG_LDS uint8_t *)smem;
+  constexpr int KM = WC % 16 == 0 ? 15 : 7;  // chunk bits that the row is mixed into
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    const int row = 64 * wm + 32 * mt + col;
+  for (int mt = 0; mt < TM; ++mt) {
+    const int row = 32 * (wm * TM + mt) + col;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < TN; ++nt)
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const f32x16 &c = acc[nt][mt];
         const u32x2 val = {pack2(c[4 * r4 + 0], c[4 * r4 + 1]), pack2(c[4 * r4 + 2], c[4 * r4 + 3])};
-        *reinterpret_cast<AG_LDS u32x2 *>(ost + row * 256 + (((8 * wn + 4 * nt + r4) ^ (row & 15)) << 4) + 8 * kb) = val;
+        *reinterpret_cast<AG_LDS u32x2 *>(ost + row * WRow + (((4 * (wn * TN + nt) + r4) ^ (row & KM)) << 4) + 8 * kb) = val;
       }
   }
-  __syncthreads();  // a row's two halves come from two waves
-  const int ochunk = lane & 15;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int row = 32 * wave + 4 * i + (lane >> 4);
-    const int64_t m = m0 + row;
-    const u32x4 val = *reinterpret_cast<const AG_LDS u32x4 *>(ost + row * 256 + ((ochunk ^ (row & 15)) << 4));
-    if (m >= M) continue;
-    const int64_t b = m / L, tt = m - b * L;
-    uint16_t *dst = out + (((size_t)which_t * (M / L) * hp + (size_t)b * hp + head_t) * L + tt) * kDh + 8 * ochunk;
-    *reinterpret_cast<u32x4 *>(dst) = val;
-    if (COMPACT) {  // this token's row in the cache, if it is kept and fits
-      const int u = (int)b * hp + head_t;
-      const uint64_t word = cp.words[(size_t)u * cp.nw + (tt >> 6)];
-      if ((word >> (tt & 63)) & 1ull) {
-        const int c = cp.blk_off[(size_t)u * (cp.nw + 1) + (tt >> 6)] + __popcll(word & ((1ull << (tt & 63)) - 1ull));
+  const int hd = hp * kDh;
+  // COMPACT: the cache row of every (token, head) of the tile, -1 for none; looked up by all threads at once
+  constexpr int NH = (BN + kDh - 1) / kDh;  // heads of a tile, which starts at one or lies inside one
+  __shared__ int32_t dest[COMPACT ? BM * NH : 1];
+  if (COMPACT) {
+    for (int i = tid; i < BM * NH; i += NT) {
+      const int row = i / NH, nh = n0 + (i % NH) * kDh, which = nh / hd, head = (nh - which * hd) / kDh;
+      const int64_t m = m0 + row;
+      int32_t to = -1;
+      if (m < M) {
+        const int64_t b = m / L;
+        const int tt = (int)(m - b * L), u = (int)b * hp + head;
+        const uint64_t word = cp.words[(size_t)u * cp.nw + (tt >> 6)];
+        const int pre = cp.blk_off[(size_t)u * (cp.nw + 1) + (tt >> 6)];
         const int64_t r0 = cp.row_off[u], cap = cp.row_off[u + 1] - r0;
-        if (c < cap) {
-          uint16_t *crow = (which_t == 0 ? cp.kc : cp.vc) + (size_t)(r0 + c) * kDh;
-          *reinterpret_cast<u32x4 *>(crow + 8 * ochunk) = val;
-          if (which_t == 0 && ochunk == 0) cp.idx[r0 + c] = cp.pos0 + (int)tt;
-        } else if (which_t == 0 && ochunk == 0) {
-          atomicOr(cp.d_err, 1);  // the row is dropped, nothing is written out of bounds
+        const bool writes = which == 0 && nh % kDh == 0;  // K tile with the head's first column: idx, len and the error word
+        if ((word >> (tt & 63)) & 1ull) {
+          const int c = pre + __popcll(word & ((1ull << (tt & 63)) - 1ull));
+          if (c < cap) {
+            to = (int32_t)(r0 + c);
+            if (writes) cp.idx[to] = cp.pos0 + tt;
+          } else if (writes) {
+            atomicOr(cp.d_err, 1);  // the row is dropped, nothing is written out of bounds
+          }
+        }
+        if (writes && tt == 0) {  // the sequence's first token: the unit's length
+          const int kept = cp.blk_off[(size_t)u * (cp.nw + 1) + cp.nw];
+          cp.len[u] = (int)(kept < cap ? kept : cap);
         }
       }
+      dest[i] = to;
     }
   }
-  if (COMPACT && which_t == 0) {  // the K tile that holds a sequence's first token writes the unit's length
-    const int64_t bb = (m0 + L - 1) / L + tid;  // thread t: the t-th sequence that starts inside this tile
-    if (bb * L < m0 + kBM && bb * L < M) {
-      const int u = (int)bb * hp + head_t;
-      const int64_t cap = cp.row_off[u + 1] - cp.row_off[u];
-      const int kept = cp.blk_off[(size_t)u * (cp.nw + 1) + cp.nw];
-      cp.len[u] = (int)(kept < cap ? kept : cap);
+  __syncthreads();  // a row's pieces come from several waves
+  constexpr int RPI = NT / WC;  // rows per pass of the workgroup
+  const int chunk = tid % WC, n = n0 + 8 * chunk;                       // this thread's 8 columns, the same in every pass
+  const int which = n / hd, head = (n - which * hd) / kDh, d = n % kDh;  // which tensor, which head, which feature
+  uint16_t *const out_h = out + (size_t)which * M * hd + (size_t)head * L * kDh + d;
+  int64_t b = m0 / L;
+  int tt = (int)(m0 - b * L) + tid / WC;  // sequence and position of this thread's row
+  for (int row = tid / WC; row < BM; row += RPI, tt += RPI) {
+    if (m0 + row >= M) break;
+    while (tt >= L) { tt -= L; ++b; }
+    const u32x4 val = *reinterpret_cast<const AG_LDS u32x4 *>(ost + row * WRow + ((chunk ^ (row & KM)) << 4));
+    *reinterpret_cast<u32x4 *>(out_h + ((size_t)b * hp * L + tt) * kDh) = val;
+    if (COMPACT) {
+      const int32_t to = dest[row * NH + (n - n0) / kDh];
+      if (to >= 0) *reinterpret_cast<u32x4 *>((which == 0 ? cp.kc : cp.vc) + (size_t)to * kDh + d) = val;
     }
   }
+}
+
+template <typename CFG, bool COMPACT>
+hipError_t launch_proj(ag_ctx *ctx, hipStream_t s, const void *x, const void *w, int64_t M, int K, int N, int L, int hp, void *out,
+                       const ag_proj_compact &cp) {
+  if (CFG::Lds > 48 * 1024) {
+    static std::atomic<bool> allowed[64];  // said once per device
+    if (!allowed[ctx->device & 63].load(std::memory_order_relaxed)) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_proj_gemm_kernel<CFG, COMPACT>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, CFG::Lds);
+      if (e != hipSuccess) return e;
+      allowed[ctx->device & 63].store(true, std::memory_order_relaxed);
+    }
+  }
+  const int m_tiles = (int)((M + CFG::BM - 1) / CFG::BM), n_tiles = N / CFG::BN;
+  const unsigned blocks = (unsigned)(((int64_t)m_tiles * n_tiles + 7) / 8 * 8);
+  AG_LAUNCH(ag_time_kernel(ctx, AG_K_MHA_PROJ), (ag_proj_gemm_kernel<CFG, COMPACT>), dim3(blocks), dim3(CFG::NT), CFG::Lds, s,
+            (const uint16_t *)x, (const uint16_t *)w, M, K, N, L, hp, (uint16_t *)out, cp, m_tiles, n_tiles);
+  return hipGetLastError();
+}
+
+// The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each was measured to
+// take on this chip with K = 4096 (us; `alone`: a few tiles, `full`: every slot taken -- the chip's clock falls with the
+// number of busy CUs, and two workgroups on one CU share it).
+//   256 x 256: 1.13 PFLOP/s where there are tiles for whole rounds (8192 tokens x 8192 columns: 586 -> 478 us; with
+//              128 x 128 tiles LDS bounds it); one tile takes 78 us.
+//   128 x 128: 0.93 PFLOP/s, but fills the chip from a quarter of the columns x tokens on.
+//   128 x 192: 1536 columns (three tensors of four heads) in whole rounds where 128 x 128 leaves a quarter of the CUs idle.
+//   64 x 64  : few tokens, where one tile's chain of stages is the time: 128 k-steps per barrier (64 to 300 tokens: 40 -> 16 us).
+typedef proj_cfg<256, 256, 2, 4, 32, 4> cfg_256x256;
+typedef proj_cfg<128, 128, 2, 2, 32, 4> cfg_128x128;
+typedef proj_cfg<128, 192, 2, 2, 32, 4> cfg_128x192;
+typedef proj_cfg<64, 64, 2, 2, 128, 4> cfg_64x64;
+
+float proj_time(int64_t M, int N, int bm, int bn, int slots, int num_cu, float alone, float full) {
+  const int64_t tiles = (M + bm - 1) / bm * (N / bn), rounds = tiles / slots, last = tiles - rounds * slots;
+  float t = (float)rounds * full;
+  if (last > 0) {
+    const float per_cu = (float)last / (float)num_cu;  // up to one workgroup per CU, then the second ones
+    if (slots == num_cu) t += alone + (full - alone) * per_cu;
+    else t += per_cu <= 1.f ? alone * (1.f + 0.1f * per_cu) : alone * 1.1f + (full - alone * 1.1f) * (per_cu - 1.f);
+  }
+  return t;
+}
+
+template <bool COMPACT>
+hipError_t launch_proj_any(ag_ctx *ctx, hipStream_t s, const void *x, const void *w, int64_t M, int K, int N, int L, int hp, void *out,
+                           const ag_proj_compact &cp) {
+  const int cu = ctx->num_cu;
+  const float never = 3.0e38f;
+  const float t128 = proj_time(M, N, 128, 128, 2 * cu, cu, 39.f, 73.f);
+  const float t256 = N % 256 == 0 ? proj_time(M, N, 256, 256, cu, cu, 78.f, 120.f) : never;
+  // (a tile that starts inside a head is not made for the compaction's look-up of cache rows)
+  const float t192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, 128, 192, 2 * cu, cu, 49.f, 95.f) : never;
+  const float t64 = K % 128 == 0 ? proj_time(M, N, 64, 64, cu, cu, 15.f, 17.f) : never;
+  if (t64 < t128 && t64 < t256 && t64 < t192) return launch_proj<cfg_64x64, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
+  if (t256 < t128 && t256 < t192) return launch_proj<cfg_256x256, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
+  if constexpr (!COMPACT)
+    if (t192 < t128) return launch_proj<cfg_128x192, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
+  return launch_proj<cfg_128x128, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
 }
 
 }  // namespace
@@ -262,10 +370,7 @@ hipError_t ag_launch_gate_mha(ag_ctx *ctx, hipStream_t s, const void *x, int B, 
   ag_prefill_bf16_plan(ctx->num_cu, B, L, hp, hp, 128, ws, &plan, &part);
   if (!ws.ok) return hipSuccess;  // caller reports AG_EWORKSPACE
 
-  AG_LAUNCH(ag_time_kernel(ctx, AG_K_MHA_PROJ), ag_proj_gemm_kernel<false>,
-            dim3(N / kBNc, (unsigned)((tokens + kBM - 1) / kBM)), dim3(256), 0, s, (const uint16_t *)x,
-            (const uint16_t *)w_qkv, tokens, d_model, N, L, hp, qkv, ag_proj_compact{});
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_proj_any<false>(ctx, s, x, w_qkv, tokens, d_model, N, L, hp, qkv, ag_proj_compact{});
   if (e != hipSuccess) return e;
   // every token is kept (no flags to read): mask words, prefix counts and the launch plan of the attention kernel
   if ((e = ag_launch_flag_scan(ctx, s, nullptr, units, L, words, blk_off, &plan)) != hipSuccess) return e;
@@ -296,8 +401,5 @@ hipError_t ag_launch_project_compact(ag_ctx *ctx, hipStream_t s, const void *x, 
   hipError_t e = ag_launch_flag_scan(ctx, s, flags, units, L, words, blk_off, nullptr);
   if (e != hipSuccess) return e;
   const ag_proj_compact cp{words, blk_off, row_off, (uint16_t *)kc, (uint16_t *)vc, idx, len, ctx->d_err, nw, pos0};
-  AG_LAUNCH(ag_time_kernel(ctx, AG_K_MHA_PROJ), ag_proj_gemm_kernel<true>,
-            dim3(N / kBNc, (unsigned)((tokens + kBM - 1) / kBM)), dim3(256), 0, s, (const uint16_t *)x,
-            (const uint16_t *)w_kv, tokens, d_model, N, L, Hkv, (uint16_t *)kv_out, cp);
-  return hipGetLastError();
+  return launch_proj_any<true>(ctx, s, x, w_kv, tokens, d_model, N, L, Hkv, kv_out, cp);
 }
