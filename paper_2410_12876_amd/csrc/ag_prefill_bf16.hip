@@ -1,7 +1,7 @@
 // Flag-masked causal prefill attention (Eq. 2 under the mask of Eq. 5), bf16, head dimension 128 -- the
 // tuned CDNA4 kernel.  Same formulation as ag_prefill.hip (attention over the compacted rows with a per-query
 // boundary: cnt[j] + 1 rows for a kept token, whose own row is cache row cnt[j]; cnt[j] rows plus its own
-// key/value from the uncompacted tensors, which initialise the online softmax, for an evicted one), built for gfx950:
+// key/value from the uncompacted tensors, which join after the last tile, for an evicted one), built for gfx950:
 //
 //   * K and V tiles (64 cache rows x 256 B) go from global memory straight into LDS (buffer_load ... lds,
 //     no register staging), double-buffered, one workgroup barrier per step.
@@ -43,6 +43,10 @@
 
 namespace {
 
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+
 // GB = query heads of one KV group per workgroup (one per wave).  n_split = chunks per item in the grid,
 // chunk_tiles_dev = key tiles per chunk (device value, NULL without a split); part = partial states
 // [item][chunk][4 waves][66][64] fp32 and tickets = per-item arrival counters (n_split > 1).
@@ -52,7 +56,7 @@ namespace {
 // NW = waves per workgroup: 4 (two workgroups per CU).  (8, one workgroup per CU with twice the queries sharing
 // every K/V tile, also works without the band variant but is slower: the whole CU then moves in step.)
 template <int D, int GB, bool BAND, int NW>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
+__global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void ag_prefill_bf16_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     const uint64_t *__restrict__ words, const int32_t *__restrict__ blk_off, const uint16_t *__restrict__ kc,
     const uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off, int L, int Hq, int Hkv, int nw, int n_hy,
@@ -73,6 +77,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kGroupB];  // [K0][K1][V0][V1], each [row][256 B]
   // BAND: per band tile, the rows whose value row held a NaN or an infinity (see scrub_band_v below)
   __shared__ uint32_t nf_rows[BAND ? 3 : 1][2];
+  __shared__ float own_score[NW * 32];  // per row: the score of the query's own token (a register too many in the tile loop)
 
   const int G = Hq / Hkv;
   const int HB = G / GB;
@@ -124,6 +129,18 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   const int j0 = qtile * BM + (w4 / GB) * 32;
   const int jq = min(j0 + col, L - 1);
 
+  // The query rows need nothing but the head: they are on their way before the scalar inputs arrive (rows past the end: zeros).
+  constexpr int QL = kTileB / NW / kRowB / RPI, QP = 32 / (QL * RPI);  // whole-row loads per staging pass, passes
+  u32x4 sq[QP][QL];
+  {
+    const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(q + ((size_t)(b * Hq + head) * L + j0) * D), 0, j0 < L ? (uint32_t)min(32, L - j0) * kRowB : 0u, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < QP * QL; ++i)
+      sq[i / QL][i % QL] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, lane * 16, i * 1024, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
   // All scalar inputs of the workgroup in one round of loads.  The 32 queries of a wave lie in one 64-token
   // mask word (j0 is a multiple of 32), so one (word, prefix) pair gives every per-query boundary of the wave.
   const uint64_t *wu = words + (size_t)u * nw;
@@ -134,45 +151,52 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   const int pre_w = bo[jw], pre_b = bo[jb >> 6], kept_u = bo[nw];
   const int chunk_tiles = chunk_tiles_dev ? *chunk_tiles_dev : 0x7fffffff / kBN;
   const int64_t ro0 = row_off[u], ro1 = row_off[u + 1];
-  auto cnt_in = [](uint64_t w, int pre, int j) { return pre + __popcll(w & ((1ull << (j & 63)) - 1ull)); };
+  auto cnt_in = [](uint64_t w, int pre, int j) -> int { return pre + (int)__popcll(w & ((1ull << (j & 63)) - 1ull)); };
   const int len_u = (int)min((int64_t)kept_u, ro1 - ro0);
   // A kept token's own key and value are row cnt(j) of the compacted rows, so its visible set is simply the first
   // cnt(j) + 1 of them; only an evicted token (or one whose row did not fit the cache) takes its own k, v from the
-  // uncompacted tensors.  bnd = number of compacted rows query j sees.
+  // uncompacted tensors, after the last tile.  bnd = number of compacted rows query j sees.
   auto in_cache = [&](uint64_t w, int pre, int j) { return ((w >> (j & 63)) & 1ull) != 0 && cnt_in(w, pre, j) < len_u; };
-  auto bnd_in = [&](uint64_t w, int pre, int j) { return cnt_in(w, pre, j) + (in_cache(w, pre, j) ? 1 : 0); };
+  auto bnd_in = [&](uint64_t w, int pre, int j) -> int { return cnt_in(w, pre, j) + (in_cache(w, pre, j) ? 1 : 0); };
   // (all boundaries are clamped to the rows the cache holds: after a capacity overflow the rows that did not fit
   // are simply not there -- their tokens count as evicted -- and nothing past len_u is attended)
   const int cnt_q = min(bnd_in(word_w, pre_w, jq), len_u);
-  const bool own_kv = chunk == 0 && !in_cache(word_w, pre_w, jq);  // this query's diagonal term comes from k, v
-  const int cnt_wave_lo = min(bnd_in(word_w, pre_w, min(j0, L - 1)), len_u);
-  const int cnt_wave_hi = j0 < L ? min(bnd_in(word_w, pre_w, min(j0 + 31, L - 1)), len_u) : 0;
+  const uint32_t own_rows = (uint32_t)__ballot(!in_cache(word_w, pre_w, jq));  // rows of the wave whose own k, v are not in the cache
+  const int cnt_wave_lo = __builtin_amdgcn_readfirstlane(min(bnd_in(word_w, pre_w, min(j0, L - 1)), len_u));
+  const int cnt_wave_hi = __builtin_amdgcn_readfirstlane(j0 < L ? min(bnd_in(word_w, pre_w, min(j0 + 31, L - 1)), len_u) : 0);
   const int cnt_blk = min(bnd_in(word_b, pre_b, jb), len_u);
   const int n_tiles = (cnt_blk + kBN - 1) / kBN;       // key tiles of the item
   const int tile0 = chunk > 0 ? chunk * chunk_tiles : 0;  // this workgroup's chunk: tiles [tile0, tile0 + n_steps)
   if (chunk > 0 && tile0 >= n_tiles) return;           // empty chunk (the whole workgroup leaves)
   const int n_chunks = max(1, (n_tiles + chunk_tiles - 1) / chunk_tiles);
-  // band tiles (chunk 0 only): 64-aligned tiles of original token positions that can hold a key of this
-  // workgroup's queries, i.e. positions [first query - (n_recent - 1), last query - 1]
-  int n_band = 0, band_t0 = 0;
+  // band tiles (chunk 0 only): the original token positions that can be a key of this workgroup's queries,
+  // [first query - (n_recent - 1), last query - 1], 64 at a time from the first
+  int n_band = 0, band_p0 = 0;
   uint64_t bw0 = 0, bw1 = 0, bw2 = 0;  // keep masks of the band tiles
   if (BAND && chunk == 0) {
     const int klo = max(0, qtile * BM - (n_recent - 1)), khi = jb - 1;
     if (khi >= klo) {
-      band_t0 = klo >> 6;
-      n_band = (khi >> 6) - band_t0 + 1;  // <= 3 because n_recent <= 64 and BM <= 128
+      band_p0 = klo;
+      n_band = ((khi - klo) >> 6) + 1;  // <= 3 because n_recent <= 64 and BM <= 128
       // keep bits of the tokens that are among the compacted rows: all kept ones, unless the cache overflowed --
       // a kept token that found no room is not there, so the band must show it like an evicted one
       auto in_cache_bits = [&](int t) {
+        if (t >= nw) return (uint64_t)0;
         uint64_t w = wu[t];
         const int room = len_u - bo[t];
         if (room <= 0) return (uint64_t)0;
         while (__popcll(w) > room) w &= ~(1ull << (63 - __clzll(w)));  // (never entered without an overflow)
         return w;
       };
-      bw0 = in_cache_bits(band_t0);
-      if (n_band > 1) bw1 = in_cache_bits(band_t0 + 1);
-      if (n_band > 2) bw2 = in_cache_bits(band_t0 + 2);
+      const int t0 = klo >> 6, sh = klo & 63;
+      auto join = [&](uint64_t lo, uint64_t hi) { return sh ? (lo >> sh) | (hi << (64 - sh)) : lo; };
+      const uint64_t w0 = in_cache_bits(t0), w1 = in_cache_bits(t0 + 1);
+      bw0 = join(w0, w1);
+      if (n_band > 1) {
+        const uint64_t w2 = in_cache_bits(t0 + 2);
+        bw1 = join(w1, w2);
+        if (n_band > 2) bw2 = join(w2, in_cache_bits(t0 + 3));
+      }
     }
   }
   // steps of this workgroup: the band tiles first, then its chunk of compacted tiles
@@ -206,7 +230,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   const uint32_t ld_base = (uint32_t)(size_t)((AG_LDS uint8_t *)smem) + w4 * RPW * kRowB;
   auto issue_k = [&](int i_step) {  // K of the tile of step i_step -> K buffer i_step & 1
     const bool bnd = BAND && i_step < n_band;
-    const int soff = (bnd ? band_t0 + i_step : tile0 + i_step - n_band) * kTileB;
+    const int soff = bnd ? band_p0 * kRowB + i_step * kTileB : (tile0 + i_step - n_band) * kTileB;
     const __amdgpu_buffer_rsrc_t rsrc = bnd ? kb_rsrc : k_rsrc;
 #pragma unroll
     for (int i = 0; i < LI; ++i) {
@@ -217,7 +241,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   };
   auto issue_v = [&](int i_step) {
     const bool bnd = BAND && i_step < n_band;
-    const int soff = (bnd ? band_t0 + i_step : tile0 + i_step - n_band) * kTileB;
+    const int soff = bnd ? band_p0 * kRowB + i_step * kTileB : (tile0 + i_step - n_band) * kTileB;
     const __amdgpu_buffer_rsrc_t rsrc = bnd ? vb_rsrc : v_rsrc;
 #pragma unroll
     for (int i = 0; i < LI; ++i) {
@@ -226,37 +250,35 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
                    :: "s"(dv), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "memory");
     }
   };
-  if (n_steps > 0) { issue_k(0); issue_v(0); }
-  if (n_steps > 1) issue_k(1);
-
-  // ---- Q fragments (B operand of S^T): lane (query col, half hb), k-step ks: Q[j][16 ks + 8 hb .. +8); for chunk 0
-  // also the query's own key row (same layout) and value row (lane: d = 32 dt + 8 r4 + 4 hb .. +4) ----
-  // A lane needs 16-byte pieces of ITS query's row, so direct loads would touch 64 different cache lines per
-  // instruction (measured: 4.5 us of a workgroup's 7 us start-up).  Instead the wave reads its 32 rows with
-  // whole-line loads (lane -> row 4 j + lane/16, 16-byte chunk lane%16: 1 KiB contiguous per instruction) and turns
-  // them into fragments through a private 4 KiB corner of the V1 tile buffer, 16 rows at a time; V1 is not a
-  // load target before the first step.  Chunks are XOR-swizzled with the row so that both sides are conflict-free.
-  uint4 qf[KS], kself[KS];
-  uint2 vself[DT][4];
+  // ---- the query rows, and for the own tokens their keys ----
+  // As fragments a lane needs 16-byte pieces of ITS query's row, so direct loads would touch 64 different cache lines per
+  // instruction (measured: 4.5 us).  Instead the wave reads its 32 rows with whole-line loads (lane -> row RPI j + lane / CPR,
+  // 16-byte chunk lane % CPR: 1 KiB contiguous per instruction) and turns the queries into fragments through a private 4 KiB
+  // corner of the V1 tile buffer, 16 rows at a time; V1 is not a load target before the first step.  Chunks are XOR-swizzled
+  // with the row so that both sides are conflict-free.  A key row is only read where it is needed (elsewhere the offset lies
+  // past the descriptor's end: no traffic, zeros), and only for the score of the query's own token, which the lanes that hold
+  // the row's pieces add up as they are; the value row is not read before the output is written.
+  // (Keys and values of the own tokens as fragments through the corner, and the state started from them, took 8.6 us of
+  // a workgroup's 27 on average before its first tile in a 4096-token layer; now 5.1.)
+  const int srow = lane / CPR, schunk = lane % CPR;
+  const uint32_t own_bytes = j0 < L ? (uint32_t)min(32, L - j0) * kRowB : 0u;  // the wave's rows that exist
+  constexpr uint32_t kNowhere = 0x40000000u;  // an offset past any descriptor used with it
+  uint4 qf[KS];
   {
-    const int srow = lane / CPR, schunk = lane % CPR;
     constexpr int RP = (kTileB / NW) / kRowB;  // rows per pass: the wave's corner of V1 holds RP whole rows
     constexpr int NP = 32 / RP;                // passes
     constexpr int LP = RP / RPI;               // whole-row loads per pass (RPI rows each)
-    u32x4 sq[NP][LP], sk[NP][LP], sv[NP][LP];
+    const __amdgpu_buffer_rsrc_t kw_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(k + ((size_t)u * L + j0) * D), 0, own_bytes, 0x00020000);
+    u32x4 sk[NP][LP];
 #pragma unroll
     for (int h = 0; h < NP; ++h)
 #pragma unroll
       for (int j = 0; j < LP; ++j) {
-        const int row = min(j0 + RP * h + RPI * j + srow, L - 1);
-        // All three loads are unconditional (conditional ones end up in scratch memory).  A row whose k, v are not
-        // needed -- a kept token, or any row in a later chunk of a split item -- is pointed at the wave's first row
-        // instead, which costs one cache line per wave instead of HBM traffic per row.
-        const int kv_row = (chunk == 0 && !in_cache(word_w, pre_w, row)) ? row : min(j0, L - 1);
-        sq[h][j] = *reinterpret_cast<const u32x4 *>(q + ((size_t)(b * Hq + head) * L + row) * D + 8 * schunk);
-        sk[h][j] = *reinterpret_cast<const u32x4 *>(k + ((size_t)u * L + kv_row) * D + 8 * schunk);
-        sv[h][j] = *reinterpret_cast<const u32x4 *>(v + ((size_t)u * L + kv_row) * D + 8 * schunk);
+        const int row = RP * h + RPI * j + srow;
+        sk[h][j] = __builtin_amdgcn_raw_buffer_load_b128(kw_rsrc, ((own_rows >> row) & 1u) ? row * kRowB + schunk * 16 : kNowhere, 0, 0);
       }
+    if (n_steps > 0) { issue_k(0); issue_v(0); }
+    if (n_steps > 1) issue_k(1);
     AG_LDS uint8_t *stage = (AG_LDS uint8_t *)smem + 3 * kTileB + w4 * (kTileB / NW);
     const int rr = col % RP;  // this lane's row inside a pass
     const int rk = geo::key(rr);
@@ -267,53 +289,44 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    auto put = [&](const u32x4 (&x)[LP]) {
+#pragma unroll
+    for (int h = 0; h < NP; ++h) {
       wave_sync();  // the previous contents have been read
 #pragma unroll
       for (int j = 0; j < LP; ++j) {
-        const int r = RPI * j + srow;
-        *reinterpret_cast<AG_LDS u32x4 *>(stage + r * kRowB + ((schunk ^ geo::key(r)) << 4)) = x[j];
+        const int rw = RPI * j + srow;
+        *reinterpret_cast<AG_LDS u32x4 *>(stage + rw * kRowB + ((schunk ^ geo::key(rw)) << 4)) = sq[h][j];
       }
       wave_sync();  // the rows are there for every lane
-    };
-    auto get4 = [&](int off) {
-      const u32x4 x = *reinterpret_cast<const AG_LDS u32x4 *>(stage + off);
-      return make_uint4(x[0], x[1], x[2], x[3]);
-    };
+      if ((col / RP) == h) {
 #pragma unroll
-    for (int h = 0; h < NP; ++h) {
-      const bool mine = (col / RP) == h;
-      put(sq[h]);
-      if (mine) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          qf[ks] = get4(rr * kRowB + (((2 * ks + hb) ^ rk) << 4));
-      }
-      if (chunk == 0) {
-        put(sk[h]);
-        if (mine) {
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-            kself[ks] = get4(rr * kRowB + (((2 * ks + hb) ^ rk) << 4));
-        }
-        put(sv[h]);
-        if (mine) {
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-            {
-              const u32x2 x = *reinterpret_cast<const AG_LDS u32x2 *>(stage + rr * kRowB + (((4 * dt + r4) ^ rk) << 4) + 8 * hb);
-              vself[dt][r4] = make_uint2(x[0], x[1]);
-            }
+        for (int ks = 0; ks < KS; ++ks) {
+          const u32x4 x = *reinterpret_cast<const AG_LDS u32x4 *>(stage + rr * kRowB + (((2 * ks + hb) ^ rk) << 4));
+          qf[ks] = make_uint4(x[0], x[1], x[2], x[3]);
         }
       }
     }
+    // own scores: a row's CPR lanes each multiply their piece, then add up; lane schunk == i keeps row group i's
+    float mine = 0.f;
+#pragma unroll
+    for (int h = 0; h < NP; ++h)
+#pragma unroll
+      for (int j = 0; j < LP; ++j) {
+        float d = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)sq[h][j][e]), __builtin_bit_cast(bf16x2, (uint32_t)sk[h][j][e]), d, false);
+        d += dpp_move<0xB1>(d);                  // lane ^ 1
+        d += dpp_move<0x4E>(d);                  // lane ^ 2
+        d += dpp_move<0x141>(d);                 // the other quad of the 8 lanes
+        if (CPR == 16) d += dpp_move<0x140>(d);  // the other 8 of the 16
+        mine = schunk == LP * h + j ? d : mine;
+      }
+    if (schunk < NP * LP) own_score[w4 * 32 + RPI * schunk + srow] = mine * qscale;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the corner is read out before anyone may load V(1) over it
   }
-  __builtin_amdgcn_sched_barrier(0);  // keep the loads above ahead of the arithmetic below
 
-  // ---- initial online-softmax state: chunk 0 starts from the query's own token, the others from nothing ----
+  // ---- initial online-softmax state: nothing seen ----
   float m_run = kEmptyMax;  // reference maximum of the exponentials, log2 units
   float l_run = 0.f;        // each half (hb) of a column holds part of the row sum
   f32x16 acc_o[DT];         // O^T: acc_o[dt][r] = (d = 32 dt + 8 (r/4) + 4 hb + r%4, query col)
@@ -321,32 +334,6 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_o[dt][r] = 0.f;
-  if (chunk == 0) {
-    float s_self = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const uint32_t qa[4] = {qf[ks].x, qf[ks].y, qf[ks].z, qf[ks].w};
-      const uint32_t ka[4] = {kself[ks].x, kself[ks].y, kself[ks].z, kself[ks].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s_self = fmaf(__uint_as_float(qa[e] << 16), __uint_as_float(ka[e] << 16), s_self);
-        s_self = fmaf(__uint_as_float(qa[e] & 0xffff0000u), __uint_as_float(ka[e] & 0xffff0000u), s_self);
-      }
-    }
-    s_self += __shfl_xor(s_self, 32, 64);
-    // (selects, not arithmetic: what was loaded for a query that does not use it may be anything)
-    m_run = own_kv ? s_self * qscale : kEmptyMax;
-    l_run = own_kv && hb == 0 ? 1.f : 0.f;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        acc_o[dt][4 * r4 + 0] = own_kv ? __uint_as_float(vself[dt][r4].x << 16) : 0.f;
-        acc_o[dt][4 * r4 + 1] = own_kv ? __uint_as_float(vself[dt][r4].x & 0xffff0000u) : 0.f;
-        acc_o[dt][4 * r4 + 2] = own_kv ? __uint_as_float(vself[dt][r4].y << 16) : 0.f;
-        acc_o[dt][4 * r4 + 3] = own_kv ? __uint_as_float(vself[dt][r4].y & 0xffff0000u) : 0.f;
-      }
-  }
 
   // ---- loop-invariant LDS byte offsets of this lane's fragments ----
   // K fragment (A of S^T): row 32 sub + col, logical chunk 2 ks + hb
@@ -455,10 +442,10 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
         }
     }
   };
-  // band tile of step i: key position t = 64 (band_t0 + i) + kk is visible to query jq iff it lies among the
+  // band tile of step i: key position t = band_p0 + 64 i + kk is visible to query jq iff it lies among the
   // n_recent - 1 positions before jq and its keep bit is clear (kept tokens are among the compacted rows)
   auto band_mask = [&](int i, f32x16 (&acc)[2]) {
-    const int r0 = (band_t0 + i) * kBN;
+    const int r0 = band_p0 + i * kBN;
     const uint64_t bword = i == 0 ? bw0 : (i == 1 ? bw1 : bw2);
 #pragma unroll
     for (int sub = 0; sub < 2; ++sub) {
@@ -477,7 +464,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
   // does step i hold a key that some query of this wave may see?  (wave-uniform)
   auto vis = [&](int i) -> bool {
     if (BAND && i < n_band) {
-      const int r0 = (band_t0 + i) * kBN;
+      const int r0 = band_p0 + i * kBN;
       return j0 < L && r0 <= j0 + 30 && r0 + kBN - 1 >= j0 - (n_recent - 1);
     }
     return (tile0 + i - n_band) * kBN < cnt_wave_hi;
@@ -535,14 +522,28 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
       }
     }
   };
-  // keys of band tile i (bit kk = position 64 (band_t0 + i) + kk) that query jq sees through its window
+  // keys of band tile i (bit kk = position band_p0 + 64 i + kk) that query jq sees through its window
   auto band_visible = [&](int i) -> uint64_t {
-    const int r0 = (band_t0 + i) * kBN;
+    const int r0 = band_p0 + i * kBN;
     const uint64_t bword = i == 0 ? bw0 : (i == 1 ? bw1 : bw2);
     const int lo = max(0, jq - (n_recent - 1) - r0), hi = min(kBN - 1, jq - 1 - r0);
     if (hi < lo) return 0ull;
     const uint64_t win = (hi - lo == 63 ? ~0ull : ((1ull << (hi - lo + 1)) - 1ull)) << lo;
     return win & ~bword;
+  };
+  // The value rows of the wave's own tokens (zeros for the others: an offset past the descriptor's end) -> the wave's
+  // quarter of the K buffers, chunks XOR-swizzled with the row.
+  auto issue_own_v = [&] {
+    const __amdgpu_buffer_rsrc_t vw_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(v + ((size_t)u * L + j0) * D), 0, own_bytes, 0x00020000);
+    int lane_e = lane;  // (laundered: computed here, not kept in registers across the tile loop)
+    asm volatile("" : "+v"(lane_e));
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+      const int row = RPI * i + lane_e / CPR;
+      const uint32_t off = ((own_rows >> row) & 1u) ? (uint32_t)(row * kRowB + (((lane_e % CPR) ^ geo::key(row)) << 4)) : kNowhere;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"((uint32_t)(size_t)((AG_LDS uint8_t *)smem) + w4 * 32 * kRowB + i * 1024), "v"(off), "s"(vw_rsrc) : "memory");
+    }
   };
   // One pipeline step.  cur holds S^T of this group's tile of step i; nxt receives that of step i + 1.
   // At the top (after the barrier) K(i+1) and V(i) are resident; the step then requests K(i+2) into the K
@@ -553,6 +554,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
     __syncthreads();                                  // ... and everyone's; step i-1 is fully consumed
     if (i + 2 < n_steps) issue_k(i + 2);
     if (i + 1 < n_steps) issue_v(i + 1);
+    else issue_own_v();  // the K buffers are both free in the last step
     const int c0 = (tile0 + i - n_band) * kBN;
     const bool vis_cur = vis(i);                                                 // wave-uniform
     const bool vis_nxt = i + 1 < n_steps && vis(i + 1);                          // wave-uniform
@@ -590,10 +592,24 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
     }
   };
   f32x16 acc_a[2], acc_b[2];
+  if (n_steps == 0) issue_own_v();
   if (n_steps > 0) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (n_steps > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LI) : "memory");  // K(0); V(0) and K(1) may be on their way
+    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LI) : "memory");
     __syncthreads();
-    if (vis(0)) s_tile(0, acc_a);
+    if (vis(0)) {
+      s_tile(0, acc_a);
+      // the first reference is the first tile's own maximum, so that its weights are formed once
+      if (BAND && n_band > 0) band_mask(0, acc_a);
+      else mask_tile(tile0 * kBN, acc_a);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc_a[sub][r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * qscale;
+      m_run = mx > m_run ? mx : m_run;
+    }
   }
   for (int i = 0; i < n_steps; i += 2) {
     step(i, acc_a, acc_b);
@@ -618,12 +634,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
     __hip_atomic_store(&mine[16 * DT * 64], m_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&mine[(16 * DT + 1) * 64], l_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();  // every wave's state is out, and nobody reads the tile buffers any more
-    int *last = reinterpret_cast<int *>(smem);
+    __syncthreads();  // every wave's state is out
+    __shared__ int last;
     if (tid == 0)
-      *last = __hip_atomic_fetch_add(&tickets[item], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
+      last = __hip_atomic_fetch_add(&tickets[item], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
     __syncthreads();
-    if (!*last) return;
+    if (!last) return;
     auto peek = [](const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
     float m = m_run;
     for (int c = 0; c < n_chunks; ++c)
@@ -632,12 +648,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
     // arrives last: two chunks are one commutative addition of this chunk's registers and the other's state; more
     // are added in chunk order starting from zero, this chunk's own state read back like the others'.
     if (n_chunks == 2) {
-      const float f_own = __builtin_amdgcn_exp2f(m_run - m);
-      l_run = mul_round(l_run, f_own);
+      const float f_mine = __builtin_amdgcn_exp2f(m_run - m);
+      l_run = mul_round(l_run, f_mine);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round(acc_o[dt][r], f_own);
+        for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round(acc_o[dt][r], f_mine);
     } else {
       l_run = 0.f;
 #pragma unroll
@@ -655,29 +671,39 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void ag_prefill_bf16_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round_add(peek(&sc[(16 * dt + r) * 64]), f, acc_o[dt][r]);
     }
+    m_run = m;
   }
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const float inv = 1.f / l_tot;
-  // Output rows leave as whole 256-byte rows.  A lane owns one query and 4-element pieces of its row, so direct
-  // stores would be 16 instructions of 64 scattered 8-byte pieces each; instead the wave lays its 32 rows out in
-  // 8 KiB of the (now unused) tile buffers, 16-byte chunks XOR-swizzled with the row, and stores them with 8
-  // instructions of 4 whole rows each (lane -> row 4 i + lane / 16, chunk lane % 16).
-  __syncthreads();  // every wave is done with the K/V tiles
+  // ---- the query's own token, if it is not among the compacted rows, and the division ----
+  // Output rows leave as whole rows.  A lane owns one query and 4-element pieces of its row, so direct stores would be 16
+  // instructions of 64 scattered 8-byte pieces each; instead the lane's pieces replace the own value row's in the wave's
+  // quarter of the K buffers, and leave with 1 KiB per instruction (lane -> row RPI i + lane / CPR, chunk lane % CPR).
   {
-    AG_LDS uint8_t *ost = (AG_LDS uint8_t *)smem + w4 * (32 * kRowB);
     // (the lane number is laundered through an empty asm so that the addresses below are computed here, from one
     // register, instead of being shared with the look-alike ones of the query staging and kept alive -- in spill
     // slots, for the recent-token variant -- across the whole tile loop)
     int lane_e = lane;
     asm volatile("" : "+v"(lane_e));
     const int col_e = lane_e & 31, hb_e = lane_e >> 5;
+    const bool own = (own_rows >> col_e) & 1u;
+    const float s_own = own_score[w4 * 32 + col_e];
+    const float m_all = own ? fmaxf(m_run, s_own) : m_run;
+    const float f_run = __builtin_amdgcn_exp2f(m_run - m_all), f_own = own ? __builtin_amdgcn_exp2f(s_own - m_all) : 0.f;
+    const float inv = 1.f / ((l_run + __shfl_xor(l_run, 32, 64)) * f_run + f_own);
+    const float g_run = f_run * inv, g_own = own ? f_own * inv : 0.f;  // out = g_run O + g_own v
+    AG_LDS uint8_t *ost = (AG_LDS uint8_t *)smem + w4 * (32 * kRowB);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the own value rows are there
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
-        const u32x2 o = {pack2(acc_o[dt][4 * r4 + 0] * inv, acc_o[dt][4 * r4 + 1] * inv),
-                         pack2(acc_o[dt][4 * r4 + 2] * inv, acc_o[dt][4 * r4 + 3] * inv)};
-        *reinterpret_cast<AG_LDS u32x2 *>(ost + col_e * kRowB + (((4 * dt + r4) ^ geo::key(col_e)) << 4) + 8 * hb_e) = o;
+        AG_LDS u32x2 *piece = reinterpret_cast<AG_LDS u32x2 *>(ost + col_e * kRowB + (((4 * dt + r4) ^ geo::key(col_e)) << 4) + 8 * hb_e);
+        const u32x2 w = *piece;
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o[e] = fmaf(g_own, __uint_as_float((e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16), acc_o[dt][4 * r4 + e] * g_run);
+        const u32x2 x = {pack2(o[0], o[1]), pack2(o[2], o[3])};
+        *piece = x;
       }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // one lane's store is another lane's load
     __builtin_amdgcn_wave_barrier();
