@@ -123,11 +123,10 @@ __device__ __forceinline__ float kg_sum(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// What a tile reads: rows row0 .. row0 + 31 of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
+// What a tile reads: 32 rows of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
 struct dec_tile {
-  const void *k, *v;  // first row of the array the tile belongs to
-  uint32_t bytes;     // cache rows: size of the array (rows past its end read as zeros)
-  int row0;
+  const void *k, *v;  // the tile's first row (64-bit addresses: a unit's rows may span more than the 4 GiB a descriptor can)
+  uint32_t bytes;     // cache rows: size of the rows that exist (the others read as zeros)
   uint32_t vis;
   bool ring;          // ring slots: rows whose bit is clear are not even read (they may hold anything)
 };
@@ -176,11 +175,10 @@ template <int D, int G> struct wave_bf16 {
                             ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(at >> 32)) << 32);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)base_s, 0, __builtin_amdgcn_readfirstlane(t.bytes), 0x00020000);
-    const int soff = __builtin_amdgcn_readfirstlane(t.row0 * kRowB);
 #pragma unroll
     for (int i = 0; i < NL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off(i)), "s"(rsrc), "s"(soff + i * RPI * kRowB) : "memory");
+                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off(i)), "s"(rsrc), "s"(i * RPI * kRowB) : "memory");
   }
   __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, lds_addr); }
   __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, lds_addr + kTileRows * kRowB); }
@@ -194,7 +192,7 @@ template <int D, int G> struct wave_bf16 {
       for (int kv = 0; kv < 2; ++kv) {
         x[kv][i] = make_uint4(0, 0, 0, 0);
         if (see)
-          x[kv][i] = chunk16(static_cast<const uint8_t *>(kv ? t.v : t.k) + (size_t)(t.row0 + i * RPI) * kRowB + ld_off(i), loose);
+          x[kv][i] = chunk16(static_cast<const uint8_t *>(kv ? t.v : t.k) + i * RPI * kRowB + ld_off(i), loose);
       }
     }
 #pragma unroll
@@ -389,8 +387,8 @@ template <int D, int G> struct wave_f32 {
     }
     for (int i = first; i < last; i += step) {
       const dec_tile t = get(i);
-      const nt_f32x4 *K = reinterpret_cast<const nt_f32x4 *>(t.k) + (size_t)t.row0 * LPR + seg;
-      const nt_f32x4 *V = reinterpret_cast<const nt_f32x4 *>(t.v) + (size_t)t.row0 * LPR + seg;
+      const nt_f32x4 *K = reinterpret_cast<const nt_f32x4 *>(t.k) + seg;
+      const nt_f32x4 *V = reinterpret_cast<const nt_f32x4 *>(t.v) + seg;
       for (int it0 = 0; it0 < NIT; it0 += UN) {
         nt_f32x4 kk[UN], vv[UN];
         bool ok[UN];
@@ -724,13 +722,14 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
     if (t0 + wt < t1 || own)
       wv.run(static_cast<const T *>(a.q) + (size_t)u * G * D, t0 + wt, t1, team, a.qscale, own, kn, vn, a.loose, [&](int i) {
         if (i >= extra) {
-          const int r = (i - extra) * kTileRows;
-          return dec_tile{K, V, (uint32_t)n * (uint32_t)(D * sizeof(T)), r,
-                          n - r >= 32 ? 0xffffffffu : (1u << max(0, n - r)) - 1u, false};
+          const int64_t r = (int64_t)(i - extra) * kTileRows;
+          const int have = max(0, min(kTileRows, (int)(n - r)));
+          return dec_tile{K + r * D, V + r * D, (uint32_t)have * (uint32_t)(D * sizeof(T)),
+                          have == kTileRows ? 0xffffffffu : (1u << have) - 1u, false};
         }
-        const size_t ring0 = (size_t)u * a.ring.n * D;
+        const size_t ring0 = ((size_t)u * a.ring.n + (size_t)i * kTileRows) * D;
         return dec_tile{static_cast<const T *>(a.ring.k) + ring0, static_cast<const T *>(a.ring.v) + ring0, 0u,
-                        i * kTileRows, (uint32_t)(ring_vis >> (32 * i)), true};
+                        (uint32_t)(ring_vis >> (32 * i)), true};
       });
     wv.leave((AG_LDS float *)my_lds);
     __syncthreads();

@@ -61,3 +61,26 @@ def test_decode_takes_new_rows_at_any_even_address():
         assert np.array_equal(gk[a:a + n], ref.k[a:a + n])
     ctx.poll_error()
     ctx.close()
+
+
+def test_decode_unit_of_more_than_four_gib():
+    """A unit whose K (and V) rows span more than 32 bits of bytes: the only keys that matter lie past that point.  Every
+    cached key is 0 except two that draw all the weight, so the output is the mean of their values (to the n exp(-60) of the rest)."""
+    n, D = (1 << 24) + 70, 128
+    ctx = make_ctx(1, 1, 1, 1, D, ag.AG_BF16, cache_rows=n + 1)
+    k, v = (torch.zeros(n + 1, D, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    hot = [(1 << 24) + 5, n - 1]
+    for i, r in enumerate(hot):
+        k[r, 0] = 1.0
+        v[r] = 1.0 + i
+    cache = ag.KVCache(k, v, torch.zeros(n + 1, dtype=torch.int32, device=DEV), torch.tensor([0, n + 1], device=DEV),
+                       torch.tensor([n], dtype=torch.int32, device=DEV), 1, 1, D, total_rows=n + 1)
+    q = torch.zeros(1, 1, D, dtype=torch.bfloat16, device=DEV)
+    q[..., 0] = 60.0
+    new = torch.zeros(1, 1, D, dtype=torch.bfloat16, device=DEV)
+    out = torch.empty_like(q)
+    ag.ag_decode_attn(ctx, q, new, new, None, n, 1.0, cache, out)
+    assert torch.all(out == 1.5), out
+    assert int(cache.len[0]) == n + 1
+    ctx.poll_error()
+    ctx.close()
