@@ -31,8 +31,8 @@
 //     (measured: workgroup i runs on XCD i % 8, engine (i / 8) % 4), so the index -> (head, query tile) map
 //     decides both L2 locality and balance.  All tiles of one head are given to one XCD (its K/V stay in that
 //     XCD's L2), longest first; the flag scan's last workgroup first deals the heads to the XCDs in
-//     snake order of their kept-row counts, and the heads of an XCD rotate over its engines from one query tile
-//     to the next, so every engine gets about the same number of key tiles although heads keep 20 % to 90 %.
+//     snake order of their kept-row counts, and the heads of an XCD and their chunks rotate over its engines from
+//     query tile to query tile, so every engine gets about the same number of key tiles although heads keep 20 % to 90 %.
 #include <stdlib.h>
 #include <string.h>
 
@@ -90,18 +90,23 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   // The first n_sp rows of query tiles (the longest) have n_split workgroups per item, one per key chunk; a shorter
   // row cannot hold an item of more than one chunk (a chunk is never shorter than max_tiles / n_split tiles) and has
   // one workgroup per item.
-  const int per_qt = n_hy * n_split;
-  const int split_blocks = n_sp * per_qt;
-  int rem, chunk, qt_idx;
-  if ((int)blockIdx.x < split_blocks) {
-    rem = blockIdx.x % per_qt;
+  // Position pos of a row goes to XCD pos % 8 and, inside it, to a shader engine that follows from the place of its group
+  // of 8 in the grid, (i / 8) % 4.  Where a row's groups -- n_hy / 8 heads times its chunks -- are 2, 4, ... an engine would
+  // get the same group of every row: only second chunks, most of them empty, or always the head that keeps most (16 groups
+  // of 4 heads x 1501 tokens: the first chunks, nearly all of the work, on two of the four engines; 50 us instead of
+  // 35).  So the groups of a row are rotated, by one every second row: for any number of groups each engine then
+  // gets every group equally often (counted for 1 to 32).
+  const int split_blocks = n_sp * n_hy * n_split;
+  const bool in_split = (int)blockIdx.x < split_blocks;
+  const int i_part = in_split ? (int)blockIdx.x : (int)blockIdx.x - split_blocks;
+  const int per_qt = in_split ? n_hy * n_split : n_hy;
+  const int row = i_part / per_qt;
+  int qt_idx = in_split ? row : n_sp + row;
+  int rem = i_part - row * per_qt, chunk = 0;
+  if ((n_hy & 7) == 0 && !head_major) rem = (rem + 8 * (qt_idx >> 1)) % per_qt;
+  if (in_split) {
     chunk = rem / n_hy;
-    qt_idx = blockIdx.x / per_qt;
-  } else {
-    const int r2 = blockIdx.x - split_blocks;
-    rem = r2 % n_hy;
-    chunk = 0;
-    qt_idx = n_sp + r2 / n_hy;
+    rem -= chunk * n_hy;
   }
   if (head_major) {
     // Many heads: the resident workgroups should cover few of them, or a head's K/V rows leave the L2 between
@@ -113,15 +118,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     if (rem >= n_hy) return;  // the grid is rounded up to whole groups of 8 heads
   }
   const int qtile = n_qt - 1 - qt_idx;  // longest rows first
-  // Position pos of a row goes to XCD pos % 8 and, inside it, to shader engine (pos / 8) % 4: both fixed for all
-  // rows.  order[] gives each XCD its heads; rotating them over the XCD's positions from row to row lets every
-  // shader engine see all of them, instead of one engine being stuck with the head that keeps most.
-  const int pos = rem % n_hy;
-  int hy = pos;
-  if (order && !head_major) {
-    const int n_slot = n_hy >> 3;
-    hy = order[(((pos >> 3) + qt_idx) % n_slot) * 8 + (pos & 7)];
-  }
+  const int hy = order && !head_major ? order[rem] : rem;  // order[] gives each XCD its heads
   const int u = hy / HB;
   const int hblk = hy - u * HB;
   const int b = u / Hkv, g = u - b * Hkv;
