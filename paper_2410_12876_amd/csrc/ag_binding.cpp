@@ -68,6 +68,12 @@ int64_t dim(const at::Tensor &t, int want, int i) {
   return t.size(i);
 }
 
+// A size of a tensor of which nothing else is looked at: it may have any number of dimensions beyond that one.
+int64_t size_of(const at::Tensor &t, int i) {
+  if (t.dim() <= i) fail(PyExc_IndexError, "a tensor argument has too few dimensions");
+  return t.size(i);
+}
+
 // The struct behind a ctypes structure (None: NULL).  The caller holds a reference to it for the length of the call.
 template <typename T> T *struct_of(PyObject *o) {
   if (o == Py_None) return nullptr;
@@ -119,7 +125,7 @@ template <typename F> PyObject *call(F &&f) {
 // feat, w_gate, bias, tau, n_sink, logits_out, flags_out
 AG_BINDING(gate, 7) {
   const at::Tensor &x = tensor(a[0]), &w = tensor(a[1]);
-  const int B = dim(x, 3, 0), L = dim(x, 3, 1), d = dim(x, 3, 2), H = dim(w, 2, 1), n_sink = int_of(a[4]);
+  const int B = dim(x, 3, 0), L = dim(x, 3, 1), d = dim(x, 3, 2), H = size_of(w, 1), n_sink = int_of(a[4]);
   const ag_dtype dt = dtype_of(x);
   const void *xp = ptr(a[0]), *wp = ptr(a[1]);
   const float *bias = ptr_as<float>(a[2]), tau = float_of(a[3]);
@@ -131,7 +137,7 @@ AG_BINDING(gate, 7) {
 // h, norm_w, eps, w_gate, bias, tau, n_sink, x_out, logits_out, flags_out
 AG_BINDING(rmsnorm_gate, 10) {
   const at::Tensor &h = tensor(a[0]), &w = tensor(a[3]);
-  const int B = dim(h, 3, 0), L = dim(h, 3, 1), d = dim(h, 3, 2), H = dim(w, 2, 1), n_sink = int_of(a[6]);
+  const int B = dim(h, 3, 0), L = dim(h, 3, 1), d = dim(h, 3, 2), H = size_of(w, 1), n_sink = int_of(a[6]);
   const ag_dtype dt = dtype_of(h);
   const void *hp = ptr(a[0]), *g = ptr(a[1]), *wp = ptr(a[3]);
   const float eps = float_of(a[2]), *bias = ptr_as<float>(a[4]), tau = float_of(a[5]);
@@ -143,7 +149,7 @@ AG_BINDING(rmsnorm_gate, 10) {
 
 // k, v, flags, pos0, cache
 AG_BINDING(compact_kv, 5) {
-  const int L = dim(tensor(a[0]), 4, 2), pos0 = int_of(a[3]);
+  const int L = size_of(tensor(a[0]), 2), pos0 = int_of(a[3]);
   const void *k = ptr(a[0]), *v = ptr(a[1]);
   const uint8_t *f = ptr_as<uint8_t>(a[2]);
   ag_kv_cache *c = struct_of<ag_kv_cache>(a[4]);
@@ -175,7 +181,7 @@ AG_BINDING(project_compact_kv, 6) {
 // q, k, v, flags, scale, cache, n_recent, out
 AG_BINDING(prefill_attn, 8) {
   const at::Tensor &q = tensor(a[0]);
-  const int B = dim(q, 4, 0), Hq = dim(q, 4, 1), L = dim(q, 4, 2), D = dim(q, 4, 3), Hkv = dim(tensor(a[1]), 4, 1), n = int_of(a[6]);
+  const int B = dim(q, 4, 0), Hq = dim(q, 4, 1), L = dim(q, 4, 2), D = dim(q, 4, 3), Hkv = size_of(tensor(a[1]), 1), n = int_of(a[6]);
   const ag_dtype dt = dtype_of(q);
   const void *qp = ptr(a[0]), *k = ptr(a[1]), *v = ptr(a[2]);
   const uint8_t *f = ptr_as<uint8_t>(a[3]);
@@ -188,7 +194,7 @@ AG_BINDING(prefill_attn, 8) {
 // q, k, v, flags, scale, pos0, cache, n_recent, out
 AG_BINDING(compact_prefill_attn, 9) {
   const at::Tensor &q = tensor(a[0]);
-  const int B = dim(q, 4, 0), Hq = dim(q, 4, 1), L = dim(q, 4, 2), D = dim(q, 4, 3), Hkv = dim(tensor(a[1]), 4, 1);
+  const int B = dim(q, 4, 0), Hq = dim(q, 4, 1), L = dim(q, 4, 2), D = dim(q, 4, 3), Hkv = size_of(tensor(a[1]), 1);
   const int pos0 = int_of(a[5]), n = int_of(a[7]);
   const ag_dtype dt = dtype_of(q);
   const void *qp = ptr(a[0]), *k = ptr(a[1]), *v = ptr(a[2]);
@@ -202,8 +208,7 @@ AG_BINDING(compact_prefill_attn, 9) {
 // q, k_new, v_new, new_flags, pos, scale, cache, ring, out
 AG_BINDING(decode_attn, 9) {
   const at::Tensor &q = tensor(a[0]);
-  if (q.dim() < 2) fail(PyExc_ValueError, "q has the wrong number of dimensions");
-  const int Hq = q.size(1), pos = int_of(a[4]);
+  const int Hq = size_of(q, 1), pos = int_of(a[4]);
   const void *qp = ptr(a[0]), *k = ptr(a[1]), *v = ptr(a[2]);
   const uint8_t *f = ptr_as<uint8_t>(a[3]);
   const float scale = float_of(a[5]);
@@ -216,8 +221,7 @@ AG_BINDING(decode_attn, 9) {
 // q, k_new, v_new, new_flags, pos, scale, cache, out
 AG_BINDING(decode_attn_static, 8) {
   const at::Tensor &q = tensor(a[0]);
-  if (q.dim() < 2) fail(PyExc_ValueError, "q has the wrong number of dimensions");
-  const int Hq = q.size(1), pos = int_of(a[4]);
+  const int Hq = size_of(q, 1), pos = int_of(a[4]);
   const void *qp = ptr(a[0]), *k = ptr(a[1]), *v = ptr(a[2]);
   const uint8_t *f = ptr_as<uint8_t>(a[3]);
   const float scale = float_of(a[5]);
@@ -240,7 +244,7 @@ AG_BINDING(recent_fill, 5) {
 // x, w_qkv, h_prime, d_prime, w_o, bias, tau, n_sink, logits_out, flags_out
 AG_BINDING(gate_mha, 10) {
   const at::Tensor &x = tensor(a[0]), &wo = tensor(a[4]);
-  const int B = dim(x, 3, 0), L = dim(x, 3, 1), d = dim(x, 3, 2), H = dim(wo, 2, 1);
+  const int B = dim(x, 3, 0), L = dim(x, 3, 1), d = dim(x, 3, 2), H = size_of(wo, 1);
   const int hp = int_of(a[2]), dp = int_of(a[3]), n_sink = int_of(a[7]);
   const ag_dtype dt = dtype_of(x);
   const void *xp = ptr(a[0]), *w = ptr(a[1]), *wop = ptr(a[4]);

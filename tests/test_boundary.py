@@ -122,6 +122,21 @@ def test_error_paths_without_device(lib):
     ctx.close()
 
 
+def test_a_tensor_that_only_gives_one_size_may_have_other_dimensions(lib):
+    # such calls reach the library (and end at the missing device); too few dimensions are an error of the binding
+    ctx = ag.Context(device=-1, workspace=1 << 20)
+    q, k, f = torch.zeros(1, 4, 8, 64), torch.zeros(1, 2, 8, 64), torch.zeros(1, 2, 8, dtype=torch.uint8)
+    x, w, cache = torch.zeros(1, 8, 64), torch.zeros(64, 2), make_cache()
+    flat, rows = k.view(1, 2, -1), k.view(1, 2, 8, 8, 8)
+    expect(ag.AG_EHIP, ag.ag_prefill_attn, ctx, q, flat, flat, f, 0.125, cache, q.clone(), stream=0)
+    expect(ag.AG_EHIP, ag.ag_compact_prefill_attn, ctx, q, flat, flat, f, 0.125, 0, cache, q.clone(), stream=0)
+    expect(ag.AG_EHIP, ag.ag_compact_kv, ctx, rows, rows, f, 0, cache, stream=0)
+    expect(ag.AG_EHIP, ag.ag_gate, ctx, x, w.view(64, 2, 1), torch.zeros(2), 0.5, 0, None, f, stream=0)
+    with pytest.raises(IndexError):
+        ag.ag_gate(ctx, x, w.view(-1), torch.zeros(2), 0.5, 0, None, f, stream=0)
+    ctx.close()
+
+
 def test_workspace_too_small_is_reported(lib):
     ctx = ag.Context(device=-1, workspace=1024)
     q = torch.zeros(1, 4, 256, 64)
