@@ -190,8 +190,8 @@ def decode_leg(args, torch, ag, W):
     Three passes from the same starting lengths: (1) eager launches, no instrumentation: wall clock; (2) the same
     steps captured once into ONE HIP graph (every step's position and inputs are baked into its nodes) and replayed:
     wall clock -- the graph's result is first checked against the eager pass bit for bit; (3) eager with the library's
-    per-launch events: kernel durations.  The headline of the leg is the whole step (both kernels and the gaps
-    between them) of the faster of (1) and (2); the streaming kernel alone is reported beside it."""
+    per-launch events: kernel durations.  The headline of the leg is the whole step (gaps included) of the
+    faster of (1) and (2); the kernel alone is reported beside it (decode_merge times the same launch)."""
     steps, warm = args.decode_steps, min(args.warmup, 8)
     wl = W.config3(B=args.decode_batch, steps=steps + warm)
     B, Hq, Hkv, D = wl.B, wl.Hq, wl.Hkv, wl.D
@@ -279,7 +279,7 @@ def decode_leg(args, torch, ag, W):
     med = lambda xs: sorted(xs)[len(xs) // 2]
     step_ms = best / steps * 1e3
     res = {
-        "metric": "decode attention HBM GB/s, whole step (both kernels, gaps included)",
+        "metric": "decode attention HBM GB/s, whole step (gaps included)",
         "value": bytes_per_step / (step_ms * 1e-3) / 1e9, "unit": "GB/s",
         "steps": steps, "ms_per_step": step_ms, "launch": "one hip graph of all steps" if use_graph else "eager",
         "ms_per_step_eager": {"min": min(eager_s) / steps * 1e3, "median": med(eager_s) / steps * 1e3,
@@ -288,7 +288,7 @@ def decode_leg(args, torch, ag, W):
                                                            "median": med(graph_s) / steps * 1e3,
                                                            "max": max(graph_s) / steps * 1e3},
         "kernel_ms": {"decode_partial": part_ms, "decode_merge": merge_ms},
-        "roofline": {"kernel": "ag_decode_partial_kernel<bf16,128,1>", "bound": "hbm", "achieved": ach,
+        "roofline": {"kernel": "ag_decode_kernel<bf16,128,1>", "bound": "hbm", "achieved": ach,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
                      "frac_step": bytes_per_step / (step_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "traffic": TRAFFIC_BYTES.get(("decode", B, steps)),
@@ -621,8 +621,8 @@ def cpu_baseline(wl, W):
 # profiles/bench_cfg2_prefill_cfg3_decode_hbm_traffic.md (2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE, in KiB, the
 # factors calibrated on the 1 GiB copy kernel); they hold for the default workloads only.
 TRAFFIC_BYTES = {
-    ("prefill", 4096): int((2.0 * 66377 + 39503) * 1024),
-    ("decode", 32, 256): int((2.0 * 576164 + 10405) * 1024),
+    ("prefill", 4096): int((2.0 * 65671 + 39503) * 1024),
+    ("decode", 32, 256): int((2.0 * 575995 + 1150) * 1024),
 }
 
 

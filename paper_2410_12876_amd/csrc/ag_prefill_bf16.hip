@@ -13,8 +13,8 @@
 //     head-dim column, which is the A-operand layout of O^T += V^T . P^T.
 //   * A lane owns one query: S^T = K . Q^T and O^T = V^T . P^T on v_mfma_f32_32x32x16_bf16, P packed with
 //     v_cvt_pk_bf16_f32 straight from the S^T accumulators, row max / sum / rescale as per-lane scalars.
-//   * The reference maximum is only raised (and O rescaled) when a row's new maximum exceeds it by more than
-//     2^8; otherwise the stale maximum is kept, which is exact after the final division by the row sum.
+//   * The first tile's maximum is the reference; it is only raised (and O rescaled) when a lane's sum of weights exceeds
+//     kLazyLimit; otherwise the stale maximum is kept, which is exact after the final division by the row sum.
 //   * Software pipeline: S^T of the next tile is issued while the softmax of the current tile runs.
 //   * Small launches (one 4096-token layer is ~1000 workgroups of very different length) are bounded by
 //     their longest workgroup, the last query tile of the head that keeps most.  There the key range of a
@@ -382,11 +382,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   // the common case is therefore three per element and a half: one fused multiply-add (scale, minus the reference
   // maximum), one exponential, half a pack, half a dot2 that sums the PACKED pair -- the row sum is then the sum of
   // exactly the bf16 weights the second MFMA multiplies with.  No maximum is taken there: the exponentials are formed
-  // against the reference maximum as it stands, and only if a lane's sum of weights then exceeds 2^kLazyLog2 (or is
-  // not a number: the first tile, whose reference is still "nothing seen") does the wave take the slow branch, which
+  // against the reference maximum as it stands, and only if a lane's sum of weights then exceeds kLazyLimit (or is
+  // not a number: the first tile that a query sees any key of, if that is not the item's first) does the wave take the slow branch, which
   // finds the row maxima, raises the references that need it and forms the weights again.  A stale reference is
   // exact after the final division by the row sum -- floating point is indifferent to the common factor -- and
-  // 2^kLazyLog2 times the 64 keys of a tile times the tiles of the longest prompt stays far inside fp32's range.
+  // kLazyLimit times the 64 keys of a tile times the tiles of the longest prompt stays far inside fp32's range.
   // A lane raises its own reference only (its pair lane^32 decides with it), so a query never depends on the
   // queries that share its wave.
   float psum;
