@@ -302,13 +302,17 @@ template <int D, int G> struct wave_bf16 {
         p[e] = __builtin_amdgcn_exp2f(p[e] - m);
         l += p[e];
       }
-      const uint4 ph = make_uint4(pack2(p[0], p[1]), pack2(p[2], p[3]), pack2(p[4], p[5]), pack2(p[6], p[7]));
-      const uint32_t hw[4] = {ph.x, ph.y, ph.z, ph.w};
+      // p = high part (its first 16 bits) + remainder, the latter taken a 2^-23 of p too large: where p is not 0 it is
+      // positive, so that an infinite value comes out of both products with the same sign, as it would of one.
+      uint32_t hw[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        lo[2 * e] = p[2 * e] - __uint_as_float(hw[e] << 16);
-        lo[2 * e + 1] = p[2 * e + 1] - __uint_as_float(hw[e] & 0xffff0000u);
+        const uint32_t p0 = __float_as_uint(p[2 * e]), p1 = __float_as_uint(p[2 * e + 1]) & 0xffff0000u;
+        hw[e] = (p0 >> 16) | p1;
+        lo[2 * e] = fmaf(p[2 * e], 1.f + 0x1p-23f, -__uint_as_float(p0 & 0xffff0000u));
+        lo[2 * e + 1] = fmaf(p[2 * e + 1], 1.f + 0x1p-23f, -__uint_as_float(p1));
       }
+      const uint4 ph = make_uint4(hw[0], hw[1], hw[2], hw[3]);
       const uint4 pl = make_uint4(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]), pack2(lo[4], lo[5]), pack2(lo[6], lo[7]));
       if (more)
         asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NL) : "memory");  // V has landed (the next K may not have)
@@ -823,7 +827,8 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
             L *= keep; A0 *= keep; A1 *= keep;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              const float w = k0 + j < n_rec ? __builtin_amdgcn_exp2f(ml[j].x - M) : 0.f;
+              if (k0 + j >= n_rec) break;  // (not weight 0: a record may hold infinities)
+              const float w = __builtin_amdgcn_exp2f(ml[j].x - M);
               L = fmaf(w, ml[j].y, L);
               A0 = fmaf(w, o[j].x, A0);
               A1 = fmaf(w, o[j].y, A1);

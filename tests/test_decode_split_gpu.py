@@ -84,3 +84,30 @@ def test_decode_unit_of_more_than_four_gib():
     assert int(cache.len[0]) == n + 1
     ctx.poll_error()
     ctx.close()
+
+
+@pytest.mark.parametrize("D,lens", [(128, [40, 1, 500, 3000]), (64, [40, 1, 2100, 9000]), (128, [7000] * 40)])
+def test_decode_infinite_values_stay_infinite(D, lens):
+    """An infinite value in the first, the last or the new row of a unit (whole units, pieces, equal ranges): its feature is
+    that infinity, the others are the result without it.  The keys draw equal weights, so no weight rounds to 0."""
+    lens = np.asarray(lens, dtype=np.int32)
+    U = len(lens)
+    wl = W.decode_batch(62, "inf", "bf16", 1, 2 * U, U, D, lens, 1, pos0=int(lens.max()) + 1)
+    ctx = make_ctx(1, 1, 2 * U, U, D, ag.AG_BF16, cache_rows=int(wl.row_off[-1]))
+    cache = cache_from_host(1, U, D, wl.k_cache, wl.v_cache, wl.idx, wl.row_off, wl.len0)
+    q, kn, vn, _ = wl.step_inputs(0, 0.5)
+    q, kn, vn = dev(q), dev(kn), dev(vn)
+    q.zero_()
+    want = torch.empty_like(q)
+    no = torch.zeros(1, U, dtype=torch.uint8, device=DEV)  # the new token is not appended: both calls see the same rows
+    ag.ag_decode_attn(ctx, q, kn, vn, no, wl.pos0, wl.scale, cache, want)
+    for u in range(U):
+        a = int(wl.row_off[u])
+        cache.v[a, 5] = float("inf")
+        cache.v[a + int(lens[u]) - 1, D - 1] = float("-inf")
+        vn[0, u, 9] = float("inf")
+    want[..., 5], want[..., D - 1], want[..., 9] = float("inf"), float("-inf"), float("inf")
+    out = torch.empty_like(q)
+    ag.ag_decode_attn(ctx, q, kn, vn, no, wl.pos0, wl.scale, cache, out)
+    assert torch.equal(out, want)
+    ctx.close()
