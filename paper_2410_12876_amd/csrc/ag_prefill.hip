@@ -46,7 +46,7 @@ __device__ __forceinline__ float over_kg_sum(float x) {
 //     VW consecutive features and a row leaves memory whole.  A lane ends up with 4 VW consecutive output features.
 // The query's own token starts the state of the last wave, the evicted tokens of a recent-token window are added lane by
 // lane (a row that a query does not see is not read for it, whatever it holds).  In a tile that some query sees only
-// in part, values that are not finite are kept out of the product and put back as NaN where they are seen.
+// in part, values that are not finite are kept out of the product and added lane by lane where they are seen.
 // 128 tokens, 4 heads of 64: 22.4 us with one wave per query on the vector ALU.
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__restrict__ q, const float *__restrict__ k,
@@ -126,7 +126,6 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
     if (__any(see)) add_row(max(t, 0), see);
   }
 
-  bool poisoned = false;
   const int n_tiles = (cnt_hi + 15) / 16;
   for (int tile = wave; tile < n_tiles; tile += NW) {
     const int c0 = tile * 16;
@@ -157,24 +156,6 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
       if (part && c0 + 4 * kg + r >= cnt) p[r] = -INFINITY;
       mx = fmaxf(mx, p[r]);
     }
-    if (part) {
-      uint32_t bad_rows = 0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        bool bad = false;
-#pragma unroll
-        for (int h = 0; h < VH; ++h)
-#pragma unroll
-          for (int e = 0; e < VW; ++e)
-            if ((__float_as_uint(vf[r][h][e]) & 0x7f800000u) == 0x7f800000u) { bad = true; vf[r][h][e] = 0.f; }
-        const uint64_t any = __ballot(bad);
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          if ((any >> (16 * g)) & 0xffffull) bad_rows |= 1u << (4 * g + r);
-      }
-      const int seen = min(max(cnt - c0, 0), 16);
-      poisoned |= (bad_rows & ((1u << seen) - 1u)) != 0;
-    }
     const float mn = fmaxf(m, over_kg_max(mx));
     const float alpha = exp2f(m - mn);
     m = mn;
@@ -183,6 +164,17 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
     for (int r = 0; r < 4; ++r) {
       p[r] = exp2f(p[r] - mn);
       l += p[r];
+    }
+    bool odd = false;
+    if (part) {  // 0 times what a query does not see would be NaN: values that are not finite wait ...
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+          for (int e = 0; e < VW; ++e)
+            if ((__float_as_uint(vf[r][h][e]) & 0x7f800000u) == 0x7f800000u) { odd = true; vf[r][h][e] = 0.f; }
+      odd = __any(odd);
     }
 #pragma unroll
     for (int h = 0; h < VH; ++h)
@@ -194,9 +186,26 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
 #pragma unroll
         for (int r = 0; r < 4; ++r) o[h][r][e] = acc[r];
       }
+    if (odd) {  // ... and are added one by one where they are seen
+#pragma unroll 1
+      for (int i = 0; i < 16; ++i) {
+        const float mine = i & 2 ? (i & 1 ? p[3] : p[2]) : (i & 1 ? p[1] : p[0]);
+        const float w = __shfl(mine, 16 * (i >> 2) + col, 64);
+        if (c0 + i >= cnt) continue;
+        const float *vr = Vc + (size_t)(c0 + i) * D + 4 * VW * kg;
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+              const float x = vr[16 * VW * h + VW * r + e];
+              if ((__float_as_uint(x) & 0x7f800000u) == 0x7f800000u) o[h][r][e] = fmaf(w, x, o[h][r][e]);
+            }
+      }
+    }
   }
   l = over_kg_sum(l);
-  if (poisoned) l = __builtin_nanf("");
   float *mine = st[wave][col];
   if (kg == 0) { mine[0] = m; mine[1] = l; }
 #pragma unroll

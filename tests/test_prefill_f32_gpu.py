@@ -41,3 +41,20 @@ def test_a_kept_nan_reaches_only_later_queries():
     v[:, :, 40] = np.nan
     got = host_f32(_prefill_recent(W.store(q, "f32"), W.store(k, "f32"), W.store(v, "f32"), flags, 0.125, 1, True))
     assert np.isfinite(got[:, :, :40]).all() and np.isnan(got[:, :, 40:]).any(axis=-1).all()
+
+
+def test_an_infinite_value_stays_in_its_feature():
+    """Kept tokens with one infinite feature each, at both ends of a tile that is seen in part and of one that is seen whole:
+    queries that see one get that infinity in that feature, everything else is the result without it."""
+    B, H, L, D = 1, 2, 100, 64
+    g = np.random.default_rng(6)
+    q, k, v = (g.standard_normal((B, H, L, D)).astype(np.float32) for _ in range(3))
+    flags = np.ones((B, H, L), dtype=np.uint8)
+    ref = oracle.prefill_attn(q, k, v, flags, 0.125)
+    for t, d, x in ((0, 3, np.inf), (31, 40, -np.inf), (99, 7, np.inf), (50, 63, -np.inf)):
+        v[:, :, t, d] = x
+        ref[:, :, t:, d] = x
+    got = host_f32(_prefill_recent(W.store(q, "f32"), W.store(k, "f32"), W.store(v, "f32"), flags, 0.125, 1, True))
+    fin = np.isfinite(ref)
+    assert np.array_equal(got[~fin], ref[~fin])
+    assert attn_error("f32", np.where(fin, got, 0), np.where(fin, ref, 0)) <= 1e-5
