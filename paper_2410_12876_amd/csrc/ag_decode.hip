@@ -42,7 +42,9 @@ constexpr int kTileRows = 32;    // rows a wave takes at a time
 constexpr int kFewUnits = 256;   // up to here 8 waves per workgroup and one workgroup per CU: a unit's rows are spread over
                                  // as many waves as LDS can feed; beyond, 4 waves and two workgroups per CU, so that one
                                  // streams while the other merges
-constexpr float kEmptyMax = -1.0e30f;  // reference maximum before any row (finite on purpose)
+// Reference maximum before any row: the least finite number, so that no state that holds a row is below it (differences of
+// maxima stay numbers or become -infinity, of which the exponential is 0).
+constexpr float kEmptyMax = -3.40282347e+38f;
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -122,6 +124,10 @@ __device__ __forceinline__ float kg_sum(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
+
+// The maximum that the state of the new token's own key starts from.  Alone (no cache row, no ring slot seen) its weight is 1
+// whatever its score is; a score that overflowed to -infinity counts as the least finite one; NaN stays NaN.
+__device__ __forceinline__ float own_max(float s, bool alone) { return alone ? 0.f : (s < kEmptyMax ? kEmptyMax : s); }
 
 // What a tile reads: 32 rows of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
 struct dec_tile {
@@ -204,10 +210,10 @@ template <int D, int G> struct wave_bf16 {
   }
 
   // Tiles first, first + step, ... < last of the segment; get(i) describes tile i.  q: the G query rows of the unit.
-  // own: start from the new token's key and value instead of from nothing.
+  // own: start from the new token's key and value instead of from nothing; alone: nothing else is seen (see own_max).
   // (a ring tile can only be a wave's first: there are no more of them than waves)
   template <typename GET>
-  __device__ __forceinline__ void run(const uint16_t *q, int first, int last, int step, float qscale, bool own,
+  __device__ __forceinline__ void run(const uint16_t *q, int first, int last, int step, float qscale, bool own, bool alone,
                                       const uint16_t *k_new, const uint16_t *v_new, bool loose, GET &&get) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -249,7 +255,7 @@ template <int D, int G> struct wave_bf16 {
         s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qa.z), __builtin_bit_cast(bf16x2, kn[ks].z), s, false);
         s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, qa.w), __builtin_bit_cast(bf16x2, kn[ks].w), s, false);
       }
-      m = kg_sum(s) * qscale;
+      m = own_max(kg_sum(s) * qscale, alone);
       l = kg == 0 ? 1.f : 0.f;  // (summed over the key groups at the end)
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -373,7 +379,7 @@ template <int D, int G> struct wave_f32 {
     return group_sum<LPR>(fmaf(q.w, k[3], d)) * qscale;
   }
   template <typename GET>
-  __device__ __forceinline__ void run(const float *q, int first, int last, int step, float qscale, bool own,
+  __device__ __forceinline__ void run(const float *q, int first, int last, int step, float qscale, bool own, bool alone,
                                       const float *k_new, const float *v_new, bool, GET &&get) {
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) qr[gg] = reinterpret_cast<const float4 *>(q + (size_t)gg * D)[seg];
@@ -381,7 +387,7 @@ template <int D, int G> struct wave_f32 {
       const nt_f32x4 kn = reinterpret_cast<const nt_f32x4 *>(k_new)[seg], vn = reinterpret_cast<const nt_f32x4 *>(v_new)[seg];
 #pragma unroll
       for (int gg = 0; gg < G; ++gg) {
-        const float s = score(qr[gg], kn, qscale);
+        const float s = own_max(score(qr[gg], kn, qscale), alone);
         if (grp == 0) {
           m[gg] = s; l[gg] = 1.f;
 #pragma unroll
@@ -724,7 +730,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
     // the wave that never has more tiles than another one takes the new token
     const bool own = first_piece && wt == team - 1;
     if (t0 + wt < t1 || own)
-      wv.run(static_cast<const T *>(a.q) + (size_t)u * G * D, t0 + wt, t1, team, a.qscale, own, kn, vn, a.loose, [&](int i) {
+      wv.run(static_cast<const T *>(a.q) + (size_t)u * G * D, t0 + wt, t1, team, a.qscale, own, n == 0 && ring_vis == 0, kn, vn, a.loose, [&](int i) {
         if (i >= extra) {
           const int64_t r = (int64_t)(i - extra) * kTileRows;
           const int have = max(0, min(kTileRows, (int)(n - r)));
