@@ -13,6 +13,7 @@
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kEmptyMax = -3.40282347e+38f;  // maximum before any key: the least finite number, no score lies below it
 
 // exclusive prefix count of the keep flags at token j of one unit
 __device__ __forceinline__ int cnt_at(const uint64_t *__restrict__ words, const int32_t *__restrict__ bo, int j) {
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
 #pragma unroll
     for (int t = 0; t < KT; ++t) qf[t] = *reinterpret_cast<const f32x4 *>(qr + 16 * t);
   }
-  float m = -1.0e30f, l = 0.f;
+  float m = kEmptyMax, l = 0.f;
   float o[VH][4][VW];  // o[h][r][e]: feature 16 VW h + VW (4 kg + r) + e of query col
 #pragma unroll
   for (int h = 0; h < VH; ++h)
@@ -91,8 +92,9 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
 #pragma unroll
       for (int e = 0; e < VW; ++e) o[h][r][e] = 0.f;
 
-  // one more key for this lane's query: row t of the uncompacted k, v, if `see`
-  auto add_row = [&](int t, bool see) {
+  // one more key for this lane's query: row t of the uncompacted k, v, if `see`; alone: it is the only one, and weighs 1
+  // whatever its score is (a score that overflowed to -infinity counts as the least finite one elsewhere)
+  auto add_row = [&](int t, bool see, bool alone) {
     const float *kr = k + ((size_t)u * L + t) * D + 4 * kg, *vr = v + ((size_t)u * L + t) * D + 4 * VW * kg;
     float s = 0.f;
     if (see) {
@@ -104,6 +106,7 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
       }
     }
     s = over_kg_sum(s) * qscale;  // (the four lanes of a query agree on `see`)
+    s = alone ? 0.f : (s < kEmptyMax ? kEmptyMax : s);
     if (see) {
       const float mn = fmaxf(m, s), alpha = exp2f(m - mn), p = exp2f(s - mn);
       m = mn;
@@ -118,12 +121,12 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
         }
     }
   };
-  if (wave == NW - 1) add_row(j, true);
+  if (wave == NW - 1) add_row(j, true, cnt == 0 && (n_recent == 1 || j == 0));
   for (int i = 1 + wave; i < n_recent; i += NW) {
     const int t = j - i;
     bool see = t >= 0;
     if (see) see = !(((wu[t >> 6] >> (t & 63)) & 1ull) && cnt_at(wu, bo, t) < cap_u);  // (else a cache row already)
-    if (__any(see)) add_row(max(t, 0), see);
+    if (__any(see)) add_row(max(t, 0), see, false);
   }
 
   const int n_tiles = (cnt_hi + 15) / 16;
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(64 * NW) void ag_prefill_f32_kernel(const float *__
   for (int i = threadIdx.x; i < 16 * (D / 4); i += 64 * NW) {
     const int qq = i / (D / 4), d = 4 * (i % (D / 4));
     if (j0 + qq >= L) continue;
-    float M = -1.0e30f, Ls = 0.f;
+    float M = kEmptyMax, Ls = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, st[w][qq][0]);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};

@@ -1,5 +1,7 @@
 """Scores at the far ends of fp32: attention over rows that all score near -2^105 is still the softmax of their differences,
 and a query that sees nothing but its own token gets that token's value whatever the score is -- also one that overflowed."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -8,6 +10,7 @@ import oracle
 import paper_2410_12876_amd as ag
 import workloads as W
 from gpu_util import DEV, attn_error, attn_tolerance, cache_from_host, dev, ensure_built, host_f32, make_ctx
+from test_parity_configs_gpu import _prefill_recent
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +79,39 @@ def test_decode_of_an_empty_cache_is_the_new_value_whatever_the_score(dtype, D, 
     ag.ag_decode_attn_recent(ctx, q, k, v, torch.zeros(1, U, dtype=torch.uint8, device=DEV), 40, 0.125, cache, rr, out)
     assert torch.equal(out[:, :8], v[:, :8]) and torch.isfinite(out[:, 8].float()).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,L", [("f32", 2, 2, 64, 70), ("f32", 4, 1, 128, 33)])
+@pytest.mark.parametrize("n_recent", [1, 5])
+@pytest.mark.parametrize("keep", [0.0, 0.4])
+def test_prefill_of_scores_far_below_zero(dtype, Hq, Hkv, D, L, n_recent, keep):
+    """Every fourth key scores half as low as the others: the visible ones of them share the weight (evicted ones too, as a
+    query's own token or inside the window); a query that sees none averages what it sees."""
+    g = np.random.default_rng(71)
+    kk = _one_feature((1, Hkv, L, D), -LOW)
+    kk[:, :, ::4, 0] *= 0.5
+    q, k, v = W.store(_one_feature((1, Hq, L, D), Q0), dtype), W.store(kk, dtype), W.store(g.standard_normal((1, Hkv, L, D)).astype(np.float32), dtype)
+    flags = (g.random((1, Hkv, L)) < keep).astype(np.uint8)
+    got = host_f32(_prefill_recent(q, k, v, flags, SCALE, n_recent))
+    want = oracle.prefill_attn(q.f32, k.f32, v.f32, flags, SCALE, n_recent=n_recent)
+    assert np.isfinite(got).all() and attn_error(dtype, got, want) <= attn_tolerance(dtype, want)
+    if keep == 0.0 and n_recent == 1:
+        assert np.array_equal(got, np.repeat(v.f32, Hq // Hkv, axis=1))
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 256)])
+def test_prefill_of_a_fully_evicted_head_is_the_own_value_whatever_the_score(dtype, D):
+    B, H, L = 1, 2, 150
+    g = np.random.default_rng(72)
+    q, k, v = (g.standard_normal((B, H, L, D)).astype(np.float32) for _ in range(3))
+    big = np.float32(2.0 ** 100)
+    for t, (a, b) in enumerate([(big, big), (big, -big), (np.nan, 1.0), (np.inf, 1.0), (-np.inf, 1.0), (1.0, np.nan)]):
+        q[:, :, 10 * t], k[:, :, 10 * t] = 0.0, 0.0
+        q[:, :, 10 * t, 0], k[:, :, 10 * t, 0] = a, b
+    flags = np.zeros((B, H, L), dtype=np.uint8)
+    tv = W.store(v, dtype)
+    for n_recent in (1, 2):
+        got = host_f32(_prefill_recent(W.store(q, dtype), W.store(k, dtype), tv, flags, 1.0 / math.sqrt(D), n_recent))
+        assert np.array_equal(got[:, :, 0], tv.f32[:, :, 0])
+        if n_recent == 1:
+            assert np.array_equal(got, tv.f32)
