@@ -683,9 +683,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     const int col_e = lane_e & 31, hb_e = lane_e >> 5;
     const bool own = (own_rows >> col_e) & 1u;
     const float s_own = own_score[w4 * 32 + col_e];
+    // (a query that has seen no key but its own has no maximum to compare with: its token weighs 1 whatever its score is)
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const bool only = own && l_tot == 0.f;
     const float m_all = own ? fmaxf(m_run, s_own) : m_run;
-    const float f_run = __builtin_amdgcn_exp2f(m_run - m_all), f_own = own ? __builtin_amdgcn_exp2f(s_own - m_all) : 0.f;
-    const float inv = 1.f / ((l_run + __shfl_xor(l_run, 32, 64)) * f_run + f_own);
+    const float f_run = only ? 0.f : __builtin_amdgcn_exp2f(m_run - m_all);
+    const float f_own = only || (own && s_own == m_all) ? 1.f : own ? __builtin_amdgcn_exp2f(s_own - m_all) : 0.f;
+    const float inv = 1.f / (l_tot * f_run + f_own);
     const float g_run = f_run * inv, g_own = own ? f_own * inv : 0.f;  // out = g_run O + g_own v
     AG_LDS uint8_t *ost = (AG_LDS uint8_t *)smem + w4 * (32 * kRowB);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the own value rows are there

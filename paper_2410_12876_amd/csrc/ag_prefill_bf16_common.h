@@ -17,7 +17,7 @@ typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
 constexpr int kBN = 64;                    // keys per tile
 constexpr float kLazyLimit = 1073741824.f; // 2^30: a lane's sum of weights above this raises its reference maximum
-constexpr float kEmptyMax = -1.0e30f;      // "no key seen yet" reference maximum (finite on purpose)
+constexpr float kEmptyMax = -3.40282347e+38f;  // reference maximum before any key: the least finite number, no score lies below it
 
 // Tile geometry for head dimension HD (128 or 64): a K or V tile is 64 rows of HD bf16, row-major in LDS, its
 // 16-byte chunks XOR-swizzled with a key taken from the row so that the three access patterns -- 1 KiB contiguous

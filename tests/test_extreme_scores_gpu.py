@@ -81,7 +81,8 @@ def test_decode_of_an_empty_cache_is_the_new_value_whatever_the_score(dtype, D, 
     ctx.close()
 
 
-@pytest.mark.parametrize("dtype,Hq,Hkv,D,L", [("f32", 2, 2, 64, 70), ("f32", 4, 1, 128, 33)])
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,L", [("f32", 2, 2, 64, 70), ("f32", 4, 1, 128, 33), ("bf16", 2, 2, 128, 300),
+                                              ("bf16", 4, 1, 64, 200), ("bf16", 8, 2, 128, 70)])
 @pytest.mark.parametrize("n_recent", [1, 5])
 @pytest.mark.parametrize("keep", [0.0, 0.4])
 def test_prefill_of_scores_far_below_zero(dtype, Hq, Hkv, D, L, n_recent, keep):
@@ -99,7 +100,7 @@ def test_prefill_of_scores_far_below_zero(dtype, Hq, Hkv, D, L, n_recent, keep):
         assert np.array_equal(got, np.repeat(v.f32, Hq // Hkv, axis=1))
 
 
-@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 256)])
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 256), ("bf16", 128), ("bf16", 64)])
 def test_prefill_of_a_fully_evicted_head_is_the_own_value_whatever_the_score(dtype, D):
     B, H, L = 1, 2, 150
     g = np.random.default_rng(72)
@@ -115,3 +116,19 @@ def test_prefill_of_a_fully_evicted_head_is_the_own_value_whatever_the_score(dty
         assert np.array_equal(got[:, :, 0], tv.f32[:, :, 0])
         if n_recent == 1:
             assert np.array_equal(got, tv.f32)
+
+
+@pytest.mark.parametrize("D", [128, 64])
+def test_prefill_bf16_own_score_that_overflowed_takes_all_the_weight(D):
+    """An evicted query whose own score is +infinity, beside kept ones that it sees."""
+    B, H, L = 1, 2, 200
+    g = np.random.default_rng(73)
+    q, k, v = (g.standard_normal((B, H, L, D)).astype(np.float32) for _ in range(3))
+    flags = (g.random((B, H, L)) < 0.5).astype(np.uint8)
+    flags[:, :, :60], flags[:, :, 60::20] = 1, 0
+    q[:, :, 60::20], k[:, :, 60::20] = 0.0, 0.0
+    q[:, :, 60::20, 0], k[:, :, 60::20, 0] = np.float32(2.0 ** 100), np.float32(2.0 ** 100)
+    k[:, :, :, 0] = np.where(flags != 0, 0.0, k[:, :, :, 0])
+    tv = W.store(v, "bf16")
+    got = host_f32(_prefill_recent(W.store(q, "bf16"), W.store(k, "bf16"), tv, flags, 1.0 / math.sqrt(D), 1))
+    assert np.array_equal(got[:, :, 60::20], tv.f32[:, :, 60::20])
