@@ -111,3 +111,31 @@ def test_decode_infinite_values_stay_infinite(D, lens):
     ag.ag_decode_attn(ctx, q, kn, vn, no, wl.pos0, wl.scale, cache, out)
     assert torch.equal(out, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,G,half", [(128, 1, 1), (128, 4, 20), (128, 1, 300), (64, 2, 1000), (64, 8, 33), (128, 8, 6000)])
+def test_decode_weights_keep_24_bits(D, G, half):
+    """Half of a unit's rows have value 1 and score 0, the other half value -1 and a score lower by d, 2^-14 to 2^-13: the output is
+    tanh(d / 2), what is left of sums that cancel to a few 2^-15.  A weight of 24 bits has a relative error of up to 2^-23 (one
+    unit in the last place from the exponential, half of one from its argument), so the output one of 2 * 2^-23 / 2^-14 = 0.4 %
+    plus half a bf16 spacing (0.4 %); of weights of 16 bits up to a quarter of it would be left."""
+    U, n = 8, 2 * half
+    k, v = torch.zeros(U, n + 1, D, device=DEV), torch.zeros(U, n + 1, D, device=DEV)
+    step = 2.0 ** -14 * (1.0 + torch.arange(U, device=DEV) / 8.0)
+    k[:, half:n, 3] = -step[:, None]
+    v[:, :half], v[:, half:n] = 1.0, -1.0
+    ro = torch.arange(U + 1, device=DEV) * (n + 1)
+    cache = ag.KVCache(k.view(-1, D).bfloat16(), v.view(-1, D).bfloat16(), torch.zeros(U * (n + 1), dtype=torch.int32, device=DEV), ro,
+                       torch.full((U,), n, dtype=torch.int32, device=DEV), 1, U, D)
+    ctx = make_ctx(1, 1, U * G, U, D, ag.AG_BF16, cache_rows=U * (n + 1))
+    q = torch.zeros(1, U * G, D, dtype=torch.bfloat16, device=DEV)
+    q[..., 3], q[..., 5] = 1.0, 64.0
+    kn, vn = torch.zeros(1, U, D, dtype=torch.bfloat16, device=DEV), torch.ones(1, U, D, dtype=torch.bfloat16, device=DEV)
+    kn[..., 5] = -64.0                                       # the new token has no weight
+    out = torch.empty_like(q)
+    ag.ag_decode_attn(ctx, q, kn, vn, None, n, 1.0, cache, out)
+    want = torch.tanh(step.double() / 2).repeat_interleave(G)[None, :, None].expand(1, U * G, D)
+    err = float(((out.double() - want).abs() / want).max())
+    print("relative error %.4f" % err)
+    assert err <= 0.008
+    ctx.close()
