@@ -139,3 +139,29 @@ def test_decode_weights_keep_24_bits(D, G, half):
     print("relative error %.4f" % err)
     assert err <= 0.008
     ctx.close()
+
+
+@pytest.mark.parametrize("D,G", [(128, 1), (64, 4)])
+def test_decode_infinite_value_of_a_tiny_weight(D, G):
+    """The infinity comes through at any weight that is not 0: 2^-60 to 2^-124, the least that the exponential gives."""
+    U, n = 16, 40
+    k, v = torch.zeros(U, n + 1, D, device=DEV), torch.ones(U, n + 1, D, device=DEV)
+    low = torch.linspace(60.0, 124.0, U, device=DEV).round()
+    k[:, 7, 3] = -low
+    v[:, 7, 9] = float("inf")
+    v[:, 7, 11] = -float("inf")
+    cache = ag.KVCache(k.view(-1, D).bfloat16(), v.view(-1, D).bfloat16(), torch.zeros(U * (n + 1), dtype=torch.int32, device=DEV),
+                       torch.arange(U + 1, device=DEV) * (n + 1), torch.full((U,), n, dtype=torch.int32, device=DEV), 1, U, D)
+    ctx = make_ctx(1, 1, U * G, U, D, ag.AG_BF16, cache_rows=U * (n + 1))
+    q = torch.zeros(1, U * G, D, dtype=torch.bfloat16, device=DEV)
+    q[..., 3] = 1.0
+    new = torch.zeros(1, U, D, dtype=torch.bfloat16, device=DEV)
+    out = torch.empty_like(q)
+    ag.ag_decode_attn(ctx, q, new, torch.ones_like(new), None, n, 0.6931471805599453, cache, out)
+    want = torch.ones_like(out)
+    want[..., 9], want[..., 11] = float("inf"), -float("inf")
+    for u in range(U):
+        for g in range(G):
+            if not torch.equal(out[0, u * G + g], want[0, u * G + g]): print("weight 2^-%d" % int(low[u]), out[0, u * G + g, 7:13].tolist())
+    assert torch.equal(out, want)
+    ctx.close()
