@@ -153,7 +153,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-  // The fragments of one 16-k slab are read from LDS while the MFMAs of the slab before it run, also across a stage's end:
+  // ST > 2: the fragments of one 16-k slab are read from LDS while the MFMAs of the slab before it run, also across a stage's end:
   // after a barrier the first MFMAs find their operands in registers.  For that the NEXT stage must have landed at every
   // barrier, and a stage's place in the ring is free after the barrier that follows its last slab.
   constexpr int NS = BK / 16, NM = TN * TM, RPM = (2 * TN + TM + NM - 1) / NM;  // slabs per stage, MFMAs per slab, reads per MFMA
@@ -171,40 +171,61 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt) b[mt] = *reinterpret_cast<const AG_LDS bf16x8 *>(S + (x_base ^ (sl << 5)) + mt * 32 * XRow);
   };
+  if constexpr (ST == 2) {
+    // Two stages: what one workgroup waits for, the other one of its CU covers, and with half the barriers and no fragments
+    // held ahead the two together are faster than two of the pipelined loop below.
+    issue(0, 0);
+    for (int t = 0; t < T; ++t) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's share of stage t has landed
+      __syncthreads();                                  // ... and everyone's; stage t - 1 is fully read
+      if (t + 1 < T) issue(t + 1, (t + 1) & 1);
+      const AG_LDS uint8_t *S = (const AG_LDS uint8_t *)smem + (t & 1) * CFG::Stage;
 #pragma unroll
-  for (int t = 0; t < ST; ++t)
-    if (t < T) issue(t, t);
-  if (T > ST - 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 2) * (XL + WL)) : "memory");  // stages 0 and 1 have landed
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  read((const AG_LDS uint8_t *)smem, 0, fa[0], fb[0]);
-  int buf = 0;
-  for (int t = 0; t < T; ++t) {
-    const AG_LDS uint8_t *S = (const AG_LDS uint8_t *)smem + buf * CFG::Stage;
-    const int nxt = buf + 1 == ST ? 0 : buf + 1;
-    const AG_LDS uint8_t *Sn = (const AG_LDS uint8_t *)smem + nxt * CFG::Stage;
+      for (int sl = 0; sl < NS; ++sl) {
+        read(S, sl, fa[0], fb[0]);
 #pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-      const int cur = sl & 1;
-      if (sl + 1 < NS) read(S, sl + 1, fa[cur ^ 1], fb[cur ^ 1]);
-      else read(Sn, 0, fa[cur ^ 1], fb[cur ^ 1]);  // (after the last stage: stale bytes that nothing uses)
+        for (int nt = 0; nt < TN; ++nt)
 #pragma unroll
-      for (int nt = 0; nt < TN; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt)
-          acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][nt], fb[cur][mt], acc[nt][mt], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < NM; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          for (int mt = 0; mt < TM; ++mt)
+            acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][nt], fb[0][mt], acc[nt][mt], 0, 0, 0);
       }
     }
-    // this wave's share of stage t + 2 has landed (t + 3 .. may be on their way) ...
-    if (t + ST - 1 < T) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 3) * (XL + WL)) : "memory");
+  } else {
+#pragma unroll
+    for (int t = 0; t < ST; ++t)
+      if (t < T) issue(t, t);
+    if (T > ST - 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 2) * (XL + WL)) : "memory");  // stages 0 and 1 have landed
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();  // ... and everyone's; stage t is fully read
-    if (t + ST < T) issue(t + ST, buf);
-    buf = nxt;
+    __syncthreads();
+    read((const AG_LDS uint8_t *)smem, 0, fa[0], fb[0]);
+    int buf = 0;
+    for (int t = 0; t < T; ++t) {
+      const AG_LDS uint8_t *S = (const AG_LDS uint8_t *)smem + buf * CFG::Stage;
+      const int nxt = buf + 1 == ST ? 0 : buf + 1;
+      const AG_LDS uint8_t *Sn = (const AG_LDS uint8_t *)smem + nxt * CFG::Stage;
+#pragma unroll
+      for (int sl = 0; sl < NS; ++sl) {
+        const int cur = sl & 1;
+        if (sl + 1 < NS) read(S, sl + 1, fa[cur ^ 1], fb[cur ^ 1]);
+        else read(Sn, 0, fa[cur ^ 1], fb[cur ^ 1]);  // (after the last stage: stale bytes that nothing uses)
+#pragma unroll
+        for (int nt = 0; nt < TN; ++nt)
+#pragma unroll
+          for (int mt = 0; mt < TM; ++mt)
+            acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][nt], fb[cur][mt], acc[nt][mt], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+      }
+      // this wave's share of stage t + 2 has landed (t + 3 .. may be on their way) ...
+      if (t + ST - 1 < T) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 3) * (XL + WL)) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();  // ... and everyone's; stage t is fully read
+      if (t + ST < T) issue(t + ST, buf);
+      buf = nxt;
+    }
   }
 
   // ---- epilogue: acc[nt][mt][r] = C[token m0 + 32 (wm TM + mt) + col][n0 + 32 (wn TN + nt) + 8 (r/4) + 4 kb + r%4] ----
@@ -297,28 +318,38 @@ hipError_t launch_proj(ag_ctx *ctx, hipStream_t s, const void *x, const void *w,
   return hipGetLastError();
 }
 
-// The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each was measured to
-// take on this chip with K = 4096 (us; `alone`: a few tiles, `full`: every slot taken -- the chip's clock falls with the
-// number of busy CUs, and two workgroups on one CU share it).
-//   256 x 256: 1.13 PFLOP/s where there are tiles for whole rounds (8192 tokens x 8192 columns: 586 -> 478 us; with
-//              128 x 128 tiles LDS bounds it); one tile takes 78 us.
-//   128 x 128: 0.93 PFLOP/s, but fills the chip from a quarter of the columns x tokens on.
-//   128 x 192: 1536 columns (three tensors of four heads) in whole rounds where 128 x 128 leaves a quarter of the CUs idle.
+// The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each takes on this chip
+// (measured over 64 to 16384 tokens, 1536 to 8192 columns, K = 1024, 2048 and 4096; the choice is within 3 % of the fastest
+// of the four there, and on no size more than 1 us slower than 128 x 128 tiles throughout).
+//   256 x 256: 1.13 PFLOP/s where there are tiles for whole rounds (8192 tokens x 8192 columns: 446 us; with 128 x 128
+//              tiles, which LDS bounds, 526); one tile takes 80 us.
+//   128 x 128: 1.0 PFLOP/s with two workgroups on every CU, and fills the chip from a quarter of the columns x tokens on.  In
+//              two stages of 64 k-steps; in four of 32, with the fragments read ahead, it is slower as soon as CUs hold two of
+//              them (1536 columns: 2900 tokens 67 us against 49, 8192 tokens 114 against 102).
+//   128 x 192: 1536 columns (three tensors of four heads) in whole rounds where 128 x 128 leaves a rest.
 //   64 x 64  : few tokens, where one tile's chain of stages is the time: 128 k-steps per barrier (64 to 300 tokens: 40 -> 16 us).
 typedef proj_cfg<256, 256, 2, 4, 32, 4> cfg_256x256;
-typedef proj_cfg<128, 128, 2, 2, 32, 4> cfg_128x128;
+typedef proj_cfg<128, 128, 2, 2, 64, 2> cfg_128x128;
 typedef proj_cfg<128, 192, 2, 2, 32, 4> cfg_128x192;
 typedef proj_cfg<64, 64, 2, 2, 128, 4> cfg_64x64;
 
-float proj_time(int64_t M, int N, int bm, int bn, int slots, int num_cu, float alone, float full) {
-  const int64_t tiles = (M + bm - 1) / bm * (N / bn), rounds = tiles / slots, last = tiles - rounds * slots;
-  float t = (float)rounds * full;
-  if (last > 0) {
-    const float per_cu = (float)last / (float)num_cu;  // up to one workgroup per CU, then the second ones
-    if (slots == num_cu) t += alone + (full - alone) * per_cu;
-    else t += per_cu <= 1.f ? alone * (1.f + 0.1f * per_cu) : alone * 1.1f + (full - alone * 1.1f) * (per_cu - 1.f);
+// A round's time ends with its slowest CU: `few` tiles take as long as one, `one` workgroup on every CU a little longer (the
+// clock falls with the number of busy CUs), and as soon as some CUs hold two workgroups the round takes what those take,
+// `second`, up to `full` with two on every CU (per_cu == 1: there is no second).  us at K = 4096, beside a part per round that
+// does not grow with K.
+struct proj_cost {
+  int per_cu;
+  float few, one, second, full, fixed;
+};
+float proj_time(int64_t M, int N, int K, int bm, int bn, int num_cu, const proj_cost &c) {
+  const int64_t tiles = (M + bm - 1) / bm * (N / bn), slots = (int64_t)c.per_cu * num_cu, rounds = tiles / slots, last = tiles - rounds * slots;
+  float t = (float)rounds * c.full;
+  if (last > num_cu) t += c.second + (c.full - c.second) * (float)(last - num_cu) / (float)num_cu;
+  else if (last > 0) {
+    const float busy = (float)last / (float)num_cu;
+    t += c.few + (c.one - c.few) * busy * busy * busy;
   }
-  return t;
+  return t * (float)K / 4096.f + c.fixed * (float)(rounds + (last > 0));
 }
 
 template <bool COMPACT>
@@ -326,11 +357,11 @@ hipError_t launch_proj_any(ag_ctx *ctx, hipStream_t s, const void *x, const void
                            const ag_proj_compact &cp) {
   const int cu = ctx->num_cu;
   const float never = 3.0e38f;
-  const float t128 = proj_time(M, N, 128, 128, 2 * cu, cu, 39.f, 73.f);
-  const float t256 = N % 256 == 0 ? proj_time(M, N, 256, 256, cu, cu, 78.f, 120.f) : never;
+  const float t128 = proj_time(M, N, K, 128, 128, cu, {2, 34.f, 39.f, 43.5f, 57.f, 4.5f});
+  const float t256 = N % 256 == 0 ? proj_time(M, N, K, 256, 256, cu, {1, 74.f, 106.f, 0.f, 106.f, 7.f}) : never;
   // (a tile that starts inside a head is not made for the compaction's look-up of cache rows)
-  const float t192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, 128, 192, 2 * cu, cu, 49.f, 95.f) : never;
-  const float t64 = K % 128 == 0 ? proj_time(M, N, 64, 64, cu, cu, 15.f, 17.f) : never;
+  const float t192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, K, 128, 192, cu, {2, 43.5f, 48.5f, 65.f, 86.f, 5.5f}) : never;
+  const float t64 = K % 128 == 0 ? proj_time(M, N, K, 64, 64, cu, {1, 12.f, 13.6f, 0.f, 13.f, 2.8f}) : never;
   if (t64 < t128 && t64 < t256 && t64 < t192) return launch_proj<cfg_64x64, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
   if (t256 < t128 && t256 < t192) return launch_proj<cfg_256x256, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
   if constexpr (!COMPACT)

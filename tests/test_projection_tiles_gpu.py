@@ -48,7 +48,8 @@ def test_project_compact_tiles(B, L, d, Hkv):
         assert np.array_equal(gk[a:a + n], ref.k[a:a + n]) and np.array_equal(gv[a:a + n], ref.v[a:a + n])
 
 
-@pytest.mark.parametrize("B,L,d,hp", [(1, 70, 128, 4), (1, 4096, 64, 4), (2, 1900, 128, 4), (1, 1200, 192, 2)])
+@pytest.mark.parametrize("B,L,d,hp", [(1, 70, 128, 4), (1, 4096, 64, 4), (2, 1900, 128, 4), (1, 1200, 192, 2), (1, 5401, 128, 4),
+                                      (3, 1801, 64, 4)])
 def test_gate_mha_tiles(B, L, d, hp):
     """The gate module end to end on these tiles: logits against fp32 torch on the CPU with the four tensors it stores in bf16
     rounded where it rounds them (the tolerance of the module's own tests for that reference: 1e-2)."""
