@@ -944,14 +944,16 @@ hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows,
   const int blocks = (int)std::min<int64_t>(NW == 8 ? ctx->num_cu : 2 * ctx->num_cu, pieces);
   a.max_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(records / 2, blocks));
   for (a.team = NW; a.team > 1 && (int64_t)a.U * a.team > (int64_t)blocks * NW;) a.team /= 2;
-  if (shmem > 48 * 1024) {
-    static std::atomic<size_t> allowed[64];  // per device: the largest size asked for so far
-    std::atomic<size_t> &most = allowed[ctx->device & 63];
-    if (most.load(std::memory_order_relaxed) < shmem) {
+  // The limit is raised once per device, to what the largest step needs: a limit that followed the size of each call could be
+  // lowered by one thread under another one's launch.
+  constexpr size_t kMost = (size_t)NW * wave_t::kWaveB + (NW == 8 ? 0 : (size_t)kDecodeMaxUnits * 4);
+  if (kMost > 48 * 1024) {
+    static std::atomic<bool> allowed[64];
+    if (!allowed[ctx->device & 63].load(std::memory_order_relaxed)) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_decode_kernel<T, D, G, NW>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMost);
       if (e != hipSuccess) return e;
-      most.store(shmem, std::memory_order_relaxed);
+      allowed[ctx->device & 63].store(true, std::memory_order_relaxed);
     }
   }
   // (both timing ids report this launch: the merge is part of it)

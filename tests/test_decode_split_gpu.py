@@ -1,5 +1,7 @@
 """How the decode launch cuts its work: whole units, pieces of long ones, equal ranges over many; tile edges; arguments
 that are not 16-byte aligned.  All against the oracle."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -165,3 +167,51 @@ def test_decode_infinite_value_of_a_tiny_weight(D, G):
             if not torch.equal(out[0, u * G + g], want[0, u * G + g]): print("weight 2^-%d" % int(low[u]), out[0, u * G + g, 7:13].tolist())
     assert torch.equal(out, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,G,D", [("bf16", 1, 128), ("f32", 8, 128)])
+def test_decode_steps_of_different_sizes_from_several_threads(dtype, G, D):
+    """The LDS of a step grows with its units, and its limit belongs to the kernel: threads with contexts and streams of their
+    own, each at another number of units."""
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def made(U):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(U)
+        k, v = (torch.randn(U * 4, D, generator=g, device=DEV).to(td) for _ in range(2))
+        q = torch.randn(1, U * G, D, generator=g, device=DEV).to(td)
+        new = torch.randn(1, U, D, generator=g, device=DEV).to(td)
+        cache = ag.KVCache(k, v, torch.zeros(U * 4, dtype=torch.int32, device=DEV), torch.arange(U + 1, device=DEV) * 4,
+                           torch.full((U,), 3, dtype=torch.int32, device=DEV), 1, U, D)
+        no = torch.zeros(1, U, dtype=torch.uint8, device=DEV)
+        ctx = make_ctx(1, 1, U * G, U, D, ag.AG_BF16 if dtype == "bf16" else ag.AG_F32, cache_rows=U * 4)
+        return ctx, q, new, no, cache
+    sizes = [300, 8192, 1000, 5000]
+    sets = [made(U) for U in sizes]
+    got, errors = [None] * len(sizes), []
+    torch.cuda.synchronize()
+
+    def work(i):
+        try:
+            ctx, q, new, no, cache = sets[i]
+            s = torch.cuda.Stream()
+            outs = [torch.empty_like(q) for _ in range(20)]
+            torch.cuda.synchronize()
+            for o in outs:
+                ag.ag_decode_attn(ctx, q, new, new, no, 9, 0.1, cache, o, stream=s)
+            s.synchronize()
+            assert all(torch.equal(o, outs[0]) for o in outs)
+            got[i] = outs[0]
+        except Exception as e:  # noqa: BLE001  (reported by the main thread)
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(sizes))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for (ctx, q, new, no, cache), o in zip(sets, got):
+        out = torch.empty_like(q)
+        ag.ag_decode_attn(ctx, q, new, new, no, 9, 0.1, cache, out)
+        assert torch.equal(o, out) and torch.isfinite(out.float()).all()
+        ctx.close()
