@@ -550,7 +550,8 @@ hipError_t ag_launch_gate(ag_ctx *ctx, hipStream_t s, const void *feat, ag_dtype
   const int per_wave = (d_in / 64 + kFusedWaves - 1) / kFusedWaves;  // 64-feature chunks per wave
   const ag_evpair ev = ag_time_kernel(ctx, AG_K_GATE);
   // From two tiles per CU on, and as far as a wave's part of W fits its registers, tiles stream through one workgroup per CU.
-  if (tiles >= 2 * ctx->num_cu && per_wave <= 8) {
+  // (Its loads go straight into LDS, 16 bytes a lane: features that are not so aligned go through registers, below.)
+  if (tiles >= 2 * ctx->num_cu && per_wave <= 8 && (reinterpret_cast<uintptr_t>(feat) & 15) == 0) {
     const size_t shmem = (size_t)kFusedWaves * (kRing * 2048 + 4096);
 #define AG_GATE_STREAM(RAWV, NCHV)                                                                                    \
   do {                                                                                                                \

@@ -5,8 +5,10 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
-from gpu_util import ensure_built
+import paper_2410_12876_amd as ag
+from gpu_util import DEV, dev, ensure_built, make_ctx
 from test_parity_gpu import check_gate, rand_t
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +32,20 @@ def test_gate_tiles(dtype, B, L, d_in, H, n_sink):
     w = rand_t(72, (d_in, H), dtype, 1.0 / math.sqrt(d_in))
     bias = np.random.default_rng(73).standard_normal(H).astype(np.float32) * 0.2
     check_gate(x, w, bias, 0.5, n_sink, 1e-4 if dtype == "bf16" else 2e-5)
+
+
+@pytest.mark.parametrize("L,d_in,H,by", [(8200, 512, 32, 1), (8192, 128, 6, 4), (40, 4096, 32, 3)])
+def test_gate_features_at_any_even_address(L, d_in, H, by):
+    """Features that do not start at a multiple of 16 bytes, few and many tokens: bit for bit what aligned ones give."""
+    x, w = dev(rand_t(74, (1, L, d_in), "bf16", 0.5)), dev(rand_t(75, (d_in, H), "bf16", 1.0 / math.sqrt(d_in)))
+    moved = torch.zeros(x.numel() + 8, dtype=x.dtype, device=DEV)[by:by + x.numel()].view(x.shape).copy_(x)
+    assert moved.data_ptr() % 16 == 2 * by
+    bias = torch.zeros(H, device=DEV)
+    ctx = make_ctx(1, L, H, H, 64, ag.AG_BF16, d_in=d_in)
+    got = []
+    for t in (x, moved):
+        logits, flags = torch.zeros(1, L, H, device=DEV), torch.full((1, H, L), 7, dtype=torch.uint8, device=DEV)
+        ag.ag_gate(ctx, t, w, bias, 0.5, 1, logits, flags)
+        got.append((logits, flags))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]) and got[0][0].abs().max() > 0.1
+    ctx.close()
