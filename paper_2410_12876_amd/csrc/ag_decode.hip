@@ -141,8 +141,9 @@ struct dec_tile {
 };
 
 // ---- bf16: one wave's pass over its tiles on MFMA -----------------------------------------------------------
-// Lane = (query head q = lane % 16, key group kg = lane / 16); heads q >= G are zero columns.
-template <int D, int G> struct wave_bf16 {
+// Lane = (query head q = lane % 16, key group kg = lane / 16); heads q >= G are zero columns.  EVEN: the caches start at an
+// even address that is no multiple of 16; their rows go through registers (direct loads into LDS are not used for those).
+template <int D, int G, bool EVEN> struct wave_bf16 {
   static constexpr int kRowB = D * 2, CPR = kRowB / 16, RPI = 64 / CPR;  // RPI rows per load instruction
   static constexpr int NL = kTileRows / RPI;                             // load instructions per tile and operand
   static constexpr int kWaveB = 2 * kTileRows * kRowB;                   // the wave's LDS: K tile, V tile
@@ -178,19 +179,28 @@ template <int D, int G> struct wave_bf16 {
   }
   // Cache rows of one operand straight into LDS; rows past the array arrive as zeros.  Every cached row is read once per
   // step: non-temporal, so that the stream does not push the small hot data (queries, lengths, records) out of the caches.
-  __device__ __forceinline__ void load(const dec_tile &t, const void *base, uint32_t dst) {
+  __device__ __forceinline__ void load(const dec_tile &t, const void *base, int to) {
     const uint64_t at = (uint64_t)base;  // (wave-uniform, as the loads need it; said explicitly)
     const uint64_t base_s = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)at) |
                             ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(at >> 32)) << 32);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)base_s, 0, __builtin_amdgcn_readfirstlane(t.bytes), 0x00020000);
+    if constexpr (EVEN) {
+      u32x4 x[NL];
+#pragma unroll
+      for (int i = 0; i < NL; ++i) x[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, ld_off(i) + i * RPI * kRowB, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NL; ++i) *reinterpret_cast<AG_LDS u32x4 *>(lds + to + i * RPI * kRowB + lane * 16) = x[i];
+      return;
+    }
+    const uint32_t dst = lds_addr + to;
 #pragma unroll
     for (int i = 0; i < NL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
                    :: "s"(dst + i * RPI * kRowB), "v"(ld_off(i)), "s"(rsrc), "s"(i * RPI * kRowB) : "memory");
   }
-  __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, lds_addr); }
-  __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, lds_addr + kTileRows * kRowB); }
+  __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, 0); }
+  __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, kTileRows * kRowB); }
   // Ring slots, through registers: only the visible rows are read, the others become zeros.
   __device__ __forceinline__ void load_ring(const dec_tile &t, bool loose) {
     uint4 x[2][NL];
@@ -469,9 +479,9 @@ template <int D, int G> struct wave_f32 {
     }
   }
 };
-template <typename T, int D, int G> struct wave_of;
-template <int D, int G> struct wave_of<uint16_t, D, G> { typedef wave_bf16<D, G> type; };
-template <int D, int G> struct wave_of<float, D, G> { typedef wave_f32<D, G> type; };
+template <typename T, int D, int G, bool EVEN> struct wave_of;
+template <int D, int G, bool EVEN> struct wave_of<uint16_t, D, G, EVEN> { typedef wave_bf16<D, G, EVEN> type; };
+template <int D, int G, bool EVEN> struct wave_of<float, D, G, EVEN> { typedef wave_f32<D, G> type; };
 
 struct dec_args {
   const void *q, *k_new, *v_new;
@@ -505,9 +515,9 @@ __device__ __forceinline__ int wave_prefix(int x, int &total) {
   return y - x;
 }
 
-template <typename T, int D, int G, int NW>
+template <typename T, int D, int G, int NW, bool EVEN>
 __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
-  typedef typename wave_of<T, D, G>::type wave_t;
+  typedef typename wave_of<T, D, G, EVEN>::type wave_t;
   constexpr int NT = 64 * NW, SF = wave_t::kStateF;
   constexpr int CPT = (int)(D * sizeof(T) / 16);  // 16-byte chunks per row
   constexpr bool kRegs = NW == 8;                 // the work list lives in registers (at most 256 units)
@@ -854,7 +864,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
     }
     if (first_piece && tt < 2 * CPT) {  // the new token: its cache row (nobody reads past len in this launch) and its ring slot
       if (new_flag != 0 && sl < 0) {
-        reinterpret_cast<uint4 *>(static_cast<T *>(tt < CPT ? a.kc : a.vc) + (size_t)(ro + n) * D)[tt % CPT] = new_row;
+        put16(reinterpret_cast<uint8_t *>(static_cast<T *>(tt < CPT ? a.kc : a.vc) + (size_t)(ro + n) * D) + 16 * (tt % CPT), new_row, EVEN);
         if (tt == 0) a.idx[ro + n] = a.pos;
       } else if (new_flag != 0 && tt == 0) {
         atomicOr(a.d_err, 1);
@@ -935,9 +945,9 @@ __global__ __launch_bounds__(256) void ag_ring_fill_kernel(const T *__restrict__
 
 int64_t max_records(int units, int64_t cache_rows) { return cache_rows / kChunk + units; }
 
-template <typename T, int D, int G, int NW>
+template <typename T, int D, int G, int NW, bool EVEN>
 hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, int64_t records) {
-  typedef typename wave_of<T, D, G>::type wave_t;
+  typedef typename wave_of<T, D, G, EVEN>::type wave_t;
   const size_t shmem = (size_t)NW * wave_t::kWaveB + (NW == 8 ? 0 : (size_t)a.U * 4);
   // one workgroup per CU (8 waves) or two (4 waves); no more than the step can have pieces
   const int64_t pieces = a.U + total_rows / (NW * kTileRows) + 1;
@@ -950,7 +960,7 @@ hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows,
   if (kMost > 48 * 1024) {
     static std::atomic<bool> allowed[64];
     if (!allowed[ctx->device & 63].load(std::memory_order_relaxed)) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_decode_kernel<T, D, G, NW>),
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&ag_decode_kernel<T, D, G, NW, EVEN>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMost);
       if (e != hipSuccess) return e;
       allowed[ctx->device & 63].store(true, std::memory_order_relaxed);
@@ -958,7 +968,7 @@ hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows,
   }
   // (both timing ids report this launch: the merge is part of it)
   ag_tick(ctx, AG_K_DECODE_MERGE, s);
-  AG_LAUNCH(ag_time_kernel(ctx, AG_K_DECODE_PARTIAL), (ag_decode_kernel<T, D, G, NW>), dim3(blocks), dim3(64 * NW), shmem, s, a);
+  AG_LAUNCH(ag_time_kernel(ctx, AG_K_DECODE_PARTIAL), (ag_decode_kernel<T, D, G, NW, EVEN>), dim3(blocks), dim3(64 * NW), shmem, s, a);
   ag_tock(ctx, AG_K_DECODE_MERGE, s);
   return hipGetLastError();
 }
@@ -968,7 +978,10 @@ hipError_t launch_t(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, 
   const int64_t records = max_records(a.U, total_rows);
   a.rec = ws.take<float>((size_t)records * G * (D + 2));
   if (!ws.ok) return hipSuccess;
-  return a.U <= kFewUnits ? launch_nw<T, D, G, 8>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4>(ctx, s, a, total_rows, records);
+  if constexpr (sizeof(T) == 2)
+    if ((((uintptr_t)a.kc | (uintptr_t)a.vc) & 15) != 0)
+      return a.U <= kFewUnits ? launch_nw<T, D, G, 8, true>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4, true>(ctx, s, a, total_rows, records);
+  return a.U <= kFewUnits ? launch_nw<T, D, G, 8, false>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4, false>(ctx, s, a, total_rows, records);
 }
 
 template <typename T, int D>

@@ -215,3 +215,30 @@ def test_decode_steps_of_different_sizes_from_several_threads(dtype, G, D):
         ag.ag_decode_attn(ctx, q, new, new, no, 9, 0.1, cache, out)
         assert torch.equal(o, out) and torch.isfinite(out.float()).all()
         ctx.close()
+
+
+@pytest.mark.parametrize("D,G,lens,by", [(128, 1, [40, 0, 700, 1300, 33], 1), (64, 4, [5, 900, 2100], 4), (128, 8, [6000], 3),
+                                         (128, 2, [70, 3, 31, 500] * 66, 5)])
+def test_decode_over_caches_at_any_even_address(D, G, lens, by):
+    """Caches that do not start at a multiple of 16 bytes: outputs, appended rows and lengths bit for bit those of aligned ones."""
+    U = len(lens)
+    wl = W.decode_batch(63, "even", "bf16", 1, U * G, U, D, np.asarray(lens, dtype=np.int32), 2, pos0=6100, fill_slack=float("nan"))
+    ctx = make_ctx(1, 1, U * G, U, D, ag.AG_BF16, cache_rows=int(wl.row_off[-1]))
+    got = []
+    for shift in (0, by):
+        cache = cache_from_host(1, U, D, wl.k_cache, wl.v_cache, wl.idx, wl.row_off, wl.len0)
+        if shift:
+            k, v = (torch.zeros(t.numel() + 8, dtype=t.dtype, device=DEV)[shift:shift + t.numel()].view(t.shape).copy_(t) for t in (cache.k, cache.v))
+            cache = ag.KVCache(k, v, cache.idx, cache.row_off, cache.len, 1, U, D)
+            assert k.data_ptr() % 16 == 2 * shift % 16
+        outs = []
+        for i in range(2):
+            q, kn, vn, flags = wl.step_inputs(i, 0.5)
+            outs.append(torch.empty_like(dev(q)))
+            ag.ag_decode_attn(ctx, dev(q), dev(kn), dev(vn), dev(flags), wl.pos0 + i, wl.scale, cache, outs[-1])
+        got.append(outs + [cache.k, cache.v, cache.idx, cache.len])
+    ctx.poll_error()
+    for a, b in zip(*got):
+        assert torch.equal(a.nan_to_num(-77.0), b.nan_to_num(-77.0))
+    assert torch.isfinite(got[0][0].float()).all() and torch.isfinite(got[0][1].float()).all()
+    ctx.close()
