@@ -529,8 +529,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     return win & ~bword;
   };
   // The value rows of the wave's own tokens (zeros for the others: an offset past the descriptor's end) -> the wave's
-  // quarter of the K buffers, chunks XOR-swizzled with the row.
-  auto issue_own_v = [&] {
+  // quarter of the K buffers, chunks XOR-swizzled with the row.  (Straight into LDS while the last step runs; where v is not
+  // 16-byte aligned, through registers after it -- but for the recent-token variant, whose band tiles take v directly in any
+  // case and which has no scalar registers left for the choice: 2 us of a launch of 64 heads x 1501 tokens.)
+  const bool v_direct = BAND || (reinterpret_cast<uintptr_t>(v) & 15) == 0;
+  auto issue_own_v = [&](bool through_regs) {
     const __amdgpu_buffer_rsrc_t vw_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(v + ((size_t)u * L + j0) * D), 0, own_bytes, 0x00020000);
     int lane_e = lane;  // (laundered: computed here, not kept in registers across the tile loop)
     asm volatile("" : "+v"(lane_e));
@@ -538,8 +541,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     for (int i = 0; i < 32 / RPI; ++i) {
       const int row = RPI * i + lane_e / CPR;
       const uint32_t off = ((own_rows >> row) & 1u) ? (uint32_t)(row * kRowB + (((lane_e % CPR) ^ geo::key(row)) << 4)) : kNowhere;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                   :: "s"((uint32_t)(size_t)((AG_LDS uint8_t *)smem) + w4 * 32 * kRowB + i * 1024), "v"(off), "s"(vw_rsrc) : "memory");
+      AG_LDS uint8_t *to = (AG_LDS uint8_t *)smem + w4 * 32 * kRowB + i * 1024;
+      if (through_regs) {
+        *reinterpret_cast<AG_LDS u32x4 *>(to + lane_e * 16) = __builtin_amdgcn_raw_buffer_load_b128(vw_rsrc, off, 0, 0);
+      } else {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :: "s"((uint32_t)(size_t)to), "v"(off), "s"(vw_rsrc) : "memory");
+      }
     }
   };
   // One pipeline step.  cur holds S^T of this group's tile of step i; nxt receives that of step i + 1.
@@ -551,7 +559,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     __syncthreads();                                  // ... and everyone's; step i-1 is fully consumed
     if (i + 2 < n_steps) issue_k(i + 2);
     if (i + 1 < n_steps) issue_v(i + 1);
-    else issue_own_v();  // the K buffers are both free in the last step
+    else if (v_direct) issue_own_v(false);  // the K buffers are both free in the last step
     const int c0 = (tile0 + i - n_band) * kBN;
     const bool vis_cur = vis(i);                                                 // wave-uniform
     const bool vis_nxt = i + 1 < n_steps && vis(i + 1);                          // wave-uniform
@@ -589,7 +597,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     }
   };
   f32x16 acc_a[2], acc_b[2];
-  if (n_steps == 0) issue_own_v();
+  if (n_steps == 0 && v_direct) issue_own_v(false);
   if (n_steps > 0) {
     if (n_steps > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LI) : "memory");  // K(0); V(0) and K(1) may be on their way
     else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LI) : "memory");
@@ -692,6 +700,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     const float inv = 1.f / (l_tot * f_run + f_own);
     const float g_run = f_run * inv, g_own = own ? f_own * inv : 0.f;  // out = g_run O + g_own v
     AG_LDS uint8_t *ost = (AG_LDS uint8_t *)smem + w4 * (32 * kRowB);
+    if (!v_direct) {
+      issue_own_v(true);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // one lane's store is another lane's load
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the own value rows are there
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)

@@ -221,3 +221,22 @@ def test_packed_cache_layout_cut_off_at_the_allocation():
     assert over == 3 and np.array_equal(cache.len.cpu().numpy(), rc.len) and rc.len[5] == 7 and (rc.len[6:] == 0).all()
     assert np.array_equal(cache.k.cpu().numpy()[:total], rc.k[:total])
     ctx.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,D,by", [(2, 2, 300, 128, 1), (8, 2, 77, 64, 4), (4, 1, 700, 128, 3), (2, 2, 33, 64, 7)])
+def test_prefill_bf16_of_tensors_at_any_even_address(Hq, Hkv, L, D, by):
+    """q, k, v and out that do not start at a multiple of 16 bytes: bit for bit what aligned ones give."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    q, k, v = (torch.randn(1, h, L, D, generator=g, device=DEV).bfloat16() for h in (Hq, Hkv, Hkv))
+    flags = (torch.rand(1, Hkv, L, generator=g, device=DEV) < 0.6).to(torch.uint8)
+    flags[:, :, :5], flags[:, 0] = 0, flags[:, 0] & (torch.arange(L, device=DEV) % 64 < 40)
+    moved = [torch.zeros(t.numel() + 8, dtype=t.dtype, device=DEV)[by:by + t.numel()].view(t.shape).copy_(t) for t in (q, k, v, q)]
+    ctx = make_ctx(1, L, Hq, Hkv, D, ag.AG_BF16)
+    got = []
+    for a, b, c, out in ((q, k, v, torch.empty_like(q)), moved):
+        cache = new_cache(1, Hkv, D, torch.bfloat16, oracle.slab_row_off(Hkv, L))
+        ag.ag_compact_prefill_attn(ctx, a, b, c, flags, 1.0 / math.sqrt(D), 0, cache, out)
+        got.append((out, cache.k, cache.v, cache.len))
+    assert all(torch.equal(x, y) for x, y in zip(*got)) and torch.isfinite(got[0][0].float()).all()
+    ctx.close()
