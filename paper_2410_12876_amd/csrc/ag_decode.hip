@@ -197,7 +197,7 @@ template <int D, int G, bool EVEN> struct wave_bf16 {
 #pragma unroll
     for (int i = 0; i < NL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off(i)), "s"(rsrc), "s"(i * RPI * kRowB) : "memory");
+                   :: "s"(dst + i * RPI * kRowB), "v"(ld_off(i)), "s"(rsrc), "s"(i * RPI * kRowB) : "m0", "memory");
   }
   __device__ __forceinline__ void load_k(const dec_tile &t) { load(t, t.k, 0); }
   __device__ __forceinline__ void load_v(const dec_tile &t) { load(t, t.v, kTileRows * kRowB); }

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
         __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, (uint32_t)d_in * (uint32_t)(RAW ? H_f : kNP) * 2u, 0x00020000);
     const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)wst);
     const int off = (((blockIdx.x >> 3) & 31) * 512 + threadIdx.x) * 16;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(off), "s"(w_rsrc) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(dst), "v"(off), "s"(w_rsrc) : "m0", "memory");
   }
   const int rows = (int)min(16u, tokens - tok0);
   const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -247,8 +247,8 @@ __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate_stream_kernel(
           __builtin_amdgcn_make_buffer_rsrc((void *)(x + (size_t)t0 * d_in), 0, rows * (uint32_t)d_in * 2u, 0x00020000);
       const uint32_t dst = ring_addr + slot_in * 2048;
       const int soff = (wave + kFusedWaves * ip) * 128;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(row_off[0]), "s"(rsrc), "s"(soff) : "memory");
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst + 1024), "v"(row_off[1]), "s"(rsrc), "s"(soff) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(row_off[0]), "s"(rsrc), "s"(soff) : "m0", "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst + 1024), "v"(row_off[1]), "s"(rsrc), "s"(soff) : "m0", "memory");
       slot_in = slot_in + 1 == kRing ? 0 : slot_in + 1;
       if (++ip == mine) { ip = 0; it += stride; }
     }

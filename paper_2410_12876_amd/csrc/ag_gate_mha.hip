@@ -120,11 +120,11 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
 #pragma unroll
     for (int i = 0; i < XL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(base + (wave * XL + i) * 1024), "v"(xoff[i]), "s"(x_rsrc), "s"(xs) : "memory");
+                   :: "s"(base + (wave * XL + i) * 1024), "v"(xoff[i]), "s"(x_rsrc), "s"(xs) : "m0", "memory");
 #pragma unroll
     for (int i = 0; i < WL; ++i)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(base + CFG::XTile + (wave * WL + i) * 1024), "v"(woff[i]), "s"(w_rsrc), "s"(ws) : "memory");
+                   :: "s"(base + CFG::XTile + (wave * WL + i) * 1024), "v"(woff[i]), "s"(w_rsrc), "s"(ws) : "m0", "memory");
   };
 
   // ---- loop-invariant LDS offsets of this lane's fragments ----

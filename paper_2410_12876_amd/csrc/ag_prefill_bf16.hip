@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     for (int i = 0; i < LI; ++i) {
       const uint32_t dk = ld_base + (i_step & 1) * kTileB + i * RPI * kRowB;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(dk), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "memory");
+                   :: "s"(dk), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "m0", "memory");
     }
   };
   auto issue_v = [&](int i_step) {
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     for (int i = 0; i < LI; ++i) {
       const uint32_t dv = ld_base + 2 * kTileB + (i_step & 1) * kTileB + i * RPI * kRowB;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(dv), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "memory");
+                   :: "s"(dv), "v"(ld_off[i]), "s"(rsrc), "s"(soff) : "m0", "memory");
     }
   };
   // ---- the query rows, and for the own tokens their keys ----
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
         *reinterpret_cast<AG_LDS u32x4 *>(to + lane_e * 16) = __builtin_amdgcn_raw_buffer_load_b128(vw_rsrc, off, 0, 0);
       } else {
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                     :: "s"((uint32_t)(size_t)to), "v"(off), "s"(vw_rsrc) : "memory");
+                     :: "s"((uint32_t)(size_t)to), "v"(off), "s"(vw_rsrc) : "m0", "memory");
       }
     }
   };

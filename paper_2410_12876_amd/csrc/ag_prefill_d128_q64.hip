@@ -125,7 +125,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int i = 0; i < LI; ++i) {
       const uint32_t dk = ld_base + (i_step & 1) * kTileB + i * 4 * kRowB;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(dk), "v"(ld_off[i]), "s"(k_rsrc), "s"(soff) : "memory");
+                   :: "s"(dk), "v"(ld_off[i]), "s"(k_rsrc), "s"(soff) : "m0", "memory");
     }
   };
   auto issue_v = [&](int i_step) {
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int i = 0; i < LI; ++i) {
       const uint32_t dv = ld_base + 2 * kTileB + (i_step & 1) * kTileB + i * 4 * kRowB;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                   :: "s"(dv), "v"(ld_off[i]), "s"(v_rsrc), "s"(soff) : "memory");
+                   :: "s"(dv), "v"(ld_off[i]), "s"(v_rsrc), "s"(soff) : "m0", "memory");
     }
   };
   if (n_steps > 0) { issue_k(0); issue_v(0); }
