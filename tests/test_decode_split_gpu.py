@@ -24,9 +24,17 @@ def _lib():
     ("bf16", 1, 4, 4, 128, [31, 32, 33, 0]),                    # one tile, its edges
     ("bf16", 1, 8, 8, 64, [1, 63, 64, 65, 1023, 1024, 1025, 2]),   # a unit of 32 tiles stays whole, 33 are cut (8 waves)
     ("bf16", 1, 8, 2, 128, [9000, 1025]),                       # few units, many pieces
-    ("bf16", 2, 32, 8, 128, [7000] * 15 + [3]),                 # more pieces than workgroups: equal ranges
-    ("bf16", 65, 4, 4, 128, [5, 170, 40, 480]),                 # 260 units: 4 waves, ranges that hold many units
+    ("bf16", 2, 32, 8, 128, [7000] * 15 + [3]),                 # more than one round of the launch: pieces of two rounds
+    # more than 64 units of more than two rounds: equal ranges, 8 waves
+    ("bf16", 24, 16, 4, 128, [1500, 2900, 3000, 1700]),
+    ("bf16", 32, 8, 4, 64, [2500, 3000, 1600]),
+    ("bf16", 50, 4, 4, 128, [3000, 1500, 2, 700, 2222]),
+    ("f32", 25, 8, 4, 64, [3000, 2000]),
+    ("f32", 25, 4, 4, 128, [3000, 2000]),
+    ("bf16", 65, 4, 4, 128, [5, 170, 40, 480]),                 # 260 units: 4 waves, a team of them per unit
+    ("bf16", 65, 8, 4, 128, [5, 1170, 40, 2480]),               # ... equal ranges, as one unit is long
     ("bf16", 100, 16, 4, 64, [600, 30, 2000, 0]),
+    ("f32", 68, 4, 4, 128, [40, 1500]),
     ("bf16", 1, 8, 1, 128, [12345]),                            # one unit, eight heads
     ("f32", 1, 4, 4, 64, [33, 992, 2500, 0]),
     ("f32", 70, 8, 4, 128, [7, 100, 31, 250]),
@@ -88,9 +96,10 @@ def test_decode_unit_of_more_than_four_gib():
     ctx.close()
 
 
-@pytest.mark.parametrize("D,lens", [(128, [40, 1, 500, 3000]), (64, [40, 1, 2100, 9000]), (128, [7000] * 40)])
+@pytest.mark.parametrize("D,lens", [(128, [40, 1, 500, 3000]), (64, [40, 1, 2100, 9000]), (128, [7000] * 40),
+                                    (128, [2000, 2500, 1800] * 32), (64, [3500, 2500, 2800, 2600] * 32)])
 def test_decode_infinite_values_stay_infinite(D, lens):
-    """An infinite value in the first, the last or the new row of a unit (whole units, pieces, equal ranges): its feature is
+    """An infinite value in the first, the last or the new row of a unit (whole units, pieces, equal ranges in the last two): its feature is
     that infinity, the others are the result without it.  The keys draw equal weights, so no weight rounds to 0."""
     lens = np.asarray(lens, dtype=np.int32)
     U = len(lens)
@@ -241,4 +250,51 @@ def test_decode_over_caches_at_any_even_address(D, G, lens, by):
     for a, b in zip(*got):
         assert torch.equal(a.nan_to_num(-77.0), b.nan_to_num(-77.0))
     assert torch.isfinite(got[0][0].float()).all() and torch.isfinite(got[0][1].float()).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype,U,G,D,lens,n_recent", [
+    ("bf16", 96, 1, 128, [1500, 2900, 40], 64),   # equal ranges of 8 waves: two ring tiles in front of every unit, also at cuts
+    ("bf16", 120, 4, 64, [2500, 900, 1300], 64),
+    ("f32", 100, 2, 64, [3000, 2000], 40),
+    ("bf16", 300, 2, 128, [1100, 30, 0], 33),     # ... of 4 waves
+    ("bf16", 9, 1, 128, [0, 700, 1500], 64),      # whole units and pieces
+    ("bf16", 300, 1, 64, [100, 0], 64)])          # a team of waves per unit
+def test_decode_ring_in_every_split(dtype, U, G, D, lens, n_recent):
+    """Ring slots of which some are evicted tokens inside the window, some kept ones, some outside or empty, holding NaN where
+    they are not to be seen; against the oracle over the cache rows followed by the visible slots."""
+    len0 = np.resize(np.asarray(lens, dtype=np.int32), U)
+    wl = W.decode_batch(64, "ring", dtype, 1, U * G, U, D, len0, 1, pos0=4000, fill_slack=float("nan"))
+    g = np.random.default_rng(U)
+    rk, rv = (W.store(g.standard_normal((U, n_recent, D)).astype(np.float32), dtype).f32 for _ in range(2))
+    pos = 4000 - 1 - (4000 - 1 - np.arange(n_recent)) % n_recent * np.ones((U, 1), dtype=np.int64)  # slot p % n: p in [pos - n, pos)
+    pos = np.where(g.random((U, n_recent)) < 0.2, -(1 << 30), pos).astype(np.int32)
+    kept = (g.random((U, n_recent)) < 0.4).astype(np.uint8)
+    see = (pos > 4000 - n_recent) & (pos < 4000) & (kept == 0)
+    assert see.any() and not see.all()
+    # the oracle's cache: a unit's rows, then its visible slots
+    n_see = see.sum(axis=1)
+    ro = np.concatenate([[0], np.cumsum(len0.astype(np.int64) + n_see + 1)])
+    ck, cv = np.zeros((int(ro[-1]), D), np.float32), np.zeros((int(ro[-1]), D), np.float32)
+    for u in range(U):
+        a, n, m = int(ro[u]), int(len0[u]), int(n_see[u])
+        src = int(wl.row_off[u])
+        ck[a:a + n], cv[a:a + n] = wl.k_cache.f32[src:src + n], wl.v_cache.f32[src:src + n]
+        ck[a + n:a + n + m], cv[a + n:a + n + m] = rk[u, see[u]], rv[u, see[u]]
+    ref = oracle.Cache(ck, cv, np.zeros(int(ro[-1]), np.int32), ro, (len0 + n_see).astype(np.int32))
+    q, kn, vn, _ = wl.step_inputs(0, 0.5)
+    want, _ = oracle.decode_step(q.f32, kn.f32, vn.f32, None, wl.pos0, ref, wl.scale)
+    rk[~see], rv[~see] = np.nan, np.nan
+    ring = ag.RecentRing(dev(W.store(rk, dtype)), dev(W.store(rv, dtype)), dev(kept), dev(pos), n_recent)
+    ctx = make_ctx(1, 1, U * G, U, D, ag.AG_BF16 if dtype == "bf16" else ag.AG_F32, cache_rows=int(wl.row_off[-1]))
+    cache = cache_from_host(1, U, D, wl.k_cache, wl.v_cache, wl.idx, wl.row_off, wl.len0)
+    out = torch.empty_like(dev(q))
+    print("ring", dtype, U, G, D, n_recent, flush=True)
+    ag.ag_decode_attn_recent(ctx, dev(q), dev(kn), dev(vn), None, 4000, wl.scale, cache, ring, out)
+    got = host_f32(out)
+    assert np.isfinite(got).all() and attn_error(dtype, got, want) <= attn_tolerance(dtype, want)
+    assert np.array_equal(cache.len.cpu().numpy(), len0 + 1)
+    slot = 4000 % n_recent
+    assert torch.equal(ring.k[:, slot], dev(kn)[0]) and (ring.pos[:, slot] == 4000).all() and (ring.flags[:, slot] == 1).all()
+    ctx.poll_error()
     ctx.close()
