@@ -57,7 +57,7 @@ ag_status need_device(ag_ctx *ctx) {
 
 }  // namespace
 
-constexpr size_t kTailBytes = 256 + (kDecodeMaxUnits + 1) * sizeof(int32_t);
+constexpr size_t kTailBytes = 256 + (kDecodeMaxUnits + kDecodeArriveInts) * sizeof(int32_t);
 
 extern "C" {
 

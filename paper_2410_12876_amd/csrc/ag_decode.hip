@@ -47,6 +47,7 @@ constexpr int kFewUnits = 256;   // up to here 8 waves per workgroup and one wor
 // Reference maximum before any row: the least finite number, so that no state that holds a row is below it (differences of
 // maxima stay numbers or become -infinity, of which the exponential is 0).
 constexpr float kEmptyMax = -3.40282347e+38f;
+constexpr int kArriveSplit = 64; // workgroups (of 4 waves) from which their arrivals are counted at several addresses
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -493,7 +494,7 @@ struct dec_args {
   void *out;
   float *rec;           // records [id][G][D + 2]: o, max, sum
   int32_t *tickets;     // [U] pieces of a unit that have stored their record; zero between launches
-  int32_t *arrived;     // [1] workgroups that have read len[]; zero between launches
+  int32_t *arrived;     // [kDecodeArriveInts] workgroups that have read len[] (see arrive); zero between launches
   int32_t *d_err;
   int U, pos, max_wgs;  // max_wgs: workgroups the equal-range split may use (two records each)
   int team;             // waves per unit where every unit can have its own (4-wave workgroups; else unused)
@@ -555,7 +556,16 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   // The lengths may only change once every workgroup has read them.  Each one counts its arrival when all its waves have
   // (4 waves: after the barrier below; 8 waves, which need no barrier before their first merge: after that), and the one
   // that arrives last counts the appended rows, at its end.
-  int order = -1;
+  // At one address that takes 19 ns per workgroup, one after the other, which is the tail of a short step with one for every
+  // unit (264 units of up to 186 rows: 13.8 -> 9.4 us, 512: 14.9 -> 10.8): there they count at kDecodeArriveGroups addresses,
+  // and the last ones of those at one more.  With 8 waves, which count late and are fewer, the second trip costs more than it
+  // saves (64 units of up to 300 rows: 8.1 us, with it 9.1).
+  const int groups = !kRegs && (int)gridDim.x >= kArriveSplit ? kDecodeArriveGroups : 1;
+  int order = -1;  // (thread 0) place of this workgroup among those that count where it does
+  auto arrive = [&] {
+    order = __hip_atomic_fetch_add(a.arrived + (groups == 1 ? 0 : kDecodeArriveStride * (1 + wg % kDecodeArriveGroups)), 1,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   if constexpr (kRegs) {
     int base_t[UPL], base_i[UPL], cnt_t[UPL], cnt_i[UPL];
 #pragma unroll
@@ -635,7 +645,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
     for (int o = 32; o > 0; o >>= 1) max_t = max(max_t, __shfl_xor(max_t, o, 64));
     if (lane == 0) { w_sum[wave][0] = sum_t; w_sum[wave][1] = max_t; }
     __syncthreads();
-    if (tid == 0) order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) arrive();
     int base = pre;
     max_t = 0;
 #pragma unroll
@@ -761,8 +771,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
       });
     wv.leave((AG_LDS float *)my_lds);
     __syncthreads();
-    if (kRegs && tid == 0 && (PIECE || order < 0))
-      order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kRegs && tid == 0 && (PIECE || order < 0)) arrive();
 
     // ---- merge the waves' states (every wave of the team left one); thread -> (head, two neighbouring columns) ----
     auto store_out = [&](int gg, int d, float A0, float A1, float L) {
@@ -892,8 +901,14 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   // ---- the last workgroup to arrive counts the appended rows ----
   __syncthreads();
   if (tid == 0) {
-    if (kRegs && order < 0) order = __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = order == (int)gridDim.x - 1;
+    if (kRegs && order < 0) arrive();
+    int last = (int)gridDim.x - 1;
+    if (groups > 1) {
+      const int mine = ((int)gridDim.x - wg % kDecodeArriveGroups + kDecodeArriveGroups - 1) / kDecodeArriveGroups;  // that count with this one
+      order = order == mine - 1 ? __hip_atomic_fetch_add(a.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+      last = kDecodeArriveGroups - 1;
+    }
+    s_last = order == last;
   }
   __syncthreads();
   if (!s_last) return;
@@ -913,7 +928,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
         if (v0 + j * NT < U && f[j] != 0 && s_len[v0 + j * NT] < 0) a.len[v0 + j * NT] = (s_len[v0 + j * NT] & 0x7fffffff) + 1;
     }
   }
-  if (tid == 0) *a.arrived = 0;
+  if (tid <= kDecodeArriveGroups) a.arrived[kDecodeArriveStride * tid] = 0;
 }
 
 // After prefilling: the ring takes the last min(L, n_recent) prompt tokens of every unit (kept or not); the other

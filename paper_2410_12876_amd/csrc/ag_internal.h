@@ -13,6 +13,8 @@ enum { AG_K_GATE = 0, AG_K_GATE_FINALIZE, AG_K_FLAG_SCAN, AG_K_COMPACT, AG_K_PRE
        AG_K_DECODE_MERGE, AG_K_MHA_PROJ, AG_K_MHA_ATTN, AG_K_NORM_GATE, AG_K_COUNT };
 constexpr int kTimerSlots = 1024;  // launches remembered per kernel id
 constexpr int kDecodeMaxUnits = 8192;  // (batch, KV head) units of one decode step
+constexpr int kDecodeArriveGroups = 16, kDecodeArriveStride = 64;  // counters of a step's workgroups, 256 bytes apart
+constexpr int kDecodeArriveInts = (1 + kDecodeArriveGroups) * kDecodeArriveStride;
 constexpr size_t kStaticScratchBytes = size_t(16) << 20;  // per-GPU static scratch of ag_decode_attn_static
 
 struct ag_timer {
@@ -26,7 +28,7 @@ struct ag_ctx {
   char *ws;         // device workspace
   size_t ws_bytes;
   int32_t *d_err;   // sticky device error word (bit 0: cache capacity overflow)
-  int32_t *decode_tickets;  // [kDecodeMaxUnits + 1] arrival counters of a decode step: zero between launches
+  int32_t *decode_tickets;  // [kDecodeMaxUnits + kDecodeArriveInts] arrival counters of a decode step: zero between launches
   char *static_scratch;   // this device's copy of the library's static scratch array (ag_decode_attn_static)
   bool timing;
   ag_timer timers[AG_K_COUNT];
