@@ -17,12 +17,12 @@
 //   * Segments (what a workgroup works on between two merges) are chosen on the device.  If the whole step gives every
 //     workgroup at most one segment -- a unit of up to 2 rounds of its waves stays whole, a longer one is cut into the
 //     smallest pieces that fit the launch -- a unit's pieces meet once; otherwise the tiles of all units are laid end to end and cut
-//     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.  Many short units (more
-//     than a CU-filling launch has workgroups for) are given to single waves or pairs of them instead, all at once.
+//     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.  More than kFewUnits units of a
+//     few rounds each are given to four, two or one wave each instead, all at once.
 //   * A unit inside one workgroup is finished there, through LDS.  The pieces of a longer one are stored as records
 //     (written through, complete before the arrival is counted); the piece that arrives last merges them in order.
 //   * A short step costs instructions as much as memory round trips (two waves share a SIMD, so each vector instruction of
-//     the straight-line path is 8 cycles): up to 256 units every wave builds the work list in its own registers, without
+//     the straight-line path is 8 cycles): up to 128 units every wave builds the work list in its own registers, without
 //     LDS and barriers, and all addresses are one XOR away from a base.
 #include <algorithm>
 #include <atomic>
@@ -41,9 +41,11 @@ namespace {
 
 constexpr int kChunk = 128;      // cache rows per record of scratch space (ag_decode_scratch_bytes)
 constexpr int kTileRows = 32;    // rows a wave takes at a time
-constexpr int kFewUnits = 256;   // up to here 8 waves per workgroup and one workgroup per CU: a unit's rows are spread over
+constexpr int kFewUnits = 128;   // up to here 8 waves per workgroup and one workgroup per CU: a unit's rows are spread over
                                  // as many waves as LDS can feed; beyond, 4 waves and two workgroups per CU, so that one
-                                 // streams while the other merges
+                                 // streams while the other merges.  (160 to 256 units on 8 waves: whole workgroups for short
+                                 // units, 256 of up to 100 rows 10.9 us against 7.2 on 4; equal ranges for long ones, 224 of up
+                                 // to 700 rows 20.8 against 12.6.  128 units are level.)
 // Reference maximum before any row: the least finite number, so that no state that holds a row is below it (differences of
 // maxima stay numbers or become -infinity, of which the exponential is 0).
 constexpr float kEmptyMax = -3.40282347e+38f;
@@ -521,7 +523,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   typedef typename wave_of<T, D, G, EVEN>::type wave_t;
   constexpr int NT = 64 * NW, SF = wave_t::kStateF;
   constexpr int CPT = (int)(D * sizeof(T) / 16);  // 16-byte chunks per row
-  constexpr bool kRegs = NW == 8;                 // the work list lives in registers (at most 256 units)
+  constexpr bool kRegs = NW == 8;                 // the work list lives in registers (at most kFewUnits units)
   constexpr int UPL = kFewUnits / 64;             // ... that many units per lane: unit 64 j + lane
   // The arguments lie in three cache lines of memory that may be far away: all of them are requested here, in one trip,
   // instead of one line after the other as the code below comes to need them.
@@ -656,7 +658,10 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
     }
     // Every unit at once, on a.team waves each, if none of them takes longer than 8 rounds of those: then one pass
     // (no merges, or one of two or four waves) is cheaper than several units one after the other on the whole workgroup.
-    by_piece = (int64_t)U * a.team <= (int64_t)gridDim.x * NW && max_t <= 8 * a.team && extra <= a.team;
+    // (6 rounds of 16 KiB where a few CUs would get a second unit and the others wait for them: 264 units of up to 1000 rows
+    // of 256 bytes 22.4 us at once, 20.5 in equal ranges; from 300 units on the launch is even enough.)
+    const int most = D * sizeof(T) >= 256 && 2 * U > (int)gridDim.x && 16 * U <= 9 * (int)gridDim.x ? 6 : 8;
+    by_piece = (int64_t)U * a.team <= (int64_t)gridDim.x * NW && max_t <= most * a.team && extra <= a.team;
     if (by_piece) {
       team = a.team;
       u = wg * (NW / team) + wave / team;

@@ -25,14 +25,17 @@ def _lib():
     ("bf16", 1, 8, 8, 64, [1, 63, 64, 65, 1023, 1024, 1025, 2]),   # a unit of 32 tiles stays whole, 33 are cut (8 waves)
     ("bf16", 1, 8, 2, 128, [9000, 1025]),                       # few units, many pieces
     ("bf16", 2, 32, 8, 128, [7000] * 15 + [3]),                 # more than one round of the launch: pieces of two rounds
-    # more than 64 units of more than two rounds: equal ranges, 8 waves
+    # 65 to 128 units of more than two rounds: equal ranges, 8 waves
     ("bf16", 24, 16, 4, 128, [1500, 2900, 3000, 1700]),
     ("bf16", 32, 8, 4, 64, [2500, 3000, 1600]),
-    ("bf16", 50, 4, 4, 128, [3000, 1500, 2, 700, 2222]),
     ("f32", 25, 8, 4, 64, [3000, 2000]),
     ("f32", 25, 4, 4, 128, [3000, 2000]),
-    ("bf16", 65, 4, 4, 128, [5, 170, 40, 480]),                 # 260 units: 4 waves, a team of them per unit
-    ("bf16", 65, 8, 4, 128, [5, 1170, 40, 2480]),               # ... equal ranges, as one unit is long
+    # more than 128 units: 4 waves, a team of them per unit, or equal ranges where one unit is long for that
+    ("bf16", 43, 3, 3, 128, [5, 170, 40, 480]),
+    ("bf16", 65, 4, 4, 128, [5, 170, 40, 480]),
+    ("bf16", 66, 4, 4, 128, [900, 40, 1000]),                   # 264 units: 8 of 256 CUs would have two, so equal ranges from 6 rounds on
+    ("bf16", 50, 4, 4, 128, [3000, 1500, 2, 700, 2222]),
+    ("bf16", 65, 8, 4, 128, [5, 1170, 40, 2480]),
     ("bf16", 100, 16, 4, 64, [600, 30, 2000, 0]),
     ("f32", 68, 4, 4, 128, [40, 1500]),
     ("bf16", 1, 8, 1, 128, [12345]),                            # one unit, eight heads
