@@ -376,7 +376,7 @@ def config5_stack_leg(args, torch, ag, W):
             "prompt_ms_all_layers": t_prompt * 1e3, "prompt_tokens_per_s": B * L / t_prompt,
             "decode_tokens": tokens, "decode_ms_per_token": t_dec / tokens * 1e3,
             "decode_tokens_per_s": B * tokens / t_dec, "decode_bytes_per_token": byts,
-            "decode_gbs": byts * tokens / t_dec / 1e9, "decode_launches_per_token": 2 * layers,
+            "decode_gbs": byts * tokens / t_dec / 1e9, "decode_launches_per_token": layers,
             "seconds_prompt_plus_decode": t_prompt + t_dec}
 
 
@@ -621,8 +621,8 @@ def cpu_baseline(wl, W):
 # profiles/bench_cfg2_prefill_cfg3_decode_hbm_traffic.md (2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE, in KiB, the
 # factors calibrated on the 1 GiB copy kernel); they hold for the default workloads only.
 TRAFFIC_BYTES = {
-    ("prefill", 4096): int((2.0 * 65671 + 39503) * 1024),
-    ("decode", 32, 256): int((2.0 * 575995 + 1150) * 1024),
+    ("prefill", 4096): int((2.0 * 65530 + 39503) * 1024),
+    ("decode", 32, 256): int((2.0 * 576003 + 1151) * 1024),
 }
 
 

@@ -23,8 +23,8 @@
  *     with events); give work that is meant to run concurrently a context of its own.
  *   - Flags: uint8, 1 (any non-zero) = retain, 0 = evict, stored head-major [B, Hkv, L].
  *   - GQA: query head i reads KV head i / (Hq / Hkv); flags and caches are per KV head.
- *   - Supported: dtype bf16 with D = 128 or 64 (MFMA path) and fp32 with D <= 256 (plain-ALU path);
- *     H_f <= 32; Hq / Hkv in {1, 2, 4, 8}.
+ *   - Supported: dtype bf16 with D = 128 or 64 and fp32 with D = 32, 64, 128 or 256 (decode: 64 or 128), all on the
+ *     matrix cores but the fp32 decode; H_f <= 32; Hq / Hkv in {1, 2, 4, 8}.
  */
 #ifndef AG_H
 #define AG_H
@@ -235,8 +235,8 @@ ag_status ag_decode_attn(ag_ctx *ctx, void *hip_stream, const void *q, const voi
 
 /*
  * ag_decode_attn for callers that cannot allocate device memory or be handed a workspace: code running under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and same
- * results as ag_decode_attn, but the per-item records that the two decode kernels exchange live in a static
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernel and same
+ * results as ag_decode_attn, but the records that the workgroups of a step exchange live in a static
  * device array of the library (ag_decode_static_scratch_bytes() = 16 MiB per GPU, held until the process ends)
  * instead of the context's workspace; the call allocates and frees nothing and a context made with
  * workspace_bytes = 0 is enough.  The array's device address is looked up once per GPU inside ag_create.

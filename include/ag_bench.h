@@ -21,7 +21,8 @@ extern "C" {
  * duration and the number of launches of one kernel id in [0, ag_timing_kernels()).
  * Ids: 0 gate (GEMM), 1 gate_finalize, 2 flag_scan, 3 compact, 4 prefill, 5 decode_partial, 6 decode_merge,
  * 7 mha_proj, 8 mha_attn, 9 norm_gate; ag_timing_kernel_name gives the names.  A decode step is one launch that also
- * merges: ids 5 and 6 both time it (5 attached to the launch, 6 bracketing it).
+ * merges: ids 5 and 6 both time it (5 attached to the launch, 6 bracketing it), so a sum over the ids leaves one of them
+ * out.  Id 1 is not used any more (the gate is one launch): it reads 0 launches.
  */
 int ag_timing_kernels(void);
 const char *ag_timing_kernel_name(int kernel_id);

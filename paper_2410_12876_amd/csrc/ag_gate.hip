@@ -134,8 +134,9 @@ constexpr int kFusedWaves = 8;
 // and ALL of W for every workgroup, 384 KiB at 4096 x 32 features, 2.7 us) and the LDS behind it, not HBM.  Hence
 // v_mfma_f32_16x16x32_bf16 (a 32-row MFMA would read every x fragment twice), chunks processed in the order they arrive
 // while the later ones are on their way, no column tile beyond H_f, and W's first touch spread over the chip: the
-// workgroups of an XCD each request a different 1/32 of W before anything else, so that it is in their L2 when 32 of
-// them want it at once; without that its lines queue behind the features of the whole launch.
+// workgroups of an XCD each request other 8 KiB of W's first 256 (all of it at 4096 x 32 features) before anything else, so
+// that they are in their L2 when 32 of them want them at once; without that its lines queue behind the features of the whole
+// launch.
 template <bool RAW, int PF>  // PF = chunks a wave keeps in flight
 __global__ __launch_bounds__(64 * kFusedWaves, 2) void ag_gate16_kernel(
     const uint16_t *__restrict__ x, const uint4 *__restrict__ wp, uint32_t tokens, int d_in, int L, int H_f,

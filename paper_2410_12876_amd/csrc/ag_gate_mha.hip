@@ -319,8 +319,8 @@ hipError_t launch_proj(ag_ctx *ctx, hipStream_t s, const void *x, const void *w,
 }
 
 // The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each takes on this chip
-// (measured over 64 to 16384 tokens, 1536 to 8192 columns, K = 1024, 2048 and 4096; the choice is within 3 % of the fastest
-// of the four there, and on no size more than 1 us slower than 128 x 128 tiles throughout).
+// (measured over 64 to 16384 tokens, 1536 to 8192 columns, K = 1024, 2048 and 4096; the choice is within 3 % (once 6 %) of the fastest
+// of the four there, and on no size more than 2 us slower than 128 x 128 tiles throughout).
 //   256 x 256: 1.13 PFLOP/s where there are tiles for whole rounds (8192 tokens x 8192 columns: 446 us; with 128 x 128
 //              tiles, which LDS bounds, 526); one tile takes 80 us.
 //   128 x 128: 1.0 PFLOP/s with two workgroups on every CU, and fills the chip from a quarter of the columns x tokens on.  In

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   // of 8 in the grid, (i / 8) % 4.  Where a row's groups -- n_hy / 8 heads times its chunks -- are 2, 4, ... an engine would
   // get the same group of every row: only second chunks, most of them empty, or always the head that keeps most (16 groups
   // of 4 heads x 1501 tokens: the first chunks, nearly all of the work, on two of the four engines; 50 us instead of
-  // 35).  So the groups of a row are rotated, by one every second row: for any number of groups each engine then
+  // 38).  So the groups of a row are rotated, by one every second row: for any number of groups each engine then
   // gets every group equally often (counted for 1 to 32).
   const int split_blocks = n_sp * n_hy * n_split;
   const bool in_split = (int)blockIdx.x < split_blocks;
