@@ -4,7 +4,7 @@
 // round trips.  The kernel therefore does everything in one launch -- it builds its own work list from len[] (no host
 // read-back), streams the rows, merges, takes in the new token and appends it -- and hands data between workgroups only
 // where a unit is too long for one.
-//   * Work is counted in tiles of 32 rows of one unit; a wave takes every NW-th tile of its workgroup's segment, so the
+//   * Work is counted in tiles of 32 rows (fp32: mostly 16) of one unit; a wave takes every NW-th tile of its workgroup's segment, so the
 //     waves run without a barrier until their segment ends.  The slots of the recent-token ring are extra tiles in front
 //     of a unit's cache rows; the new token's own key and value (the diagonal of Eq. 5) are the state one wave starts from.
 //   * bf16 runs on MFMA: K and V rows go from memory to the wave's own LDS by direct loads (whole rows; the next tile's K
@@ -15,7 +15,7 @@
 //     sum of p |v|: 0.9e-8 to 1.0e-8, as with products and sums on the vector ALU; with two bf16 numbers 3e-7.  (Third number:
 //     0.35 us per step of 8 units of up to 777 rows, nothing where memory is the bound.)  fp32 caches run on the vector ALU.
 //   * Segments (what a workgroup works on between two merges) are chosen on the device.  If the whole step gives every
-//     workgroup at most one segment -- a unit of up to 2 rounds of its waves stays whole, a longer one is cut into the
+//     workgroup at most one segment -- a unit of up to 2 rounds of its waves (kWholeRounds) stays whole, a longer one is cut into the
 //     smallest pieces that fit the launch -- a unit's pieces meet once; otherwise the tiles of all units are laid end to end and cut
 //     into equal ranges, one per workgroup, and only the units at the cuts cross workgroups.  More than kFewUnits units of a
 //     few rounds each are given to four, two or one wave each instead, all at once.
@@ -40,12 +40,12 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 namespace {
 
 constexpr int kChunk = 128;      // cache rows per record of scratch space (ag_decode_scratch_bytes)
-constexpr int kTileRows = 32;    // rows a wave takes at a time
-constexpr int kFewUnits = 128;   // up to here 8 waves per workgroup and one workgroup per CU: a unit's rows are spread over
-                                 // as many waves as LDS can feed; beyond, 4 waves and two workgroups per CU, so that one
-                                 // streams while the other merges.  (160 to 256 units on 8 waves: whole workgroups for short
-                                 // units, 256 of up to 100 rows 10.9 us against 7.2 on 4; equal ranges for long ones, 224 of up
-                                 // to 700 rows 20.8 against 12.6.  128 units are level.)
+// Up to here 8 waves per workgroup and one workgroup per CU: a unit's rows are spread over as many waves as LDS can feed; beyond,
+// 4 waves and two workgroups per CU, so that one streams while the other merges.  (160 to 256 units on 8 waves: whole workgroups
+// for short units, 256 of up to 100 rows 10.9 us against 7.2 on 4; equal ranges for long ones, 224 of up to 700 rows 20.8 against
+// 12.6.  128 units are level.  fp32, four heads of 128 per unit: 160 units of up to 500 rows 17.7 us on 8 waves, 24.7 on 4; 256 of
+// up to 30 rows 10.9 and 9.1, of up to 1000 rows 40.1 and 38.7.)
+template <typename T> constexpr int kFewUnits = sizeof(T) == 2 ? 128 : 192;
 // Reference maximum before any row: the least finite number, so that no state that holds a row is below it (differences of
 // maxima stay numbers or become -infinity, of which the exponential is 0).
 constexpr float kEmptyMax = -3.40282347e+38f;
@@ -135,7 +135,7 @@ __device__ __forceinline__ float kg_sum(float x) {
 // whatever its score is; a score that overflowed to -infinity counts as the least finite one; NaN stays NaN.
 __device__ __forceinline__ float own_max(float s, bool alone) { return alone ? 0.f : (s < kEmptyMax ? kEmptyMax : s); }
 
-// What a tile reads: 32 rows of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
+// What a tile reads: up to 32 rows of k and v; those whose bit in `vis` is clear are not seen (wave-uniform).
 struct dec_tile {
   const void *k, *v;  // the tile's first row (64-bit addresses: a unit's rows may span more than the 4 GiB a descriptor can)
   uint32_t bytes;     // cache rows: size of the rows that exist (the others read as zeros)
@@ -147,10 +147,13 @@ struct dec_tile {
 // Lane = (query head q = lane % 16, key group kg = lane / 16); heads q >= G are zero columns.  EVEN: the caches start at an
 // even address that is no multiple of 16; their rows go through registers (direct loads into LDS are not used for those).
 template <int D, int G, bool EVEN> struct wave_bf16 {
+  static constexpr int kTileRows = 32;                                   // rows a wave takes at a time
   static constexpr int kRowB = D * 2, CPR = kRowB / 16, RPI = 64 / CPR;  // RPI rows per load instruction
   static constexpr int NL = kTileRows / RPI;                             // load instructions per tile and operand
   static constexpr int kWaveB = 2 * kTileRows * kRowB;                   // the wave's LDS: K tile, V tile
   static constexpr int kStateF = D + 4;                                  // floats per head of the state a wave leaves
+  // rounds of the workgroup's waves up to which a unit stays whole, and up to which it is left to a team (see the kernel)
+  static constexpr int kWholeRounds = kRowB >= 256 ? 2 : 4, kTeamRounds = 8;
   static constexpr int KS = D / 32, DT = D / 16;
   bf16x8 qf[KS];
   f32x4 o[DT];
@@ -377,8 +380,16 @@ template <int D, int G, bool EVEN> struct wave_bf16 {
 // ---- fp32: one wave's pass on the vector ALU; each group of LPR lanes owns one row per load -------------------
 template <int D, int G> struct wave_f32 {
   static constexpr int EPL = 4, LPR = D / EPL, GPW = 64 / LPR;   // lanes per row, rows per load
+  // A round of 16 rows per wave takes up to 5 us (eight heads of 128: 64 products of 128 terms per lane group, and the next loads wait
+  // behind them), so tiles are what one batch of loads covers and little of a round is left over.  8 units of up to 500 rows, four
+  // and eight heads of 128 per unit: 21.3 and 34.9 us a step with tiles of 32 rows and units whole up to two rounds, 11.2 and 15.7
+  // with these; one head of 64 (32-row tiles): up to 1000 rows 7.5 whole up to two rounds, 9.6 up to four.  Teams: 256 units of up
+  // to 186 rows (three rounds), four and eight heads of 128: 14.8 and 22.0 us at once, 24.1 and 36.5 in equal ranges; at 8 (4) rounds
+  // about level; one head of 128 at 16 rounds 32.4 at once, 27.5 in ranges.
+  static constexpr int UN = G <= 2 ? 8 : 4;                      // rows in flight per lane group
+  static constexpr int kTileRows = UN * GPW > 16 ? UN * GPW : 16;
+  static constexpr int kWholeRounds = G * D >= 256 ? 1 : 2, kTeamRounds = G * D >= 1024 ? 4 : 8;
   static constexpr int NIT = kTileRows / GPW;                    // loads that cover a tile
-  static constexpr int UN = (G <= 2 ? 8 : 4) < NIT ? (G <= 2 ? 8 : 4) : NIT;  // rows in flight per lane group
   static constexpr int kStateF = D + 4;
   static constexpr int kWaveB = G * kStateF * 4;
   float4 qr[G];
@@ -522,9 +533,10 @@ template <typename T, int D, int G, int NW, bool EVEN>
 __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   typedef typename wave_of<T, D, G, EVEN>::type wave_t;
   constexpr int NT = 64 * NW, SF = wave_t::kStateF;
+  constexpr int kTileRows = wave_t::kTileRows, kWholeTiles = wave_t::kWholeRounds * NW;
   constexpr int CPT = (int)(D * sizeof(T) / 16);  // 16-byte chunks per row
   constexpr bool kRegs = NW == 8;                 // the work list lives in registers (at most kFewUnits units)
-  constexpr int UPL = kFewUnits / 64;             // ... that many units per lane: unit 64 j + lane
+  constexpr int UPL = kFewUnits<T> / 64;             // ... that many units per lane: unit 64 j + lane
   // The arguments lie in three cache lines of memory that may be far away: all of them are requested here, in one trip,
   // instead of one line after the other as the code below comes to need them.
   asm volatile("" :: "s"(a.q), "s"(a.len), "s"(a.U), "s"(a.ring.n));
@@ -538,7 +550,6 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
   const int extra = has_ring ? (a.ring.n + kTileRows - 1) / kTileRows : 0;
 
   // ---- the work list: tiles per unit (at least one), and the pieces it is cut into ----
-  constexpr int kWholeTiles = (D * sizeof(T) >= 256 ? 2 : 4) * NW;
   int piece = NW;  // tiles per piece: `rounds` rounds of the workgroup's waves
   uint32_t piece_inv = (uint32_t)((1ull << 32) / NW);  // ceil(2^32 / piece): x / piece for x piece < 2^32
   auto tiles_of = [&](int n) { return max(1, extra + (int)((unsigned)(n + kTileRows - 1) / kTileRows)); };
@@ -656,12 +667,12 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
       total_t += w_sum[w][0];
       max_t = max(max_t, w_sum[w][1]);
     }
-    // Every unit at once, on a.team waves each, if none of them takes longer than 8 rounds of those: then one pass
+    // Every unit at once, on a.team waves each, if none of them takes longer than 8 (kTeamRounds) rounds of those: then one pass
     // (no merges, or one of two or four waves) is cheaper than several units one after the other on the whole workgroup.
     // (6 rounds of 16 KiB where a few CUs would get a second unit and the others wait for them: 264 units of up to 1000 rows
     // of 256 bytes 22.4 us at once, 20.5 in equal ranges; from 300 units on the launch is even enough.)
-    const int most = D * sizeof(T) >= 256 && 2 * U > (int)gridDim.x && 16 * U <= 9 * (int)gridDim.x ? 6 : 8;
-    by_piece = (int64_t)U * a.team <= (int64_t)gridDim.x * NW && max_t <= most * a.team && extra <= a.team;
+    const int most = sizeof(T) == 2 && D == 128 && 2 * U > (int)gridDim.x && 16 * U <= 9 * (int)gridDim.x ? 6 : wave_t::kTeamRounds;
+    by_piece = (int64_t)U * a.team <= (int64_t)gridDim.x * NW && max_t <= most * a.team && (!has_ring || a.ring.n <= 32 * a.team);
     if (by_piece) {
       team = a.team;
       u = wg * (NW / team) + wave / team;
@@ -772,7 +783,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ag_decode_kernel(dec_args a) {
         }
         const size_t ring0 = ((size_t)u * a.ring.n + (size_t)i * kTileRows) * D;
         return dec_tile{static_cast<const T *>(a.ring.k) + ring0, static_cast<const T *>(a.ring.v) + ring0, 0u,
-                        (uint32_t)(ring_vis >> (32 * i)), true};
+                        (uint32_t)(ring_vis >> (kTileRows * i)), true};
       });
     wv.leave((AG_LDS float *)my_lds);
     __syncthreads();
@@ -969,8 +980,9 @@ template <typename T, int D, int G, int NW, bool EVEN>
 hipError_t launch_nw(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, int64_t records) {
   typedef typename wave_of<T, D, G, EVEN>::type wave_t;
   const size_t shmem = (size_t)NW * wave_t::kWaveB + (NW == 8 ? 0 : (size_t)a.U * 4);
-  // one workgroup per CU (8 waves) or two (4 waves); no more than the step can have pieces
-  const int64_t pieces = a.U + total_rows / (NW * kTileRows) + 1;
+  // one workgroup per CU (8 waves) or two (4 waves); no more than the step can have pieces, nor than there are records (a piece's
+  // record has the number of its workgroup)
+  const int64_t pieces = std::min<int64_t>(a.U + total_rows / (NW * wave_t::kTileRows) + 1, records);
   const int blocks = (int)std::min<int64_t>(NW == 8 ? ctx->num_cu : 2 * ctx->num_cu, pieces);
   a.max_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(records / 2, blocks));
   for (a.team = NW; a.team > 1 && (int64_t)a.U * a.team > (int64_t)blocks * NW;) a.team /= 2;
@@ -1000,8 +1012,8 @@ hipError_t launch_t(ag_ctx *ctx, hipStream_t s, dec_args a, int64_t total_rows, 
   if (!ws.ok) return hipSuccess;
   if constexpr (sizeof(T) == 2)
     if ((((uintptr_t)a.kc | (uintptr_t)a.vc) & 15) != 0)
-      return a.U <= kFewUnits ? launch_nw<T, D, G, 8, true>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4, true>(ctx, s, a, total_rows, records);
-  return a.U <= kFewUnits ? launch_nw<T, D, G, 8, false>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4, false>(ctx, s, a, total_rows, records);
+      return a.U <= kFewUnits<T> ? launch_nw<T, D, G, 8, true>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4, true>(ctx, s, a, total_rows, records);
+  return a.U <= kFewUnits<T> ? launch_nw<T, D, G, 8, false>(ctx, s, a, total_rows, records) : launch_nw<T, D, G, 4, false>(ctx, s, a, total_rows, records);
 }
 
 template <typename T, int D>

@@ -41,6 +41,15 @@ def _lib():
     ("bf16", 1, 8, 1, 128, [12345]),                            # one unit, eight heads
     ("f32", 1, 4, 4, 64, [33, 992, 2500, 0]),
     ("f32", 70, 8, 4, 128, [7, 100, 31, 250]),
+    # fp32: tiles of 16 rows (32 of D = 64 with one or two heads), whole up to one round, teams up to 8 (4 at eight heads of 128); 192 units are few
+    ("f32", 1, 64, 8, 128, [15, 16, 17, 0, 128, 129, 145, 500]),
+    ("f32", 1, 16, 8, 64, [256, 257, 1, 33, 16, 255, 2000, 31]),
+    ("f32", 24, 32, 8, 128, [186, 60, 0, 17]),
+    ("f32", 193, 4, 1, 128, [512, 30, 511]),
+    ("f32", 193, 4, 1, 128, [513, 0, 511]),
+    ("f32", 65, 32, 4, 128, [256, 30, 241, 16]),
+    ("f32", 65, 32, 4, 128, [257, 15]),
+    ("f32", 130, 16, 4, 64, [250, 241, 1]),                     # two waves a unit
 ])
 def test_decode_work_split(dtype, B, Hq, Hkv, D, lens):
     U = B * Hkv
@@ -262,7 +271,11 @@ def test_decode_over_caches_at_any_even_address(D, G, lens, by):
     ("f32", 100, 2, 64, [3000, 2000], 40),
     ("bf16", 300, 2, 128, [1100, 30, 0], 33),     # ... of 4 waves
     ("bf16", 9, 1, 128, [0, 700, 1500], 64),      # whole units and pieces
-    ("bf16", 300, 1, 64, [100, 0], 64)])          # a team of waves per unit
+    ("bf16", 300, 1, 64, [100, 0], 64),           # a team of waves per unit
+    ("f32", 1, 8, 128, [65], 64),                 # fp32: four ring tiles; fewer records than pieces of one round
+    ("f32", 9, 8, 128, [0, 700, 150], 64),
+    ("f32", 300, 2, 64, [100, 0], 64),
+    ("f32", 600, 4, 64, [60, 0, 17], 49)])
 def test_decode_ring_in_every_split(dtype, U, G, D, lens, n_recent):
     """Ring slots of which some are evicted tokens inside the window, some kept ones, some outside or empty, holding NaN where
     they are not to be seen; against the oracle over the cache rows followed by the visible slots."""
