@@ -57,7 +57,7 @@ ag_status need_device(ag_ctx *ctx) {
 
 }  // namespace
 
-constexpr size_t kTailBytes = 256 + (kDecodeMaxUnits + kDecodeArriveInts) * sizeof(int32_t);
+constexpr size_t kTailBytes = 256 + (kDecodeMaxUnits + kDecodeArriveInts + kPrefillTickets) * sizeof(int32_t);
 
 extern "C" {
 
@@ -81,6 +81,7 @@ ag_status ag_create(ag_ctx **out, int device, size_t workspace_bytes) {
     if (e == hipSuccess) {  // behind the workspace: the error word and the arrival counters, all zero
       ctx->d_err = reinterpret_cast<int32_t *>(ctx->ws + ctx->ws_bytes);
       ctx->decode_tickets = reinterpret_cast<int32_t *>(ctx->ws + ctx->ws_bytes + 256);
+      ctx->prefill_tickets = ctx->decode_tickets + kDecodeMaxUnits + kDecodeArriveInts;
       e = hipMemset(ctx->d_err, 0, kTailBytes);
     }
     if (e == hipSuccess) e = ag_static_scratch(device, &ctx->static_scratch);

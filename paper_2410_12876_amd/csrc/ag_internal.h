@@ -15,6 +15,7 @@ constexpr int kTimerSlots = 1024;  // launches remembered per kernel id
 constexpr int kDecodeMaxUnits = 8192;  // (batch, KV head) units of one decode step
 constexpr int kDecodeArriveGroups = 16, kDecodeArriveStride = 64;  // counters of a step's workgroups, 256 bytes apart
 constexpr int kDecodeArriveInts = (1 + kDecodeArriveGroups) * kDecodeArriveStride;
+constexpr int kPrefillTickets = 8192;  // arrival counters of the prefill items that are cut into chunks
 constexpr size_t kStaticScratchBytes = size_t(16) << 20;  // per-GPU static scratch of ag_decode_attn_static
 
 struct ag_timer {
@@ -29,6 +30,7 @@ struct ag_ctx {
   size_t ws_bytes;
   int32_t *d_err;   // sticky device error word (bit 0: cache capacity overflow)
   int32_t *decode_tickets;  // [kDecodeMaxUnits + kDecodeArriveInts] arrival counters of a decode step: zero between launches
+  int32_t *prefill_tickets; // [kPrefillTickets] arrival counters of a prefill launch without a flag scan: zero between launches
   char *static_scratch;   // this device's copy of the library's static scratch array (ag_decode_attn_static)
   bool timing;
   ag_timer timers[AG_K_COUNT];
@@ -127,6 +129,7 @@ struct ag_pf_plan {
   int n_hy, HB, BM, n_items, n_split, slots, max_tiles;
   int NW;                // waves per workgroup of the prefill kernel (4 or 8)
   int head_major;        // block order of the prefill kernel: a head's query tiles together (many heads)
+  int chunk_tiles_all;   // the same where the host knows it (chunk_tiles == NULL)
   int n_sp;              // query-tile rows (the longest ones) that can hold an item longer than one chunk
 };
 

@@ -48,8 +48,9 @@ template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
 }
 
 // GB = query heads of one KV group per workgroup (one per wave).  n_split = chunks per item in the grid,
-// chunk_tiles_dev = key tiles per chunk (device value, NULL without a split); part = partial states
-// [item][chunk][4 waves][66][64] fp32 and tickets = per-item arrival counters (n_split > 1).
+// chunk_tiles_dev = key tiles per chunk (device value; NULL: chunk_tiles_all); part = partial states
+// [item][chunk][4 waves][66][64] fp32 and tickets = per-item arrival counters (n_split > 1), left at zero.
+// words == NULL: every token is kept (words, blk_off and row_off are not read) and unit u's rows are k, v [u L, (u + 1) L).
 // BAND = the recent-token variant (Table 6 of the appendix): the evicted tokens among the n_recent - 1 tokens just before a query
 // stay visible to it.  They are read from the uncompacted K/V as up to three extra 64-key "band" tiles that run
 // through the same pipeline ahead of the compacted tiles of chunk 0, with their own mask.
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     const uint64_t *__restrict__ words, const int32_t *__restrict__ blk_off, const uint16_t *__restrict__ kc,
     const uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off, int L, int Hq, int Hkv, int nw, int n_hy,
-    int n_split, int n_sp, const int32_t *__restrict__ chunk_tiles_dev, float qscale, int n_recent,
+    int n_split, int n_sp, const int32_t *__restrict__ chunk_tiles_dev, int chunk_tiles_all, float qscale, int n_recent,
     const int32_t *__restrict__ order, int head_major, uint16_t *__restrict__ out, int out_token_major,
     float *__restrict__ part, int32_t *__restrict__ tickets) {
   typedef pf_geom<D> geo;
@@ -144,10 +145,15 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   const int32_t *bo = blk_off + (size_t)u * (nw + 1);
   const int jw = min(j0, L - 1) >> 6;                         // mask word of this wave's queries
   const int jb = min(qtile * BM + BM - 1, L - 1);             // last query of the workgroup
-  const uint64_t word_w = wu[jw], word_b = wu[jb >> 6];
-  const int pre_w = bo[jw], pre_b = bo[jb >> 6], kept_u = bo[nw];
-  const int chunk_tiles = chunk_tiles_dev ? *chunk_tiles_dev : 0x7fffffff / kBN;
-  const int64_t ro0 = row_off[u], ro1 = row_off[u + 1];
+  uint64_t word_w = ~0ull, word_b = ~0ull;
+  int pre_w = 64 * jw, pre_b = jb & ~63, kept_u = L;
+  int64_t ro0 = (int64_t)u * L, ro1 = ro0 + L;
+  if (words) {
+    word_w = wu[jw]; word_b = wu[jb >> 6];
+    pre_w = bo[jw]; pre_b = bo[jb >> 6]; kept_u = bo[nw];
+    ro0 = row_off[u]; ro1 = row_off[u + 1];
+  }
+  const int chunk_tiles = chunk_tiles_dev ? *chunk_tiles_dev : chunk_tiles_all;
   auto cnt_in = [](uint64_t w, int pre, int j) -> int { return pre + (int)__popcll(w & ((1ull << (j & 63)) - 1ull)); };
   const int len_u = (int)min((int64_t)kept_u, ro1 - ro0);
   // A kept token's own key and value are row cnt(j) of the compacted rows, so its visible set is simply the first
@@ -645,6 +651,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
       last = __hip_atomic_fetch_add(&tickets[item], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
     __syncthreads();
     if (!last) return;
+    if (tid == 0) tickets[item] = 0;  // ready for the next launch
     auto peek = [](const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
     float m = m_run;
     for (int c = 0; c < n_chunks; ++c)
@@ -764,11 +771,12 @@ void ag_prefill_bf16_plan(int num_cu, int B, int L, int Hq, int Hkv, int D, ws_c
   plan->max_tiles = (L + kBN - 1) / kBN;
   plan->slots = (8 / plan->NW) * num_cu;
   plan->n_split = 1;
+  plan->chunk_tiles_all = 0x7fffffff / kBN;
   // Two chunks at most per item, unless the items are so few (few heads) that even their halves leave workgroup
   // slots empty: then more, until the chunks cover the slots (the merge adds the states in chunk order, so it stays
   // reproducible).  Measured with 4 heads x 4096 all-kept tokens: 2 chunks 54 us, up to 4 chunks 49.5 us, up to 8
   // chunks 68 us -- the chunk that arrives last fetches the other states one after the other.
-  if (items < (int64_t)8 * num_cu && plan->max_tiles > 16) {
+  if (items < (int64_t)8 * num_cu && items <= kPrefillTickets && plan->max_tiles > 16) {
     plan->n_split = 2;
     while (items * plan->n_split < (int64_t)plan->slots && plan->n_split < 8 && plan->max_tiles / (2 * plan->n_split) >= 8)
       plan->n_split *= 2;
@@ -815,13 +823,13 @@ hipError_t ag_launch_prefill_bf16(hipStream_t s, const void *q, const void *k, c
   const int64_t blocks = plan.head_major ? (int64_t)((plan.n_hy + 7) / 8) * 8 * n_qt
                                          : (int64_t)plan.n_hy * (plan.n_sp * plan.n_split + (n_qt - plan.n_sp));
   const dim3 grid((unsigned)blocks), block(64 * plan.NW);
-  if (D == 128 && n_recent == 1 && ag_prefill_q64_enabled())  // 64 queries per wave: 2 waves per workgroup, same plan
+  if (D == 128 && n_recent == 1 && words && ag_prefill_q64_enabled())  // 64 queries per wave: 2 waves per workgroup, same plan
     return ag_launch_prefill_d128_q64(s, q, k, v, words, blk_off, L, Hq, Hkv, qscale, kc, vc, row_off, out, plan, part,
                                       out_token_major, ev, (unsigned)blocks);
 #define AG_PF(DD, GG, BB)                                                                                            \
   AG_LAUNCH(ev, (ag_prefill_bf16_kernel<DD, GG, BB, 4>), grid, block, 0, s, (const uint16_t *)q, (const uint16_t *)k,  \
             (const uint16_t *)v, words, blk_off, (const uint16_t *)kc, (const uint16_t *)vc, row_off, L, Hq, Hkv, nw,  \
-            plan.n_hy, plan.n_split, plan.n_sp, plan.chunk_tiles, qscale, n_recent, plan.order, plan.head_major,        \
+            plan.n_hy, plan.n_split, plan.n_sp, plan.chunk_tiles, plan.chunk_tiles_all, qscale, n_recent, plan.order, plan.head_major,        \
             (uint16_t *)out, out_token_major ? 1 : 0, part, plan.tickets)
 #define AG_PFD(DD)                                                                                   \
   do {                                                                                               \
