@@ -47,16 +47,18 @@ template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
+constexpr int kMaxChunks = 8;  // chunks that an item is cut into at most
+
 // GB = query heads of one KV group per workgroup (one per wave).  n_split = chunks per item in the grid,
-// chunk_tiles_dev = key tiles per chunk (device value; NULL: chunk_tiles_all); part = partial states
-// [item][chunk][4 waves][66][64] fp32 and tickets = per-item arrival counters (n_split > 1), left at zero.
-// words == NULL: every token is kept (words, blk_off and row_off are not read) and unit u's rows are k, v [u L, (u + 1) L).
+// chunk_tiles_dev = key tiles per chunk (device value, NULL without a split; ALL: chunk_tiles_all); part = partial states
+// [item][chunk][4 waves][66][64] fp32 and tickets = per-item arrival counters (n_split > 1; ALL: left at zero).
+// ALL: every token is kept (words, blk_off and row_off are not read) and unit u's rows are k, v [u L, (u + 1) L).
 // BAND = the recent-token variant (Table 6 of the appendix): the evicted tokens among the n_recent - 1 tokens just before a query
 // stay visible to it.  They are read from the uncompacted K/V as up to three extra 64-key "band" tiles that run
 // through the same pipeline ahead of the compacted tiles of chunk 0, with their own mask.
 // NW = waves per workgroup: 4 (two workgroups per CU).  (8, one workgroup per CU with twice the queries sharing
 // every K/V tile, also works without the band variant but is slower: the whole CU then moves in step.)
-template <int D, int GB, bool BAND, int NW>
+template <int D, int GB, bool BAND, int NW, bool ALL = false>
 __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void ag_prefill_bf16_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     const uint64_t *__restrict__ words, const int32_t *__restrict__ blk_off, const uint16_t *__restrict__ kc,
@@ -96,7 +98,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   // get the same group of every row: only second chunks, most of them empty, or always the head that keeps most (16 groups
   // of 4 heads x 1501 tokens: the first chunks, nearly all of the work, on two of the four engines; 50 us instead of
   // 38).  So the groups of a row are rotated, by one every second row: for any number of groups each engine then
-  // gets every group equally often (counted for 1 to 32).
+  // gets every group equally often (counted for 1 to 32).  The same holds for fewer than 8 heads whose chunks fill whole
+  // groups (4 heads x 8000 tokens in 4 chunks, two groups a row: 120 us with the first chunks on two engines, 98 rotated); a
+  // rotation by whole groups leaves every head on its XCDs.
   const int split_blocks = n_sp * n_hy * n_split;
   const bool in_split = (int)blockIdx.x < split_blocks;
   const int i_part = in_split ? (int)blockIdx.x : (int)blockIdx.x - split_blocks;
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   const int row = i_part / per_qt;
   int qt_idx = in_split ? row : n_sp + row;
   int rem = i_part - row * per_qt, chunk = 0;
-  if ((n_hy & 7) == 0 && !head_major) rem = (rem + 8 * (qt_idx >> 1)) % per_qt;
+  if ((per_qt & 7) == 0 && !head_major) rem = (rem + 8 * (qt_idx >> 1)) % per_qt;
   if (in_split) {
     chunk = rem / n_hy;
     rem -= chunk * n_hy;
@@ -148,12 +152,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   uint64_t word_w = ~0ull, word_b = ~0ull;
   int pre_w = 64 * jw, pre_b = jb & ~63, kept_u = L;
   int64_t ro0 = (int64_t)u * L, ro1 = ro0 + L;
-  if (words) {
+  if constexpr (!ALL) {
     word_w = wu[jw]; word_b = wu[jb >> 6];
     pre_w = bo[jw]; pre_b = bo[jb >> 6]; kept_u = bo[nw];
     ro0 = row_off[u]; ro1 = row_off[u + 1];
   }
-  const int chunk_tiles = chunk_tiles_dev ? *chunk_tiles_dev : chunk_tiles_all;
+  const int chunk_tiles = ALL ? chunk_tiles_all : chunk_tiles_dev ? *chunk_tiles_dev : 0x7fffffff / kBN;
   auto cnt_in = [](uint64_t w, int pre, int j) -> int { return pre + (int)__popcll(w & ((1ull << (j & 63)) - 1ull)); };
   const int len_u = (int)min((int64_t)kept_u, ro1 - ro0);
   // A kept token's own key and value are row cnt(j) of the compacted rows, so its visible set is simply the first
@@ -631,19 +635,30 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   // ---- an item cut into chunks: store this chunk's state; the chunk that arrives last merges and writes ----
   if (n_chunks > 1) {
     const size_t item = (size_t)qtile * n_hy + hy;
-    float *st = part + (item * n_split * NW + w4) * geo::kState + lane;  // state of chunk c at st + c * cstride
-    const size_t cstride = (size_t)NW * geo::kState;
-    // The states travel through memory between workgroups of one launch.  They are written through and read
-    // past the caches (system-scope relaxed accesses), so no cache-wide write-back or invalidate is needed: the
-    // stores are complete (vmcnt 0) before the workgroup's arrival is counted, and the last arrival reads after it.
-    float *mine = st + chunk * cstride;
+    // A wave's state: 4 DT pieces of [64 lanes][4 values], then [64 lanes][m, l].  The states travel through memory between
+    // workgroups of one launch.  They are written through and read past the caches (sc0 and sc1, as system-scope atomics
+    // would), so no cache-wide write-back or invalidate is needed: the stores are complete (vmcnt 0) before the
+    // workgroup's arrival is counted, and the last arrival reads after it.
+    constexpr int kStateB = geo::kState * 4, kThrough = 17;  // bytes of a wave's state; sc0 | sc1
+    const __amdgpu_buffer_rsrc_t p_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(part + item * n_split * NW * geo::kState), 0, n_split * NW * kStateB, 0x00020000);
+    const int w_off = __builtin_amdgcn_readfirstlane(w4) * kStateB;
+    auto at = [&](int c) -> int { return c * NW * kStateB + w_off; };  // chunk c's state of this wave
+    auto peek4 = [&](int c, int piece) -> f32x4 {
+      return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(p_rsrc, lane * 16, at(c) + piece * 1024, kThrough));
+    };
+    auto peek_ml = [&](int c) -> f32x2 {
+      return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(p_rsrc, lane * 8, at(c) + 4 * DT * 1024, kThrough));
+    };
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        __hip_atomic_store(&mine[(16 * dt + r) * 64], acc_o[dt][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&mine[16 * DT * 64], m_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&mine[(16 * DT + 1) * 64], l_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 x = {acc_o[dt][4 * r4], acc_o[dt][4 * r4 + 1], acc_o[dt][4 * r4 + 2], acc_o[dt][4 * r4 + 3]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), p_rsrc, lane * 16, at(chunk) + (4 * dt + r4) * 1024, kThrough);
+      }
+    const f32x2 ml = {m_run, l_run};
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ml), p_rsrc, lane * 8, at(chunk) + 4 * DT * 1024, kThrough);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // every wave's state is out
     __shared__ int last;
@@ -651,37 +666,68 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
       last = __hip_atomic_fetch_add(&tickets[item], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_chunks - 1;
     __syncthreads();
     if (!last) return;
-    if (tid == 0) tickets[item] = 0;  // ready for the next launch
-    auto peek = [](const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
-    float m = m_run;
-    for (int c = 0; c < n_chunks; ++c)
-      if (c != chunk) m = fmaxf(m, peek(&st[c * cstride + 16 * DT * 64]));
+    if (ALL && tid == 0) tickets[item] = 0;  // no flag scan clears them for the next launch
     // Rounded product + rounded product (never a fused multiply-add), so that the result does not depend on which chunk
     // arrives last: two chunks are one commutative addition of this chunk's registers and the other's state; more
     // are added in chunk order starting from zero, this chunk's own state read back like the others'.
+    // With three or more chunks what bounds this is the round trip to memory, so as many loads as registers allow are on their
+    // way together (the empty asm keeps the arithmetic behind them): 4 heads x 2000 tokens 22.9 -> 20.5 us.  With two it gives nothing.
+    float m;
     if (n_chunks == 2) {
-      const float f_mine = __builtin_amdgcn_exp2f(m_run - m);
-      l_run = mul_round(l_run, f_mine);
+      const f32x2 o_ml = peek_ml(1 - chunk);
+      const float m_c = o_ml[0], l_c = o_ml[1];
+      m = fmaxf(m_run, m_c);
+      const float f_mine = __builtin_amdgcn_exp2f(m_run - m), f = __builtin_amdgcn_exp2f(m_c - m);
+      l_run = mul_round_add(l_c, f, mul_round(l_run, f_mine));
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round(acc_o[dt][r], f_mine);
+        for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round_add(peek4(1 - chunk, 4 * dt + r / 4)[r % 4], f, mul_round(acc_o[dt][r], f_mine));
     } else {
+      // at most kMaxChunks chunks; a load past the last one repeats it and is not used
+      float mc[kMaxChunks], lc[kMaxChunks];
+#pragma unroll
+      for (int c = 0; c < kMaxChunks; ++c) {
+        const f32x2 c_ml = peek_ml(min(c, n_chunks - 1));
+        mc[c] = c_ml[0];
+        lc[c] = c_ml[1];
+      }
+      asm volatile("" ::: "memory");
+      m = mc[0];
+#pragma unroll
+      for (int c = 1; c < kMaxChunks; ++c) m = fmaxf(m, mc[c]);
       l_run = 0.f;
+#pragma unroll
+      for (int c = 0; c < kMaxChunks; ++c) {
+        mc[c] = __builtin_amdgcn_exp2f(mc[c] - m);
+        if (c < n_chunks) l_run = mul_round_add(lc[c], mc[c], l_run);
+      }
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[dt][r] = 0.f;
-    }
-    for (int c = 0; c < n_chunks; ++c) {
-      if (n_chunks == 2 && c == chunk) continue;
-      const float *sc = st + c * cstride;
-      const float f = __builtin_amdgcn_exp2f(peek(&sc[16 * DT * 64]) - m);
-      l_run = mul_round_add(peek(&sc[(16 * DT + 1) * 64]), f, l_run);
+      constexpr int DP = DT / 2, CP = 3;  // CP chunks x DP x 16 values on their way: 96 registers (128 spill)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+      for (int c0 = 0; c0 < kMaxChunks; c0 += CP) {
+        if (c0 >= n_chunks) break;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round_add(peek(&sc[(16 * dt + r) * 64]), f, acc_o[dt][r]);
+        for (int d0 = 0; d0 < DT; d0 += DP) {
+          f32x4 x[CP][4 * DP];
+#pragma unroll
+          for (int c = 0; c < CP; ++c)
+#pragma unroll
+            for (int g = 0; g < 4 * DP; ++g) x[c][g] = peek4(min(c0 + c, n_chunks - 1), 4 * d0 + g);
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int c = 0; c < CP; ++c)
+            if (c0 + c < n_chunks) {
+#pragma unroll
+              for (int dt = 0; dt < DP; ++dt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_o[d0 + dt][r] = mul_round_add(x[c][4 * dt + r / 4][r % 4], mc[c0 + c < kMaxChunks ? c0 + c : 0], acc_o[d0 + dt][r]);
+            }
+        }
+      }
     }
     m_run = m;
   }
@@ -774,11 +820,11 @@ void ag_prefill_bf16_plan(int num_cu, int B, int L, int Hq, int Hkv, int D, ws_c
   plan->chunk_tiles_all = 0x7fffffff / kBN;
   // Two chunks at most per item, unless the items are so few (few heads) that even their halves leave workgroup
   // slots empty: then more, until the chunks cover the slots (the merge adds the states in chunk order, so it stays
-  // reproducible).  Measured with 4 heads x 4096 all-kept tokens: 2 chunks 54 us, up to 4 chunks 49.5 us, up to 8
-  // chunks 68 us -- the chunk that arrives last fetches the other states one after the other.
+  // reproducible).  Measured with 4 heads x 4096 all-kept tokens: 2 chunks 54 us, up to 4 chunks 37.5 us, up to 8
+  // chunks 36 to 41 us, by the chunks' length -- more states through memory, and a start-up for each.
   if (items < (int64_t)8 * num_cu && items <= kPrefillTickets && plan->max_tiles > 16) {
     plan->n_split = 2;
-    while (items * plan->n_split < (int64_t)plan->slots && plan->n_split < 8 && plan->max_tiles / (2 * plan->n_split) >= 8)
+    while (items * plan->n_split < (int64_t)plan->slots && plan->n_split < kMaxChunks && plan->max_tiles / (2 * plan->n_split) >= 8)
       plan->n_split *= 2;
   }
   *part = nullptr;
@@ -826,8 +872,8 @@ hipError_t ag_launch_prefill_bf16(hipStream_t s, const void *q, const void *k, c
   if (D == 128 && n_recent == 1 && words && ag_prefill_q64_enabled())  // 64 queries per wave: 2 waves per workgroup, same plan
     return ag_launch_prefill_d128_q64(s, q, k, v, words, blk_off, L, Hq, Hkv, qscale, kc, vc, row_off, out, plan, part,
                                       out_token_major, ev, (unsigned)blocks);
-#define AG_PF(DD, GG, BB)                                                                                            \
-  AG_LAUNCH(ev, (ag_prefill_bf16_kernel<DD, GG, BB, 4>), grid, block, 0, s, (const uint16_t *)q, (const uint16_t *)k,  \
+#define AG_PF(DD, GG, BB, ...)                                                                                       \
+  AG_LAUNCH(ev, (ag_prefill_bf16_kernel<DD, GG, BB, 4, ##__VA_ARGS__>), grid, block, 0, s, (const uint16_t *)q, (const uint16_t *)k,  \
             (const uint16_t *)v, words, blk_off, (const uint16_t *)kc, (const uint16_t *)vc, row_off, L, Hq, Hkv, nw,  \
             plan.n_hy, plan.n_split, plan.n_sp, plan.chunk_tiles, plan.chunk_tiles_all, qscale, n_recent, plan.order, plan.head_major,        \
             (uint16_t *)out, out_token_major ? 1 : 0, part, plan.tickets)
@@ -839,7 +885,10 @@ hipError_t ag_launch_prefill_bf16(hipStream_t s, const void *q, const void *k, c
       if (GB == 1) { AG_PF(DD, 1, false); } else if (GB == 2) { AG_PF(DD, 2, false); } else { AG_PF(DD, 4, false); } \
     }                                                                                                \
   } while (0)
-  if (D == 128) AG_PFD(128); else if (D == 64) AG_PFD(64); else return hipErrorInvalidValue;
+  if (!words) {  // every token is kept: the attention inside the gate module
+    if (D != 128 || GB != 1 || n_recent != 1) return hipErrorInvalidValue;
+    AG_PF(128, 1, false, true);
+  } else if (D == 128) AG_PFD(128); else if (D == 64) AG_PFD(64); else return hipErrorInvalidValue;
 #undef AG_PFD
 #undef AG_PF
   return hipGetLastError();
