@@ -22,6 +22,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
@@ -59,13 +60,17 @@ struct ag_proj_compact {
 // wave (TM = TN = 2) the reads alone fill all of LDS's 128 bytes a cycle at the full MFMA rate; 64 x 128 per wave needs 96
 // and the loads' own writes 31.  And under that load the chip's power: the vendor library's 8192^3 product reaches
 // 1.24 PFLOP/s here.
-template <int BM_, int BN_, int WM_, int WN_, int BK_, int ST_> struct proj_cfg {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, ST = ST_;
-  static constexpr int NT = 64 * WM * WN, TM = BM / WM / 32, TN = BN / WN / 32;
+// KS = 2: two waves share each block of MFMA tiles, each taking half of the 16-k slabs of a stage; their sums meet at the end.  A
+// workgroup that has its CU to itself has two waves per SIMD then, and one issues while the other waits for LDS or the barrier, with no
+// more LDS reads than one wave would make (K = 4096, 1536 columns: 2000 tokens 39.8 -> 32.3 us, 4096 tokens 55.2 -> 51.2).
+template <int BM_, int BN_, int WM_, int WN_, int BK_, int ST_, int KS_ = 1> struct proj_cfg {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, ST = ST_, KS = KS_;
+  static constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 32, TN = BN / WN / 32;
   static constexpr int XRow = BK * 2, WRow = BN * 2;             // bytes per LDS row of the X and W tiles
   static constexpr int XTile = BM * XRow, WTile = BK * WRow, Stage = XTile + WTile;
   static constexpr int XL = XTile / 1024 / (NT / 64), WL = WTile / 1024 / (NT / 64);  // load instructions per wave and stage
   static constexpr int Lds = ST * Stage > BM * WRow ? ST * Stage : BM * WRow;
+  static_assert(KS == 1 || (KS == 2 && TM == 2 && ST > 2 && BK / 16 % 4 == 0 && Lds >= NT * TN * 64), "the waves of a pair exchange half of their sums");
   static_assert(XTile % (1024 * (NT / 64)) == 0 && WTile % (1024 * (NT / 64)) == 0, "whole load instructions per wave");
   // swizzle keys (chunks of 16 bytes): X rows of 64, 128 or 256 bytes, W rows of 128 bytes or more
   static __device__ __forceinline__ int xkey(int r) { return BK == 32 ? (r >> 2) & 3 : BK == 64 ? (r >> 1) & 7 : r & 15; }
@@ -85,7 +90,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave % CFG::WN, wm = wave / CFG::WN;
+  const int wn = wave % CFG::WN, wm = wave / CFG::WN % CFG::WM, kq = wave / (CFG::WN * CFG::WM);
   const int col = lane & 31, kb = lane >> 5;
   // Workgroup -> tile: workgroup i runs on XCD i % 8.  An XCD takes a contiguous part of the tile list, which walks groups
   // of 8 token tiles column by column, so that the tiles in flight on it share W and X panels in its L2.
@@ -157,7 +162,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
   // ST > 2: the fragments of one 16-k slab are read from LDS while the MFMAs of the slab before it run, also across a stage's end:
   // after a barrier the first MFMAs find their operands in registers.  For that the NEXT stage must have landed at every
   // barrier, and a stage's place in the ring is free after the barrier that follows its last slab.
-  constexpr int NS = BK / 16, NM = TN * TM, RPM = (2 * TN + TM + NM - 1) / NM;  // slabs per stage, MFMAs per slab, reads per MFMA
+  constexpr int NS = BK / 16 / CFG::KS, NM = TN * TM, RPM = (2 * TN + TM + NM - 1) / NM;  // slabs per stage, MFMAs per slab, reads per MFMA
   const int T = K / BK;
   bf16x8 fa[2][TN], fb[2][TM];
   auto read = [&](const AG_LDS uint8_t *S, int sl, bf16x8 (&a)[TN], bf16x8 (&b)[TM]) {
@@ -198,7 +203,8 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
     if (T > ST - 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((ST - 2) * (XL + WL)) : "memory");  // stages 0 and 1 have landed
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    read((const AG_LDS uint8_t *)smem, 0, fa[0], fb[0]);
+    const int sl0 = kq * NS;  // this wave's first slab of a stage
+    read((const AG_LDS uint8_t *)smem, sl0, fa[0], fb[0]);
     int buf = 0;
     for (int t = 0; t < T; ++t) {
       const AG_LDS uint8_t *S = (const AG_LDS uint8_t *)smem + buf * CFG::Stage;
@@ -207,8 +213,8 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
 #pragma unroll
       for (int sl = 0; sl < NS; ++sl) {
         const int cur = sl & 1;
-        if (sl + 1 < NS) read(S, sl + 1, fa[cur ^ 1], fb[cur ^ 1]);
-        else read(Sn, 0, fa[cur ^ 1], fb[cur ^ 1]);  // (after the last stage: stale bytes that nothing uses)
+        if (sl + 1 < NS) read(S, sl0 + sl + 1, fa[cur ^ 1], fb[cur ^ 1]);
+        else read(Sn, sl0, fa[cur ^ 1], fb[cur ^ 1]);  // (after the last stage: stale bytes that nothing uses)
 #pragma unroll
         for (int nt = 0; nt < TN; ++nt)
 #pragma unroll
@@ -235,10 +241,37 @@ __global__ __launch_bounds__(CFG::NT, 2) void ag_proj_gemm_kernel(const uint16_t
   // kept token, to its cache row.
   __syncthreads();  // every wave is done with the last stage
   AG_LDS uint8_t *ost = (AG_LDS uint8_t *)smem;
+  if constexpr (CFG::KS == 2) {  // a pair of waves: each hands the other half of its sums over and finishes token tile kq
+    AG_LDS f32x4 *give = (AG_LDS f32x4 *)smem + (size_t)wave * TN * 256 + lane;
+    AG_LDS f32x4 *take = (AG_LDS f32x4 *)smem + (size_t)(wave ^ (CFG::WM * CFG::WN)) * TN * 256 + lane;
+#pragma unroll
+    for (int nt = 0; nt < TN; ++nt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        f32x4 g;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = acc[nt][0][4 * r4 + e], b = acc[nt][1][4 * r4 + e];
+          g[e] = kq ? a : b;
+          acc[nt][0][4 * r4 + e] = kq ? b : a;
+        }
+        give[(nt * 4 + r4) * 64] = g;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < TN; ++nt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 g = take[(nt * 4 + r4) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[nt][0][4 * r4 + e] += g[e];
+      }
+    __syncthreads();
+  }
   constexpr int KM = WC % 16 == 0 ? 15 : 7;  // chunk bits that the row is mixed into
 #pragma unroll
-  for (int mt = 0; mt < TM; ++mt) {
-    const int row = 32 * (wm * TM + mt) + col;
+  for (int mt = 0; mt < TM / CFG::KS; ++mt) {
+    const int row = 32 * (wm * TM + mt + kq) + col;  // (kq = 0 where a wave has its tiles to itself)
 #pragma unroll
     for (int nt = 0; nt < TN; ++nt)
 #pragma unroll
@@ -321,18 +354,25 @@ hipError_t launch_proj(ag_ctx *ctx, hipStream_t s, const void *x, const void *w,
 
 // The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each takes on this chip
 // (measured over 64 to 16384 tokens, 1536 to 8192 columns, K = 1024, 2048 and 4096; the choice is within 3 % (once 6 %) of the fastest
-// of the four there, and on no size more than 2 us slower than 128 x 128 tiles throughout).
+// of the first four there, and on no size more than 2 us slower than 128 x 128 tiles throughout).
 //   256 x 256: 1.13 PFLOP/s where there are tiles for whole rounds (8192 tokens x 8192 columns: 446 us; with 128 x 128
 //              tiles, which LDS bounds, 526); one tile takes 80 us.
 //   128 x 128: 1.0 PFLOP/s with two workgroups on every CU, and fills the chip from a quarter of the columns x tokens on.  In
 //              two stages of 64 k-steps; in four of 32, with the fragments read ahead, it is slower as soon as CUs hold two of
 //              them (1536 columns: 2900 tokens 67 us against 49, 8192 tokens 114 against 102).
 //   128 x 192: 1536 columns (three tensors of four heads) in whole rounds where 128 x 128 leaves a rest.
+//   128 x 192, 128 x 128, 128 x 64 with KS = 2 and 160, 128 or 96 KB of stages, one workgroup on a CU: where the tiles do not
+//              fill the chip more than once (1536 columns: 3000 tokens 48.0 -> 42.3 us, 2000 tokens 39.8 -> 32.3, 1000 tokens
+//              28.9 -> 24.3); a second round loses to two workgroups per CU (2700 tokens in 264 tiles of 128 x 128: 64.6 against
+//              48.5).  With three stages instead of four a load has too little time (2000 tokens: 40.6).
 //   64 x 64  : few tokens, where one tile's chain of stages is the time: 128 k-steps per barrier (64 to 300 tokens: 40 -> 16 us).
 typedef proj_cfg<256, 256, 2, 4, 32, 4> cfg_256x256;
 typedef proj_cfg<128, 128, 2, 2, 64, 2> cfg_128x128;
 typedef proj_cfg<128, 192, 2, 2, 32, 4> cfg_128x192;
 typedef proj_cfg<64, 64, 2, 2, 128, 4> cfg_64x64;
+typedef proj_cfg<128, 192, 2, 2, 64, 4, 2> cfg_128x192_k2;
+typedef proj_cfg<128, 128, 2, 2, 64, 4, 2> cfg_128x128_k2;
+typedef proj_cfg<128, 64, 2, 1, 64, 4, 2> cfg_128x64_k2;
 
 // A round's time ends with its slowest CU: `few` tiles take as long as one, `one` workgroup on every CU a little longer (the
 // clock falls with the number of busy CUs), and as soon as some CUs hold two workgroups the round takes what those take,
@@ -363,11 +403,21 @@ hipError_t launch_proj_any(ag_ctx *ctx, hipStream_t s, const void *x, const void
   // (a tile that starts inside a head is not made for the compaction's look-up of cache rows)
   const float t192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, K, 128, 192, cu, {2, 43.5f, 48.5f, 65.f, 86.f, 5.5f}) : never;
   const float t64 = K % 128 == 0 ? proj_time(M, N, K, 64, 64, cu, {1, 12.f, 13.6f, 0.f, 13.f, 2.8f}) : never;
-  if (t64 < t128 && t64 < t256 && t64 < t192) return launch_proj<cfg_64x64, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
-  if (t256 < t128 && t256 < t192) return launch_proj<cfg_256x256, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
-  if constexpr (!COMPACT)
-    if (t192 < t128) return launch_proj<cfg_128x192, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
-  return launch_proj<cfg_128x128, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp);
+  const float k192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, K, 128, 192, cu, {1, 37.f, 46.5f, 0.f, 46.5f, 4.5f}) : never;
+  const float k128 = proj_time(M, N, K, 128, 128, cu, {1, 27.f, 30.f, 0.f, 32.f, 4.f});
+  const float k64 = proj_time(M, N, K, 128, 64, cu, {1, 20.f, 21.5f, 0.f, 21.5f, 3.f});
+  const float best = std::min({t128, t256, t192, t64, k192, k128, k64});
+#define AG_PROJ(CFG) launch_proj<CFG, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp)
+  if (best == t64) return AG_PROJ(cfg_64x64);
+  if (best == t256) return AG_PROJ(cfg_256x256);
+  if (best == k64) return AG_PROJ(cfg_128x64_k2);
+  if (best == k128) return AG_PROJ(cfg_128x128_k2);
+  if constexpr (!COMPACT) {
+    if (best == t192) return AG_PROJ(cfg_128x192);
+    if (best == k192) return AG_PROJ(cfg_128x192_k2);
+  }
+  return AG_PROJ(cfg_128x128);
+#undef AG_PROJ
 }
 
 }  // namespace

@@ -1,5 +1,6 @@
 """The projection GEMM at the sizes where its tile changes (64 x 64, 128 x 128, 256 x 256 with the compaction; 128 x 192 for the
-gate module's three tensors), with ragged token tiles, feature counts that the deepest stage does not divide, sequences
+gate module's three tensors; 128 x 64, 128 x 128 and 128 x 192 with two waves to a block) and the gate module's attention
+with its items in 2, 4 and 8 chunks: ragged token tiles, feature counts that the deepest stage does not divide, sequences
 shorter than a tile, and few k-steps."""
 import math
 
@@ -21,7 +22,8 @@ def _lib():
 
 
 @pytest.mark.parametrize("B,L,d,Hkv", [(1, 1, 128, 1), (2, 63, 192, 2), (3, 65, 256, 4), (1, 129, 64, 32), (1, 700, 128, 32),
-                                       (5, 200, 64, 32), (40, 100, 128, 8), (3, 700, 192, 32), (1, 4100, 128, 32)])
+                                       (5, 200, 64, 32), (40, 100, 128, 8), (3, 700, 192, 32), (1, 4100, 128, 32),
+                                       (1, 130, 1024, 32), (2, 250, 1088, 32)])
 def test_project_compact_tiles(B, L, d, Hkv):
     g = np.random.default_rng(L + d)
     x = W.store((0.5 * g.standard_normal((B, L, d))).astype(np.float32), "bf16")
@@ -49,7 +51,8 @@ def test_project_compact_tiles(B, L, d, Hkv):
 
 
 @pytest.mark.parametrize("B,L,d,hp", [(1, 70, 128, 4), (1, 4096, 64, 4), (2, 1900, 128, 4), (1, 1200, 192, 2), (1, 5401, 128, 4),
-                                      (3, 1801, 64, 4)])
+                                      (3, 1801, 64, 4), (1, 3600, 1024, 4), (1, 2000, 1088, 4), (1, 1000, 1024, 4),
+                                      (1, 6000, 64, 4), (1, 4500, 64, 2), (1, 4500, 64, 1)])
 def test_gate_mha_tiles(B, L, d, hp):
     """The gate module end to end on these tiles: logits against fp32 torch on the CPU with the four tensors it stores in bf16
     rounded where it rounds them (the tolerance of the module's own tests for that reference: 1e-2)."""
