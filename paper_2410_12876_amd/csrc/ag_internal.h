@@ -80,7 +80,8 @@ static inline ag_evpair ag_time_kernel(ag_ctx *ctx, int id) {
 //   * The 8 XCDs have an L2 each, and those L2s are not kept coherent with one another inside a kernel; a plain store
 //     may sit dirty in its XCD's L2 and a plain load may hit a stale line.  The data that is exchanged is therefore
 //     written ONLY with system-scope atomic stores and read ONLY with system-scope atomic loads, which the compiler
-//     turns into global_store / global_load with the sc0 and sc1 bits set (checked in the generated code): such a store
+//     turns into global_store / global_load with the sc0 and sc1 bits set (checked in the generated code), or, 16 bytes a lane
+//     (prefill states), with buffer stores and loads that carry the same two bits: such a store
 //     is written through to memory and such a load is served from memory, never from a line cached earlier.  That is
 //     the per-access form of what a release fence (write back the whole L2) and an acquire fence (invalidate it) would
 //     do for all lines -- and those two fences were measured to stall every workgroup of the XCD.
@@ -129,7 +130,7 @@ struct ag_pf_plan {
   int n_hy, HB, BM, n_items, n_split, slots, max_tiles;
   int NW;                // waves per workgroup of the prefill kernel (4 or 8)
   int head_major;        // block order of the prefill kernel: a head's query tiles together (many heads)
-  int chunk_tiles_all;   // the same where the host knows it (chunk_tiles == NULL)
+  int chunk_tiles_all;   // the same where the host knows it (every token kept)
   int n_sp;              // query-tile rows (the longest ones) that can hold an item longer than one chunk
 };
 
