@@ -47,6 +47,11 @@ ag_status ag_probe_mfma_data(ag_ctx *ctx, void *hip_stream, int iters, double *t
 ag_status ag_probe_mfma_duty(ag_ctx *ctx, void *hip_stream, int iters, int idle, double *tflops);
 ag_status ag_probe_copy(ag_ctx *ctx, void *hip_stream, size_t bytes, double *gbs);
 
+/* Which tile the projection GEMM takes on a GPU of num_cu compute units for tokens x columns at K features: tile = {tokens, columns,
+ * waves that share a block of MFMA tiles}.  compaction: 0 for ag_gate_mha (columns = 3 h' 128), 1 for ag_project_compact_kv
+ * (columns = 2 Hkv 128).  Needs no device; AG_EINVAL where K is no multiple of 64 or columns of 128. */
+ag_status ag_probe_projection_tile(int64_t tokens, int K, int columns, int compaction, int num_cu, int tile[3]);
+
 #ifdef __cplusplus
 }
 #endif

@@ -26,7 +26,7 @@ STATUS_NAMES = ["AG_OK", "AG_EINVAL", "AG_EUNSUPPORTED", "AG_ECAPACITY", "AG_EWO
 
 EXPORTS = ["ag_create", "ag_destroy", "ag_last_error", "ag_workspace_bytes", "ag_poll_error",
            "ag_timing_kernels", "ag_timing_kernel_name", "ag_timing_enable", "ag_timing_read",
-           "ag_probe_mfma", "ag_probe_mfma_data", "ag_probe_mfma_duty", "ag_probe_copy", "ag_gate", "ag_rmsnorm_gate", "ag_compact_kv", "ag_pack_row_off", "ag_prefill_attn", "ag_prefill_attn_recent",
+           "ag_probe_mfma", "ag_probe_mfma_data", "ag_probe_mfma_duty", "ag_probe_copy", "ag_probe_projection_tile", "ag_gate", "ag_rmsnorm_gate", "ag_compact_kv", "ag_pack_row_off", "ag_prefill_attn", "ag_prefill_attn_recent",
            "ag_compact_prefill_attn", "ag_project_compact_kv", "ag_project_compact_workspace_bytes", "ag_decode_attn", "ag_decode_attn_static", "ag_decode_static_scratch_bytes", "ag_decode_scratch_bytes", "ag_recent_fill", "ag_decode_attn_recent", "ag_gate_mha", "ag_gate_mha_workspace_bytes"]
 
 
@@ -86,6 +86,8 @@ def load() -> C.CDLL:
     lib.ag_probe_mfma_duty.argtypes = [vp, vp, i32, i32, C.POINTER(C.c_double)]
     lib.ag_probe_copy.restype = C.c_int
     lib.ag_probe_copy.argtypes = [vp, vp, C.c_size_t, C.POINTER(C.c_double)]
+    lib.ag_probe_projection_tile.restype = C.c_int
+    lib.ag_probe_projection_tile.argtypes = [i64, i32, i32, i32, i32, C.POINTER(C.c_int)]
     lib.ag_gate.restype = C.c_int
     lib.ag_gate.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, i32, f32, i32, vp, vp]
     lib.ag_rmsnorm_gate.restype = C.c_int

@@ -355,9 +355,10 @@ hipError_t launch_proj(ag_ctx *ctx, hipStream_t s, const void *x, const void *w,
   return hipGetLastError();
 }
 
-// The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each takes on this chip
-// (measured over 64 to 16384 tokens, 1536 to 8192 columns, K = 1024, 2048 and 4096; the choice is within 3 % (once 6 %) of the fastest
-// of the first four there, and on no size more than 2 us slower than 128 x 128 tiles throughout).
+// The tile for a product: the one whose rounds of workgroups take the least time, from what a round of each takes on this chip.
+// (All seven tiles timed at 354 products -- 64 to 8200 tokens, 384 to 8192 columns, K = 1024, 2048 and 4096 -- the choice is within
+// 2 %, 0.3 us, of the fastest at each, 0.02 % in the mean; at 117 others, drawn at random after the costs were set, within 3.4 %, 0.45 us,
+// and 0.08 %.)
 //   256 x 256: 1.13 PFLOP/s where there are tiles for whole rounds (8192 tokens x 8192 columns: 446 us; with 128 x 128
 //              tiles, which LDS bounds, 526); one tile takes 80 us.
 //   128 x 128: 1.0 PFLOP/s with two workgroups on every CU, and fills the chip from a quarter of the columns x tokens on.  In
@@ -396,34 +397,61 @@ float proj_time(int64_t M, int N, int K, int bm, int bn, int num_cu, const proj_
   return t * (float)K / 4096.f + c.fixed * (float)(rounds + (last > 0));
 }
 
+struct proj_tile {
+  int bm, bn, bk, ks;
+  proj_cost cost;
+};
+constexpr proj_tile kProjTiles[] = {  // of two that take the same time the first
+    {64, 64, 128, 1, {1, 12.f, 13.6f, 0.f, 13.f, 2.8f}},
+    {256, 256, 32, 1, {1, 74.f, 106.f, 0.f, 106.f, 7.f}},
+    {128, 64, 64, 2, {1, 19.f, 21.f, 0.f, 21.f, 5.f}},
+    {128, 128, 64, 2, {1, 25.5f, 29.f, 0.f, 31.f, 6.f}},
+    {128, 192, 32, 1, {2, 43.5f, 48.5f, 65.f, 86.f, 5.5f}},
+    {128, 192, 64, 2, {1, 33.f, 42.f, 0.f, 42.f, 7.f}},
+    {128, 128, 64, 1, {2, 34.f, 39.f, 43.5f, 57.f, 4.5f}},
+};
+
+const proj_tile &pick_proj_tile(int64_t M, int N, int K, bool compact, int num_cu) {
+  const proj_tile *best = nullptr;
+  float least = 0.f;
+  for (const proj_tile &t : kProjTiles) {
+    // (a tile that starts inside a head and ends in the next is not made for the compaction's look-up of cache rows)
+    if (N % t.bn || K % t.bk || (compact && t.bn > kDh && t.bn % kDh)) continue;
+    const float us = proj_time(M, N, K, t.bm, t.bn, num_cu, t.cost);
+    if (!best || us < least) best = &t, least = us;
+  }
+  return *best;  // 128 x 128 always fits
+}
+
 template <bool COMPACT>
 hipError_t launch_proj_any(ag_ctx *ctx, hipStream_t s, const void *x, const void *w, int64_t M, int K, int N, int L, int hp, void *out,
                            const ag_proj_compact &cp) {
-  const int cu = ctx->num_cu;
-  const float never = 3.0e38f;
-  const float t128 = proj_time(M, N, K, 128, 128, cu, {2, 34.f, 39.f, 43.5f, 57.f, 4.5f});
-  const float t256 = N % 256 == 0 ? proj_time(M, N, K, 256, 256, cu, {1, 74.f, 106.f, 0.f, 106.f, 7.f}) : never;
-  // (a tile that starts inside a head is not made for the compaction's look-up of cache rows)
-  const float t192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, K, 128, 192, cu, {2, 43.5f, 48.5f, 65.f, 86.f, 5.5f}) : never;
-  const float t64 = K % 128 == 0 ? proj_time(M, N, K, 64, 64, cu, {1, 12.f, 13.6f, 0.f, 13.f, 2.8f}) : never;
-  const float k192 = !COMPACT && N % 192 == 0 ? proj_time(M, N, K, 128, 192, cu, {1, 37.f, 46.5f, 0.f, 46.5f, 4.5f}) : never;
-  const float k128 = proj_time(M, N, K, 128, 128, cu, {1, 27.f, 30.f, 0.f, 32.f, 4.f});
-  const float k64 = proj_time(M, N, K, 128, 64, cu, {1, 20.f, 21.5f, 0.f, 21.5f, 3.f});
-  const float best = std::min({t128, t256, t192, t64, k192, k128, k64});
-#define AG_PROJ(CFG) launch_proj<CFG, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp)
-  if (best == t64) return AG_PROJ(cfg_64x64);
-  if (best == t256) return AG_PROJ(cfg_256x256);
-  if (best == k64) return AG_PROJ(cfg_128x64_k2);
-  if (best == k128) return AG_PROJ(cfg_128x128_k2);
+  const proj_tile &t = pick_proj_tile(M, N, K, COMPACT, ctx->num_cu);
+#define AG_PROJ(CFG) \
+  if (t.bm == CFG::BM && t.bn == CFG::BN && t.ks == CFG::KS) return launch_proj<CFG, COMPACT>(ctx, s, x, w, M, K, N, L, hp, out, cp)
+  AG_PROJ(cfg_64x64);
+  AG_PROJ(cfg_256x256);
+  AG_PROJ(cfg_128x64_k2);
+  AG_PROJ(cfg_128x128_k2);
   if constexpr (!COMPACT) {
-    if (best == t192) return AG_PROJ(cfg_128x192);
-    if (best == k192) return AG_PROJ(cfg_128x192_k2);
+    AG_PROJ(cfg_128x192);
+    AG_PROJ(cfg_128x192_k2);
   }
-  return AG_PROJ(cfg_128x128);
+  AG_PROJ(cfg_128x128);
 #undef AG_PROJ
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
+
+extern "C" ag_status ag_probe_projection_tile(int64_t tokens, int K, int columns, int compaction, int num_cu, int tile[3]) {
+  if (!tile || tokens < 1 || K < 64 || K % 64 || columns < kDh || columns % kDh || num_cu < 1) return AG_EINVAL;
+  const proj_tile &t = pick_proj_tile(tokens, columns, K, compaction != 0, num_cu);
+  tile[0] = t.bm;
+  tile[1] = t.bn;
+  tile[2] = t.ks;
+  return AG_OK;
+}
 
 size_t ag_ws_gate_mha_bytes(int B, int L, int d_model, int hp, int H_f) {
   (void)d_model;

@@ -1,6 +1,6 @@
-"""The projection GEMM at the sizes where its tile changes (64 x 64, 128 x 128, 256 x 256 with the compaction; 128 x 192 for the
-gate module's three tensors; 128 x 64, 128 x 128 and 128 x 192 with two waves to a block) and the gate module's attention
-with its items in 2, 4 and 8 chunks: ragged token tiles, feature counts that the deepest stage does not divide, sequences
+"""The projection GEMM on each of its tiles (64 x 64, 128 x 128, 256 x 256, and 128 x 64 and 128 x 128 with two waves to a block; the
+gate module's three tensors also on the two of 128 x 192: test_projection_tile_choice.py checks that the sizes below take them all)
+and the gate module's attention with its items in 2, 4 and 8 chunks: ragged token tiles, feature counts that the deepest stage does not divide, sequences
 shorter than a tile, and few k-steps."""
 import math
 
@@ -21,9 +21,14 @@ def _lib():
     ensure_built()
 
 
-@pytest.mark.parametrize("B,L,d,Hkv", [(1, 1, 128, 1), (2, 63, 192, 2), (3, 65, 256, 4), (1, 129, 64, 32), (1, 700, 128, 32),
-                                       (5, 200, 64, 32), (40, 100, 128, 8), (3, 700, 192, 32), (1, 4100, 128, 32),
-                                       (1, 130, 1024, 32), (2, 250, 1088, 32)])
+PROJECT_COMPACT = [(1, 1, 128, 1), (2, 63, 192, 2), (3, 65, 256, 4), (1, 129, 64, 32), (1, 700, 128, 32), (5, 200, 64, 32), (40, 100, 128, 8),
+                   (3, 700, 192, 32), (1, 4100, 128, 32), (1, 130, 1024, 32), (2, 250, 1088, 32)]
+GATE_MHA = [(1, 70, 128, 4), (1, 4096, 64, 4), (2, 1900, 128, 4), (1, 1200, 192, 2), (1, 5401, 128, 4), (3, 1801, 64, 4), (1, 3600, 1024, 4),
+            (1, 2000, 1088, 4), (1, 1000, 1024, 4), (1, 6000, 64, 4), (1, 4500, 64, 2), (1, 4500, 64, 1), (1, 3999, 2112, 4),
+            (1, 4500, 1088, 4), (1, 8203, 192, 4)]
+
+
+@pytest.mark.parametrize("B,L,d,Hkv", PROJECT_COMPACT)
 def test_project_compact_tiles(B, L, d, Hkv):
     g = np.random.default_rng(L + d)
     x = W.store((0.5 * g.standard_normal((B, L, d))).astype(np.float32), "bf16")
@@ -50,9 +55,7 @@ def test_project_compact_tiles(B, L, d, Hkv):
         assert np.array_equal(gk[a:a + n], ref.k[a:a + n]) and np.array_equal(gv[a:a + n], ref.v[a:a + n])
 
 
-@pytest.mark.parametrize("B,L,d,hp", [(1, 70, 128, 4), (1, 4096, 64, 4), (2, 1900, 128, 4), (1, 1200, 192, 2), (1, 5401, 128, 4),
-                                      (3, 1801, 64, 4), (1, 3600, 1024, 4), (1, 2000, 1088, 4), (1, 1000, 1024, 4),
-                                      (1, 6000, 64, 4), (1, 4500, 64, 2), (1, 4500, 64, 1)])
+@pytest.mark.parametrize("B,L,d,hp", GATE_MHA)
 def test_gate_mha_tiles(B, L, d, hp):
     """The gate module end to end on these tiles: logits against fp32 torch on the CPU with the four tensors it stores in bf16
     rounded where it rounds them (the tolerance of the module's own tests for that reference: 1e-2)."""
