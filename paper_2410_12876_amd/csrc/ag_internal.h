@@ -81,7 +81,7 @@ static inline ag_evpair ag_time_kernel(ag_ctx *ctx, int id) {
 //     may sit dirty in its XCD's L2 and a plain load may hit a stale line.  The data that is exchanged is therefore
 //     written ONLY with system-scope atomic stores and read ONLY with system-scope atomic loads, which the compiler
 //     turns into global_store / global_load with the sc0 and sc1 bits set (checked in the generated code), or, 16 bytes a lane
-//     (prefill states), with buffer stores and loads that carry the same two bits: such a store
+//     (the chunk states of ag_prefill_bf16.hip), with buffer stores and loads that are given the same two bits: such a store
 //     is written through to memory and such a load is served from memory, never from a line cached earlier.  That is
 //     the per-access form of what a release fence (write back the whole L2) and an acquire fence (invalidate it) would
 //     do for all lines -- and those two fences were measured to stall every workgroup of the XCD.
@@ -91,8 +91,10 @@ static inline ag_evpair ag_time_kernel(ag_ctx *ctx, int id) {
 //   * The counter itself is a device-scope atomic add (executed in memory-side atomic units, one copy for all XCDs).
 //     The reader's loads are issued after its workgroup has seen the counter's value (a barrier in between), so they
 //     come after the add in time, and being served from memory they observe everything written before it.
-// In the language's terms the accesses are relaxed atomics ordered by that argument about the hardware, not by
-// release/acquire semantics; the tests that alternate launches under concurrent memory traffic and compare bits guard it.
+// In the language's terms the accesses are relaxed atomics -- the buffer accesses not even that: their pointer must not be
+// __restrict__, so that an asm with a memory clobber, a barrier and the counter's add hold them in place -- ordered by that argument
+// about the hardware, not by release/acquire semantics; the tests that alternate launches under concurrent memory traffic and compare
+// bits guard it, for decode, for two chunks an item and for up to 4 and 8.
 
 // Bump allocator over the context's workspace; every block is 256-byte aligned.
 struct ws_cursor {

@@ -51,7 +51,7 @@ constexpr int kMaxChunks = 8;  // chunks that an item is cut into at most
 
 // GB = query heads of one KV group per workgroup (one per wave).  n_split = chunks per item in the grid,
 // chunk_tiles_dev = key tiles per chunk (device value, NULL without a split; ALL: chunk_tiles_all); part = partial states
-// [item][chunk][4 waves][66][64] fp32 and tickets = per-item arrival counters (n_split > 1; ALL: left at zero).
+// [item][chunk][4 waves], each 4 DT x [64 lanes][4] + [64][m, l] fp32, and tickets = per-item arrival counters (n_split > 1; ALL: left at zero).
 // ALL: every token is kept (words, blk_off and row_off are not read) and unit u's rows are k, v [u L, (u + 1) L).
 // BAND = the recent-token variant (Table 6 of the appendix): the evicted tokens among the n_recent - 1 tokens just before a query
 // stay visible to it.  They are read from the uncompacted K/V as up to three extra 64-key "band" tiles that run
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     const uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off, int L, int Hq, int Hkv, int nw, int n_hy,
     int n_split, int n_sp, const int32_t *__restrict__ chunk_tiles_dev, int chunk_tiles_all, float qscale, int n_recent,
     const int32_t *__restrict__ order, int head_major, uint16_t *__restrict__ out, int out_token_major,
-    float *__restrict__ part, int32_t *__restrict__ tickets) {
+    float *part, int32_t *__restrict__ tickets) {  // (part: other workgroups write it while this one runs, so not __restrict__)
   typedef pf_geom<D> geo;
   constexpr int kRowB = geo::kRowB, kTileB = geo::kTileB, kGroupB = geo::kGroupB;
   constexpr int CPR = geo::CPR;  // 16-byte chunks per row: 16 (D = 128) or 8 (D = 64)
@@ -638,7 +638,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     // A wave's state: 4 DT pieces of [64 lanes][4 values], then [64 lanes][m, l].  The states travel through memory between
     // workgroups of one launch.  They are written through and read past the caches (sc0 and sc1, as system-scope atomics
     // would), so no cache-wide write-back or invalidate is needed: the stores are complete (vmcnt 0) before the
-    // workgroup's arrival is counted, and the last arrival reads after it.
+    // workgroup's arrival is counted, and the last arrival reads after it.  To the compiler they are ordinary accesses; what keeps
+    // them on their sides of the wait, the barriers and the count is that each of those may touch any memory that
+    // is not known to be this workgroup's alone.
     constexpr int kStateB = geo::kState * 4, kThrough = 17;  // bytes of a wave's state; sc0 | sc1
     const __amdgpu_buffer_rsrc_t p_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(part + item * n_split * NW * geo::kState), 0, n_split * NW * kStateB, 0x00020000);
