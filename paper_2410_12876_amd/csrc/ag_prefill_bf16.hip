@@ -37,6 +37,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ag_prefill_bf16_common.h"
 
@@ -50,7 +51,7 @@ template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
 constexpr int kMaxChunks = 8;  // chunks that an item is cut into at most
 
 // GB = query heads of one KV group per workgroup (one per wave).  n_split = chunks per item in the grid,
-// chunk_tiles_dev = key tiles per chunk (device value, NULL without a split; ALL: chunk_tiles_all); part = partial states
+// chunk_tiles_arg = key tiles per chunk (on the device, NULL without a split; ALL: the number itself); part = partial states
 // [item][chunk][4 waves], each 4 DT x [64 lanes][4] + [64][m, l] fp32, and tickets = per-item arrival counters (n_split > 1; ALL: left at zero).
 // ALL: every token is kept (words, blk_off and row_off are not read) and unit u's rows are k, v [u L, (u + 1) L).
 // BAND = the recent-token variant (Table 6 of the appendix): the evicted tokens among the n_recent - 1 tokens just before a query
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
     const uint64_t *__restrict__ words, const int32_t *__restrict__ blk_off, const uint16_t *__restrict__ kc,
     const uint16_t *__restrict__ vc, const int64_t *__restrict__ row_off, int L, int Hq, int Hkv, int nw, int n_hy,
-    int n_split, int n_sp, const int32_t *__restrict__ chunk_tiles_dev, int chunk_tiles_all, float qscale, int n_recent,
+    int n_split, int n_sp, std::conditional_t<ALL, int, const int32_t *> chunk_tiles_arg, float qscale, int n_recent,
     const int32_t *__restrict__ order, int head_major, uint16_t *__restrict__ out, int out_token_major,
     float *part, int32_t *__restrict__ tickets) {  // (part: other workgroups write it while this one runs, so not __restrict__)
   typedef pf_geom<D> geo;
@@ -157,7 +158,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     pre_w = bo[jw]; pre_b = bo[jb >> 6]; kept_u = bo[nw];
     ro0 = row_off[u]; ro1 = row_off[u + 1];
   }
-  const int chunk_tiles = ALL ? chunk_tiles_all : chunk_tiles_dev ? *chunk_tiles_dev : 0x7fffffff / kBN;
+  int chunk_tiles;
+  if constexpr (ALL) chunk_tiles = chunk_tiles_arg;
+  else chunk_tiles = chunk_tiles_arg ? *chunk_tiles_arg : 0x7fffffff / kBN;
   auto cnt_in = [](uint64_t w, int pre, int j) -> int { return pre + (int)__popcll(w & ((1ull << (j & 63)) - 1ull)); };
   const int len_u = (int)min((int64_t)kept_u, ro1 - ro0);
   // A kept token's own key and value are row cnt(j) of the compacted rows, so its visible set is simply the first
@@ -672,8 +675,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
     // Rounded product + rounded product (never a fused multiply-add), so that the result does not depend on which chunk
     // arrives last: two chunks are one commutative addition of this chunk's registers and the other's state; more
     // are added in chunk order starting from zero, this chunk's own state read back like the others'.
-    // With three or more chunks what bounds this is the round trip to memory, so as many loads as registers allow are on their
-    // way together (the empty asm keeps the arithmetic behind them): 4 heads x 2000 tokens 22.9 -> 20.5 us.  With two it gives nothing.
+    // What bounds this is the round trip to memory; a state's loads are on their way together.  (Three states at a time, 96 registers of
+    // loads, were no faster -- 4 heads x 2000 tokens in 4 chunks: 20.4 us, one at a time 19.9 -- and cost every launch: 8 bytes of
+    // scratch per lane at D = 64 and in the recent-token variant of one head, 241 VGPRs at D = 128 instead of 237.)
     float m;
     if (n_chunks == 2) {
       const f32x2 o_ml = peek_ml(1 - chunk);
@@ -686,49 +690,22 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round_add(peek4(1 - chunk, 4 * dt + r / 4)[r % 4], f, mul_round(acc_o[dt][r], f_mine));
     } else {
-      // at most kMaxChunks chunks; a load past the last one repeats it and is not used
-      float mc[kMaxChunks], lc[kMaxChunks];
-#pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) {
-        const f32x2 c_ml = peek_ml(min(c, n_chunks - 1));
-        mc[c] = c_ml[0];
-        lc[c] = c_ml[1];
-      }
-      asm volatile("" ::: "memory");
-      m = mc[0];
-#pragma unroll
-      for (int c = 1; c < kMaxChunks; ++c) m = fmaxf(m, mc[c]);
+      m = peek_ml(0)[0];
+      for (int c = 1; c < n_chunks; ++c) m = fmaxf(m, peek_ml(c)[0]);
       l_run = 0.f;
-#pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) {
-        mc[c] = __builtin_amdgcn_exp2f(mc[c] - m);
-        if (c < n_chunks) l_run = mul_round_add(lc[c], mc[c], l_run);
-      }
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[dt][r] = 0.f;
-      constexpr int DP = DT / 2, CP = 3;  // CP chunks x DP x 16 values on their way: 96 registers (128 spill)
+#pragma unroll 1
+      for (int c = 0; c < n_chunks; ++c) {
+        const f32x2 c_ml = peek_ml(c);
+        const float f = __builtin_amdgcn_exp2f(c_ml[0] - m);
+        l_run = mul_round_add(c_ml[1], f, l_run);
 #pragma unroll
-      for (int c0 = 0; c0 < kMaxChunks; c0 += CP) {
-        if (c0 >= n_chunks) break;
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int d0 = 0; d0 < DT; d0 += DP) {
-          f32x4 x[CP][4 * DP];
-#pragma unroll
-          for (int c = 0; c < CP; ++c)
-#pragma unroll
-            for (int g = 0; g < 4 * DP; ++g) x[c][g] = peek4(min(c0 + c, n_chunks - 1), 4 * d0 + g);
-          asm volatile("" ::: "memory");
-#pragma unroll
-          for (int c = 0; c < CP; ++c)
-            if (c0 + c < n_chunks) {
-#pragma unroll
-              for (int dt = 0; dt < DP; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc_o[d0 + dt][r] = mul_round_add(x[c][4 * dt + r / 4][r % 4], mc[c0 + c < kMaxChunks ? c0 + c : 0], acc_o[d0 + dt][r]);
-            }
-        }
+          for (int r = 0; r < 16; ++r) acc_o[dt][r] = mul_round_add(peek4(c, 4 * dt + r / 4)[r % 4], f, acc_o[dt][r]);
       }
     }
     m_run = m;
@@ -874,22 +851,23 @@ hipError_t ag_launch_prefill_bf16(hipStream_t s, const void *q, const void *k, c
   if (D == 128 && n_recent == 1 && words && ag_prefill_q64_enabled())  // 64 queries per wave: 2 waves per workgroup, same plan
     return ag_launch_prefill_d128_q64(s, q, k, v, words, blk_off, L, Hq, Hkv, qscale, kc, vc, row_off, out, plan, part,
                                       out_token_major, ev, (unsigned)blocks);
-#define AG_PF(DD, GG, BB, ...)                                                                                       \
+#define AG_PF(DD, GG, BB, CT, ...)                                                                                   \
   AG_LAUNCH(ev, (ag_prefill_bf16_kernel<DD, GG, BB, 4, ##__VA_ARGS__>), grid, block, 0, s, (const uint16_t *)q, (const uint16_t *)k,  \
             (const uint16_t *)v, words, blk_off, (const uint16_t *)kc, (const uint16_t *)vc, row_off, L, Hq, Hkv, nw,  \
-            plan.n_hy, plan.n_split, plan.n_sp, plan.chunk_tiles, plan.chunk_tiles_all, qscale, n_recent, plan.order, plan.head_major,        \
+            plan.n_hy, plan.n_split, plan.n_sp, CT, qscale, n_recent, plan.order, plan.head_major,        \
             (uint16_t *)out, out_token_major ? 1 : 0, part, plan.tickets)
 #define AG_PFD(DD)                                                                                   \
   do {                                                                                               \
+    const int32_t *ct = plan.chunk_tiles;                                                            \
     if (n_recent > 1) {                                                                              \
-      if (GB == 1) { AG_PF(DD, 1, true); } else if (GB == 2) { AG_PF(DD, 2, true); } else { AG_PF(DD, 4, true); }    \
+      if (GB == 1) { AG_PF(DD, 1, true, ct); } else if (GB == 2) { AG_PF(DD, 2, true, ct); } else { AG_PF(DD, 4, true, ct); }    \
     } else {                                                                                         \
-      if (GB == 1) { AG_PF(DD, 1, false); } else if (GB == 2) { AG_PF(DD, 2, false); } else { AG_PF(DD, 4, false); } \
+      if (GB == 1) { AG_PF(DD, 1, false, ct); } else if (GB == 2) { AG_PF(DD, 2, false, ct); } else { AG_PF(DD, 4, false, ct); } \
     }                                                                                                \
   } while (0)
   if (!words) {  // every token is kept: the attention inside the gate module
     if (D != 128 || GB != 1 || n_recent != 1) return hipErrorInvalidValue;
-    AG_PF(128, 1, false, true);
+    AG_PF(128, 1, false, plan.chunk_tiles_all, true);
   } else if (D == 128) AG_PFD(128); else if (D == 64) AG_PFD(64); else return hipErrorInvalidValue;
 #undef AG_PFD
 #undef AG_PF
