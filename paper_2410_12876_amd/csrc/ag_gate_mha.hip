@@ -6,7 +6,7 @@
 // Three stages, all bf16 with fp32 accumulation, d'_k = 128:
 //   1. ag_proj_gemm_kernel: X [tokens, d] . W_qkv [d, 3 h' 128] on v_mfma_f32_32x32x16_bf16, written head-major
 //      ([3][B, h', L, 128]) so that stage 2 reads it like any Q/K/V.
-//   2. the tuned D = 128 prefill kernel with every flag set: the "compacted" rows of a head are then its K'/V'
+//   2. the tuned D = 128 prefill kernel with every token kept: the "compacted" rows of a head are then its K'/V'
 //      themselves, so no copy is made; the output is written token-major [B, L, h' 128], the feature layout of
 //   3. the gate kernels of ag_gate.hip with d_in = h' 128 and W_g = W^{O'}.
 #include <string.h>
@@ -61,8 +61,11 @@ struct ag_proj_compact {
 // and the loads' own writes 31.  And under that load the chip's power: the vendor library's 8192^3 product reaches
 // 1.24 PFLOP/s here.
 // KS = 2: two waves share each block of MFMA tiles, each taking half of the 16-k slabs of a stage; their sums meet at the end.  A
-// workgroup that has its CU to itself has two waves per SIMD then, and one issues while the other waits for LDS or the barrier, with no
-// more LDS reads than one wave would make (K = 4096, 1536 columns: 2000 tokens 39.8 -> 32.3 us, 4096 tokens 55.2 -> 51.2).
+// workgroup that has its CU to itself then has two waves per SIMD (one with 128 x 64 tiles, which would leave half of the SIMDs empty),
+// and one issues while the other waits for LDS or the barrier, with no more LDS reads than one wave would make (K = 4096, 1536
+// columns: 2000 tokens 39.8 -> 32.3 us, 4096 tokens 55.2 -> 51.2).  A sum over k is two fp32 sums added at the end instead of one, so last
+// bits of the bf16 results differ from the other tiles'; against 64 bits neither is better: the gate module's logits, 22 inputs of 100 to
+// 6000 tokens, K = 2048 and 4096, are off by 3.3956e-3 (2-norm) in the mean without pairs and by 3.3954e-3 with.
 template <int BM_, int BN_, int WM_, int WN_, int BK_, int ST_, int KS_ = 1> struct proj_cfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, ST = ST_, KS = KS_;
   static constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 32, TN = BN / WN / 32;
@@ -475,7 +478,8 @@ hipError_t ag_launch_gate_mha(ag_ctx *ctx, hipStream_t s, const void *x, int B, 
   const size_t per = (size_t)tokens * hp * kDh;
   uint16_t *qkv = ws.take<uint16_t>(3 * per);
   uint16_t *feat = ws.take<uint16_t>(per);
-  (void)ws.take<char>(ag_ws_scan_bytes(units, L) + ag_align256((size_t)(units + 1) * 8));  // (unused; a workspace that was too small stays so)
+  // (not used since the attention needs no scan; it stays in the sum, so that a workspace that was refused as too small still is)
+  (void)ws.take<char>(ag_ws_scan_bytes(units, L) + ag_align256((size_t)(units + 1) * 8));
   ag_pf_plan plan;
   float *part = nullptr;
   ag_prefill_bf16_plan(ctx->num_cu, B, L, hp, hp, 128, ws, &plan, &part);

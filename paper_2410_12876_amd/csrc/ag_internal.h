@@ -132,7 +132,7 @@ struct ag_pf_plan {
   int n_hy, HB, BM, n_items, n_split, slots, max_tiles;
   int NW;                // waves per workgroup of the prefill kernel (4 or 8)
   int head_major;        // block order of the prefill kernel: a head's query tiles together (many heads)
-  int chunk_tiles_all;   // the same where the host knows it (every token kept)
+  int chunk_tiles_all;   // key tiles per chunk where every token is kept: the host's own number, no chunk_tiles is read
   int n_sp;              // query-tile rows (the longest ones) that can hold an item longer than one chunk
 };
 
