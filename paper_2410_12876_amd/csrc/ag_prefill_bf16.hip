@@ -99,10 +99,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   // get the same group of every row: only second chunks, most of them empty, or always the head that keeps most (16 groups
   // of 4 heads x 1501 tokens: the first chunks, nearly all of the work, on two of the four engines; 50 us instead of
   // 38).  So the groups of a row are rotated, by one every second row: for any number of groups each engine then
-  // gets every group equally often (counted for 1 to 32).  The same holds for fewer than 8 heads, and other numbers that are no
-  // multiple of 8, whose chunks fill an even number of groups (4 heads x 8000 tokens in 4 chunks, two groups a row: 101 us with the first
-  // chunks on two engines, 74 rotated); a rotation by whole groups leaves every head on its XCDs.  An odd number of
-  // groups already starts each row one engine further on and stays as it is (20 heads x 2048 tokens in 2 chunks: 35 us, 38 rotated).
+  // gets every group equally often (counted for 1 to 32).  The same holds for other numbers of heads whose chunks fill an even
+  // number of groups (4 heads x 8000 tokens in 4 chunks, two groups a row: 101 us with the first chunks on two engines, 74 rotated); a
+  // rotation by whole groups leaves every head on its XCDs.  An odd number of groups starts each row one engine further on by itself and
+  // stays as it is (20 heads x 2048 tokens in 2 chunks: 35 us, 38 rotated), and so do six (12 heads in 4 chunks) where three
+  // workgroups share a CU (D = 64 x 2400 tokens: 21.3 us, 24.1 rotated; with a window, two a CU, 36.6 and 33.5; D = 128 x 2600: 36.8 and 32.1).
   const int split_blocks = n_sp * n_hy * n_split;
   const bool in_split = (int)blockIdx.x < split_blocks;
   const int i_part = in_split ? (int)blockIdx.x : (int)blockIdx.x - split_blocks;
@@ -111,7 +112,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && !BAND ? 12 / NW : 8 / NW) void 
   int qt_idx = in_split ? row : n_sp + row;
   int rem = i_part - row * per_qt, chunk = 0;
   // (one test without branches in between: those cost 0.25 of 12.5 us where a launch is one round of short items, 333 tokens)
-  if ((((n_hy & 7) == 0) | ((per_qt & 15) == 0)) & !head_major) rem = (rem + 8 * (qt_idx >> 1)) % per_qt;
+  const bool rotates = ((n_hy & 7) == 0) | (((per_qt & 15) == 0) & (D == 128 || BAND || per_qt <= 32));
+  if (rotates & !head_major) rem = (rem + 8 * (qt_idx >> 1)) % per_qt;
   if (in_split) {
     chunk = rem / n_hy;
     rem -= chunk * n_hy;
